@@ -317,26 +317,176 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(uint4* __restrict
     g[i] = make_uint4(0, 0, 0, 0);
 }
 
-// Any shape: one thread per output element, the segment's rows in order.  Correct, not tuned.
-template <bool P_F32, bool Q_F32>
-__global__ __launch_bounds__(256) void wgrad_generic_kernel(const void* __restrict__ P, const void* __restrict__ Q,
-                                                            uint16_t* __restrict__ G,
-                                                            const int32_t* __restrict__ seg_off,
-                                                            const int32_t* __restrict__ buf_expert, int Mdim,
-                                                            int Ndim) {
-  const int r = blockIdx.z;
-  const int n = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int m = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (n >= Ndim || m >= Mdim) return;
-  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
-  float s = 0.f;
-  for (int k = 0; k < rows; ++k) {
-    const size_t row = (size_t)seg0 + k;
-    const float p = P_F32 ? ((const float*)P)[row * Mdim + m] : bf16_bits_to_f32(((const uint16_t*)P)[row * Mdim + m]);
-    const float q = Q_F32 ? ((const float*)Q)[row * Ndim + n] : bf16_bits_to_f32(((const uint16_t*)Q)[row * Ndim + n]);
-    s = fmaf(p, q, s);
+// Any shape and either storage type of the operands that have one (the other operand is bf16): 128 x 128 tile of G per
+// work-group, four waves of 64 x 64, 32 rows of the segment per step.  Both operands are staged through registers
+// (the next step's loads are in flight during the current step's MFMAs) into a double-buffered k-major LDS tile of
+// 256-byte rows and fetched with the transposing LDS read; the chunk swizzle is the one of the kernel above.
+// fp32 values keep all their 24 bits: x = a + b + c with a, b, c the bf16 numbers that hold bits 0..7, 8..15 and
+// 16..23 of the significand (cut, not rounded: each remainder is exact), so that three MFMAs sum the same exact
+// products as fp32 multiplications would, in fp32.
+// The contraction is short and the output large: at T = 4096, d = 1024, h = 4096, 16 experts, fp32 storage (2 523
+// kept rows) both launches write 268 MB, 56 us at the rate of a large copy, and multiply 3 x 42 GFLOP, 79 us at the
+// rate of a large matrix product; they take 138 + 126 us (one thread per output element with scalar products, which
+// this replaces: 12.8 ms).  64 KiB of LDS and 128-wide tiles leave room for two work-groups per compute unit, so that
+// one's stores run beside the other's MFMAs.
+constexpr int kAnyTile = 128;
+constexpr int kAnyRow = kAnyTile * 2;              // bytes of an LDS row
+constexpr int kAnyPlane = kWgK * kAnyRow;          // 8 KiB: one bf16 plane of one operand's step
+
+__device__ __forceinline__ int any_swz(int row) { return ((row & 3) | (((row >> 3) & 1) << 2)) << 1; }
+
+// 8 fp32 values -> the three bf16 planes described above, 16 bytes each
+__device__ __forceinline__ void split3(const u32x4& lo4, const u32x4& hi4, uint4 (&out)[3]) {
+  uint32_t part[3][8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    float x = __uint_as_float(i < 4 ? lo4[i] : hi4[i - 4]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t cut = __float_as_uint(x) & 0xFFFF0000u;
+      part[q][i] = cut;
+      x = x == __uint_as_float(cut) ? 0.f : x - __uint_as_float(cut);  // (an infinity leaves no remainder)
+    }
   }
-  G[((size_t)buf_expert[r] * Mdim + m) * Ndim + n] = f32_to_bf16_bits(s);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    auto two = [&](int i) { return (part[q][i] >> 16) | part[q][i + 1]; };
+    out[q] = make_uint4(two(0), two(2), two(4), two(6));
+  }
+}
+
+// One operand's share of a step for this thread: two pieces of 8 consecutive columns of one row each
+template <bool F32>
+struct AnyStage {
+  static constexpr int kPlanes = F32 ? 3 : 1;
+  static constexpr int kBytes = kPlanes * kAnyPlane;
+  u32x4 v[F32 ? 4 : 2];
+
+  // rows at or past `rows` re-read the last row here and become zeros in store()
+  __device__ __forceinline__ void load(const char* base, size_t ld, int col0, int cols, int k0, int rows, int tid) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = tid + i * kWgThreads, row = min(k0 + (c >> 4), rows - 1);
+      const int col = min(col0 + (c & 15) * 8, cols - 8);  // columns past the end repeat the last ones (not stored)
+      const u32x4* p = (const u32x4*)(base + (size_t)row * ld + (size_t)col * (F32 ? 4 : 2));
+      if (F32) { v[2 * i] = p[0]; v[2 * i + 1] = p[1]; }
+      else v[i] = p[0];
+    }
+  }
+  __device__ __forceinline__ void store(char* lds, int k0, int rows, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = tid + i * kWgThreads, row = c >> 4;
+      const bool live = k0 + row < rows;
+      char* dst = lds + row * kAnyRow + (((c & 15) ^ any_swz(row)) << 4);
+      if (F32) {
+        uint4 part[3];
+        split3(v[2 * i], v[2 * i + 1], part);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *(uint4*)(dst + q * kAnyPlane) = live ? part[q] : make_uint4(0, 0, 0, 0);
+      } else {
+        const u32x4 z = {0, 0, 0, 0};
+        *(u32x4*)dst = live ? v[i] : z;
+      }
+    }
+  }
+};
+
+template <bool P_F32, bool Q_F32>
+__global__ __launch_bounds__(kWgThreads, 2) void wgrad_any_kernel(const char* __restrict__ P, const char* __restrict__ Q,
+                                                                  uint16_t* __restrict__ G,
+                                                                  const int32_t* __restrict__ seg_off,
+                                                                  const int32_t* __restrict__ buf_expert, int Mdim,
+                                                                  int Ndim, int MT, int NT, int total) {
+  using SP = AnyStage<P_F32>;
+  using SQ = AnyStage<Q_F32>;
+  constexpr int kStageBytes = SP::kBytes + SQ::kBytes;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  // consecutive tiles of a segment share operand tiles: an XCD (work-groups with equal id mod 8) walks a contiguous run
+  const int id = blockIdx.x, per = total >> 3, rest = total & 7, x = id & 7;
+  const int lin = x * per + min(x, rest) + (id >> 3);
+  const int mt = lin % MT, nt = (lin / MT) % NT, r = lin / (MT * NT);
+  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = mt * kAnyTile, n0 = nt * kAnyTile;
+  const size_t ldP = (size_t)Mdim * (P_F32 ? 4 : 2), ldQ = (size_t)Ndim * (Q_F32 ? 4 : 2);
+  const char* Ps = P + (size_t)seg0 * ldP;
+  const char* Qs = Q + (size_t)seg0 * ldQ;
+
+  const int wm = wave >> 1, wn = wave & 1;
+  const int kq = lane >> 4, l16 = lane & 15;
+  int off_m[4], off_n[4];
+  {
+    const int row = 8 * kq + (l16 >> 2), b1 = (l16 & 3) >> 1, inner = (l16 & 1) * 8, sw = any_swz(row);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) off_m[j] = row * kAnyRow + (((8 * wm + 2 * j + b1) ^ sw) << 4) + inner;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) off_n[j] = SP::kBytes + row * kAnyRow + (((8 * wn + 2 * j + b1) ^ sw) << 4) + inner;
+  }
+  f32x4 acc[4][4];  // [n subtile][m subtile]
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  if (rows > 0) {
+    SP sp;
+    SQ sq;
+    sp.load(Ps, ldP, m0, Mdim, 0, rows, tid);
+    sq.load(Qs, ldQ, n0, Ndim, 0, rows, tid);
+    int buf = 0;
+    for (int k0 = 0; k0 < rows; k0 += kWgK) {
+      char* st = smem + buf * kStageBytes;
+      sp.store(st, k0, rows, tid);
+      sq.store(st + SP::kBytes, k0, rows, tid);
+      __syncthreads();  // (the other buffer's readers are past the previous step's barrier: one barrier per step)
+      sp.load(Ps, ldP, m0, Mdim, k0 + kWgK, rows, tid);
+      sq.load(Qs, ldQ, n0, Ndim, k0 + kWgK, rows, tid);
+      lds_cptr pt = (lds_cptr)(uintptr_t)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)st;
+      bf16x8 fm[SP::kPlanes][4], fn[SQ::kPlanes][4];
+#pragma unroll
+      for (int q = 0; q < SP::kPlanes; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fm[q][j] = read_tr8_sw<kAnyRow>(pt + q * kAnyPlane + off_m[j]);
+#pragma unroll
+      for (int q = 0; q < SQ::kPlanes; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fn[q][j] = read_tr8_sw<kAnyRow>(pt + q * kAnyPlane + off_n[j]);
+#pragma unroll
+      for (int qp = 0; qp < SP::kPlanes; ++qp)
+#pragma unroll
+        for (int qq = 0; qq < SQ::kPlanes; ++qq)
+#pragma unroll
+          for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+            for (int mj = 0; mj < 4; ++mj)
+              acc[ni][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[qq][ni], fm[qp][mj], acc[ni][mj], 0, 0, 0);
+      buf ^= 1;
+    }
+  }
+  // Through LDS, so that a row of the tile leaves as 256 contiguous bytes (chunk index XORed with the row)
+  __syncthreads();
+#pragma unroll
+  for (int mj = 0; mj < 4; ++mj) {
+    char* row = smem + (wm * 64 + mj * 16 + l16) * kAnyRow + (kq & 1) * 8;
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) {
+      const f32x4 v = acc[ni][mj];
+      *(uint2*)(row + (((8 * wn + 2 * ni + (kq >> 1)) ^ l16) << 4)) =
+          make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    }
+  }
+  __syncthreads();
+  uint16_t* Gt = G + ((size_t)buf_expert[r] * Mdim + m0) * Ndim + n0;
+  const int rrow = tid >> 4, rcol = tid & 15;
+  if (n0 + rcol * 8 < Ndim) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = rrow + 16 * i;
+      const uint4 v = *(const uint4*)(smem + row * kAnyRow + ((rcol ^ (row & 15)) << 4));
+      if (m0 + row < Mdim) nt_store16(v, (uint4*)(Gt + (size_t)row * Ndim + rcol * 8));
+    }
+  }
 }
 
 template <bool P_F32, bool Q_F32>
@@ -360,9 +510,15 @@ int launch_wgrad(const void* P, const void* Q, void* G, const int32_t* seg_off, 
       return launch_status();
     }
   }
-  if (ceil_div(Mdim, 4) > 65535 || E > 65535) return LOCMOE_ERR_SHAPE;
-  hipLaunchKernelGGL((wgrad_generic_kernel<P_F32, Q_F32>), dim3(ceil_div(Ndim, 64), ceil_div(Mdim, 4), E), dim3(256),
-                     0, st, P, Q, (uint16_t*)G, seg_off, buf_expert, Mdim, Ndim);
+  const int MT = ceil_div(Mdim, kAnyTile), NT = ceil_div(Ndim, kAnyTile);
+  const long long tiles = (long long)E * MT * NT;
+  if (tiles > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+  auto any = wgrad_any_kernel<P_F32, Q_F32>;
+  constexpr int smem = 2 * (AnyStage<P_F32>::kBytes + AnyStage<Q_F32>::kBytes);  // 32 or 64 KiB; the tile of G needs 32
+  static std::atomic<uint64_t> any_lds;
+  if (!allow_lds((const void*)any, smem, any_lds)) return LOCMOE_ERR_HIP;
+  hipLaunchKernelGGL(any, dim3((unsigned)tiles), dim3(kWgThreads), smem, st, (const char*)P, (const char*)Q,
+                     (uint16_t*)G, seg_off, buf_expert, Mdim, Ndim, MT, NT, (int)tiles);
   return launch_status();
 }
 
