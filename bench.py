@@ -359,7 +359,7 @@ def main() -> int:
         backward = time_backward(lm, hz, wl, torch, np, c, desc, sets, W_in_rm, W_out_rm, W_in, W_out, stream, reps, K)
     dom = "ffn_in" if ms["ffn_in"] >= ms["ffn_out"] else "ffn_out"
     achieved = flops / (ms[dom] * 1e-3) / 1e12
-    kname = "ffn_gemm_dma_persistent" if desc.w_packed else "ffn_gemm_256"
+    kname = "ffn_gemm_dma_persistent" if desc.w_packed else "ffn_gemm_any"
     traffic, traffic_note = None, "the tracked counters are for the config-4 bench workload with packed weights"
     if desc.w_packed and c.cfg == 4 and not args.capacity:
         kib, traffic_note = profiled_traffic()

@@ -3,11 +3,11 @@
 //   O = H . W_out[e]^T          (rows x d, rounded once to the storage type)
 // Both weights are stored row-major in Eq. 1's orientation ([h,d] and [d,h]), so both GEMMs
 // contract over the contiguous axis of both operands ("NT" form): every MFMA fragment is one
-// 16-byte LDS read.  bf16 MFMA (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
+// 16-byte LDS read.  bf16 MFMA (v_mfma_f32_16x16x32_bf16), fp32 accumulation.
 //
 // Kernels that share the operand orientation and the epilogue:
-//   ffn_gemm_generic         any shape the descriptor allows, fp32 or bf16 activations (fallback)
-//   ffn_gemm_256             256x256x64 tiles, register-staged double buffer, row-major weights
+//   ffn_gemm_any             any shape the descriptor allows, fp32 or bf16 activations, row-major weights: tiles of up to
+//                            192 x 128, LDS rings filled by direct-to-LDS loads
 //   ffn_gemm_dma_persistent  256x256x32 tiles, LDS rings filled by direct-to-LDS loads, weights pre-packed
 //                            by locmoe_pack_weights into the LDS image of each k-step; four waves with the
 //                            accumulators in the accumulation registers; one work-group per compute unit
@@ -42,10 +42,6 @@ __device__ __forceinline__ float gelu_bf16(float v) {
 #pragma unroll
   for (int k = kGeluDegree - 1; k >= 0; --k) q = fmaf(q, x, kGeluCoef[k]);
   return 0.5f * fmaf(-x, __builtin_amdgcn_exp2f(q), v + fabsf(v));
-}
-
-__device__ __forceinline__ f32x16 mfma_bf16(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
 // GeLU'(v) = Phi(v) + v phi(v) for factors of outputs that are rounded to bf16, from the same polynomial:
@@ -91,193 +87,205 @@ __device__ __forceinline__ void store_quad(void* C, uint16_t* aux, size_t row, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// Generic kernel: 64x64x32 tile, 4 waves, any K and N that are multiples of 8, fp32 or bf16
-// activations.  Correct for every shape the descriptor allows; not tuned.
+// Any K and N that are multiples of 8, fp32 (rounded to bf16 between LDS and the MFMA) or bf16 activations, row-major
+// weights: tiles of up to 192 (fp32: 128) rows x BN columns, k-steps of 64 (32), four waves (2 along m x 2 along n,
+// 16-row subtiles interleaved between the waves of an axis).  Both operands reach LDS by direct-to-LDS copies into a ring of stages
+// that fills half of a compute unit's LDS: two work-groups per compute unit (one's epilogue and barriers run beside
+// the other's MFMAs) with 32 to 48 KiB of copies each in flight.  Slot functions as in the DMA kernels below: 64-byte
+// rows chunk ^ (row/2 mod 4), 128-byte (fp32) rows chunk ^ (row/2 mod 8).  Copies past K are clamped into the row and
+// overwritten with zeros on both sides by the lanes that fetched them (an infinity times zero would be a NaN).
+//
+// Segments here are short (a hundred rows or so), so that the weight stream is what has to keep flowing: the m-tiles
+// of one weight tile run side by side on one XCD (one L2), a segment's rows are spread evenly over its m-tiles, and
+// weight tiles are dealt to the XCDs in turn (a long segment's work is spread over all of them).
+// What bounds it is the way from L2 to LDS: variants with other tiles moved 8 to 10 TB/s there (all copies of all
+// work-groups over the kernel's time), so a larger tile, that moves less, is faster as long as two work-groups fit:
+// at d = 1600, h = 6400, 40 experts, 5 003 tokens (at most 157 rows per expert) the two GEMMs take 291 + 349 us with
+// 128-row tiles staged through registers, 273 + 321 with 128-row tiles and k-steps of 32, 218 + 290 with 256-row tiles
+// and k-steps of 32, 194 + 247 as it is (whole 128-byte lines per row; 820 MB of weights each: 4.2 and 3.3 TB/s).
+// The 256 x 256 and 64 x 64 register-staged kernels that this replaces: 272 + 399 us.  fp32 storage, d = 1024,
+// h = 4096, 16 experts, 2 523 rows: 79 + 76 us (before: 105 + 155).  Long segments (2 048 rows per expert, d = 2048,
+// h = 8192, E = 8): the forward pass takes 1 160 us against 1 407 with the 256 x 256 tiles.
 // ---------------------------------------------------------------------------------------------
-constexpr int kGenThreads = 256;
-constexpr int kGenLd = 40;  // LDS row stride in bf16 elements (32 + 8 pad), 80 bytes
+constexpr int kAnyThreads = 256;
+constexpr int kAnyLds = 80 * 1024;  // half of a compute unit's
 
-template <bool A_F32, int EPI, bool OUT_F32>
-__global__ __launch_bounds__(kGenThreads) void ffn_gemm_generic(const void* __restrict__ A,
-                                                                const uint16_t* __restrict__ W,
-                                                                void* __restrict__ Cout, uint16_t* aux,
-                                                                const int32_t* __restrict__ seg_off,
-                                                                const int32_t* __restrict__ buf_expert, int Kdim,
-                                                                int Ndim, int MT) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[64 * kGenLd];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[64 * kGenLd];
-  const int r = blockIdx.y / MT, mt = blockIdx.y % MT;
-  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
-  const int m0 = mt * 64;
-  if (m0 >= rows) return;
-  const int e = buf_expert[r];
-  const int n0 = blockIdx.x * 64;
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int lrow = tid >> 2, lch = tid & 3;
-  const size_t arow = (size_t)seg0 + min(m0 + lrow, rows - 1);       // clamped: tail rows re-read the last row
-  const size_t wrow = (size_t)e * Ndim + min(n0 + lrow, Ndim - 1);
-  const int wm = wave >> 1, wn = wave & 1;
-  f32x16 acc = {0};
-  for (int k0 = 0; k0 < Kdim; k0 += 32) {
-    const int kk = k0 + lch * 8;
-    uint4 av = make_uint4(0, 0, 0, 0), bv = make_uint4(0, 0, 0, 0);
-    if (kk < Kdim) {
-      if (A_F32) {
-        const float4* p = (const float4*)((const float*)A + arow * Kdim + kk);
-        const float4 f0 = p[0], f1 = p[1];
-        av = make_uint4(pack_bf16x2(f0.x, f0.y), pack_bf16x2(f0.z, f0.w), pack_bf16x2(f1.x, f1.y),
-                        pack_bf16x2(f1.z, f1.w));
-      } else {
-        av = *(const uint4*)((const uint16_t*)A + arow * Kdim + kk);
-      }
-      bv = *(const uint4*)(W + wrow * Kdim + kk);
-    }
-    __syncthreads();
-    *(uint4*)(As + lrow * kGenLd + lch * 8) = av;
-    *(uint4*)(Bs + lrow * kGenLd + lch * 8) = bv;
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int ko = ks * 16 + (lane >> 5) * 8;
-      const bf16x8 xa = *(const bf16x8*)(As + (wm * 32 + (lane & 31)) * kGenLd + ko);
-      const bf16x8 wb = *(const bf16x8*)(Bs + (wn * 32 + (lane & 31)) * kGenLd + ko);
-      acc = mfma_bf16(wb, xa, acc);  // D[n][m]
-    }
-  }
-  const int m = m0 + wm * 32 + (lane & 31);
-  if (m < rows) {
-#pragma unroll
-    for (int vq = 0; vq < 4; ++vq) {
-      const int n = n0 + wn * 32 + vq * 8 + (lane >> 5) * 4;
-      if (n < Ndim)  // Ndim % 8 == 0 and n % 4 == 0: the quad is entirely inside or outside
-        store_quad<EPI, OUT_F32>(Cout, aux, (size_t)seg0 + m, Ndim, n, acc[vq * 4 + 0], acc[vq * 4 + 1],
-                                  acc[vq * 4 + 2], acc[vq * 4 + 3]);
-    }
+template <bool A_F32>
+struct AnyK {
+  static constexpr int kBM = A_F32 ? 128 : 192;           // rows of an m-tile at most
+  static constexpr int kBK = A_F32 ? 32 : 64;
+  static constexpr int kARow = 128;                       // bytes of an activation row in LDS: one line
+  static constexpr int kWRow = kBK * 2;
+};
+template <bool A_F32, int BN, int NJ>
+struct AnyShape : AnyK<A_F32> {
+  static constexpr int kABytes = 32 * NJ * AnyK<A_F32>::kARow;
+  static constexpr int kStage = kABytes + BN * AnyK<A_F32>::kWRow;
+  static constexpr int kStages = kAnyLds / kStage;        // 2 to 6
+};
+// Byte offset, inside a row of RB bytes (a k-step), of the 16-byte chunk that this lane of a 1 KiB copy fetches; the
+// copy's block of 1024 / RB rows is number wave + 4 i of the operand
+template <int RB>
+__device__ __forceinline__ uint32_t any_chunk(int wave, int lane) {
+  constexpr int L = RB / 16;
+  const int row = (RB == 128 ? (wave & 1) * 8 : 0) + lane / L;  // modulo 16
+  return (uint32_t)(((lane & (L - 1)) ^ ((row >> 1) & (L - 1))) << 4);
+}
+
+// vmcnt(n C) for a run-time n <= MAX
+template <int C, int MAX>
+__device__ __forceinline__ void wait_younger(int n) {
+  if constexpr (MAX == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (n >= MAX) wait_vmcnt<MAX * C>();
+    else wait_younger<C, MAX - 1>(n);
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Tuned kernel: 256x256x64 tile, 8 waves (2 along m x 4 along n, 128x64 per wave), double
-// buffered LDS (2 x 64 KiB), XOR-swizzled 16-byte slots (slot = chunk ^ (row/2 mod 8): 16 lanes
-// reading 16 consecutive rows touch all 64 banks once), bf16 activations, K % 64 == 0, N % 256 == 0.  Work-group ids are remapped so that each XCD (ids congruent mod 8 land on one
-// XCD and share its L2) walks a contiguous range of experts, with the m-tiles that share a
-// weight tile adjacent in time.
-// ---------------------------------------------------------------------------------------------
-constexpr int kBM = 256, kBN = 256, kBK = 64;
-constexpr int kFastThreads = 512;
-constexpr int kStageBytes = (kBM + kBN) * kBK * 2;  // 64 KiB
-constexpr int kFastSmem = 2 * kStageBytes;
+// One tile of at most 32 NJ rows.  rows_left: live rows from the tile's first (>= 1).
+template <bool A_F32, int EPI, bool OUT_F32, int BN, int NJ>
+__device__ __forceinline__ void any_tile(const char* __restrict__ A, const char* __restrict__ W, void* __restrict__ Cout,
+                                         uint16_t* aux, size_t crow0, int rows_left, int n0, int Kdim, int Ndim,
+                                         uint32_t lds0, char* smem) {
+  using S = AnyShape<A_F32, BN, NJ>;
+  constexpr int NI = BN / 32;                                  // 16-column subtiles of a wave
+  constexpr int kSub = S::kBK / 32;                            // MFMA depths per k-step
+  constexpr int kARows = 1024 / S::kARow, kWRows = 1024 / S::kWRow;  // rows of a 1 KiB copy
+  constexpr int CA = 32 * NJ / kARows / 4, CW = BN / kWRows / 4;     // copies per wave and step
+  constexpr int C = CA + CW;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, kq = lane >> 4, l16 = lane & 15;
 
-template <int SH>
-__device__ __forceinline__ int swz(int row, int chunk) { return (chunk ^ ((row >> SH) & 7)) << 4; }
-
-template <int EPI, bool OUT_F32, int SH>
-__global__ __launch_bounds__(kFastThreads) void ffn_gemm_256(const uint16_t* __restrict__ A,
-                                                             const uint16_t* __restrict__ W,
-                                                             void* __restrict__ Cout, uint16_t* aux,
-                                                             const int32_t* __restrict__ seg_off,
-                                                             const int32_t* __restrict__ buf_expert, int Kdim,
-                                                             int Ndim, int MT, int NT, int total) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int id = blockIdx.x;
-  const int lin = (total % 8 == 0) ? (id % 8) * (total / 8) + id / 8 : id;
-  const int mt = lin % MT, nt = (lin / MT) % NT, r = lin / (MT * NT);
-  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
-  const int m0 = mt * kBM;
-  if (m0 >= rows) return;
-  const int e = buf_expert[r];
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int wm = wave >> 2, wn = wave & 3;
-
-  // global -> LDS assignment: 4 A chunks and 4 B chunks of 16 bytes per thread and stage
-  const uint16_t* ga[4];
-  const uint16_t* gb[4];
-  int lds_w[4];
+  // copies: block wave + 4 i of an operand's stage; rows past the segment's end and columns past the last repeat the
+  // last one (not stored)
+  const uint32_t ldA = (uint32_t)Kdim * (A_F32 ? 4 : 2), ldW = (uint32_t)Kdim * 2;
+  uint32_t rowA[CA], rowW[CW];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = tid + i * kFastThreads;
-    const int row = c >> 3, kc = c & 7;
-    ga[i] = A + ((size_t)seg0 + min(m0 + row, rows - 1)) * Kdim + kc * 8;
-    gb[i] = W + ((size_t)e * Ndim + (size_t)nt * kBN + row) * Kdim + kc * 8;
-    lds_w[i] = row * (kBK * 2) + swz<SH>(row, kc);
+  for (int i = 0; i < CA; ++i)
+    rowA[i] = (uint32_t)min((wave + 4 * i) * kARows + lane / (64 / kARows), rows_left - 1) * ldA;
+#pragma unroll
+  for (int i = 0; i < CW; ++i)
+    rowW[i] = (uint32_t)min((wave + 4 * i) * kWRows + lane / (64 / kWRows), Ndim - n0 - 1) * ldW;
+  const uint32_t chA = any_chunk<S::kARow>(wave, lane), chW = any_chunk<S::kWRow>(wave, lane);
+  const int KT = (Kdim + S::kBK - 1) / S::kBK;
+  auto issue = [&](int s, int stage) {
+    const uint32_t base = lds0 + (uint32_t)stage * S::kStage + (uint32_t)wave * 1024;
+    const uint32_t ka = min((uint32_t)s * S::kARow + chA, ldA - 16), kw = min((uint32_t)s * S::kWRow + chW, ldW - 16);
+#pragma unroll
+    for (int i = 0; i < CW; ++i) dma_1k(W, rowW[i] + kw, base + S::kABytes + i * 4096);
+#pragma unroll
+    for (int i = 0; i < CA; ++i) dma_1k(A, rowA[i] + ka, base + i * 4096);
+  };
+
+  // fragment addresses inside a stage: lane l reads the 8 values k = 8 (l/16) .. +7 of row l%16 (two chunks if fp32)
+  int off_a[2], off_w[kSub];
+  {
+    const int ra = wm * 16 + l16, rw = wn * 16 + l16;  // (subtiles are 32 rows apart: the same swizzle)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      off_a[i] = ra * S::kARow + (((A_F32 ? 2 * kq + i : 4 * i + kq) ^ ((ra >> 1) & 7)) << 4);
+#pragma unroll
+    for (int i = 0; i < kSub; ++i)
+      off_w[i] = S::kABytes + rw * S::kWRow + (((4 * i + kq) ^ ((rw >> 1) & (S::kWRow / 16 - 1))) << 4);
   }
-  // LDS -> fragment addresses (byte offsets inside a stage, without the k-chunk part)
-  const int khalf = lane >> 5;
-  int a_row[4], b_row[2];
+  f32x4 acc[NI][NJ];
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi) a_row[mi] = wm * 128 + mi * 32 + (lane & 31);
+  for (int a = 0; a < NI; ++a)
 #pragma unroll
-  for (int ni = 0; ni < 2; ++ni) b_row[ni] = wn * 64 + ni * 32 + (lane & 31);
+    for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  f32x16 acc[2][4];
 #pragma unroll
-  for (int ni = 0; ni < 2; ++ni)
+  for (int s = 0; s < S::kStages - 1; ++s)
+    if (s < KT) issue(s, s);
+  int stage = 0, fill = S::kStages - 1;
+  for (int s = 0; s < KT; ++s) {
+    // this step's copies have landed when at most the younger steps' are outstanding (copies complete in issue order
+    // and the loop has no other vector memory access)
+    wait_younger<C, S::kStages - 2>(KT - 1 - s);
+    if (s == KT - 1 && (Kdim & (S::kBK - 1))) {
+      char* st = smem + stage * S::kStage + wave * 1024 + lane * 16;
+      const uint4 zero = make_uint4(0, 0, 0, 0);
+      if ((uint32_t)s * S::kARow + chA >= ldA) {
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = (f32x16){0};
-
-  // The staging registers are native vectors and the loop body has no conditionals: the prefetch
-  // of the tile after the last one is clamped to the last tile (redundant, never consumed).  With
-  // branches around the prefetch the compiler demotes these arrays to scratch memory and
-  // serialises every load.
-  u32x4 ra[4], rb[4];
+        for (int i = 0; i < CA; ++i) *(uint4*)(st + i * 4096) = zero;
+      }
+      if ((uint32_t)s * S::kWRow + chW >= ldW) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { ra[i] = *(const u32x4*)(ga[i]); rb[i] = *(const u32x4*)(gb[i]); }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    *(u32x4*)(smem + lds_w[i]) = ra[i];
-    *(u32x4*)(smem + kBM * kBK * 2 + lds_w[i]) = rb[i];
-  }
-  __syncthreads();
-
-  const int KT = Kdim / kBK;
-  for (int kt = 0; kt < KT; ++kt) {
-    {
-      const int ko = min(kt + 1, KT - 1) * kBK;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { ra[i] = *(const u32x4*)(ga[i] + ko); rb[i] = *(const u32x4*)(gb[i] + ko); }
-    }
-    const char* sa = smem + (kt & 1) * kStageBytes;
-    const char* sb = sa + kBM * kBK * 2;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int kc = ks * 2 + khalf;
-      bf16x8 fa[4], fb[2];
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni) fb[ni] = *(const bf16x8*)(sb + b_row[ni] * (kBK * 2) + swz<SH>(b_row[ni], kc));
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi) fa[mi] = *(const bf16x8*)(sa + a_row[mi] * (kBK * 2) + swz<SH>(a_row[mi], kc));
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = mfma_bf16(fb[ni], fa[mi], acc[ni][mi]);
-    }
-    {
-      char* da = smem + ((kt + 1) & 1) * kStageBytes;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        *(u32x4*)(da + lds_w[i]) = ra[i];
-        *(u32x4*)(da + kBM * kBK * 2 + lds_w[i]) = rb[i];
+        for (int i = 0; i < CW; ++i) *(uint4*)(st + S::kABytes + i * 4096) = zero;
       }
     }
     __syncthreads();
-  }
-
+    if (s + S::kStages - 1 < KT) issue(s + S::kStages - 1, fill);  // into the stage that was read one step ago
+    const char* st = smem + stage * S::kStage;
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi) {
-    const int m = m0 + wm * 128 + mi * 32 + (lane & 31);
-    if (m < rows) {
+    for (int ks = 0; ks < kSub; ++ks) {
+      bf16x8 fw[NI], fa[NJ];
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
+      for (int ni = 0; ni < NI; ++ni) fw[ni] = *(const bf16x8*)(st + off_w[ks] + ni * 32 * S::kWRow);
 #pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          const int n = nt * kBN + wn * 64 + ni * 32 + vq * 8 + khalf * 4;
-          store_quad<EPI, OUT_F32>(Cout, aux, (size_t)seg0 + m, Ndim, n, acc[ni][mi][vq * 4 + 0],
-                                    acc[ni][mi][vq * 4 + 1], acc[ni][mi][vq * 4 + 2], acc[ni][mi][vq * 4 + 3]);
+      for (int j = 0; j < NJ; ++j) {
+        const char* p = st + j * 32 * S::kARow;
+        if (A_F32) {
+          const f32x4 a = *(const f32x4*)(p + off_a[0]), b = *(const f32x4*)(p + off_a[1]);
+          const u32x4 v = {pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
+          fa[j] = __builtin_bit_cast(bf16x8, v);
+        } else {
+          fa[j] = *(const bf16x8*)(p + off_a[ks]);
         }
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+          acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ni], fa[j], acc[ni][j], 0, 0, 0);
+    }
+    fill = stage;
+    stage = stage + 1 == S::kStages ? 0 : stage + 1;
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int m = (2 * j + wm) * 16 + l16;
+    if (m < rows_left) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) {
+        const int n = n0 + (2 * ni + wn) * 16 + kq * 4;  // a lane holds D[n .. n+3][m]
+        if (n < Ndim)  // Ndim % 8 == 0 and n % 4 == 0: the quad is entirely inside or outside
+          store_quad<EPI, OUT_F32>(Cout, aux, crow0 + m, Ndim, n, acc[ni][j][0], acc[ni][j][1], acc[ni][j][2],
+                                   acc[ni][j][3]);
+      }
     }
   }
 }
 
+template <bool A_F32, int EPI, bool OUT_F32, int BN>
+__global__ __launch_bounds__(kAnyThreads, 2) void ffn_gemm_any(const char* __restrict__ A, const char* __restrict__ W,
+                                                               void* __restrict__ Cout, uint16_t* aux,
+                                                               const int32_t* __restrict__ seg_off,
+                                                               const int32_t* __restrict__ buf_expert, int Kdim,
+                                                               int Ndim, int MT, int NT, int groups) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  // work-group id -> (XCD, m-tile, weight tile): ids congruent mod 8 run on one XCD
+  const int seq = blockIdx.x >> 3, mt = seq % MT, grp = (seq / MT) * 8 + (blockIdx.x & 7);
+  if (grp >= groups) return;
+  const int n0 = (grp % NT) * BN, r = grp / NT;
+  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
+  const int mtc = (rows + AnyK<A_F32>::kBM - 1) / AnyK<A_F32>::kBM;
+  if (mt >= mtc) return;
+  const int span = ((rows + mtc - 1) / mtc + 15) & ~15, m0 = mt * span;
+  const int left = __builtin_amdgcn_readfirstlane(min(rows - m0, span));
+  if (left <= 0) return;  // (rounding the span up to whole subtiles can leave the last tile without rows)
+  const char* At = A + ((size_t)seg0 + m0) * Kdim * (A_F32 ? 4 : 2);
+  const char* Wt = W + ((size_t)buf_expert[r] * Ndim + n0) * Kdim * 2;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+#define LOCMOE_ANY_TILE(NJ) \
+  any_tile<A_F32, EPI, OUT_F32, BN, NJ>(At, Wt, Cout, aux, (size_t)seg0 + m0, left, n0, Kdim, Ndim, lds0, smem)
+  if (left <= 64) LOCMOE_ANY_TILE(2);
+  else if (A_F32 || left <= 128) LOCMOE_ANY_TILE(4);
+  else if constexpr (!A_F32) LOCMOE_ANY_TILE(6);
+#undef LOCMOE_ANY_TILE
+}
 
 // ---------------------------------------------------------------------------------------------
 // DMA kernels: 256x256 tile, k-steps of 32 taken two at a time ("double steps"), four waves, one per
@@ -308,6 +316,7 @@ __global__ __launch_bounds__(kFastThreads) void ffn_gemm_256(const uint16_t* __r
 // Rows of the tile are owned in interleaved 16-row subtiles (wave row wm owns subtiles wm, wm+2,
 // ...), so a ragged tile skips MFMAs evenly across waves, at 32-row granularity overall.
 // ---------------------------------------------------------------------------------------------
+constexpr int kBM = 256, kBN = 256;        // output tile
 constexpr int kDmaBK = 32;
 constexpr int kDmaWaves = 4;               // one wave per SIMD
 constexpr int kDmaThreads = kDmaWaves * 64;
@@ -897,26 +906,32 @@ inline bool packable(const locmoe_desc* p) {
          (long long)p->h * 2 * 256 < 0x7FFFFFFFLL;
 }
 
+template <bool A_F32, int EPI, bool OUT_F32, int BN>
+int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
+               int rows_max, int Kdim, int Ndim, hipStream_t st) {
+  if ((long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;  // the size limit of this path
+  if ((long long)Kdim * 4 * 192 > 0xFFFFFFFFLL) return LOCMOE_ERR_SHAPE;         // a tile's rows are 32-bit offsets
+  const int MT = ceil_div(rows_max, AnyK<A_F32>::kBM), NT = ceil_div(Ndim, BN);
+  const long long groups = (long long)E * NT, grid = (groups + 7) / 8 * 8 * MT;
+  if (grid > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+  auto kern = ffn_gemm_any<A_F32, EPI, OUT_F32, BN>;
+  static std::atomic<uint64_t> lds_allowed;
+  if (!allow_lds((const void*)kern, kAnyLds, lds_allowed)) return LOCMOE_ERR_HIP;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kAnyThreads), kAnyLds, st, (const char*)A, (const char*)W, C,
+                     (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, MT, NT, (int)groups);
+  return launch_status();
+}
+
 template <bool A_F32, int EPI, bool OUT_F32>
 int launch_gemm(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-                int rows_max, int Kdim, int Ndim, hipStream_t st) {
-  if (!A_F32 && Kdim % kBK == 0 && Ndim % kBN == 0) {
-    const int MT = ceil_div(rows_max, kBM), NT = Ndim / kBN;
-    const long long total = (long long)E * MT * NT;
-    if (total <= 0x7FFFFFFFLL) {
-      auto kern = ffn_gemm_256<EPI, OUT_F32, 1>;
-      static std::atomic<uint64_t> lds_allowed;
-      if (!allow_lds((const void*)kern, kFastSmem, lds_allowed)) return LOCMOE_ERR_HIP;
-      hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(kFastThreads), kFastSmem, st, (const uint16_t*)A,
-                         (const uint16_t*)W, C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, MT, NT, (int)total);
-      return launch_status();
-    }
-  }
-  const int MT = ceil_div(rows_max, 64);
-  if ((long long)E * MT > 65535) return LOCMOE_ERR_SHAPE;
-  hipLaunchKernelGGL((ffn_gemm_generic<A_F32, EPI, OUT_F32>), dim3(ceil_div(Ndim, 64), E * MT),
-                     dim3(kGenThreads), 0, st, A, (const uint16_t*)W, C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, MT);
-  return launch_status();
+                int rows_max, int rows_even, int Kdim, int Ndim, hipStream_t st) {
+  // 128 columns per tile, or 64 where that leaves some of the chip's work-group slots (two per compute unit) empty.
+  // The forward at 2 048 rows per expert (d = 2048, h = 8192, E = 8): 1 160 us with 128 columns in both GEMMs, 1 413 with 64
+  // in the second; the second GEMM at d = 1024, h = 4096, E = 16, 158 rows (64 columns: 256 tiles): 76 us against 83 to 92.
+  const long long tiles = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows_even, AnyK<A_F32>::kBM);
+  if (tiles >= 2 * cu_count())
+    return launch_any<A_F32, EPI, OUT_F32, 128>(A, W, C, aux, seg_off, buf_expert, E, rows_max, Kdim, Ndim, st);
+  return launch_any<A_F32, EPI, OUT_F32, 64>(A, W, C, aux, seg_off, buf_expert, E, rows_max, Kdim, Ndim, st);
 }
 
 }  // namespace
@@ -932,15 +947,16 @@ template <int EPI>
 int gemm_d_to_h(const locmoe_desc* desc, const void* A, const int32_t* seg_off, const int32_t* buf_expert,
                 const void* W, void* Cbf16, void* aux, unsigned int* queue, void* stream) {
   const int rows_max = desc->C < desc->T ? desc->C : desc->T;  // kept[e] <= min(C, T)
+  const int rows_even = std::min(rows_max, ceil_div(desc->T, desc->E));  // with evenly spread tokens
   if (desc->w_packed) {
     if (desc->x_dtype != LOCMOE_BF16 || !packable(desc)) return LOCMOE_ERR_ARG;
     return launch_dma<EPI>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->d, desc->h, queue,
                            as_stream(stream));
   }
   if (desc->x_dtype == LOCMOE_F32)
-    return launch_gemm<true, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->d, desc->h,
+    return launch_gemm<true, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->d, desc->h,
                                          as_stream(stream));
-  return launch_gemm<false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->d, desc->h,
+  return launch_gemm<false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->d, desc->h,
                                         as_stream(stream));
 }
 
@@ -949,15 +965,16 @@ int gemm_d_to_h(const locmoe_desc* desc, const void* A, const int32_t* seg_off, 
 int gemm_h_to_d(const locmoe_desc* desc, const void* A, const int32_t* seg_off, const int32_t* buf_expert,
                 const void* W, void* C, unsigned int* queue, void* stream) {
   const int rows_max = desc->C < desc->T ? desc->C : desc->T;
+  const int rows_even = std::min(rows_max, ceil_div(desc->T, desc->E));
   if (desc->w_packed) {
     if (desc->x_dtype != LOCMOE_BF16 || !packable(desc)) return LOCMOE_ERR_ARG;
     return launch_dma<kEpiNone>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->h, desc->d, queue,
                                 as_stream(stream));
   }
   if (desc->x_dtype == LOCMOE_F32)
-    return launch_gemm<false, kEpiNone, true>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->h,
+    return launch_gemm<false, kEpiNone, true>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->h,
                                               desc->d, as_stream(stream));
-  return launch_gemm<false, kEpiNone, false>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->h,
+  return launch_gemm<false, kEpiNone, false>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->h,
                                              desc->d, as_stream(stream));
 }
 

@@ -67,3 +67,62 @@ def test_weight_gradients_of_any_shape(env, d, h, dtype):
             ref = p.T @ q
             bound = 2.0 ** -8 * (1 + 2.0 ** -8) * ref.abs() + (z - a) * 2.0 ** -23 * (p.abs().T @ q.abs())
             assert ((got.double() - ref).abs() <= bound).all(), (r, z - a)
+
+
+def gelu(torch, v):
+    return 0.5 * v * torch.erfc(-v * 2.0 ** -0.5)
+
+
+def gelu_grad(torch, v):
+    return 0.5 * torch.erfc(-v * 2.0 ** -0.5) + v * torch.exp(-0.5 * v * v) * (2.0 * torch.pi) ** -0.5
+
+
+# (8, 8): one partial tile and k-step; 128/64-column tiles with and without remainders; k remainders of 8 and 56; the
+# last one has enough tiles for the 128-column kernel in both directions (6 x 86 >= 512)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,h", [(48, 8), (120, 264), (192, 128), (384, 1000), (264, 11000), (11016, 72)])
+def test_expert_ffn_of_any_shape(env, d, h, dtype):
+    """H, Z, out and the data gradients; GeLU's polynomial is within 5e-5 |ref| + 7e-6 (its derivative within 5e-5)."""
+    torch, lm = env
+    rows = [0, 1, 16, 17, 128, 259]
+    E, K, C = len(rows), sum(rows), 300
+    print(f"[ffn] d={d} h={h} {dtype} rows={rows}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d * 5 + h)
+    off, seg, be = segments(torch, rows)
+    xd = storage(torch, dtype)
+    desc = lm.make_desc(600, d, E, 1, h, C, dtype)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    send = rows_with_nan_tail(torch, K, 40, d, xd, gen)
+    dout = rows_with_nan_tail(torch, K, 40, d, xd, gen)
+    W_in = (torch.randn(E, h, d, generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)
+    W_out = (torch.randn(E, d, h, generator=gen, device="cuda") * h ** -0.5).to(torch.bfloat16)
+    H, Z, dZ = (torch.full((K + 40, h), float("nan"), **bf) for _ in range(3))
+    H2 = torch.empty_like(H)
+    out, dsend = (torch.full((K + 40, d), float("nan"), dtype=xd, device="cuda") for _ in range(2))
+    Wt_in, Wt_out = W_in.transpose(1, 2).contiguous(), W_out.transpose(1, 2).contiguous()
+    lm.locmoe_expert_ffn_in_save(desc, send, seg, be, W_in, H, Z)
+    lm.locmoe_expert_ffn_in(desc, send, seg, be, W_in, H2)
+    lm.locmoe_expert_ffn_out(desc, H, seg, be, W_out, out)
+    lm.locmoe_expert_ffn_dgrad(desc, dout, Z, seg, be, Wt_out, Wt_in, dZ, dsend)
+    torch.cuda.synchronize()
+    assert torch.equal(H[:K], H2[:K])
+    for t in (H, Z, dZ, out, dsend):
+        assert t[K:].isnan().all()  # nothing past the last segment is written
+    b16, u = 2.0 ** -8 * (1 + 2.0 ** -8), 2.0 ** -23
+    ulp = b16 if dtype == "bf16" else u
+    for r in range(E):
+        e, a, z = E - 1 - r, off[r], off[r + 1]
+        s, do = send[a:z].to(torch.bfloat16).double(), dout[a:z].to(torch.bfloat16).double()
+        zr, zb = s @ W_in[e].double().T, d * u * (s.abs() @ W_in[e].double().abs().T)
+        hr = gelu(torch, zr)
+        assert ((Z[a:z].double() - zr).abs() <= b16 * zr.abs() + 1.01 * zb).all(), r
+        assert ((H[a:z].double() - hr).abs() <= 1.01 * (b16 * hr.abs() + 5e-5 * hr.abs() + 7e-6 + 1.13 * zb)).all(), r
+        hs = H[a:z].double()
+        orf, ob = hs @ W_out[e].double().T, h * u * (hs.abs() @ W_out[e].double().abs().T)
+        assert ((out[a:z].double() - orf).abs() <= ulp * orf.abs() + 1.01 * ob).all(), r
+        gr = gelu_grad(torch, Z[a:z].double())
+        dh, hb = do @ W_out[e].double(), d * u * (do.abs() @ W_out[e].double().abs())
+        assert ((dZ[a:z].double() - dh * gr).abs() <= 1.01 * (b16 * (dh * gr).abs() + 5e-5 * dh.abs() + 1.13 * hb)).all(), r
+        dz = dZ[a:z].double()
+        dr, db = dz @ W_in[e].double(), h * u * (dz.abs() @ W_in[e].double().abs())
+        assert ((dsend[a:z].double() - dr).abs() <= ulp * dr.abs() + 1.01 * db).all(), r
