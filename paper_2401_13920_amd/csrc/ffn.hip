@@ -12,6 +12,7 @@
 //                            by locmoe_pack_weights into the LDS image of each k-step; four waves with the
 //                            accumulators in the accumulation registers; one work-group per compute unit
 //                            works through a queue of tiles (expert counts that are multiples of 8, up to 512)
+//   ffn_gemm_few             packed weights and at most 64 rows per segment: weight fragments straight to registers
 //   ffn_gemm_dma             the same pipeline with one tile per work-group (other expert counts)
 //
 // The weight rows feed the MFMA's A operand and the activation rows its B operand, i.e. the
@@ -783,6 +784,89 @@ __global__ __launch_bounds__(kDmaThreads) void ffn_gemm_dma_persistent(const uin
   if (queue && tid == 0) leave_queues(queue, gridDim.x);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Few rows per segment (at most 32 or 64 by capacity or token count: launch_dma), packed weights: the weights are read once for a
+// handful of rows, so this is a stream of weights that has to keep the memory busy.  A work-group takes 64 columns of
+// one segment and all of its rows; its four waves take a quarter of K each and add their sums through LDS at the end
+// (in wave order).  Weight fragments come straight from memory into registers: 16 columns of a packed block are one
+// contiguous KiB per load, and four k-steps (16 KiB per wave) are always in flight; activation fragments come from
+// L2.  No barrier until the end, no LDS traffic in the loop, and four times as many work-groups as 256-column tiles.
+// 192 tokens, d = 1024, h = 4096, 16 experts of at most 24 rows (134 MB per weight): 23.6 + 30.4 us (5.7 and 4.4 TB/s)
+// against 32.8 + 55.3 us with the 256-column tiles of the persistent kernel, of which the second GEMM has 64.
+// ---------------------------------------------------------------------------------------------
+constexpr int kFewRows = 64, kFewCols = 64, kFewDepth = 4;
+
+template <int NJ, int EPI>
+__global__ __launch_bounds__(256, 2) void ffn_gemm_few(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
+                                                       uint16_t* __restrict__ Cout, uint16_t* aux,
+                                                       const int32_t* __restrict__ seg_off,
+                                                       const int32_t* __restrict__ buf_expert, int Kdim, int Ndim) {
+  __shared__ f32x4 part[4][4][NJ][64];  // [wave][column subtile][row subtile][lane]
+  const int groups = Ndim / kFewCols, cg = blockIdx.x % groups, r = blockIdx.x / groups;
+  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
+  if (rows <= 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, kq = lane >> 4, l16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int steps = Kdim / (4 * kDmaBK);  // per wave; even (Kdim is a multiple of 256)
+  const char* pw = (const char*)Wp + ((size_t)buf_expert[r] * Ndim + (size_t)(cg >> 2) * kBN) * Kdim * 2 +
+                   (size_t)wave * steps * kPackBlock + (cg & 3) * (kFewCols * 64) + l16 * 64 +
+                   ((kq ^ ((l16 >> 1) & 3)) << 4);
+  const uint16_t* pa[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)  // rows past the segment's end repeat the last one (not stored)
+    pa[j] = A + ((size_t)seg0 + min(16 * j + l16, rows - 1)) * Kdim + (size_t)wave * steps * kDmaBK + kq * 8;
+
+  f32x4 acc[4][NJ];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 w[kFewDepth][4], x[kFewDepth][NJ];
+  auto load = [&](int u, int s) {
+    s = min(s, steps - 1);  // (steps past the last re-read it: never consumed)
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) w[u][ni] = *(const bf16x8*)(pw + (size_t)s * kPackBlock + ni * 1024);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) x[u][j] = *(const bf16x8*)(pa[j] + (size_t)s * kDmaBK);
+  };
+  auto mul = [&](int u) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int ni = 0; ni < 4; ++ni)
+        acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u][j], acc[ni][j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < kFewDepth; ++u) load(u, u);
+  int s = 0;
+  for (; s + kFewDepth <= steps; s += kFewDepth) {
+#pragma unroll
+    for (int u = 0; u < kFewDepth; ++u) {
+      mul(u);
+      load(u, s + u + kFewDepth);
+      __builtin_amdgcn_sched_barrier(0);  // (the loads stay behind the MFMAs that free their registers, and in order)
+    }
+  }
+  if (s < steps) {
+    mul(0);
+    mul(1);
+  }
+#pragma unroll
+  for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) part[wave][ni][j][lane] = acc[ni][j];
+  __syncthreads();
+  const int n = cg * kFewCols + wave * 16 + kq * 4;  // wave w finishes column subtile w
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int m = 16 * j + l16;
+    f32x4 v = part[0][wave][j][lane];
+#pragma unroll
+    for (int q = 1; q < 4; ++q) v += part[q][wave][j][lane];
+    if (m < rows) store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, n, v[0], v[1], v[2], v[3]);
+  }
+}
+
 // Weight packing (one-time): block (e, nt, kt) of 16 KiB is the LDS image of W[e][nt*256 .. +256][kt*32 .. +32]:
 // 16-byte chunk p of the block holds row p/4, k-chunk (p%4) ^ (row/2 mod 4).
 __global__ __launch_bounds__(256) void pack_weights_kernel(const uint4* __restrict__ W, uint4* __restrict__ Wp,
@@ -852,6 +936,18 @@ int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t*
   const int MT = ceil_div(rows_max, kBM), NT = Ndim / kBN;
   const long long total = (long long)E * MT * NT;
   if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+  // More than 32 rows: only where the 256-column tiles do not give every compute unit more than one, else their larger
+  // tiles read the activations less often.  Forward at 64 rows, d = 1024, h = 2048, E = 8: 53 us against 82; d = 4096,
+  // h = 8192, E = 64: 1 871 against 1 584.  At 16 rows of the latter: 1 345 against 1 415; 32 rows, d = 2048, h = 8192,
+  // E = 32, training: 2 868 against 2 952.
+  if (rows_max <= 32 || (rows_max <= kFewRows && (long long)E * NT <= cu_count())) {
+    const long long blocks = (long long)E * (Ndim / kFewCols);
+    if (blocks > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+    auto few = rows_max <= 16 ? ffn_gemm_few<1, EPI> : rows_max <= 32 ? ffn_gemm_few<2, EPI> : ffn_gemm_few<4, EPI>;
+    hipLaunchKernelGGL(few, dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
+                       (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
+    return launch_status();
+  }
   static std::atomic<uint64_t> lds_allowed[2];  // per kernel of this instantiation: devices whose LDS limit is raised
   if (E % 8 == 0 && E <= 512) {
     auto kern = ffn_gemm_dma_persistent<EPI>;

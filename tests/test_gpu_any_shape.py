@@ -82,10 +82,21 @@ def gelu_grad(torch, v):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d,h", [(48, 8), (120, 264), (192, 128), (384, 1000), (264, 11000), (11016, 72)])
 def test_expert_ffn_of_any_shape(env, d, h, dtype):
+    check_expert_ffn(env, d, h, dtype, [0, 1, 16, 17, 128, 259], 300)
+
+
+# few rows per segment with packed weights: each row-subtile variant (capacity 16, 32, 64), one to three pairs of
+# k-steps per wave (K = 256, 512, 768), the capacity above and many experts of more than 32 rows, which take the tiles
+@pytest.mark.parametrize("rows", [[0, 1, 15, 16], [32, 17, 0, 5], [64, 0, 33, 48, 1, 63, 2, 16], [65, 0, 64, 1], [33] * 64])
+@pytest.mark.parametrize("d,h", [(768, 256), (256, 768), (512, 1280)])
+def test_expert_ffn_of_few_rows(env, d, h, rows):
+    check_expert_ffn(env, d, h, "bf16", rows, max(rows), packed=True)
+
+
+def check_expert_ffn(env, d, h, dtype, rows, C, packed=False):
     """H, Z, out and the data gradients; GeLU's polynomial is within 5e-5 |ref| + 7e-6 (its derivative within 5e-5)."""
     torch, lm = env
-    rows = [0, 1, 16, 17, 128, 259]
-    E, K, C = len(rows), sum(rows), 300
+    E, K = len(rows), sum(rows)
     print(f"[ffn] d={d} h={h} {dtype} rows={rows}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(d * 5 + h)
     off, seg, be = segments(torch, rows)
@@ -100,9 +111,15 @@ def test_expert_ffn_of_any_shape(env, d, h, dtype):
     H2 = torch.empty_like(H)
     out, dsend = (torch.full((K + 40, d), float("nan"), dtype=xd, device="cuda") for _ in range(2))
     Wt_in, Wt_out = W_in.transpose(1, 2).contiguous(), W_out.transpose(1, 2).contiguous()
-    lm.locmoe_expert_ffn_in_save(desc, send, seg, be, W_in, H, Z)
-    lm.locmoe_expert_ffn_in(desc, send, seg, be, W_in, H2)
-    lm.locmoe_expert_ffn_out(desc, H, seg, be, W_out, out)
+    L_in, L_out = W_in, W_out  # in the layout that the kernels read
+    if packed:
+        desc.w_packed = 1
+        L_in, L_out = torch.empty_like(W_in), torch.empty_like(W_out)
+        lm.locmoe_pack_weights(desc, W_in, W_out, L_in, L_out)
+        lm.locmoe_pack_weights_t(desc, W_in, W_out, Wt_in, Wt_out)
+    lm.locmoe_expert_ffn_in_save(desc, send, seg, be, L_in, H, Z)
+    lm.locmoe_expert_ffn_in(desc, send, seg, be, L_in, H2)
+    lm.locmoe_expert_ffn_out(desc, H, seg, be, L_out, out)
     lm.locmoe_expert_ffn_dgrad(desc, dout, Z, seg, be, Wt_out, Wt_in, dZ, dsend)
     torch.cuda.synchronize()
     assert torch.equal(H[:K], H2[:K])
