@@ -1011,7 +1011,8 @@ inline bool packable(const locmoe_desc* p) {
 template <bool A_F32, int EPI, bool OUT_F32, int BN>
 int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
                int rows_max, int Kdim, int Ndim, hipStream_t st) {
-  if ((long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;  // the size limit of this path
+  // the size limit that fp32 storage and shapes off the 64 x 256 grid have had from the start
+  if ((A_F32 || Kdim % 64 || Ndim % 256) && (long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;
   if ((long long)Kdim * 4 * 192 > 0xFFFFFFFFLL) return LOCMOE_ERR_SHAPE;         // a tile's rows are 32-bit offsets
   const int MT = ceil_div(rows_max, AnyK<A_F32>::kBM), NT = ceil_div(Ndim, BN);
   const long long groups = (long long)E * NT, grid = (groups + 7) / 8 * 8 * MT;
