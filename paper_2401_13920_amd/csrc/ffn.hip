@@ -785,45 +785,47 @@ __global__ __launch_bounds__(kDmaThreads) void ffn_gemm_dma_persistent(const uin
 }
 
 // ---------------------------------------------------------------------------------------------
-// Few rows per segment (at most 32 or 64 by capacity or token count: launch_dma), packed weights: the weights are read once for a
-// handful of rows, so this is a stream of weights that has to keep the memory busy.  A work-group takes 64 columns of
-// one segment and all of its rows; its four waves take a quarter of K each and add their sums through LDS at the end
-// (in wave order).  Weight fragments come straight from memory into registers: 16 columns of a packed block are one
-// contiguous KiB per load, and four k-steps (16 KiB per wave) are always in flight; activation fragments come from
-// L2.  No barrier until the end, no LDS traffic in the loop, and four times as many work-groups as 256-column tiles.
-// 192 tokens, d = 1024, h = 4096, 16 experts of at most 24 rows (134 MB per weight): 23.6 + 30.4 us (5.7 and 4.4 TB/s)
-// against 32.8 + 55.3 us with the 256-column tiles of the persistent kernel, of which the second GEMM has 64.
+// Few rows per segment (at most 32 or 64 by capacity or token count: launch_dma), packed weights: the weights are read once
+// for a handful of rows, so this is a stream of weights that has to keep the memory busy.  A work-group is one wave
+// and takes 64 columns of one segment, all of its rows and all of K.  Weight fragments come straight from memory
+// into registers: 16 columns of a packed block are one contiguous KiB per load, and eight k-steps (32 KiB per wave;
+// four, 16 KiB, beside the accumulators of 64 rows) are always in flight; activation fragments come from L2.  No barrier,
+// no LDS, and four times as many work-groups as 256-column tiles.
+// Every output element is one chain of MFMAs over K in ascending order, as in the tile kernels above: an element has
+// the same bits whichever kernel makes it, so a token's result does not depend on the batch's size or capacity.
+// (Four waves that split K among them and add up at the end, which this replaces, rounded differently.)
+// us, this kernel / 256-column tiles, weights read from memory:
+//   d = 1024, h = 4096, E = 16 (134 MB per weight), first and second GEMM:
+//     16 rows 26.8 + 29.1 / 39.5 + 64.8 (5.0 and 4.6 TB/s)    32 rows 30.4 + 30.7 / 41.1 + 66.3
+//     64 rows 40.7 + 44.2 / 43.5 + 67.4
 // ---------------------------------------------------------------------------------------------
-constexpr int kFewRows = 64, kFewCols = 64, kFewDepth = 4;
+constexpr int kFewRows = 64, kFewCols = 64;
+template <int NJ> constexpr int kFewDepth = NJ == 4 ? 4 : 8;  // k-steps in flight
 
 template <int NJ, int EPI>
-__global__ __launch_bounds__(256, 2) void ffn_gemm_few(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
-                                                       uint16_t* __restrict__ Cout, uint16_t* aux,
-                                                       const int32_t* __restrict__ seg_off,
-                                                       const int32_t* __restrict__ buf_expert, int Kdim, int Ndim) {
-  __shared__ f32x4 part[4][4][NJ][64];  // [wave][column subtile][row subtile][lane]
+__global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
+                                                      uint16_t* __restrict__ Cout, uint16_t* aux,
+                                                      const int32_t* __restrict__ seg_off,
+                                                      const int32_t* __restrict__ buf_expert, int Kdim, int Ndim) {
+  constexpr int D = kFewDepth<NJ>;
   const int groups = Ndim / kFewCols, cg = blockIdx.x % groups, r = blockIdx.x / groups;
   const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
-  if (rows <= 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, kq = lane >> 4, l16 = lane & 15;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int steps = Kdim / (4 * kDmaBK);  // per wave; even (Kdim is a multiple of 256)
+  const int lane = threadIdx.x, kq = lane >> 4, l16 = lane & 15;
+  const int steps = Kdim / kDmaBK;  // a multiple of 8 (Kdim is one of 256), hence of D
   const char* pw = (const char*)Wp + ((size_t)buf_expert[r] * Ndim + (size_t)(cg >> 2) * kBN) * Kdim * 2 +
-                   (size_t)wave * steps * kPackBlock + (cg & 3) * (kFewCols * 64) + l16 * 64 +
-                   ((kq ^ ((l16 >> 1) & 3)) << 4);
+                   (cg & 3) * (kFewCols * 64) + l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4);
+  if (rows <= 0) return;
   const uint16_t* pa[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j)  // rows past the segment's end repeat the last one (not stored)
-    pa[j] = A + ((size_t)seg0 + min(16 * j + l16, rows - 1)) * Kdim + (size_t)wave * steps * kDmaBK + kq * 8;
-
+    pa[j] = A + ((size_t)seg0 + min(16 * j + l16, rows - 1)) * Kdim + kq * 8;
   f32x4 acc[4][NJ];
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 w[kFewDepth][4], x[kFewDepth][NJ];
+  bf16x8 w[D][4], x[D][NJ];
   auto load = [&](int u, int s) {
-    s = min(s, steps - 1);  // (steps past the last re-read it: never consumed)
 #pragma unroll
     for (int ni = 0; ni < 4; ++ni) w[u][ni] = *(const bf16x8*)(pw + (size_t)s * kPackBlock + ni * 1024);
 #pragma unroll
@@ -837,33 +839,26 @@ __global__ __launch_bounds__(256, 2) void ffn_gemm_few(const uint16_t* __restric
         acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u][j], acc[ni][j], 0, 0, 0);
   };
 #pragma unroll
-  for (int u = 0; u < kFewDepth; ++u) load(u, u);
-  int s = 0;
-  for (; s + kFewDepth <= steps; s += kFewDepth) {
+  for (int u = 0; u < D; ++u) load(u, u);
+  for (int s = D; s < steps; s += D) {
 #pragma unroll
-    for (int u = 0; u < kFewDepth; ++u) {
+    for (int u = 0; u < D; ++u) {
       mul(u);
-      load(u, s + u + kFewDepth);
+      load(u, s + u);
       __builtin_amdgcn_sched_barrier(0);  // (the loads stay behind the MFMAs that free their registers, and in order)
     }
   }
-  if (s < steps) {
-    mul(0);
-    mul(1);
-  }
 #pragma unroll
-  for (int ni = 0; ni < 4; ++ni)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) part[wave][ni][j][lane] = acc[ni][j];
-  __syncthreads();
-  const int n = cg * kFewCols + wave * 16 + kq * 4;  // wave w finishes column subtile w
+  for (int u = 0; u < D; ++u) mul(u);
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int m = 16 * j + l16;
-    f32x4 v = part[0][wave][j][lane];
+    if (m < rows) {
 #pragma unroll
-    for (int q = 1; q < 4; ++q) v += part[q][wave][j][lane];
-    if (m < rows) store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, n, v[0], v[1], v[2], v[3]);
+      for (int ni = 0; ni < 4; ++ni)
+        store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][j][0],
+                               acc[ni][j][1], acc[ni][j][2], acc[ni][j][3]);
+    }
   }
 }
 
@@ -943,14 +938,12 @@ int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t*
   const long long total = (long long)E * MT * NT;
   if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
   // More than 32 rows: only where the 256-column tiles do not give every compute unit more than one, else their larger
-  // tiles read the activations less often.  Forward at 64 rows, d = 1024, h = 2048, E = 8: 53 us against 82; d = 4096,
-  // h = 8192, E = 64: 1 871 against 1 584.  At 16 rows of the latter: 1 345 against 1 415; 32 rows, d = 2048, h = 8192,
-  // E = 32, training: 2 868 against 2 952.
+  // tiles read the activations less often.
   if (rows_max <= 32 || (rows_max <= kFewRows && (long long)E * NT <= cu_count())) {
     const long long blocks = (long long)E * (Ndim / kFewCols);
     if (blocks > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
     auto few = rows_max <= 16 ? ffn_gemm_few<1, EPI> : rows_max <= 32 ? ffn_gemm_few<2, EPI> : ffn_gemm_few<4, EPI>;
-    hipLaunchKernelGGL(few, dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
+    hipLaunchKernelGGL(few, dim3((unsigned)blocks), dim3(64), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
                        (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
     return launch_status();
   }

@@ -93,6 +93,40 @@ def test_expert_ffn_of_few_rows(env, d, h, rows):
     check_expert_ffn(env, d, h, "bf16", rows, max(rows), packed=True)
 
 
+def ffn_outputs(env, d, h, rows, T, C):
+    """H, Z, out, dZ and dsend of packed weights with a descriptor of T tokens and capacity C."""
+    torch, lm = env
+    E, K = len(rows), sum(rows)
+    print(f"[few] d={d} h={h} T={T} C={C} rows={rows}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d * 3 + h)
+    off, seg, be = segments(torch, rows)
+    desc = lm.make_desc(T, d, E, 1, h, C, "bf16", w_packed=True)
+    send, dout = (rows_with_nan_tail(torch, K, 0, d, torch.bfloat16, gen) for _ in range(2))
+    W_in = (torch.randn(E, h, d, generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)
+    W_out = (torch.randn(E, d, h, generator=gen, device="cuda") * h ** -0.5).to(torch.bfloat16)
+    L_in, L_out, Lt_in, Lt_out = (torch.empty_like(W_in) for _ in range(4))
+    lm.locmoe_pack_weights(desc, W_in, W_out, L_in, L_out)
+    lm.locmoe_pack_weights_t(desc, W_in, W_out, Lt_in, Lt_out)
+    H, Z, dZ = (torch.full((K, h), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    out, dsend = (torch.full((K, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    lm.locmoe_expert_ffn_in_save(desc, send, seg, be, L_in, H, Z)
+    lm.locmoe_expert_ffn_out(desc, H, seg, be, L_out, out)
+    lm.locmoe_expert_ffn_dgrad(desc, dout, Z, seg, be, Lt_out, Lt_in, dZ, dsend)
+    torch.cuda.synchronize()
+    return dict(H=H, Z=Z, out=out, dZ=dZ, dsend=dsend)
+
+
+# an element is one sum over K in one order, whichever kernel the capacity and the token count select
+@pytest.mark.parametrize("rows", [[16, 1, 15, 0], [32, 17, 0, 5, 31, 16, 1, 2], [48, 33, 0, 47], [64, 0, 33, 48, 1, 63, 2, 16]])
+@pytest.mark.parametrize("d,h", [(768, 256), (256, 2048), (512, 1280)])
+def test_bits_do_not_depend_on_capacity_or_token_count(env, d, h, rows):
+    ref = ffn_outputs(env, d, h, rows, 600, 300)
+    for T, C in ((600, max(rows)), (max(rows), 300)):
+        got = ffn_outputs(env, d, h, rows, T, C)
+        for name in ref:
+            assert env[0].equal(got[name], ref[name]), name
+
+
 def check_expert_ffn(env, d, h, dtype, rows, C, packed=False):
     """H, Z, out and the data gradients; GeLU's polynomial is within 5e-5 |ref| + 7e-6 (its derivative within 5e-5)."""
     torch, lm = env
