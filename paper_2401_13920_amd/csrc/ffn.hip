@@ -814,50 +814,51 @@ __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict
   const int steps = Kdim / kDmaBK;  // a multiple of 8 (Kdim is one of 256), hence of D
   const char* pw = (const char*)Wp + ((size_t)buf_expert[r] * Ndim + (size_t)(cg >> 2) * kBN) * Kdim * 2 +
                    (cg & 3) * (kFewCols * 64) + l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4);
-  if (rows <= 0) return;
-  const uint16_t* pa[NJ];
+  for (int m0 = 0; m0 < rows; m0 += 16 * NJ) {  // (once, unless a segment holds more rows than the descriptor says)
+    const uint16_t* pa[NJ];
 #pragma unroll
-  for (int j = 0; j < NJ; ++j)  // rows past the segment's end repeat the last one (not stored)
-    pa[j] = A + ((size_t)seg0 + min(16 * j + l16, rows - 1)) * Kdim + kq * 8;
-  f32x4 acc[4][NJ];
+    for (int j = 0; j < NJ; ++j)  // rows past the segment's end repeat the last one (not stored)
+      pa[j] = A + ((size_t)seg0 + min(m0 + 16 * j + l16, rows - 1)) * Kdim + kq * 8;
+    f32x4 acc[4][NJ];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 w[D][4], x[D][NJ];
-  auto load = [&](int u, int s) {
+      for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 w[D][4], x[D][NJ];
+    auto load = [&](int u, int s) {
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) w[u][ni] = *(const bf16x8*)(pw + (size_t)s * kPackBlock + ni * 1024);
+      for (int ni = 0; ni < 4; ++ni) w[u][ni] = *(const bf16x8*)(pw + (size_t)s * kPackBlock + ni * 1024);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) x[u][j] = *(const bf16x8*)(pa[j] + (size_t)s * kDmaBK);
-  };
-  auto mul = [&](int u) {
+      for (int j = 0; j < NJ; ++j) x[u][j] = *(const bf16x8*)(pa[j] + (size_t)s * kDmaBK);
+    };
+    auto mul = [&](int u) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni)
-        acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u][j], acc[ni][j], 0, 0, 0);
-  };
+        for (int ni = 0; ni < 4; ++ni)
+          acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u][j], acc[ni][j], 0, 0, 0);
+    };
 #pragma unroll
-  for (int u = 0; u < D; ++u) load(u, u);
-  for (int s = D; s < steps; s += D) {
+    for (int u = 0; u < D; ++u) load(u, u);
+    for (int s = D; s < steps; s += D) {
 #pragma unroll
-    for (int u = 0; u < D; ++u) {
-      mul(u);
-      load(u, s + u);
-      __builtin_amdgcn_sched_barrier(0);  // (the loads stay behind the MFMAs that free their registers, and in order)
+      for (int u = 0; u < D; ++u) {
+        mul(u);
+        load(u, s + u);
+        __builtin_amdgcn_sched_barrier(0);  // (the loads stay behind the MFMAs that free their registers, and in order)
+      }
     }
-  }
 #pragma unroll
-  for (int u = 0; u < D; ++u) mul(u);
+    for (int u = 0; u < D; ++u) mul(u);
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int m = 16 * j + l16;
-    if (m < rows) {
+    for (int j = 0; j < NJ; ++j) {
+      const int m = m0 + 16 * j + l16;
+      if (m < rows) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni)
-        store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][j][0],
-                               acc[ni][j][1], acc[ni][j][2], acc[ni][j][3]);
+        for (int ni = 0; ni < 4; ++ni)
+          store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][j][0],
+                                 acc[ni][j][1], acc[ni][j][2], acc[ni][j][3]);
+      }
     }
   }
 }

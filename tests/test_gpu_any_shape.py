@@ -127,6 +127,15 @@ def test_bits_do_not_depend_on_capacity_or_token_count(env, d, h, rows):
             assert env[0].equal(got[name], ref[name]), name
 
 
+# segments may hold more rows than min(C, T) (rows of other ranks' tokens): seg_off decides
+@pytest.mark.parametrize("T,C", [(600, 16), (600, 32), (600, 64), (16, 300)])
+def test_few_rows_kernel_covers_longer_segments(env, T, C):
+    rows = [17, 0, 130, 64, 65, 16, 1, 33]
+    ref, got = ffn_outputs(env, 256, 512, rows, 600, 300), ffn_outputs(env, 256, 512, rows, T, C)
+    for name in ref:
+        assert env[0].equal(got[name], ref[name]), name
+
+
 def check_expert_ffn(env, d, h, dtype, rows, C, packed=False):
     """H, Z, out and the data gradients; GeLU's polynomial is within 5e-5 |ref| + 7e-6 (its derivative within 5e-5)."""
     torch, lm = env
