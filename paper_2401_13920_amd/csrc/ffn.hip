@@ -785,7 +785,7 @@ __global__ __launch_bounds__(kDmaThreads) void ffn_gemm_dma_persistent(const uin
 }
 
 // ---------------------------------------------------------------------------------------------
-// Few rows per segment (at most 32 or 64 by capacity or token count: launch_dma), packed weights: the weights are read once
+// Few rows per segment (at most 64 by capacity or token count: few_rows_take), packed weights: the weights are read once
 // for a handful of rows, so this is a stream of weights that has to keep the memory busy.  A work-group is one wave
 // and takes 64 columns of one segment, all of its rows and all of K.  Weight fragments come straight from memory
 // into registers: 16 columns of a packed block are one contiguous KiB per load, and eight k-steps (32 KiB per wave;
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(kDmaThreads) void ffn_gemm_dma_persistent(const uin
 // us, this kernel / 256-column tiles, weights read from memory:
 //   d = 1024, h = 4096, E = 16 (134 MB per weight), first and second GEMM:
 //     16 rows 26.8 + 29.1 / 39.5 + 64.8 (5.0 and 4.6 TB/s)    32 rows 30.4 + 30.7 / 41.1 + 66.3
-//     64 rows 40.7 + 44.2 / 43.5 + 67.4
+//     48 rows 35.4 + 33.3 / 41.8 + 66.2                       64 rows 40.7 + 44.2 / 43.5 + 67.4
 // ---------------------------------------------------------------------------------------------
 constexpr int kFewRows = 64, kFewCols = 64;
 template <int NJ> constexpr int kFewDepth = NJ == 4 ? 4 : 8;  // k-steps in flight
@@ -861,6 +861,33 @@ __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict
       }
     }
   }
+}
+
+// Whether ffn_gemm_few takes a GEMM of at most `rows` rows per segment.  Against the tile kernels it saves each tile's
+// prologue and epilogue and fills the chip with fewer columns, but it fetches the activations four times as often, so
+// that more rows, a longer K and more tiles (`tiles` of 256 columns, all segments) speak for the tiles; those of the
+// persistent kernel cost more each than those of the kernel with one tile per work-group.  The lines lie where 38 shapes
+// (E = 4 .. 256, d = 256 .. 4096, h = 512 .. 16384) put them; us, this kernel / tiles:
+//   up to 16 rows:  2 048 tiles, K = 2048: 368 / 386;  1 024 tiles, K = 8192 (4 GiB of weights): 712 / 720;
+//                   2 048 tiles, K = 4096 (4 GiB): 751 / 746
+//   32 rows:        256 tiles, K = 8192 (1 GiB): 198 / 199;  512, K = 4096 (1 GiB): 194 / 195;  512, K = 8192: 388 / 378;
+//                   288, K = 6144: 241 / 228;  2 048, K = 2048: 403 / 403;  1 024, K = 1024: 110 / 122
+//                   one tile per work-group: 144, K = 8192: 136 / 145;  200, K = 1280: 34 / 29
+//   48 rows:        128 tiles, K = 16384: 208 / 258;  256, K = 1024: 35.4 / 41.8;  256, K = 4096: 117 / 114;
+//                   1 024, K = 1024: 128 / 129;  512, K = 2048: 119 / 112
+//                   one tile per work-group: 100, K = 10240: 134 / 161;  200, K = 1280: 41 / 30
+//   64 rows:        128 tiles, K = 8192: 121 / 139;  256, K = 1024: 40.7 / 43.5;  256, K = 4096: 132 / 117;
+//                   512, K = 1024: 73.0 / 71.7
+//                   one tile per work-group: 100, K = 10240: 153 / 161;  144, K = 8192: 184 / 149
+inline bool few_rows_take(int rows, long long tiles, int Kdim, bool persistent) {
+  const long long cus = cu_count();
+  if (rows <= 16) return Kdim <= 2048 || tiles * Kdim < cus * 32768;
+  if (rows <= 32) {
+    if (!persistent) return tiles <= cus * 5 / 8;
+    return Kdim <= 2048 || (tiles * Kdim <= cus * 8192 && (Kdim <= 4096 || tiles <= cus));
+  }
+  if (rows <= 48) return tiles <= cus / 2 || (persistent && Kdim <= 1024);
+  return rows <= kFewRows && (tiles <= cus / 2 || (persistent && Kdim <= 1024 && tiles <= cus));
 }
 
 // Weight packing: block (e, nt, kt) of 16 KiB is the LDS image of W[e][nt*256 .. +256][kt*32 .. +32]:
@@ -938,18 +965,18 @@ int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t*
   const int MT = ceil_div(rows_max, kBM), NT = Ndim / kBN;
   const long long total = (long long)E * MT * NT;
   if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-  // More than 32 rows: only where the 256-column tiles do not give every compute unit more than one, else their larger
-  // tiles read the activations less often.
-  if (rows_max <= 32 || (rows_max <= kFewRows && (long long)E * NT <= cu_count())) {
+  const bool persistent = E % 8 == 0 && E <= 512;
+  if (few_rows_take(rows_max, (long long)E * NT, Kdim, persistent)) {
     const long long blocks = (long long)E * (Ndim / kFewCols);
     if (blocks > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-    auto few = rows_max <= 16 ? ffn_gemm_few<1, EPI> : rows_max <= 32 ? ffn_gemm_few<2, EPI> : ffn_gemm_few<4, EPI>;
+    auto few = rows_max <= 16 ? ffn_gemm_few<1, EPI> : rows_max <= 32 ? ffn_gemm_few<2, EPI>
+             : rows_max <= 48 ? ffn_gemm_few<3, EPI> : ffn_gemm_few<4, EPI>;
     hipLaunchKernelGGL(few, dim3((unsigned)blocks), dim3(64), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
                        (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
     return launch_status();
   }
   static std::atomic<uint64_t> lds_allowed[2];  // per kernel of this instantiation: devices whose LDS limit is raised
-  if (E % 8 == 0 && E <= 512) {
+  if (persistent) {
     auto kern = ffn_gemm_dma_persistent<EPI>;
     if (!allow_lds((const void*)kern, kDmaSmem, lds_allowed[0])) return LOCMOE_ERR_HIP;
     // one work-group per compute unit (160 KiB of LDS each), a multiple of 8 so that every XCD gets as many
