@@ -323,7 +323,8 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(uint4* __restrict
 // 256-byte rows and fetched with the transposing LDS read; the chunk swizzle is the one of the kernel above.
 // fp32 values keep all their 24 bits: x = a + b + c with a, b, c the bf16 numbers that hold bits 0..7, 8..15 and
 // 16..23 of the significand (cut, not rounded: each remainder is exact), so that three MFMAs sum the same exact
-// products as fp32 multiplications would, in fp32.
+// products as fp32 multiplications would, in fp32.  (Bits below bf16's least subnormal, 2^-133, are lost: values under
+// 2^-109 keep fewer than 24 bits.  Infinities: see behind the loop.)
 // The contraction is short and the output large: at T = 4096, d = 1024, h = 4096, 16 experts, fp32 storage (2 523
 // kept rows) both launches write 268 MB, 56 us at the rate of a large copy, and multiply 3 x 42 GFLOP, 79 us at the
 // rate of a large matrix product; they take 138 + 126 us (one thread per output element with scalar products, which
@@ -353,6 +354,17 @@ __device__ __forceinline__ void split3(const u32x4& lo4, const u32x4& hi4, uint4
     auto two = [&](int i) { return (part[q][i] >> 16) | part[q][i + 1]; };
     out[q] = make_uint4(two(0), two(2), two(4), two(6));
   }
+}
+
+__device__ __forceinline__ bool acc_has_nan(const f32x4 (&acc)[4][4]) {
+  bool nan = false;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; v += 2) nan |= __builtin_isunordered(acc[a][b][v], acc[a][b][v + 1]);
+  return nan;
 }
 
 // One operand's share of a step for this thread: two pieces of 8 consecutive columns of one row each
@@ -462,6 +474,35 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_any_kernel(const char* __
             for (int mj = 0; mj < 4; ++mj)
               acc[ni][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[qq][ni], fm[qp][mj], acc[ni][mj], 0, 0, 0);
       buf ^= 1;
+    }
+  }
+  // An infinity in the bf16 operand times an fp32 value of at most 16 significant bits (1.0) meets a plane of zeros, and
+  // 0 * inf is a NaN where the product is an infinity.  A wave whose part of the tile holds a NaN therefore sums it again
+  // with the products themselves, row by row in fp32.  (The look at the sums costs 2 % where a segment has 160 rows.)
+  if ((P_F32 || Q_F32) && __builtin_expect(__any(acc_has_nan(acc)), 0)) {
+    int lm = wm * 64 + l16, ln = wn * 64 + kq * 4;
+    asm volatile("" : "+v"(lm), "+v"(ln));  // (none of this belongs ahead of the loop)
+    const int m = m0 + lm, n = n0 + ln;
+    auto value = [](const char* row, bool f32, int c) {
+      return f32 ? ((const float*)row)[c] : bf16_bits_to_f32(((const uint16_t*)row)[c]);
+    };
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+    for (int k = 0; k < rows; ++k) {
+      float p[4];
+#pragma unroll
+      for (int mj = 0; mj < 4; ++mj) p[mj] = value(Ps + k * ldP, P_F32, min(m + mj * 16, Mdim - 1));
+#pragma unroll
+      for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float q = value(Qs + k * ldQ, Q_F32, min(n + ni * 16 + v, Ndim - 1));
+#pragma unroll
+          for (int mj = 0; mj < 4; ++mj) acc[ni][mj][v] = fmaf(p[mj], q, acc[ni][mj][v]);
+        }
     }
   }
   // Through LDS, so that a row of the tile leaves as 256 contiguous bytes (chunk index XORed with the row)

@@ -69,6 +69,40 @@ def test_weight_gradients_of_any_shape(env, d, h, dtype):
             assert ((got.double() - ref).abs() <= bound).all(), (r, z - a)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_weight_gradients_of_infinities(env, dtype):
+    """An infinite or NaN operand gives what the products give: inf where 1.0 * inf, NaN only where 0 * inf or inf - inf.
+    The other operand's values (small whole numbers) have few significant bits."""
+    torch, lm = env
+    rows, d, h = [40, 33], 136, 264
+    E, K, C = len(rows), sum(rows), 40
+    print(f"[wgrad inf] {dtype}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    off, seg, be = segments(torch, rows)
+    ints = lambda cols, t: torch.randint(-3, 4, (K, cols), generator=gen, device="cuda").to(t)
+    send, dout = (ints(d, storage(torch, dtype)) for _ in range(2))
+    H, dZ = (ints(h, torch.bfloat16) for _ in range(2))
+    inf = float("inf")
+    for t, r, c, v in ((H, 3, 5, inf), (H, 20, 130, -inf), (H, 50, 263, inf), (H, 51, 263, -inf), (dZ, 7, 100, -inf),
+                       (dZ, 45, 0, float("nan")), (dZ, 72, 200, inf), (send, 2, 17, inf), (send, 60, 135, -inf),
+                       (dout, 11, 64, inf), (dout, 3, 70, -inf)):
+        t[r, c] = v
+    desc = lm.make_desc(600, d, E, 1, h, C, dtype)
+    dW_in = torch.empty((E, h, d), dtype=torch.bfloat16, device="cuda")
+    dW_out = torch.empty((E, d, h), dtype=torch.bfloat16, device="cuda")
+    lm.locmoe_expert_ffn_wgrad(desc, send, H, dout, dZ, seg, be, dW_in, dW_out)
+    torch.cuda.synchronize()
+    for r in range(E):
+        e, a, z = E - 1 - r, off[r], off[r + 1]
+        for got, P, Q in ((dW_in[e], dZ, send), (dW_out[e], dout, H)):
+            ref = torch.zeros(P.shape[1], Q.shape[1], dtype=torch.float64, device="cuda")
+            for k in range(a, z):
+                ref += P[k].double()[:, None] * Q[k].double()[None, :]
+            assert ref.isinf().any()
+            # finite sums are whole numbers below 2^9: exact in fp32, rounded once to bf16
+            assert torch.equal(got.double().nan_to_num(12345.0), ref.to(torch.bfloat16).double().nan_to_num(12345.0)), r
+
+
 def gelu(torch, v):
     return 0.5 * v * torch.erfc(-v * 2.0 ** -0.5)
 
