@@ -98,7 +98,10 @@ __device__ __forceinline__ void store_quad(void* C, uint16_t* aux, size_t row, i
 //
 // Segments here are short (a hundred rows or so), so that the weight stream is what has to keep flowing: the m-tiles
 // of one weight tile run side by side on one XCD (one L2), a segment's rows are spread evenly over its m-tiles, and
-// weight tiles are dealt to the XCDs in turn (a long segment's work is spread over all of them).
+// weight tiles are dealt to the XCDs in turn (a long segment's work is spread over all of them).  Where all segments are
+// full and 256 x 256 tiles would make one full turn of the chip, such tiles are still up to 8 % faster (E = 64, K = 2048,
+// N = 1024, 256 rows: 109 us against 118; E = 16, K = 4096, N = 1024, 1 024 rows: 165 against 175); with the same capacity and
+// uneven segments (97 against 97, 156 against 120) they are not, and the host does not know the rows.
 // What bounds it is the way from L2 to LDS: variants with other tiles moved 8 to 10 TB/s there (all copies of all
 // work-groups over the kernel's time), so a larger tile, that moves less, is faster as long as two work-groups fit:
 // at d = 1600, h = 6400, 40 experts, 5 003 tokens (at most 157 rows per expert) the two GEMMs take 291 + 349 us with
@@ -114,6 +117,7 @@ constexpr int kAnyLds = 80 * 1024;  // half of a compute unit's
 template <bool A_F32>
 struct AnyK {
   static constexpr int kBM = A_F32 ? 128 : 192;           // rows of an m-tile at most
+  static constexpr int kFine = 128;                       // ... of a short list
   static constexpr int kBK = A_F32 ? 32 : 64;
   static constexpr int kARow = 128;                       // bytes of an activation row in LDS: one line
   static constexpr int kWRow = kBK * 2;
@@ -260,32 +264,104 @@ __device__ __forceinline__ void any_tile(const char* __restrict__ A, const char*
   }
 }
 
-template <bool A_F32, int EPI, bool OUT_F32, int BN>
+// Inclusive sum over the wave's lanes
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1, 2, 4, 8: within 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Weight tile nt of segment r is number r NT + nt and belongs to XCD (r NT + nt) mod 8 (work-group ids congruent mod 8 run
+// on one XCD).  Without LIST no segment has more than kBM rows: a work-group takes a whole weight tile.  With LIST the
+// work-groups of an XCD take the live m-tiles of its weight tiles, those of one weight tile in a row, by their number
+// in that list, which every wave counts out for itself from seg_off.  (A work-group per possible m-tile, most of them
+// without rows, fills the compute units unevenly: work-groups go to the shader engines in turn, and where every second
+// one leaves at once, half of the engines stay empty.  Rows even in 0 .. 224, d = 2048, h = 8192, E = 32: 340 + 363 us so,
+// 261 + 267 from the list; 0 .. 640: 627 + 610 and 408 + 414.  Equal segments: 1 % less to 5 % more time, for the counting.)
+// A list that fills the XCD's `slots` (two per compute unit) once or twice is cut into m-tiles of kFine rows where
+// that does not take another turn: rows even in 0 .. 256, d = 4096, h = 16384, E = 8, second GEMM: 389 us with up to 192
+// rows, 308 with up to 128.
+template <bool A_F32, int EPI, bool OUT_F32, int BN, bool LIST>
 __global__ __launch_bounds__(kAnyThreads, 2) void ffn_gemm_any(const char* __restrict__ A, const char* __restrict__ W,
                                                                void* __restrict__ Cout, uint16_t* aux,
                                                                const int32_t* __restrict__ seg_off,
                                                                const int32_t* __restrict__ buf_expert, int Kdim,
-                                                               int Ndim, int MT, int NT, int groups) {
+                                                               int Ndim, int NT, int E, int slots) {
+  constexpr int kBM = AnyK<A_F32>::kBM, kFine = AnyK<A_F32>::kFine;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  // work-group id -> (XCD, m-tile, weight tile): ids congruent mod 8 run on one XCD
-  const int seq = blockIdx.x >> 3, mt = seq % MT, grp = (seq / MT) * 8 + (blockIdx.x & 7);
-  if (grp >= groups) return;
-  const int n0 = (grp % NT) * BN, r = grp / NT;
-  const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
-  const int mtc = (rows + AnyK<A_F32>::kBM - 1) / AnyK<A_F32>::kBM;
-  if (mt >= mtc) return;
-  const int span = ((rows + mtc - 1) / mtc + 15) & ~15, m0 = mt * span;
-  const int left = __builtin_amdgcn_readfirstlane(min(rows - m0, span));
-  if (left <= 0) return;  // (rounding the span up to whole subtiles can leave the last tile without rows)
-  const char* At = A + ((size_t)seg0 + m0) * Kdim * (A_F32 ? 4 : 2);
-  const char* Wt = W + ((size_t)buf_expert[r] * Ndim + n0) * Kdim * 2;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const int xcd = blockIdx.x & 7, lane = threadIdx.x & 63;
+  // segments r0 .. r0 + 63, one per lane: first row, rows, expert, inclusive sum of their tiles on this XCD (`all`: the
+  // last of these); `before` tiles precede them
+  int r0 = 0, before = 0, seg_l = 0, rows_l = 0, e_l = 0, cum = 0, all = 0;
+  bool fine = false;
+  auto look = [&]() {
+    const int rl = r0 + lane;
+    seg_l = seg_off[min(rl, E)];
+    rows_l = seg_off[min(rl + 1, E)] - seg_l;
+    e_l = buf_expert[min(rl, E - 1)];
+    const int first = (xcd - rl * NT) & 7, cols = first < NT ? (NT - 1 - first) / 8 + 1 : 0;  // weight tiles on this XCD
+    cum = wave_scan(cols * ((rows_l + kBM - 1) / kBM));
+    all = __builtin_amdgcn_readlane(cum, 63);
+    if (kFine < kBM && E <= 64 && all <= 2 * slots) {
+      const int cum_f = wave_scan(cols * ((rows_l + kFine - 1) / kFine)), all_f = __builtin_amdgcn_readlane(cum_f, 63);
+      if (all_f <= (all <= slots ? slots : 2 * slots)) {
+        fine = true;
+        cum = cum_f;
+        all = all_f;
+      }
+    }
+  };
+  if (LIST) look();
+  int mt = 0;
+  for (int q = blockIdx.x >> 3;;) {
+    int seg0, rows, e, mtc, nt;
+    if (!LIST) {
+      const int grp = q * 8 + xcd, r = grp / NT;
+      if (r >= E) return;
+      seg0 = seg_off[r];
+      rows = seg_off[r + 1] - seg0;
+      e = buf_expert[r];
+      mtc = (rows + kBM - 1) / kBM;  // (more than one if a segment holds more rows than the descriptor says)
+      nt = grp - r * NT;
+    } else {
+      while (q >= before + all) {
+        if (r0 + 64 >= E) return;
+        before += all;
+        r0 += 64;
+        look();
+      }
+      const int k = __builtin_popcountll(__ballot(before + cum <= q));
+      const int in = q - before - (k ? __builtin_amdgcn_readlane(cum, k - 1) : 0);
+      seg0 = __builtin_amdgcn_readlane(seg_l, k);
+      rows = __builtin_amdgcn_readlane(rows_l, k);
+      e = __builtin_amdgcn_readlane(e_l, k);
+      mtc = fine ? (rows + kFine - 1) / kFine : (rows + kBM - 1) / kBM;
+      const int g = in / mtc;
+      mt = in - g * mtc;
+      nt = ((xcd - (r0 + k) * NT) & 7) + 8 * g;
+    }
+    if (rows > 0) {
+      // rows evenly over the m-tiles, in whole subtiles: at most kBM (a multiple of 16), and the last tile has some
+      const int span = ((rows + mtc - 1) / mtc + 15) & ~15, m0 = mt * span, n0 = nt * BN;
+      const int left = __builtin_amdgcn_readfirstlane(min(rows - m0, span));
+      const char* At = A + ((size_t)seg0 + m0) * Kdim * (A_F32 ? 4 : 2);
+      const char* Wt = W + ((size_t)e * Ndim + n0) * Kdim * 2;
 #define LOCMOE_ANY_TILE(NJ) \
   any_tile<A_F32, EPI, OUT_F32, BN, NJ>(At, Wt, Cout, aux, (size_t)seg0 + m0, left, n0, Kdim, Ndim, lds0, smem)
-  if (left <= 64) LOCMOE_ANY_TILE(2);
-  else if (A_F32 || left <= 128) LOCMOE_ANY_TILE(4);
-  else if constexpr (!A_F32) LOCMOE_ANY_TILE(6);
+      if (left <= 64) LOCMOE_ANY_TILE(2);
+      else if (A_F32 || left <= 128) LOCMOE_ANY_TILE(4);
+      else if constexpr (!A_F32) LOCMOE_ANY_TILE(6);
 #undef LOCMOE_ANY_TILE
+    }
+    if (LIST) q += gridDim.x >> 3;
+    else if (++mt >= mtc) return;
+    __syncthreads();  // (the next tile's copies overwrite what this one's last step read)
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1031,31 +1107,36 @@ inline bool packable(const locmoe_desc* p) {
 
 template <bool A_F32, int EPI, bool OUT_F32, int BN>
 int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-               int rows_max, int Kdim, int Ndim, hipStream_t st) {
+               int rows_max, int T, int Kdim, int Ndim, hipStream_t st) {
   // the size limit that fp32 storage and shapes off the 64 x 256 grid have had from the start
   if ((A_F32 || Kdim % 64 || Ndim % 256) && (long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;
   if ((long long)Kdim * 4 * 192 > 0xFFFFFFFFLL) return LOCMOE_ERR_SHAPE;         // a tile's rows are 32-bit offsets
-  const int MT = ceil_div(rows_max, AnyK<A_F32>::kBM), NT = ceil_div(Ndim, BN);
-  const long long groups = (long long)E * NT, grid = (groups + 7) / 8 * 8 * MT;
+  constexpr int kBM = AnyK<A_F32>::kBM, kFine = AnyK<A_F32>::kFine;
+  const int NT = ceil_div(Ndim, BN);
+  const bool list = rows_max > kBM;
+  // m-tiles: at most those of full segments, and at most a partial one per segment beside those that T rows fill
+  const long long mtiles = std::min((long long)E * ceil_div(rows_max, kFine), (long long)E + T / kFine);
+  const long long grid = list ? 8 * ceil_div(NT, 8) * mtiles : ((long long)E * NT + 7) / 8 * 8;
   if (grid > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-  auto kern = ffn_gemm_any<A_F32, EPI, OUT_F32, BN>;
-  static std::atomic<uint64_t> lds_allowed;
-  if (!allow_lds((const void*)kern, kAnyLds, lds_allowed)) return LOCMOE_ERR_HIP;
+  auto kern = list ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true> : ffn_gemm_any<A_F32, EPI, OUT_F32, BN, false>;
+  static std::atomic<uint64_t> lds_allowed[2];
+  if (!allow_lds((const void*)kern, kAnyLds, lds_allowed[list])) return LOCMOE_ERR_HIP;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kAnyThreads), kAnyLds, st, (const char*)A, (const char*)W, C,
-                     (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, MT, NT, (int)groups);
+                     (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, NT, E, cu_count() / 4);
   return launch_status();
 }
 
 template <bool A_F32, int EPI, bool OUT_F32>
 int launch_gemm(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-                int rows_max, int rows_even, int Kdim, int Ndim, hipStream_t st) {
+                int rows_max, int T, int Kdim, int Ndim, hipStream_t st) {
   // 128 columns per tile, or 64 where that leaves some of the chip's work-group slots (two per compute unit) empty.
   // The forward at 2 048 rows per expert (d = 2048, h = 8192, E = 8): 1 160 us with 128 columns in both GEMMs, 1 413 with 64
   // in the second; the second GEMM at d = 1024, h = 4096, E = 16, 158 rows (64 columns: 256 tiles): 76 us against 83 to 92.
+  const int rows_even = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
   const long long tiles = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows_even, AnyK<A_F32>::kBM);
   if (tiles >= 2 * cu_count())
-    return launch_any<A_F32, EPI, OUT_F32, 128>(A, W, C, aux, seg_off, buf_expert, E, rows_max, Kdim, Ndim, st);
-  return launch_any<A_F32, EPI, OUT_F32, 64>(A, W, C, aux, seg_off, buf_expert, E, rows_max, Kdim, Ndim, st);
+    return launch_any<A_F32, EPI, OUT_F32, 128>(A, W, C, aux, seg_off, buf_expert, E, rows_max, T, Kdim, Ndim, st);
+  return launch_any<A_F32, EPI, OUT_F32, 64>(A, W, C, aux, seg_off, buf_expert, E, rows_max, T, Kdim, Ndim, st);
 }
 
 }  // namespace
@@ -1071,16 +1152,15 @@ template <int EPI>
 int gemm_d_to_h(const locmoe_desc* desc, const void* A, const int32_t* seg_off, const int32_t* buf_expert,
                 const void* W, void* Cbf16, void* aux, unsigned int* queue, void* stream) {
   const int rows_max = desc->C < desc->T ? desc->C : desc->T;  // kept[e] <= min(C, T)
-  const int rows_even = std::min(rows_max, ceil_div(desc->T, desc->E));  // with evenly spread tokens
   if (desc->w_packed) {
     if (desc->x_dtype != LOCMOE_BF16 || !packable(desc)) return LOCMOE_ERR_ARG;
     return launch_dma<EPI>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->d, desc->h, queue,
                            as_stream(stream));
   }
   if (desc->x_dtype == LOCMOE_F32)
-    return launch_gemm<true, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->d, desc->h,
+    return launch_gemm<true, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h,
                                          as_stream(stream));
-  return launch_gemm<false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->d, desc->h,
+  return launch_gemm<false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h,
                                         as_stream(stream));
 }
 
@@ -1089,16 +1169,15 @@ int gemm_d_to_h(const locmoe_desc* desc, const void* A, const int32_t* seg_off, 
 int gemm_h_to_d(const locmoe_desc* desc, const void* A, const int32_t* seg_off, const int32_t* buf_expert,
                 const void* W, void* C, unsigned int* queue, void* stream) {
   const int rows_max = desc->C < desc->T ? desc->C : desc->T;
-  const int rows_even = std::min(rows_max, ceil_div(desc->T, desc->E));
   if (desc->w_packed) {
     if (desc->x_dtype != LOCMOE_BF16 || !packable(desc)) return LOCMOE_ERR_ARG;
     return launch_dma<kEpiNone>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->h, desc->d, queue,
                                 as_stream(stream));
   }
   if (desc->x_dtype == LOCMOE_F32)
-    return launch_gemm<false, kEpiNone, true>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->h,
+    return launch_gemm<false, kEpiNone, true>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h,
                                               desc->d, as_stream(stream));
-  return launch_gemm<false, kEpiNone, false>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, rows_even, desc->h,
+  return launch_gemm<false, kEpiNone, false>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h,
                                              desc->d, as_stream(stream));
 }
 

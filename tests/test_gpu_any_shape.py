@@ -127,22 +127,27 @@ def test_expert_ffn_of_few_rows(env, d, h, rows):
     check_expert_ffn(env, d, h, "bf16", rows, max(rows), packed=True)
 
 
-def ffn_outputs(env, d, h, rows, T, C):
-    """H, Z, out, dZ and dsend of packed weights with a descriptor of T tokens and capacity C."""
+def ffn_outputs(env, d, h, rows, T, C, dtype="bf16", packed=True):
+    """H, Z, out, dZ and dsend with a descriptor of T tokens and capacity C."""
     torch, lm = env
     E, K = len(rows), sum(rows)
-    print(f"[few] d={d} h={h} T={T} C={C} rows={rows}", flush=True)
+    print(f"[ffn T, C] d={d} h={h} T={T} C={C} {dtype} packed={packed} rows={rows}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(d * 3 + h)
     off, seg, be = segments(torch, rows)
-    desc = lm.make_desc(T, d, E, 1, h, C, "bf16", w_packed=True)
-    send, dout = (rows_with_nan_tail(torch, K, 0, d, torch.bfloat16, gen) for _ in range(2))
+    xd = storage(torch, dtype)
+    desc = lm.make_desc(T, d, E, 1, h, C, dtype, w_packed=packed)
+    send, dout = (rows_with_nan_tail(torch, K, 0, d, xd, gen) for _ in range(2))
     W_in = (torch.randn(E, h, d, generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)
     W_out = (torch.randn(E, d, h, generator=gen, device="cuda") * h ** -0.5).to(torch.bfloat16)
-    L_in, L_out, Lt_in, Lt_out = (torch.empty_like(W_in) for _ in range(4))
-    lm.locmoe_pack_weights(desc, W_in, W_out, L_in, L_out)
-    lm.locmoe_pack_weights_t(desc, W_in, W_out, Lt_in, Lt_out)
+    L_in, L_out, Lt_in, Lt_out = W_in, W_out, torch.empty_like(W_out), torch.empty_like(W_in)
+    if packed:
+        L_in, L_out = torch.empty_like(W_in), torch.empty_like(W_out)
+        lm.locmoe_pack_weights(desc, W_in, W_out, L_in, L_out)
+        lm.locmoe_pack_weights_t(desc, W_in, W_out, Lt_in, Lt_out)
+    else:
+        lm.locmoe_transpose_weights(desc, W_in, W_out, Lt_in, Lt_out)
     H, Z, dZ = (torch.full((K, h), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(3))
-    out, dsend = (torch.full((K, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    out, dsend = (torch.full((K, d), float("nan"), dtype=xd, device="cuda") for _ in range(2))
     lm.locmoe_expert_ffn_in_save(desc, send, seg, be, L_in, H, Z)
     lm.locmoe_expert_ffn_out(desc, H, seg, be, L_out, out)
     lm.locmoe_expert_ffn_dgrad(desc, dout, Z, seg, be, Lt_out, Lt_in, dZ, dsend)
@@ -168,6 +173,26 @@ def test_few_rows_kernel_covers_longer_segments(env, T, C):
     ref, got = ffn_outputs(env, 256, 512, rows, 600, 300), ffn_outputs(env, 256, 512, rows, T, C)
     for name in ref:
         assert env[0].equal(got[name], ref[name]), name
+
+
+# row-major weights: a work-group per weight tile (min(C, T) <= 128) and lists of tiles, shorter and longer than the grid
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,C", [(600, 64), (60, 3000), (260, 3000)])
+def test_row_major_kernel_covers_longer_segments(env, T, C, dtype):
+    rows = [17, 0, 1300, 64, 193, 16, 400, 33]
+    ref, got = (ffn_outputs(env, 264, 520, rows, *tc, dtype, packed=False) for tc in ((6000, 3000), (T, C)))
+    for name in ref:
+        assert env[0].equal(got[name], ref[name]), name
+
+
+# more segments than a wave has lanes, empty ones among them, weight tiles that divide by 8 and that do not; a list that
+# fills the chip once in tiles of 128 rows, one that does not, and a long one
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,h,rows", [(280, 264, [0, 300, 1, 193, 192, 0, 129] * 10), (1024, 1024, [0, 256, 129, 0] * 32),
+                                      (64, 8200, [200, 0, 131, 600]), (1032, 2048, [1000, 0, 30, 385]),
+                                      (264, 20000, [0, 777, 0, 0, 0, 0, 0, 193])])
+def test_row_major_lists_of_tiles(env, d, h, rows, dtype):
+    check_expert_ffn(env, d, h, dtype, rows, max(rows))
 
 
 def check_expert_ffn(env, d, h, dtype, rows, C, packed=False):
