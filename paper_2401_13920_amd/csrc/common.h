@@ -125,6 +125,10 @@ __device__ __forceinline__ void dma_1k(const void* sbase, uint32_t voff, uint32_
                "s"(lds_base)
                : "memory", "m0");
 }
+// The same copy from a 64-bit address per lane
+__device__ __forceinline__ void dma_1k_far(const void* src, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_base) : "memory", "m0");
+}
 // The same copy in two parts, for runs of copies whose LDS destinations lie within 4 KiB of a common base: M0 is
 // written once (dma_base) and each copy adds an immediate offset of sub KiB (dma_1k_sub).  The hardware adds the
 // immediate to the LDS address and to the global address alike (M0 + imm + 16 l and sbase + voff + imm), so

@@ -148,8 +148,9 @@ __device__ __forceinline__ void wait_younger(int n) {
   }
 }
 
-// One tile of at most 32 NJ rows.  rows_left: live rows from the tile's first (>= 1).
-template <bool A_F32, int EPI, bool OUT_F32, int BN, int NJ>
+// One tile of at most 32 NJ rows.  rows_left: live rows from the tile's first (>= 1).  FAR: a tile's rows reach further
+// than 32-bit offsets do.
+template <bool A_F32, int EPI, bool OUT_F32, int BN, int NJ, bool FAR>
 __device__ __forceinline__ void any_tile(const char* __restrict__ A, const char* __restrict__ W, void* __restrict__ Cout,
                                          uint16_t* aux, size_t crow0, int rows_left, int n0, int Kdim, int Ndim,
                                          uint32_t lds0, char* smem) {
@@ -165,23 +166,28 @@ __device__ __forceinline__ void any_tile(const char* __restrict__ A, const char*
 
   // copies: block wave + 4 i of an operand's stage; rows past the segment's end and columns past the last repeat the
   // last one (not stored)
-  const uint32_t ldA = (uint32_t)Kdim * (A_F32 ? 4 : 2), ldW = (uint32_t)Kdim * 2;
-  uint32_t rowA[CA], rowW[CW];
+  using off_t = std::conditional_t<FAR, uint64_t, uint32_t>;
+  const off_t ldA = (off_t)Kdim * (A_F32 ? 4 : 2), ldW = (off_t)Kdim * 2;
+  off_t rowA[CA], rowW[CW];
 #pragma unroll
   for (int i = 0; i < CA; ++i)
-    rowA[i] = (uint32_t)min((wave + 4 * i) * kARows + lane / (64 / kARows), rows_left - 1) * ldA;
+    rowA[i] = (off_t)min((wave + 4 * i) * kARows + lane / (64 / kARows), rows_left - 1) * ldA;
 #pragma unroll
   for (int i = 0; i < CW; ++i)
-    rowW[i] = (uint32_t)min((wave + 4 * i) * kWRows + lane / (64 / kWRows), Ndim - n0 - 1) * ldW;
+    rowW[i] = (off_t)min((wave + 4 * i) * kWRows + lane / (64 / kWRows), Ndim - n0 - 1) * ldW;
   const uint32_t chA = any_chunk<S::kARow>(wave, lane), chW = any_chunk<S::kWRow>(wave, lane);
-  const int KT = (Kdim + S::kBK - 1) / S::kBK;
+  const int KT = (Kdim - 1) / S::kBK + 1;
+  auto copy = [](const char* base, off_t off, uint32_t lds) {
+    if constexpr (FAR) dma_1k_far(base + off, lds);
+    else dma_1k(base, off, lds);
+  };
   auto issue = [&](int s, int stage) {
     const uint32_t base = lds0 + (uint32_t)stage * S::kStage + (uint32_t)wave * 1024;
-    const uint32_t ka = min((uint32_t)s * S::kARow + chA, ldA - 16), kw = min((uint32_t)s * S::kWRow + chW, ldW - 16);
+    const off_t ka = min((off_t)s * S::kARow + chA, ldA - 16), kw = min((off_t)s * S::kWRow + chW, ldW - 16);
 #pragma unroll
-    for (int i = 0; i < CW; ++i) dma_1k(W, rowW[i] + kw, base + S::kABytes + i * 4096);
+    for (int i = 0; i < CW; ++i) copy(W, rowW[i] + kw, base + S::kABytes + i * 4096);
 #pragma unroll
-    for (int i = 0; i < CA; ++i) dma_1k(A, rowA[i] + ka, base + i * 4096);
+    for (int i = 0; i < CA; ++i) copy(A, rowA[i] + ka, base + i * 4096);
   };
 
   // fragment addresses inside a stage: lane l reads the 8 values k = 8 (l/16) .. +7 of row l%16 (two chunks if fp32)
@@ -212,11 +218,11 @@ __device__ __forceinline__ void any_tile(const char* __restrict__ A, const char*
     if (s == KT - 1 && (Kdim & (S::kBK - 1))) {
       char* st = smem + stage * S::kStage + wave * 1024 + lane * 16;
       const uint4 zero = make_uint4(0, 0, 0, 0);
-      if ((uint32_t)s * S::kARow + chA >= ldA) {
+      if ((off_t)s * S::kARow + chA >= ldA) {
 #pragma unroll
         for (int i = 0; i < CA; ++i) *(uint4*)(st + i * 4096) = zero;
       }
-      if ((uint32_t)s * S::kWRow + chW >= ldW) {
+      if ((off_t)s * S::kWRow + chW >= ldW) {
 #pragma unroll
         for (int i = 0; i < CW; ++i) *(uint4*)(st + S::kABytes + i * 4096) = zero;
       }
@@ -285,7 +291,7 @@ __device__ __forceinline__ int wave_scan(int v) {
 // A list that fills the XCD's `slots` (two per compute unit) once or twice is cut into m-tiles of kFine rows where
 // that does not take another turn: rows even in 0 .. 256, d = 4096, h = 16384, E = 8, second GEMM: 389 us with up to 192
 // rows, 308 with up to 128.
-template <bool A_F32, int EPI, bool OUT_F32, int BN, bool LIST>
+template <bool A_F32, int EPI, bool OUT_F32, int BN, bool LIST, bool FAR>
 __global__ __launch_bounds__(kAnyThreads, 2) void ffn_gemm_any(const char* __restrict__ A, const char* __restrict__ W,
                                                                void* __restrict__ Cout, uint16_t* aux,
                                                                const int32_t* __restrict__ seg_off,
@@ -352,7 +358,7 @@ __global__ __launch_bounds__(kAnyThreads, 2) void ffn_gemm_any(const char* __res
       const char* At = A + ((size_t)seg0 + m0) * Kdim * (A_F32 ? 4 : 2);
       const char* Wt = W + ((size_t)e * Ndim + n0) * Kdim * 2;
 #define LOCMOE_ANY_TILE(NJ) \
-  any_tile<A_F32, EPI, OUT_F32, BN, NJ>(At, Wt, Cout, aux, (size_t)seg0 + m0, left, n0, Kdim, Ndim, lds0, smem)
+  any_tile<A_F32, EPI, OUT_F32, BN, NJ, FAR>(At, Wt, Cout, aux, (size_t)seg0 + m0, left, n0, Kdim, Ndim, lds0, smem)
       if (left <= 64) LOCMOE_ANY_TILE(2);
       else if (A_F32 || left <= 128) LOCMOE_ANY_TILE(4);
       else if constexpr (!A_F32) LOCMOE_ANY_TILE(6);
@@ -1110,17 +1116,18 @@ int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* 
                int rows_max, int T, int Kdim, int Ndim, hipStream_t st) {
   // the size limit that fp32 storage and shapes off the 64 x 256 grid have had from the start
   if ((A_F32 || Kdim % 64 || Ndim % 256) && (long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;
-  if ((long long)Kdim * 4 * 192 > 0xFFFFFFFFLL) return LOCMOE_ERR_SHAPE;         // a tile's rows are 32-bit offsets
   constexpr int kBM = AnyK<A_F32>::kBM, kFine = AnyK<A_F32>::kFine;
+  const bool far = (long long)Kdim * (A_F32 ? 4 : 2) * kBM > 0xFFFFFFFFLL;  // (the weight rows' offsets are no larger)
   const int NT = ceil_div(Ndim, BN);
-  const bool list = rows_max > kBM;
+  const bool list = rows_max > kBM || far;
   // m-tiles: at most those of full segments, and at most a partial one per segment beside those that T rows fill
   const long long mtiles = std::min((long long)E * ceil_div(rows_max, kFine), (long long)E + T / kFine);
   const long long grid = list ? 8 * ceil_div(NT, 8) * mtiles : ((long long)E * NT + 7) / 8 * 8;
   if (grid > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-  auto kern = list ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true> : ffn_gemm_any<A_F32, EPI, OUT_F32, BN, false>;
-  static std::atomic<uint64_t> lds_allowed[2];
-  if (!allow_lds((const void*)kern, kAnyLds, lds_allowed[list])) return LOCMOE_ERR_HIP;
+  auto kern = far ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true, true>
+            : list ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true, false> : ffn_gemm_any<A_F32, EPI, OUT_F32, BN, false, false>;
+  static std::atomic<uint64_t> lds_allowed[3];
+  if (!allow_lds((const void*)kern, kAnyLds, lds_allowed[list + far])) return LOCMOE_ERR_HIP;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kAnyThreads), kAnyLds, st, (const char*)A, (const char*)W, C,
                      (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, NT, E, cu_count() / 4);
   return launch_status();

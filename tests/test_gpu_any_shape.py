@@ -195,6 +195,39 @@ def test_row_major_lists_of_tiles(env, d, h, rows, dtype):
     check_expert_ffn(env, d, h, dtype, rows, max(rows))
 
 
+# rows of more than 2^32 / 768 values (5.6 M), and so long that a tile's rows span more than 4 GiB.  The operands are zero
+# but for a few columns (the first and the last ones among them), so that the sums have few terms.
+@pytest.mark.parametrize("dtype,d,rows", [("bf16", 5_600_008, 17), ("bf16", 11_200_008, 192), ("f32", 8_400_008, 128)])
+def test_expert_ffn_of_very_long_rows(env, dtype, d, rows):
+    torch, lm = env
+    print(f"[ffn long rows] d={d} {dtype} rows={rows}", flush=True)
+    h, n = 8, 300
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    cols = torch.cat([torch.arange(8, device="cuda"), torch.randint(8, d - 8, (n - 16,), generator=gen, device="cuda"),
+                      torch.arange(d - 8, d, device="cuda")]).unique()
+    xd = storage(torch, dtype)
+    off, seg, be = segments(torch, [rows])
+    desc = lm.make_desc(rows, d, 1, 1, h, rows, dtype)
+    send = torch.zeros(rows, d, dtype=xd, device="cuda")
+    send[:, cols] = torch.randn(rows, len(cols), generator=gen, device="cuda").to(xd)
+    W_in = torch.zeros(1, h, d, dtype=torch.bfloat16, device="cuda")
+    W_in[:, :, cols] = torch.randn(1, h, len(cols), generator=gen, device="cuda").to(torch.bfloat16)
+    W_out = torch.randn(1, d, h, generator=gen, device="cuda").to(torch.bfloat16)
+    H, Z = (torch.full((rows, h), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    out = torch.full((rows, d), float("nan"), dtype=xd, device="cuda")
+    lm.locmoe_expert_ffn_in_save(desc, send, seg, be, W_in, H, Z)
+    lm.locmoe_expert_ffn_out(desc, H, seg, be, W_out, out)
+    torch.cuda.synchronize()
+    b16, u = 2.0 ** -8 * (1 + 2.0 ** -8), 2.0 ** -23
+    x, w = send[:, cols].to(torch.bfloat16).double(), W_in[0, :, cols].double()
+    ref, bound = x @ w.T, len(cols) * u * (x.abs() @ w.abs().T)
+    assert ((Z.double() - ref).abs() <= b16 * ref.abs() + 1.01 * bound).all()
+    for r in range(rows):
+        hr = H[r].double()
+        ref, bound = W_out[0].double() @ hr, h * u * (W_out[0].double().abs() @ hr.abs())
+        assert ((out[r].double() - ref).abs() <= (b16 if dtype == "bf16" else u) * ref.abs() + 1.01 * bound).all(), r
+
+
 def check_expert_ffn(env, d, h, dtype, rows, C, packed=False):
     """H, Z, out and the data gradients; GeLU's polynomial is within 5e-5 |ref| + 7e-6 (its derivative within 5e-5)."""
     torch, lm = env
