@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kAnyThreads, 2) void ffn_gemm_any(const char* __res
   };
   if (LIST) look();
   int mt = 0;
-  for (int q = blockIdx.x >> 3;;) {
+  for (int q = (blockIdx.y * gridDim.x + blockIdx.x) >> 3;;) {
     int seg0, rows, e, mtc, nt;
     if (!LIST) {
       const int grp = q * 8 + xcd, r = grp / NT;
@@ -1124,11 +1124,13 @@ int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* 
   const long long mtiles = std::min((long long)E * ceil_div(rows_max, kFine), (long long)E + T / kFine);
   const long long grid = list ? 8 * ceil_div(NT, 8) * mtiles : ((long long)E * NT + 7) / 8 * 8;
   if (grid > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+  // a launch takes fewer than 2^32 threads along x: what is beyond 2^23 work-groups goes to y (a list is walked in turns)
+  const unsigned gx = (unsigned)std::min<long long>(grid, 1 << 23), gy = list ? 1 : (unsigned)((grid + gx - 1) / gx);
   auto kern = far ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true, true>
             : list ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true, false> : ffn_gemm_any<A_F32, EPI, OUT_F32, BN, false, false>;
   static std::atomic<uint64_t> lds_allowed[3];
   if (!allow_lds((const void*)kern, kAnyLds, lds_allowed[list + far])) return LOCMOE_ERR_HIP;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kAnyThreads), kAnyLds, st, (const char*)A, (const char*)W, C,
+  hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(kAnyThreads), kAnyLds, st, (const char*)A, (const char*)W, C,
                      (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, NT, E, cu_count() / 4);
   return launch_status();
 }

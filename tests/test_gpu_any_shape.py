@@ -228,6 +228,32 @@ def test_expert_ffn_of_very_long_rows(env, dtype, d, rows):
         assert ((out[r].double() - ref).abs() <= (b16 if dtype == "bf16" else u) * ref.abs() + 1.01 * bound).all(), r
 
 
+def test_expert_ffn_of_very_many_columns(env):
+    """8 experts of 2^28 columns: 2^24 tiles of 128, more than one launch dimension takes."""
+    torch, lm = env
+    E, d, h = 8, 8, 1 << 28
+    print(f"[ffn many columns] E={E} d={d} h={h}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    off, seg, be = segments(torch, [1] * E)
+    desc = lm.make_desc(E, d, E, 1, h, 1, "bf16")
+    send = torch.randn(E, d, generator=gen, device="cuda").to(torch.bfloat16)
+    W_in = torch.empty(E, h, d, dtype=torch.bfloat16, device="cuda")
+    for e in range(E):
+        W_in[e].normal_(0.0, 1.0, generator=gen)
+    H = torch.full((E, h), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lm.locmoe_expert_ffn_in(desc, send, seg, be, W_in, H)
+    torch.cuda.synchronize()
+    b16, u, step = 2.0 ** -8 * (1 + 2.0 ** -8), 2.0 ** -23, 1 << 24
+    for r in range(E):
+        x = send[r].double()
+        for n in range(0, h, step):
+            w = W_in[E - 1 - r, n:n + step].double()
+            z, zb = (w * x).sum(1), d * u * (w * x).abs().sum(1)
+            hr = gelu(torch, z)
+            bound = 1.01 * (b16 * hr.abs() + 5e-5 * hr.abs() + 7e-6 + 1.13 * zb)
+            assert ((H[r, n:n + step].double() - hr).abs() <= bound).all(), (r, n)
+
+
 def check_expert_ffn(env, d, h, dtype, rows, C, packed=False):
     """H, Z, out and the data gradients; GeLU's polynomial is within 5e-5 |ref| + 7e-6 (its derivative within 5e-5)."""
     torch, lm = env
