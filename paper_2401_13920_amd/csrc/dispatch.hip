@@ -1,5 +1,5 @@
 // Capacity-bounded stable dispatch (capacity: Section 3.2.3).
-//   1. dispatch_hist_kernel   per block of 1024 tokens: count of tokens per expert (few tokens: counted by step 2)
+//   1. dispatch_hist_kernel   per block of 1024 tokens: count of tokens per expert (few blocks: counted by step 2)
 //   2. dispatch_slots_kernel  every block re-derives, from the [blocks,E] count matrix, the
 //      tokens before it per expert and the totals, hence kept[], the buffer order and the
 //      segment offsets; then ranks its own tokens (wave ballots + ordered wave prefixes)
@@ -38,10 +38,15 @@ constexpr int kDispWaves = kDispThreads / kWave;
 constexpr int kTokPerWave = kDispatchTokensPerBlock / kDispWaves;  // contiguous tokens per wave
 constexpr int kIter = kTokPerWave / kWave;
 // Up to this many blocks the slots kernel counts the tokens per expert itself, every block all of them, and the
-// histogram's launch is saved.
-// Slots kernel with its own counts against both kernels: 192 tokens 5.2 us against 11.1, 4 096 tokens 8.1 against 11.3,
-// 8 192 tokens 9.2 against 11.4 (16 experts): beyond that the counting takes longer than the launch.
-constexpr int kDispSelfBlocks = 8;
+// histogram's launch is saved.  The line lies where no distribution of the tokens loses.  Whole dispatch, d = 256, us,
+// own counts / both kernels, tokens spread evenly over 16 experts; all on one; half each on two of 64:
+//     192 tokens  7.9 /  9.3   7.0 /  8.8   9.8 / 11.5
+//   4 096 tokens  9.6 / 10.6   9.3 / 10.4  12.1 / 12.6
+//   5 120 tokens 10.1 / 10.4   9.8 / 10.4  12.6 / 12.7
+//   6 000 tokens 10.4 / 10.8  10.0 / 10.4  12.9 / 13.0   (on two of 16: 10.3 / 10.2)
+//   8 192 tokens 11.3 / 10.9  10.8 / 10.7  13.9 / 13.0
+// (Counted with one addition per token, 8 192 tokens on one expert took 14.5.)
+constexpr int kDispSelfBlocks = 5;
 
 // Orders this wave's LDS accesses before the call against those after it, for all lanes.
 __device__ __forceinline__ void wave_sync() {
@@ -106,7 +111,14 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int m = m0 + u * kDispThreads;
-        if (m < T) atomicAdd((m < base ? earlier : later) + c[u], 1);
+        if (m < T) {
+          // the tokens of the first lane's expert are added at once: additions to one word wait for each other
+          const int first = __builtin_amdgcn_readfirstlane(c[u]);
+          const unsigned long long same = __ballot(c[u] == first);
+          const bool mine = c[u] == first;
+          if (!mine || lane == __builtin_ctzll(same))
+            atomicAdd((m < base ? earlier : later) + c[u], mine ? __builtin_popcountll(same) : 1);
+        }
       }
     }
     __syncthreads();
@@ -302,8 +314,9 @@ void launch_copy(const void* x, const int32_t* row_token, const int32_t* seg_off
 }
 
 
-// The three launches of the dispatch; `blockcnt` holds ceil(T/1024) x E counts (every one is written by the first
-// kernel before the second reads it: nothing has to be cleared).
+// The launches of the dispatch: histogram, slots, copy.  `blockcnt` holds ceil(T/1024) x E counts (every one is written by
+// the first kernel before the second reads it: nothing has to be cleared); up to kDispSelfBlocks blocks of tokens there
+// is no histogram and `blockcnt` is not touched.
 int dispatch_launch(const locmoe_desc* desc, const void* x, const int32_t* eid, const int32_t* e2n, int32_t* pos,
                     int32_t* slot, int32_t* kept, int32_t* seg_off, int32_t* node_off, int32_t* buf_expert,
                     int32_t* row_token, void* send, int32_t* blockcnt, hipStream_t s) {

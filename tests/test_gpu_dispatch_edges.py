@@ -9,13 +9,28 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("E,N,free_map", [(4, 2, False), (12, 5, True), (300, 3, False)])
-@pytest.mark.parametrize("T", [1, 1023, 1024, 1025, 2049, 8191, 8192, 8193])
+@pytest.mark.parametrize("T", [1, 1023, 1024, 1025, 2049, 5119, 5120, 5121, 8191, 8192, 8193])
 def test_dispatch_counts_at_block_edges(T, E, N, free_map):
+    rng = np.random.default_rng(T * 31 + E)
+    check_dispatch((rng.zipf(1.3, T) % E).astype(np.int32), E, N, free_map)
+
+
+# the counting adds up the tokens of a wave that share the first one's expert: all, none but one, runs, and a last wave
+# that is not full
+@pytest.mark.parametrize("kind", ["one", "two", "runs", "first differs"])
+@pytest.mark.parametrize("T", [1, 63, 65, 1000, 5119, 5120, 5121])
+def test_dispatch_counts_of_skewed_tokens(T, kind):
+    E, m, rng = 16, np.arange(T), np.random.default_rng(T)
+    eid = {"one": np.full(T, E - 1), "two": rng.integers(0, 2, T) * 9, "runs": m // 50 % E,
+           "first differs": np.where(m % 64 == 0, 3, 4 + m % 2)}[kind]
+    check_dispatch(eid.astype(np.int32), E, 4, False)
+
+
+def check_dispatch(eid, E, N, free_map):
     import torch
     from paper_2401_13920_amd import locmoe as lm
     assert torch.cuda.is_available(), "this test needs the MI355X"
-    rng = np.random.default_rng(T * 31 + E)
-    eid = (rng.zipf(1.3, T) % E).astype(np.int32)
+    T = len(eid)
     e2n = (np.arange(E) * 7 % N if free_map else np.arange(E) // (E // N)).astype(np.int32)
     C = max(1, T // (2 * E))
     d = 8 * E
