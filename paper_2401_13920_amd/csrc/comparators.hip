@@ -61,7 +61,10 @@ __global__ __launch_bounds__(kDgThreads) void gate_dense_mfma_kernel(const uint1
 
   // Two register sets hold the two k-steps after the one in LDS: with a work-group per compute unit (T = 32 768) the
   // loads in flight are what bounds this stream of tokens.
-  // T = 32 768, d = 2048, E = 32 (134 MB): 33.4 us, 36.6 with one set.
+  // T = 32 768, d = 2048, E = 32 (134 MB, 1 GB of tokens in turn): 33 us, 36 with one set; the same tokens again and again
+  // (they stay in the last-level cache) 20.7 and 22.5.  With more than 96 experts the loads past the last k-step are left
+  // out: T = 4 096, d = 2048, E = 128, the same tokens: 24.2 us, 28.7 with them, 25.7 with one set of registers.  Below
+  // that the branch costs more than they do: T = 65 536, d = 4096, E = 64: 132 us, 122 without it.
   u32x4 rx[2][4], rw[2][NT];
   const int KT = d / kDgBK;
   auto load = [&](int set, int kt) {
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(kDgThreads) void gate_dense_mfma_kernel(const uint1
       }
     }
     store(1 - PAR);
-    load(1 - PAR, kt + 3);
+    if (NT < 4 || kt + 3 < KT) load(1 - PAR, kt + 3);
     __syncthreads();
   };
   load(0, 0);

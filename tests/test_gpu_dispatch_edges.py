@@ -48,11 +48,11 @@ def check_dispatch(eid, E, N, free_map):
     assert torch.equal(b.send[b.slot[kept].long()], x[kept])
 
 
-@pytest.mark.parametrize("d", [64, 128, 192, 320])
-def test_dense_gate_k_steps(d):
+@pytest.mark.parametrize("E,d", [(32, 64), (32, 128), (32, 192), (32, 320), (128, 128), (128, 256), (128, 384), (128, 640)])
+def test_dense_gate_k_steps(E, d):
     import torch
     from paper_2401_13920_amd import locmoe as lm
-    T, E = 130, 32
+    T = 130
     gen = torch.Generator(device="cuda").manual_seed(d)
     x = torch.randn(T, d, generator=gen, device="cuda").to(torch.bfloat16)
     Wg = torch.randn(E, d, generator=gen, device="cuda").to(torch.bfloat16)
