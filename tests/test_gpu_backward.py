@@ -222,6 +222,7 @@ def test_backward_tuned_tiles_with_ragged_segments(env):
     run_backward_case(env, wl.small_config(T=3000, d=512, E=8, N=2, h=256, clusters=4), 300)
     run_backward_case(env, wl.small_config(T=2000, d=256, E=16, N=4, h=512, clusters=3), 70)
     run_backward_case(env, wl.small_config(T=1500, d=768, E=12, N=4, h=256, clusters=3), 33)
+    run_backward_case(env, wl.small_config(T=1500, d=768, E=12, N=4, h=256, clusters=3), 80)
 
 
 def run_backward_big(env, c, C, repeats=1):
