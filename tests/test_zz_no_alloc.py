@@ -1,6 +1,7 @@
 """locmoe_dispatch_static (the dispatch for callers that cannot allocate device memory) against locmoe_dispatch,
-through the C ABI: every output bit for bit, on two calls in a row, the second on a smaller input, so that whatever
-the first call left in the library's static scratch must not leak into the second."""
+through the C ABI: every output bit for bit, on calls in a row, each on a smaller input, so that whatever the first
+call left in the library's static scratch must not leak into the second, which uses it too (more than 5 120 tokens), nor
+disturb the third, which counts without it."""
 import numpy as np
 import pytest
 
@@ -42,17 +43,21 @@ def both_ways(torch, lm, hz, c, C, T=None, e2n=None):
     return K
 
 
-def test_dispatch_static_matches_dispatch_twice_in_a_row():
+def test_dispatch_static_matches_dispatch_on_calls_in_a_row():
     import torch
     from paper_2401_13920_amd import harness as hz, locmoe as lm
     assert torch.cuda.is_available(), "this test needs the MI355X"
     lm.lib()
-    # first call: several blocks of 1024 tokens, 128 experts; second call: fewer tokens, fewer experts, a free-form
-    # expert-to-node map, fp32 rows
-    big = wl.small_config(T=9000, d=1024, E=128, N=16, h=64, clusters=9)
+    # first call: 20 blocks of 1024 tokens, 128 experts; second call: 9 blocks, fewer experts, a free-form expert-to-node
+    # map; third call: 2 blocks, which need no scratch, fp32 rows; then the second again
+    big = wl.small_config(T=20000, d=1024, E=128, N=16, h=64, clusters=9)
     both_ways(torch, lm, hz, big, 40)
+    mid = wl.small_config(T=8700, d=960, E=60, N=7, h=64, clusters=9)
+    mid_map = (np.arange(60) * 5 % 7).astype(np.int32)
+    both_ways(torch, lm, hz, mid, 100, e2n=mid_map)
     small = wl.small_config(T=1500, d=96, E=12, N=7, h=24, clusters=4, dtype="f32")
     both_ways(torch, lm, hz, small, 11, e2n=(np.arange(12) * 5 % 7).astype(np.int32))
+    both_ways(torch, lm, hz, mid, 100, e2n=mid_map)
     # beyond the stated maximum of the static scratch: refused on the host, nothing launched
     over = lm.make_desc(1024 * 257, 1024, 1024, 32, 8, 4, "bf16")
     assert over.E * 257 > 262144
