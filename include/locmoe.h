@@ -153,7 +153,9 @@ int locmoe_dispatch(const locmoe_desc* desc, const void* x, const int32_t* eid, 
  * LOCMOE_ERR_HIP if the lookup fails.  Every call on a device uses that device's one array: calls that overlap
  * on one device (other streams, other threads) race and must not be made; calls on one stream are ordered.
  * Nothing in the array has to be zero on entry (every count is written before it is read), and its contents
- * after a call are unspecified.  All other arguments, outputs and errors as locmoe_dispatch. */
+ * after a call are unspecified.  (Up to 5 120 tokens are counted without any scratch: neither the array nor
+ * locmoe_dispatch's ws is touched, but both are asked for as always.)
+ * All other arguments, outputs and errors as locmoe_dispatch. */
 #define LOCMOE_DISPATCH_STATIC_MAX_COUNTS 262144
 int locmoe_dispatch_static(const locmoe_desc* desc, const void* x, const int32_t* eid, const int32_t* e2n,
                            int32_t* pos, int32_t* slot, int32_t* kept, int32_t* seg_off, int32_t* node_off,
@@ -166,7 +168,12 @@ int locmoe_dispatch_static(const locmoe_desc* desc, const void* x, const int32_t
  *   send device [E*C,d] of x_dtype; seg_off device [E+1]; buf_expert device [E];
  *   W_in device [E,h,d] bf16 and W_out device [E,d,h] bf16, row-major in Eq. 1's orientation;
  *   H_ws device [E*C,h] bf16 scratch; out device [E*C,d] of x_dtype (rows < K written).
- *   The row count K is read on the device from seg_off: no host synchronisation. */
+ *   The row count K is read on the device from seg_off: no host synchronisation.  Kernels and grids are chosen for
+ *   segments of at most min(C, T) rows, as locmoe_dispatch makes them; a longer segment is computed whole too, except
+ *   with packed weights where E % 8 != 0 or E > 512 (rows past the last 256-row tile that min(C, T) needs may be left out).
+ *   An element of H_ws or out is one fp32 sum over K in ascending order: with one weight layout its bits do not
+ *   depend on T, C or the other rows.  LOCMOE_ERR_SHAPE with row-major weights if E*ceil(min(C,T)/64) > 65535, unless
+ *   x is bf16 and d % 256 == 0 and h % 256 == 0 (either GEMM: its inner size % 64, its outer size % 256). */
 int locmoe_expert_ffn(const locmoe_desc* desc, const void* send, const int32_t* seg_off,
                       const int32_t* buf_expert, const void* W_in, const void* W_out, void* H_ws,
                       void* out, void* stream);
@@ -204,8 +211,8 @@ int locmoe_expert_ffn_out(const locmoe_desc* desc, const void* H_ws, const int32
  *       of a call).  Contract: all bytes zero when the first call that uses it is enqueued (the caller clears it
  *       once, e.g. at allocation); every launch returns its set to zero when its last work-group finishes, so the
  *       same ws serves any number of later calls.  Calls that may run concurrently (different streams, overlapping
- *       graph replays) must be given different ws; calls ordered on one stream may share one.  Shapes that do
- *       not use the packed-weight kernels ignore ws.  LOCMOE_ERR_WORKSPACE if ws is NULL, misaligned or
+ *       graph replays) must be given different ws; calls ordered on one stream may share one.  Launches
+ *       that do not take the persistent packed-weight kernel ignore ws.  LOCMOE_ERR_WORKSPACE if ws is NULL, misaligned or
  *       ws_bytes < LOCMOE_FFN_WS_BYTES.  A workspace whose zero contract is broken gives wrong tile assignments
  *       (rows of the output missing or written twice), never an out-of-bounds access. */
 #define LOCMOE_FFN_WS_BYTES 128
@@ -315,6 +322,7 @@ int locmoe_expert_ffn_dgrad(const locmoe_desc* desc, const void* dout, const voi
 /* Eq. 1, backward with respect to the weights, summed over each expert's rows of the send buffer:
  *   dW_in[e]  = sum_r dZ[r,:] (x) send[r,:]   [h,d],     dW_out[e] = sum_r dout[r,:] (x) H[r,:]   [d,h]
  *   (fp32 accumulation, rounded once to bf16; zeros for an expert without rows: every element is written).
+ *   fp32 send and dout enter with all 24 bits down to 2^-109 in magnitude (bits below 2^-133 are dropped).
  *   send, dout device [E*C,d] x_dtype; H, dZ device [E*C,h] bf16; dW_in, dW_out device [E,h*d] bf16,
  *   row-major in Eq. 1's orientation whatever desc->w_packed says. */
 int locmoe_expert_ffn_wgrad(const locmoe_desc* desc, const void* send, const void* H, const void* dout,

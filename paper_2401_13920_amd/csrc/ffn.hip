@@ -92,7 +92,7 @@ __device__ __forceinline__ void store_quad(void* C, uint16_t* aux, size_t row, i
 // weights: tiles of up to 192 (fp32: 128) rows x BN columns, k-steps of 64 (32), four waves (2 along m x 2 along n,
 // 16-row subtiles interleaved between the waves of an axis).  Both operands reach LDS by direct-to-LDS copies into a ring of stages
 // that fills half of a compute unit's LDS: two work-groups per compute unit (one's epilogue and barriers run beside
-// the other's MFMAs) with 32 to 48 KiB of copies each in flight.  Slot functions as in the DMA kernels below: 64-byte
+// the other's MFMAs) with 32 to 64 KiB of copies each in flight.  Slot functions as in the DMA kernels below: 64-byte
 // rows chunk ^ (row/2 mod 4), 128-byte (fp32) rows chunk ^ (row/2 mod 8).  Copies past K are clamped into the row and
 // overwritten with zeros on both sides by the lanes that fetched them (an infinity times zero would be a NaN).
 //
@@ -102,14 +102,17 @@ __device__ __forceinline__ void store_quad(void* C, uint16_t* aux, size_t row, i
 // full and 256 x 256 tiles would make one full turn of the chip, such tiles are still up to 8 % faster (E = 64, K = 2048,
 // N = 1024, 256 rows: 109 us against 118; E = 16, K = 4096, N = 1024, 1 024 rows: 165 against 175); with the same capacity and
 // uneven segments (97 against 97, 156 against 120) they are not, and the host does not know the rows.
-// What bounds it is the way from L2 to LDS: variants with other tiles moved 8 to 10 TB/s there (all copies of all
-// work-groups over the kernel's time), so a larger tile, that moves less, is faster as long as two work-groups fit:
-// at d = 1600, h = 6400, 40 experts, 5 003 tokens (at most 157 rows per expert) the two GEMMs take 291 + 349 us with
-// 128-row tiles staged through registers, 273 + 321 with 128-row tiles and k-steps of 32, 218 + 290 with 256-row tiles
-// and k-steps of 32, 194 + 247 as it is (whole 128-byte lines per row; 820 MB of weights each: 4.2 and 3.3 TB/s).
-// The 256 x 256 and 64 x 64 register-staged kernels that this replaces: 272 + 399 us.  fp32 storage, d = 1024,
-// h = 4096, 16 experts, 2 523 rows: 79 + 76 us (before: 105 + 155).  Long segments (2 048 rows per expert, d = 2048,
-// h = 8192, E = 8): the forward pass takes 1 160 us against 1 407 with the 256 x 256 tiles.
+// What bounds it is how much is in flight on the way to LDS: variants with other tiles moved 8 to 10 TB/s there (all
+// copies of all work-groups over the kernel's time; from cache the same copies reach 34 TB/s when nothing waits for
+// them), and the largest form, 192 x 128, has two stages and waits for all of the next one at every step, so that 80 KiB per
+// compute unit are under way over a latency of some 2 us.  A larger tile, that moves less, is therefore faster as long as two
+// work-groups fit: at d = 1600, h = 6400, 40 experts, 5 003 tokens (at most 157 rows per expert) the two GEMMs take
+// 291 + 349 us with 128-row tiles staged through registers, 273 + 321 with 128-row tiles and k-steps of 32, 218 + 290 with
+// 256-row tiles and k-steps of 32, 182 to 194 + 245 to 247 as it is (whole 128-byte lines per row; 820 MB of weights each:
+// 4.3 and 3.3 TB/s).  The 256 x 256 and 64 x 64 register-staged kernels that this replaces: 272 + 399 us.  fp32 storage,
+// d = 1024, h = 4096, 16 experts, 3 112 rows: 76 + 58 us (before: 105 + 155).  Long segments (2 048 rows per expert,
+// d = 2048, h = 8192, E = 8): 581 + 581 us against 794 + 643 with the 256 x 256 tiles; rows even in 0 .. 2 048: 358 + 374
+// against 680 + 599.
 // ---------------------------------------------------------------------------------------------
 constexpr int kAnyThreads = 256;
 constexpr int kAnyLds = 80 * 1024;  // half of a compute unit's
@@ -1114,7 +1117,7 @@ inline bool packable(const locmoe_desc* p) {
 template <bool A_F32, int EPI, bool OUT_F32, int BN>
 int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
                int rows_max, int T, int Kdim, int Ndim, hipStream_t st) {
-  // the size limit that fp32 storage and shapes off the 64 x 256 grid have had from the start
+  // (a limit of the interface, see the header; the grid below has none that buffers of a card reach)
   if ((A_F32 || Kdim % 64 || Ndim % 256) && (long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;
   constexpr int kBM = AnyK<A_F32>::kBM, kFine = AnyK<A_F32>::kFine;
   const bool far = (long long)Kdim * (A_F32 ? 4 : 2) * kBM > 0xFFFFFFFFLL;  // (the weight rows' offsets are no larger)

@@ -323,13 +323,14 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(uint4* __restrict
 // 256-byte rows and fetched with the transposing LDS read; the chunk swizzle is the one of the kernel above.
 // fp32 values keep all their 24 bits: x = a + b + c with a, b, c the bf16 numbers that hold bits 0..7, 8..15 and
 // 16..23 of the significand (cut, not rounded: each remainder is exact), so that three MFMAs sum the same exact
-// products as fp32 multiplications would, in fp32.  (Bits below bf16's least subnormal, 2^-133, are lost: values under
-// 2^-109 keep fewer than 24 bits.  Infinities: see behind the loop.)
-// The contraction is short and the output large: at T = 4096, d = 1024, h = 4096, 16 experts, fp32 storage (2 523
-// kept rows) both launches write 268 MB, 56 us at the rate of a large copy, and multiply 3 x 42 GFLOP, 79 us at the
-// rate of a large matrix product; they take 138 + 126 us (one thread per output element with scalar products, which
-// this replaces: 12.8 ms).  64 KiB of LDS and 128-wide tiles leave room for two work-groups per compute unit, so that
-// one's stores run beside the other's MFMAs.
+// products as fp32 multiplications would, in fp32: at 60, 500 and 3 000 rows 131, 368 and 1 766 of 2 to 4 million elements
+// are not the rounded float64 sum (one thread per element with scalar products, which this replaces: 242, 655, 2 874).
+// Bits below bf16's least subnormal, 2^-133, are lost: values under 2^-109 keep fewer than 24 bits (a single product is
+// still the rounded one down to 2^-118).  Infinities: see behind the loop.
+// The contraction is short and the output large: at T = 4096, d = 1024, h = 4096, 16 experts, fp32 storage (3 112
+// kept rows) both launches write 268 MB, 54 us at the rate of a large copy, and multiply 3 x 52 GFLOP, 132 us at the
+// rate of a large matrix product; they take 174 + 158 us (the scalar kernel: 12.8 ms).  64 KiB of LDS and 128-wide tiles
+// leave room for two work-groups per compute unit, so that one's stores run beside the other's MFMAs.
 constexpr int kAnyTile = 128;
 constexpr int kAnyRow = kAnyTile * 2;              // bytes of an LDS row
 constexpr int kAnyPlane = kWgK * kAnyRow;          // 8 KiB: one bf16 plane of one operand's step
