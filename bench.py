@@ -359,7 +359,9 @@ def main() -> int:
         backward = time_backward(lm, hz, wl, torch, np, c, desc, sets, W_in_rm, W_out_rm, W_in, W_out, stream, reps, K)
     dom = "ffn_in" if ms["ffn_in"] >= ms["ffn_out"] else "ffn_out"
     achieved = flops / (ms[dom] * 1e-3) / 1e12
-    kname = "ffn_gemm_dma_persistent" if desc.w_packed else "ffn_gemm_any"
+    kname = "ffn_gemm_any"
+    if desc.w_packed:  # (at most 64 rows per expert: either packed kernel, by shape)
+        kname = "ffn_gemm_dma_persistent" if min(C, c.T) > 64 else "ffn_gemm_few or ffn_gemm_dma_persistent"
     traffic, traffic_note = None, "the tracked counters are for the config-4 bench workload with packed weights"
     if desc.w_packed and c.cfg == 4 and not args.capacity:
         kib, traffic_note = profiled_traffic()
