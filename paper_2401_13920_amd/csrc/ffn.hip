@@ -6,13 +6,13 @@
 // 16-byte LDS read.  bf16 MFMA (v_mfma_f32_16x16x32_bf16), fp32 accumulation.
 //
 // Kernels that share the operand orientation and the epilogue:
-//   ffn_gemm_any             any shape the descriptor allows, fp32 or bf16 activations, row-major weights: tiles of up to
-//                            192 x 128, LDS rings filled by direct-to-LDS loads
+//   ffn_gemm_any             (ffn_any.hip) any shape the descriptor allows, fp32 or bf16 activations, row-major weights,
+//                            and packed weights with few rows, experts or columns: tiles of up to 192 x 128 or 160 x 160
 //   ffn_gemm_dma_persistent  256x256x32 tiles, LDS rings filled by direct-to-LDS loads, weights pre-packed
 //                            by locmoe_pack_weights into the LDS image of each k-step; four waves with the
 //                            accumulators in the accumulation registers; one work-group per compute unit
 //                            works through a queue of tiles (expert counts that are multiples of 8, up to 512)
-//   ffn_gemm_few             packed weights and at most 64 rows per segment: weight fragments straight to registers
+//   ffn_gemm_few             packed weights and at most 16 rows per segment: weight fragments straight to registers
 //   ffn_gemm_dma             the same pipeline with one tile per work-group (other expert counts)
 //
 // The weight rows feed the MFMA's A operand and the activation rows its B operand, i.e. the
@@ -25,353 +25,11 @@
 #include <type_traits>
 
 #include "common.h"
-#include "gelu_coef.h"
+#include "ffn_any.h"
+#include "ffn_epilogue.h"
 
 namespace locmoe {
 namespace {
-
-// GeLU for outputs that are rounded to bf16: GeLU(v) = max(v,0) - |v| Phi(-|v|), with
-// 2 Phi(-x) = exp2(q(x)), q the degree-6 polynomial of gelu_coef.h on [0, 6] (argument clamped: the
-// tail beyond is below 6e-9).  Relative error below 5e-5, absolute below 7e-6: forty times finer than
-// the bf16 rounding that follows, at 10 vector ops and one transcendental per value (a rational erfc
-// form with the same tail behaviour costs 15 and two; the epilogue's vector work was a tenth of the
-// first GEMM's time with it).
-// max(v,0) is formed as (v + |v|)/2 so that a NaN input stays a NaN.
-__device__ __forceinline__ float gelu_bf16(float v) {
-  const float x = fminf(fabsf(v), kGeluXMax);
-  float q = kGeluCoef[kGeluDegree];
-#pragma unroll
-  for (int k = kGeluDegree - 1; k >= 0; --k) q = fmaf(q, x, kGeluCoef[k]);
-  return 0.5f * fmaf(-x, __builtin_amdgcn_exp2f(q), v + fabsf(v));
-}
-
-// GeLU'(v) = Phi(v) + v phi(v) for factors of outputs that are rounded to bf16, from the same polynomial:
-// Phi(-|v|) = exp2(q(|v|)) / 2 (absolute error below 2.3e-5), phi(v) = exp2(-v^2 log2(e)/2) / sqrt(2 pi).
-__device__ __forceinline__ float gelu_grad_bf16(float v) {
-  const float x = fminf(fabsf(v), kGeluXMax);
-  float q = kGeluCoef[kGeluDegree];
-#pragma unroll
-  for (int k = kGeluDegree - 1; k >= 0; --k) q = fmaf(q, x, kGeluCoef[k]);
-  const float tail = 0.5f * __builtin_amdgcn_exp2f(q);  // Phi(-|v|)
-  const float Phi = v >= 0.f ? 1.0f - tail : tail;
-  const float phi = 0.3989422804f * __builtin_amdgcn_exp2f(-0.7213475204f * v * v);
-  return fmaf(v, phi, Phi);
-}
-
-// What happens to an accumulator on its way to memory
-constexpr int kEpiNone = 0;      // rounded and stored
-constexpr int kEpiGelu = 1;      // GeLU, then rounded and stored (H of Eq. 1)
-constexpr int kEpiGeluSave = 2;  // the same, and the pre-activation Z is stored (bf16) to `aux` for the backward
-constexpr int kEpiGeluGrad = 3;  // multiplied by GeLU'(Z), Z read from `aux` (bf16): dZ = dH * GeLU'(Z)
-
-// One accumulator quad -> memory.  q holds D[n0..n0+3][m] for one row m.
-template <int EPI, bool OUT_F32>
-__device__ __forceinline__ void store_quad(void* C, uint16_t* aux, size_t row, int ldc, int n0, float q0, float q1,
-                                           float q2, float q3) {
-  static_assert(!(EPI != kEpiNone && OUT_F32), "the hidden activations and their gradients are stored as bf16");
-  if (EPI == kEpiGeluSave) *(uint2*)(aux + row * ldc + n0) = make_uint2(pack_bf16x2(q0, q1), pack_bf16x2(q2, q3));
-  if (EPI == kEpiGelu || EPI == kEpiGeluSave) {
-    q0 = gelu_bf16(q0); q1 = gelu_bf16(q1); q2 = gelu_bf16(q2); q3 = gelu_bf16(q3);
-  }
-  if (EPI == kEpiGeluGrad) {
-    const uint2 z = *(const uint2*)(aux + row * ldc + n0);
-    q0 *= gelu_grad_bf16(bf16_bits_to_f32(z.x & 0xFFFFu));
-    q1 *= gelu_grad_bf16(__uint_as_float(z.x & 0xFFFF0000u));
-    q2 *= gelu_grad_bf16(bf16_bits_to_f32(z.y & 0xFFFFu));
-    q3 *= gelu_grad_bf16(__uint_as_float(z.y & 0xFFFF0000u));
-  }
-  if (OUT_F32) {
-    *(float4*)((float*)C + row * ldc + n0) = make_float4(q0, q1, q2, q3);
-  } else {
-    *(uint2*)((uint16_t*)C + row * ldc + n0) = make_uint2(pack_bf16x2(q0, q1), pack_bf16x2(q2, q3));
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Any K and N that are multiples of 8, fp32 (rounded to bf16 between LDS and the MFMA) or bf16 activations, row-major
-// weights: tiles of up to 192 (fp32: 128) rows x BN columns, k-steps of 64 (32), four waves (2 along m x 2 along n,
-// 16-row subtiles interleaved between the waves of an axis).  Both operands reach LDS by direct-to-LDS copies into a ring of stages
-// that fills half of a compute unit's LDS: two work-groups per compute unit (one's epilogue and barriers run beside
-// the other's MFMAs) with 32 to 64 KiB of copies each in flight.  Slot functions as in the DMA kernels below: 64-byte
-// rows chunk ^ (row/2 mod 4), 128-byte (fp32) rows chunk ^ (row/2 mod 8).  Copies past K are clamped into the row and
-// overwritten with zeros on both sides by the lanes that fetched them (an infinity times zero would be a NaN).
-//
-// Segments here are short (a hundred rows or so), so that the weight stream is what has to keep flowing: the m-tiles
-// of one weight tile run side by side on one XCD (one L2), a segment's rows are spread evenly over its m-tiles, and
-// weight tiles are dealt to the XCDs in turn (a long segment's work is spread over all of them).  Where all segments are
-// full and 256 x 256 tiles would make one full turn of the chip, such tiles are still up to 8 % faster (E = 64, K = 2048,
-// N = 1024, 256 rows: 109 us against 118; E = 16, K = 4096, N = 1024, 1 024 rows: 165 against 175); with the same capacity and
-// uneven segments (97 against 97, 156 against 120) they are not, and the host does not know the rows.
-// What bounds it is how much is in flight on the way to LDS: variants with other tiles moved 8 to 10 TB/s there (all
-// copies of all work-groups over the kernel's time; from cache the same copies reach 34 TB/s when nothing waits for
-// them), and the largest form, 192 x 128, has two stages and waits for all of the next one at every step, so that 80 KiB per
-// compute unit are under way over a latency of some 2 us.  A larger tile, that moves less, is therefore faster as long as two
-// work-groups fit: at d = 1600, h = 6400, 40 experts, 5 003 tokens (at most 157 rows per expert) the two GEMMs take
-// 291 + 349 us with 128-row tiles staged through registers, 273 + 321 with 128-row tiles and k-steps of 32, 218 + 290 with
-// 256-row tiles and k-steps of 32, 182 to 194 + 245 to 247 as it is (whole 128-byte lines per row; 820 MB of weights each:
-// 4.3 and 3.3 TB/s).  The 256 x 256 and 64 x 64 register-staged kernels that this replaces: 272 + 399 us.  fp32 storage,
-// d = 1024, h = 4096, 16 experts, 3 112 rows: 76 + 58 us (before: 105 + 155).  Long segments (2 048 rows per expert,
-// d = 2048, h = 8192, E = 8): 581 + 581 us against 794 + 643 with the 256 x 256 tiles; rows even in 0 .. 2 048: 358 + 374
-// against 680 + 599.
-// ---------------------------------------------------------------------------------------------
-constexpr int kAnyThreads = 256;
-constexpr int kAnyLds = 80 * 1024;  // half of a compute unit's
-
-template <bool A_F32>
-struct AnyK {
-  static constexpr int kBM = A_F32 ? 128 : 192;           // rows of an m-tile at most
-  static constexpr int kFine = 128;                       // ... of a short list
-  static constexpr int kBK = A_F32 ? 32 : 64;
-  static constexpr int kARow = 128;                       // bytes of an activation row in LDS: one line
-  static constexpr int kWRow = kBK * 2;
-};
-template <bool A_F32, int BN, int NJ>
-struct AnyShape : AnyK<A_F32> {
-  static constexpr int kABytes = 32 * NJ * AnyK<A_F32>::kARow;
-  static constexpr int kStage = kABytes + BN * AnyK<A_F32>::kWRow;
-  static constexpr int kStages = kAnyLds / kStage;        // 2 to 6
-};
-// Byte offset, inside a row of RB bytes (a k-step), of the 16-byte chunk that this lane of a 1 KiB copy fetches; the
-// copy's block of 1024 / RB rows is number wave + 4 i of the operand
-template <int RB>
-__device__ __forceinline__ uint32_t any_chunk(int wave, int lane) {
-  constexpr int L = RB / 16;
-  const int row = (RB == 128 ? (wave & 1) * 8 : 0) + lane / L;  // modulo 16
-  return (uint32_t)(((lane & (L - 1)) ^ ((row >> 1) & (L - 1))) << 4);
-}
-
-// vmcnt(n C) for a run-time n <= MAX
-template <int C, int MAX>
-__device__ __forceinline__ void wait_younger(int n) {
-  if constexpr (MAX == 0) {
-    wait_vmcnt<0>();
-  } else {
-    if (n >= MAX) wait_vmcnt<MAX * C>();
-    else wait_younger<C, MAX - 1>(n);
-  }
-}
-
-// One tile of at most 32 NJ rows.  rows_left: live rows from the tile's first (>= 1).  FAR: a tile's rows reach further
-// than 32-bit offsets do.
-template <bool A_F32, int EPI, bool OUT_F32, int BN, int NJ, bool FAR>
-__device__ __forceinline__ void any_tile(const char* __restrict__ A, const char* __restrict__ W, void* __restrict__ Cout,
-                                         uint16_t* aux, size_t crow0, int rows_left, int n0, int Kdim, int Ndim,
-                                         uint32_t lds0, char* smem) {
-  using S = AnyShape<A_F32, BN, NJ>;
-  constexpr int NI = BN / 32;                                  // 16-column subtiles of a wave
-  constexpr int kSub = S::kBK / 32;                            // MFMA depths per k-step
-  constexpr int kARows = 1024 / S::kARow, kWRows = 1024 / S::kWRow;  // rows of a 1 KiB copy
-  constexpr int CA = 32 * NJ / kARows / 4, CW = BN / kWRows / 4;     // copies per wave and step
-  constexpr int C = CA + CW;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1, kq = lane >> 4, l16 = lane & 15;
-
-  // copies: block wave + 4 i of an operand's stage; rows past the segment's end and columns past the last repeat the
-  // last one (not stored)
-  using off_t = std::conditional_t<FAR, uint64_t, uint32_t>;
-  const off_t ldA = (off_t)Kdim * (A_F32 ? 4 : 2), ldW = (off_t)Kdim * 2;
-  off_t rowA[CA], rowW[CW];
-#pragma unroll
-  for (int i = 0; i < CA; ++i)
-    rowA[i] = (off_t)min((wave + 4 * i) * kARows + lane / (64 / kARows), rows_left - 1) * ldA;
-#pragma unroll
-  for (int i = 0; i < CW; ++i)
-    rowW[i] = (off_t)min((wave + 4 * i) * kWRows + lane / (64 / kWRows), Ndim - n0 - 1) * ldW;
-  const uint32_t chA = any_chunk<S::kARow>(wave, lane), chW = any_chunk<S::kWRow>(wave, lane);
-  const int KT = (Kdim - 1) / S::kBK + 1;
-  auto copy = [](const char* base, off_t off, uint32_t lds) {
-    if constexpr (FAR) dma_1k_far(base + off, lds);
-    else dma_1k(base, off, lds);
-  };
-  auto issue = [&](int s, int stage) {
-    const uint32_t base = lds0 + (uint32_t)stage * S::kStage + (uint32_t)wave * 1024;
-    const off_t ka = min((off_t)s * S::kARow + chA, ldA - 16), kw = min((off_t)s * S::kWRow + chW, ldW - 16);
-#pragma unroll
-    for (int i = 0; i < CW; ++i) copy(W, rowW[i] + kw, base + S::kABytes + i * 4096);
-#pragma unroll
-    for (int i = 0; i < CA; ++i) copy(A, rowA[i] + ka, base + i * 4096);
-  };
-
-  // fragment addresses inside a stage: lane l reads the 8 values k = 8 (l/16) .. +7 of row l%16 (two chunks if fp32)
-  int off_a[2], off_w[kSub];
-  {
-    const int ra = wm * 16 + l16, rw = wn * 16 + l16;  // (subtiles are 32 rows apart: the same swizzle)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      off_a[i] = ra * S::kARow + (((A_F32 ? 2 * kq + i : 4 * i + kq) ^ ((ra >> 1) & 7)) << 4);
-#pragma unroll
-    for (int i = 0; i < kSub; ++i)
-      off_w[i] = S::kABytes + rw * S::kWRow + (((4 * i + kq) ^ ((rw >> 1) & (S::kWRow / 16 - 1))) << 4);
-  }
-  f32x4 acc[NI][NJ];
-#pragma unroll
-  for (int a = 0; a < NI; ++a)
-#pragma unroll
-    for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll
-  for (int s = 0; s < S::kStages - 1; ++s)
-    if (s < KT) issue(s, s);
-  int stage = 0, fill = S::kStages - 1;
-  for (int s = 0; s < KT; ++s) {
-    // this step's copies have landed when at most the younger steps' are outstanding (copies complete in issue order
-    // and the loop has no other vector memory access)
-    wait_younger<C, S::kStages - 2>(KT - 1 - s);
-    if (s == KT - 1 && (Kdim & (S::kBK - 1))) {
-      char* st = smem + stage * S::kStage + wave * 1024 + lane * 16;
-      const uint4 zero = make_uint4(0, 0, 0, 0);
-      if ((off_t)s * S::kARow + chA >= ldA) {
-#pragma unroll
-        for (int i = 0; i < CA; ++i) *(uint4*)(st + i * 4096) = zero;
-      }
-      if ((off_t)s * S::kWRow + chW >= ldW) {
-#pragma unroll
-        for (int i = 0; i < CW; ++i) *(uint4*)(st + S::kABytes + i * 4096) = zero;
-      }
-    }
-    __syncthreads();
-    if (s + S::kStages - 1 < KT) issue(s + S::kStages - 1, fill);  // into the stage that was read one step ago
-    const char* st = smem + stage * S::kStage;
-#pragma unroll
-    for (int ks = 0; ks < kSub; ++ks) {
-      bf16x8 fw[NI], fa[NJ];
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) fw[ni] = *(const bf16x8*)(st + off_w[ks] + ni * 32 * S::kWRow);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const char* p = st + j * 32 * S::kARow;
-        if (A_F32) {
-          const f32x4 a = *(const f32x4*)(p + off_a[0]), b = *(const f32x4*)(p + off_a[1]);
-          const u32x4 v = {pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
-          fa[j] = __builtin_bit_cast(bf16x8, v);
-        } else {
-          fa[j] = *(const bf16x8*)(p + off_a[ks]);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-          acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ni], fa[j], acc[ni][j], 0, 0, 0);
-    }
-    fill = stage;
-    stage = stage + 1 == S::kStages ? 0 : stage + 1;
-  }
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int m = (2 * j + wm) * 16 + l16;
-    if (m < rows_left) {
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) {
-        const int n = n0 + (2 * ni + wn) * 16 + kq * 4;  // a lane holds D[n .. n+3][m]
-        if (n < Ndim)  // Ndim % 8 == 0 and n % 4 == 0: the quad is entirely inside or outside
-          store_quad<EPI, OUT_F32>(Cout, aux, crow0 + m, Ndim, n, acc[ni][j][0], acc[ni][j][1], acc[ni][j][2],
-                                   acc[ni][j][3]);
-      }
-    }
-  }
-}
-
-// Inclusive sum over the wave's lanes
-__device__ __forceinline__ int wave_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1, 2, 4, 8: within 16 lanes
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
-// Weight tile nt of segment r is number r NT + nt and belongs to XCD (r NT + nt) mod 8 (work-group ids congruent mod 8 run
-// on one XCD).  Without LIST no segment has more than kBM rows: a work-group takes a whole weight tile.  With LIST the
-// work-groups of an XCD take the live m-tiles of its weight tiles, those of one weight tile in a row, by their number
-// in that list, which every wave counts out for itself from seg_off.  (A work-group per possible m-tile, most of them
-// without rows, fills the compute units unevenly: work-groups go to the shader engines in turn, and where every second
-// one leaves at once, half of the engines stay empty.  Rows even in 0 .. 224, d = 2048, h = 8192, E = 32: 340 + 363 us so,
-// 261 + 267 from the list; 0 .. 640: 627 + 610 and 408 + 414.  Equal segments: 1 % less to 5 % more time, for the counting.)
-// A list that fills the XCD's `slots` (two per compute unit) once or twice is cut into m-tiles of kFine rows where
-// that does not take another turn: rows even in 0 .. 256, d = 4096, h = 16384, E = 8, second GEMM: 389 us with up to 192
-// rows, 308 with up to 128.
-template <bool A_F32, int EPI, bool OUT_F32, int BN, bool LIST, bool FAR>
-__global__ __launch_bounds__(kAnyThreads, 2) void ffn_gemm_any(const char* __restrict__ A, const char* __restrict__ W,
-                                                               void* __restrict__ Cout, uint16_t* aux,
-                                                               const int32_t* __restrict__ seg_off,
-                                                               const int32_t* __restrict__ buf_expert, int Kdim,
-                                                               int Ndim, int NT, int E, int slots) {
-  constexpr int kBM = AnyK<A_F32>::kBM, kFine = AnyK<A_F32>::kFine;
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
-  const int xcd = blockIdx.x & 7, lane = threadIdx.x & 63;
-  // segments r0 .. r0 + 63, one per lane: first row, rows, expert, inclusive sum of their tiles on this XCD (`all`: the
-  // last of these); `before` tiles precede them
-  int r0 = 0, before = 0, seg_l = 0, rows_l = 0, e_l = 0, cum = 0, all = 0;
-  bool fine = false;
-  auto look = [&]() {
-    const int rl = r0 + lane;
-    seg_l = seg_off[min(rl, E)];
-    rows_l = seg_off[min(rl + 1, E)] - seg_l;
-    e_l = buf_expert[min(rl, E - 1)];
-    const int first = (xcd - rl * NT) & 7, cols = first < NT ? (NT - 1 - first) / 8 + 1 : 0;  // weight tiles on this XCD
-    cum = wave_scan(cols * ((rows_l + kBM - 1) / kBM));
-    all = __builtin_amdgcn_readlane(cum, 63);
-    if (kFine < kBM && E <= 64 && all <= 2 * slots) {
-      const int cum_f = wave_scan(cols * ((rows_l + kFine - 1) / kFine)), all_f = __builtin_amdgcn_readlane(cum_f, 63);
-      if (all_f <= (all <= slots ? slots : 2 * slots)) {
-        fine = true;
-        cum = cum_f;
-        all = all_f;
-      }
-    }
-  };
-  if (LIST) look();
-  int mt = 0;
-  for (int q = (blockIdx.y * gridDim.x + blockIdx.x) >> 3;;) {
-    int seg0, rows, e, mtc, nt;
-    if (!LIST) {
-      const int grp = q * 8 + xcd, r = grp / NT;
-      if (r >= E) return;
-      seg0 = seg_off[r];
-      rows = seg_off[r + 1] - seg0;
-      e = buf_expert[r];
-      mtc = (rows + kBM - 1) / kBM;  // (more than one if a segment holds more rows than the descriptor says)
-      nt = grp - r * NT;
-    } else {
-      while (q >= before + all) {
-        if (r0 + 64 >= E) return;
-        before += all;
-        r0 += 64;
-        look();
-      }
-      const int k = __builtin_popcountll(__ballot(before + cum <= q));
-      const int in = q - before - (k ? __builtin_amdgcn_readlane(cum, k - 1) : 0);
-      seg0 = __builtin_amdgcn_readlane(seg_l, k);
-      rows = __builtin_amdgcn_readlane(rows_l, k);
-      e = __builtin_amdgcn_readlane(e_l, k);
-      mtc = fine ? (rows + kFine - 1) / kFine : (rows + kBM - 1) / kBM;
-      const int g = in / mtc;
-      mt = in - g * mtc;
-      nt = ((xcd - (r0 + k) * NT) & 7) + 8 * g;
-    }
-    if (rows > 0) {
-      // rows evenly over the m-tiles, in whole subtiles: at most kBM (a multiple of 16), and the last tile has some
-      const int span = ((rows + mtc - 1) / mtc + 15) & ~15, m0 = mt * span, n0 = nt * BN;
-      const int left = __builtin_amdgcn_readfirstlane(min(rows - m0, span));
-      const char* At = A + ((size_t)seg0 + m0) * Kdim * (A_F32 ? 4 : 2);
-      const char* Wt = W + ((size_t)e * Ndim + n0) * Kdim * 2;
-#define LOCMOE_ANY_TILE(NJ) \
-  any_tile<A_F32, EPI, OUT_F32, BN, NJ, FAR>(At, Wt, Cout, aux, (size_t)seg0 + m0, left, n0, Kdim, Ndim, lds0, smem)
-      if (left <= 64) LOCMOE_ANY_TILE(2);
-      else if (A_F32 || left <= 128) LOCMOE_ANY_TILE(4);
-      else if constexpr (!A_F32) LOCMOE_ANY_TILE(6);
-#undef LOCMOE_ANY_TILE
-    }
-    if (LIST) q += gridDim.x >> 3;
-    else if (++mt >= mtc) return;
-    __syncthreads();  // (the next tile's copies overwrite what this one's last step read)
-  }
-}
 
 // ---------------------------------------------------------------------------------------------
 // DMA kernels: 256x256 tile, k-steps of 32 taken two at a time ("double steps"), four waves, one per
@@ -870,58 +528,47 @@ __global__ __launch_bounds__(kDmaThreads) void ffn_gemm_dma_persistent(const uin
 }
 
 // ---------------------------------------------------------------------------------------------
-// Few rows per segment (at most 64 by capacity or token count: few_rows_take), packed weights: the weights are read once
+// At most 16 rows per segment (by capacity or token count), packed weights: the weights are read once
 // for a handful of rows, so this is a stream of weights that has to keep the memory busy.  A work-group is one wave
 // and takes 64 columns of one segment, all of its rows and all of K.  Weight fragments come straight from memory
-// into registers: 16 columns of a packed block are one contiguous KiB per load, and eight k-steps (32 KiB per wave;
-// four, 16 KiB, beside the accumulators of 64 rows) are always in flight; activation fragments come from L2.  No barrier,
+// into registers: 16 columns of a packed block are one contiguous KiB per load, and eight k-steps (32 KiB per wave)
+// are always in flight; activation fragments come from L2.  No barrier,
 // no LDS, and four times as many work-groups as 256-column tiles.
-// Every output element is one chain of MFMAs over K in ascending order, as in the tile kernels above: an element has
-// the same bits whichever kernel makes it, so a token's result does not depend on the batch's size or capacity.
-// (Four waves that split K among them and add up at the end, which this replaces, rounded differently.)
-// us, this kernel / 256-column tiles, weights read from memory:
-//   d = 1024, h = 4096, E = 16 (134 MB per weight), first and second GEMM:
-//     16 rows 26.8 + 29.1 / 39.5 + 64.8 (5.0 and 4.6 TB/s)    32 rows 30.4 + 30.7 / 41.1 + 66.3
-//     48 rows 35.4 + 33.3 / 41.8 + 66.2                       64 rows 40.7 + 44.2 / 43.5 + 67.4
+// Every output element is one chain of MFMAs over K in ascending order, as in the tile kernels: same bits.
+// With fewer than two waves per compute unit, and with more rows, the smaller tiles of ffn_any.hip are faster; us, here /
+// there: E = 40, d = 2560, h = 10240, even in 0 .. 4 rows 231 + 254 / 259 + 341;  E = 24, d = 3072, h = 12288, 9 rows
+// 312 + 395 / 332 + 428;  E = 16, d = 1024, h = 4096, 16 rows 26 + 28 / 26 + 26 (second GEMM: 256 waves);  two 16-row
+// subtiles: E = 16, d = 2560, h = 10240, 32 rows 176 + 172 / 151 + 146;  E = 32, d = 1280, h = 5120, 20 rows 82 + 83 / 77 + 76.
 // ---------------------------------------------------------------------------------------------
-constexpr int kFewRows = 64, kFewCols = 64;
-template <int NJ> constexpr int kFewDepth = NJ == 4 ? 4 : 8;  // k-steps in flight
+constexpr int kFewRows = 16, kFewCols = 64, kFewDepth = 8;  // (k-steps in flight)
 
-template <int NJ, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                                       uint16_t* __restrict__ Cout, uint16_t* aux,
                                                       const int32_t* __restrict__ seg_off,
                                                       const int32_t* __restrict__ buf_expert, int Kdim, int Ndim) {
-  constexpr int D = kFewDepth<NJ>;
+  constexpr int D = kFewDepth;
   const int groups = Ndim / kFewCols, cg = blockIdx.x % groups, r = blockIdx.x / groups;
   const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
   const int lane = threadIdx.x, kq = lane >> 4, l16 = lane & 15;
   const int steps = Kdim / kDmaBK;  // a multiple of 8 (Kdim is one of 256), hence of D
   const char* pw = (const char*)Wp + ((size_t)buf_expert[r] * Ndim + (size_t)(cg >> 2) * kBN) * Kdim * 2 +
                    (cg & 3) * (kFewCols * 64) + l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4);
-  for (int m0 = 0; m0 < rows; m0 += 16 * NJ) {  // (once, unless a segment holds more rows than the descriptor says)
-    const uint16_t* pa[NJ];
+  for (int m0 = 0; m0 < rows; m0 += kFewRows) {  // (once, unless a segment holds more rows than the descriptor says)
+    // (rows past the segment's end repeat the last one: not stored)
+    const uint16_t* pa = A + ((size_t)seg0 + min(m0 + l16, rows - 1)) * Kdim + kq * 8;
+    f32x4 acc[4];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)  // rows past the segment's end repeat the last one (not stored)
-      pa[j] = A + ((size_t)seg0 + min(m0 + 16 * j + l16, rows - 1)) * Kdim + kq * 8;
-    f32x4 acc[4][NJ];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 w[D][4], x[D][NJ];
+    for (int a = 0; a < 4; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 w[D][4], x[D];
     auto load = [&](int u, int s) {
 #pragma unroll
       for (int ni = 0; ni < 4; ++ni) w[u][ni] = *(const bf16x8*)(pw + (size_t)s * kPackBlock + ni * 1024);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) x[u][j] = *(const bf16x8*)(pa[j] + (size_t)s * kDmaBK);
+      x[u] = *(const bf16x8*)(pa + (size_t)s * kDmaBK);
     };
     auto mul = [&](int u) {
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-          acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u][j], acc[ni][j], 0, 0, 0);
+      for (int ni = 0; ni < 4; ++ni) acc[ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u], acc[ni], 0, 0, 0);
     };
 #pragma unroll
     for (int u = 0; u < D; ++u) load(u, u);
@@ -935,44 +582,28 @@ __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict
     }
 #pragma unroll
     for (int u = 0; u < D; ++u) mul(u);
+    if (m0 + l16 < rows) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int m = m0 + 16 * j + l16;
-      if (m < rows) {
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-          store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][j][0],
-                                 acc[ni][j][1], acc[ni][j][2], acc[ni][j][3]);
-      }
+      for (int ni = 0; ni < 4; ++ni)
+        store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m0 + l16, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][0],
+                               acc[ni][1], acc[ni][2], acc[ni][3]);
     }
   }
 }
 
-// Whether ffn_gemm_few takes a GEMM of at most `rows` rows per segment.  Against the tile kernels it saves each tile's
-// prologue and epilogue and fills the chip with fewer columns, but it fetches the activations four times as often, so
-// that more rows, a longer K and more tiles (`tiles` of 256 columns, all segments) speak for the tiles; those of the
-// persistent kernel cost more each than those of the kernel with one tile per work-group.  The lines lie where 38 shapes
-// (E = 4 .. 256, d = 256 .. 4096, h = 512 .. 16384) put them; us, this kernel / tiles:
-//   up to 16 rows:  2 048 tiles, K = 2048: 368 / 386;  1 024 tiles, K = 8192 (4 GiB of weights): 712 / 720;
-//                   2 048 tiles, K = 4096 (4 GiB): 751 / 746
-//   32 rows:        256 tiles, K = 8192 (1 GiB): 198 / 199;  512, K = 4096 (1 GiB): 194 / 195;  512, K = 8192: 388 / 378;
-//                   288, K = 6144: 241 / 228;  2 048, K = 2048: 403 / 403;  1 024, K = 1024: 110 / 122
-//                   one tile per work-group: 144, K = 8192: 136 / 145;  200, K = 1280: 34 / 29
-//   48 rows:        128 tiles, K = 16384: 208 / 258;  256, K = 1024: 35.4 / 41.8;  256, K = 4096: 117 / 114;
-//                   1 024, K = 1024: 128 / 129;  512, K = 2048: 119 / 112
-//                   one tile per work-group: 100, K = 10240: 134 / 161;  200, K = 1280: 41 / 30
-//   64 rows:        128 tiles, K = 8192: 121 / 139;  256, K = 1024: 40.7 / 43.5;  256, K = 4096: 132 / 117;
-//                   512, K = 1024: 73.0 / 71.7
-//                   one tile per work-group: 100, K = 10240: 153 / 161;  144, K = 8192: 184 / 149
-inline bool few_rows_take(int rows, long long tiles, int Kdim, bool persistent) {
-  const long long cus = cu_count();
-  if (rows <= 16) return Kdim <= 2048 || tiles * Kdim < cus * 32768;
-  if (rows <= 32) {
-    if (!persistent) return tiles <= cus * 5 / 8;
-    return Kdim <= 2048 || (tiles * Kdim <= cus * 8192 && (Kdim <= 4096 || tiles <= cus));
-  }
-  if (rows <= 48) return tiles <= cus / 2 || (persistent && Kdim <= 1024);
-  return rows <= kFewRows && (tiles <= cus / 2 || (persistent && Kdim <= 1024 && tiles <= cus));
+// Expected time in us of the tile kernels above with `rows` rows in each of E segments: prologue and launch, turns of tiles (one
+// per compute unit; a long list ends in half a turn), each an epilogue and K/64 double steps, no faster than the weights
+// (4.9 TB/s).  A fit to 44 launches of the persistent kernel (E = 8 .. 128, d = 512 .. 4096, h = 2048 .. 16384, 96 to 800
+// rows), which it meets to 9 % in the mean.
+double tiles_time(int E, int rows, int Kdim, int Ndim, bool persistent, double* turns) {
+  const int cus = cu_count(), NT = Ndim / kBN;
+  int bm = kBM;
+  auto tiles = [&]() { return (long long)E * NT * ceil_div(rows, bm); };
+  if (persistent && 2 * ((tiles() + 7) / 8) <= cus / 8) bm = 4 * ((tiles() + 7) / 8) <= cus / 8 ? kBM / 4 : kBM / 2;
+  const int sub = ceil_div(ceil_div(rows, ceil_div(rows, bm)), 16);
+  *turns = (double)tiles() / cus;
+  const double tile = 0.96 * sub + Kdim / 64 * (0.53 + 0.043 * sub);
+  return soft_max(11.4 + (*turns <= 3.0 ? ceil(*turns) : *turns + 0.63) * tile, 11.4 + (double)E * Ndim * Kdim * 2 / 4.85e6);
 }
 
 // Weight packing: block (e, nt, kt) of 16 KiB is the LDS image of W[e][nt*256 .. +256][kt*32 .. +32]:
@@ -1046,20 +677,31 @@ __global__ __launch_bounds__(256) void transpose_pack_kernel(const uint16_t* __r
 
 template <int EPI>
 int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-               int rows_max, int Kdim, int Ndim, unsigned int* queue, hipStream_t st) {
+               int rows_max, int T, int Kdim, int Ndim, unsigned int* queue, hipStream_t st) {
   const int MT = ceil_div(rows_max, kBM), NT = Ndim / kBN;
   const long long total = (long long)E * MT * NT;
   if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
   const bool persistent = E % 8 == 0 && E <= 512;
-  if (few_rows_take(rows_max, (long long)E * NT, Kdim, persistent)) {
-    const long long blocks = (long long)E * (Ndim / kFewCols);
-    if (blocks > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-    auto few = rows_max <= 16 ? ffn_gemm_few<1, EPI> : rows_max <= 32 ? ffn_gemm_few<2, EPI>
-             : rows_max <= 48 ? ffn_gemm_few<3, EPI> : ffn_gemm_few<4, EPI>;
-    hipLaunchKernelGGL(few, dim3((unsigned)blocks), dim3(64), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
+  const long long waves = (long long)E * (Ndim / kFewCols);
+  if (rows_max <= kFewRows && waves >= 2 * cu_count() && waves <= 0x7FFFFFFFLL) {
+    hipLaunchKernelGGL(ffn_gemm_few<EPI>, dim3((unsigned)waves), dim3(64), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
                        (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
     return launch_status();
   }
+  // Few rows per segment, few experts, narrow outputs: tiles of 256 columns, which cost a prologue of some 10 us, leave
+  // compute units idle or empty, and the smaller tiles of ffn_any.hip are faster (us, tiles here / there):
+  //   E = 16, d = 1024, h = 4096, both GEMMs: 96 rows 44 + 65 / 29 + 30;  255 rows 53 + 70 / 53 + 60;  640 uneven 97 + 86 / 83 + 74
+  //   E = 4, d = 2048, h = 8192: 100 rows 42 + 117 / 33 + 46;  250 rows 54 + 155 / 48 + 60
+  //   E = 64, d = 1024, h = 4096: 48 rows 123 + 110 / 111 + 98;  256 rows 180 + 146 / 203 + 187
+  //   E = 8, d = 4096, h = 16384: 200 rows 228 + 278 / 313 + 283;  500 rows 426 + 380 / 561 + 578
+  // A tenth is asked for, so that a misjudged time does not cost more than is gained, but not with up to two segments per
+  // XCD and two turns of tiles: there uneven segments, which the times do not know, speak for the small tiles (E = 16 above:
+  // judged alike at 512 rows, though not with Z to write or read: 106 + 110 / 106 + 121; E = 64, d = 2048, h = 8192, even in 0 .. 200 rows, second GEMM, judged alike: 427 / 468).
+  const int rows = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
+  double turns = 0.0;
+  const double here = tiles_time(E, rows, Kdim, Ndim, persistent, &turns);
+  if (any_gemm_time(E, rows, Kdim, Ndim) < (E <= 16 && turns <= 2.0 && EPI <= kEpiGelu ? 1.0 : 0.9) * here)
+    return any_gemm<false, true, EPI, false>(A, Wp, C, aux, seg_off, buf_expert, E, rows_max, T, Kdim, Ndim, st);
   static std::atomic<uint64_t> lds_allowed[2];  // per kernel of this instantiation: devices whose LDS limit is raised
   if (persistent) {
     auto kern = ffn_gemm_dma_persistent<EPI>;
@@ -1114,43 +756,6 @@ inline bool packable(const locmoe_desc* p) {
          (long long)p->h * 2 * 256 < 0x7FFFFFFFLL;
 }
 
-template <bool A_F32, int EPI, bool OUT_F32, int BN>
-int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-               int rows_max, int T, int Kdim, int Ndim, hipStream_t st) {
-  // (a limit of the interface, see the header; the grid below has none that buffers of a card reach)
-  if ((A_F32 || Kdim % 64 || Ndim % 256) && (long long)E * ceil_div(rows_max, 64) > 65535) return LOCMOE_ERR_SHAPE;
-  constexpr int kBM = AnyK<A_F32>::kBM, kFine = AnyK<A_F32>::kFine;
-  const bool far = (long long)Kdim * (A_F32 ? 4 : 2) * kBM > 0xFFFFFFFFLL;  // (the weight rows' offsets are no larger)
-  const int NT = ceil_div(Ndim, BN);
-  const bool list = rows_max > kBM || far;
-  // m-tiles: at most those of full segments, and at most a partial one per segment beside those that T rows fill
-  const long long mtiles = std::min((long long)E * ceil_div(rows_max, kFine), (long long)E + T / kFine);
-  const long long grid = list ? 8 * ceil_div(NT, 8) * mtiles : ((long long)E * NT + 7) / 8 * 8;
-  if (grid > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-  // a launch takes fewer than 2^32 threads along x: what is beyond 2^23 work-groups goes to y (a list is walked in turns)
-  const unsigned gx = (unsigned)std::min<long long>(grid, 1 << 23), gy = list ? 1 : (unsigned)((grid + gx - 1) / gx);
-  auto kern = far ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true, true>
-            : list ? ffn_gemm_any<A_F32, EPI, OUT_F32, BN, true, false> : ffn_gemm_any<A_F32, EPI, OUT_F32, BN, false, false>;
-  static std::atomic<uint64_t> lds_allowed[3];
-  if (!allow_lds((const void*)kern, kAnyLds, lds_allowed[list + far])) return LOCMOE_ERR_HIP;
-  hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(kAnyThreads), kAnyLds, st, (const char*)A, (const char*)W, C,
-                     (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim, NT, E, cu_count() / 4);
-  return launch_status();
-}
-
-template <bool A_F32, int EPI, bool OUT_F32>
-int launch_gemm(const void* A, const void* W, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-                int rows_max, int T, int Kdim, int Ndim, hipStream_t st) {
-  // 128 columns per tile, or 64 where that leaves some of the chip's work-group slots (two per compute unit) empty.
-  // The forward at 2 048 rows per expert (d = 2048, h = 8192, E = 8): 1 160 us with 128 columns in both GEMMs, 1 413 with 64
-  // in the second; the second GEMM at d = 1024, h = 4096, E = 16, 158 rows (64 columns: 256 tiles): 76 us against 83 to 92.
-  const int rows_even = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
-  const long long tiles = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows_even, AnyK<A_F32>::kBM);
-  if (tiles >= 2 * cu_count())
-    return launch_any<A_F32, EPI, OUT_F32, 128>(A, W, C, aux, seg_off, buf_expert, E, rows_max, T, Kdim, Ndim, st);
-  return launch_any<A_F32, EPI, OUT_F32, 64>(A, W, C, aux, seg_off, buf_expert, E, rows_max, T, Kdim, Ndim, st);
-}
-
 }  // namespace
 }  // namespace locmoe
 
@@ -1166,13 +771,13 @@ int gemm_d_to_h(const locmoe_desc* desc, const void* A, const int32_t* seg_off, 
   const int rows_max = desc->C < desc->T ? desc->C : desc->T;  // kept[e] <= min(C, T)
   if (desc->w_packed) {
     if (desc->x_dtype != LOCMOE_BF16 || !packable(desc)) return LOCMOE_ERR_ARG;
-    return launch_dma<EPI>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->d, desc->h, queue,
+    return launch_dma<EPI>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h, queue,
                            as_stream(stream));
   }
   if (desc->x_dtype == LOCMOE_F32)
-    return launch_gemm<true, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h,
+    return any_gemm<true, false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h,
                                          as_stream(stream));
-  return launch_gemm<false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h,
+  return any_gemm<false, false, EPI, false>(A, W, Cbf16, aux, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->d, desc->h,
                                         as_stream(stream));
 }
 
@@ -1183,13 +788,13 @@ int gemm_h_to_d(const locmoe_desc* desc, const void* A, const int32_t* seg_off, 
   const int rows_max = desc->C < desc->T ? desc->C : desc->T;
   if (desc->w_packed) {
     if (desc->x_dtype != LOCMOE_BF16 || !packable(desc)) return LOCMOE_ERR_ARG;
-    return launch_dma<kEpiNone>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->h, desc->d, queue,
+    return launch_dma<kEpiNone>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h, desc->d, queue,
                                 as_stream(stream));
   }
   if (desc->x_dtype == LOCMOE_F32)
-    return launch_gemm<false, kEpiNone, true>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h,
+    return any_gemm<false, false, kEpiNone, true>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h,
                                               desc->d, as_stream(stream));
-  return launch_gemm<false, kEpiNone, false>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h,
+  return any_gemm<false, false, kEpiNone, false>(A, W, C, nullptr, seg_off, buf_expert, desc->E, rows_max, desc->T, desc->h,
                                              desc->d, as_stream(stream));
 }
 

@@ -175,6 +175,20 @@ def test_few_rows_kernel_covers_longer_segments(env, T, C):
         assert env[0].equal(got[name], ref[name]), name
 
 
+# every tile shape, packed and row-major (weight tiles in runs and dealt out), lists of up to 64 segments and of more, and
+# weight tiles that end in the next block of 256 packed columns or past the last: the bits that one other shape gives
+@pytest.mark.parametrize("d,h,rows", [(256, 512, [150, 0, 1, 97, 128, 129, 33, 16]),                 # 128 x 32
+                                      (256, 2304, [161, 0, 160, 1, 130, 96, 65, 32] * 4),            # 160 x 160, 128 x 64
+                                      (512, 1280, [150, 33, 149, 0, 64, 150, 128, 17] * 8),          # 160 x 160, 192 x 128
+                                      (256, 768, [140, 0, 139, 1, 96, 97, 15, 129] * 16)])           # 128 segments
+def test_tile_shapes_give_the_same_bits(env, d, h, rows):
+    ref = ffn_outputs(env, d, h, rows, 600, 300, packed=False)
+    for packed in (False, True):
+        got = ffn_outputs(env, d, h, rows, len(rows) * max(rows), max(rows), packed=packed)
+        for name in ref:
+            assert env[0].equal(got[name], ref[name]), (name, packed)
+
+
 # row-major weights: a work-group per weight tile (min(C, T) <= 128) and lists of tiles, shorter and longer than the grid
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,C", [(600, 64), (60, 3000), (260, 3000)])
