@@ -34,8 +34,7 @@ __device__ __forceinline__ void group_argmax(float& v, int& i) {
 }
 
 struct RouteWs {
-  int32_t* cnt;    // [blocks][E]
-  float* psum;     // [blocks][E]
+  int2* cell;      // [blocks][E]: count, bits of the probability sum
   int32_t* home;   // [blocks][N]
   int32_t* local;  // [blocks]
 };
@@ -43,27 +42,22 @@ struct RouteWs {
 __host__ __device__ inline RouteWs route_ws(void* ws, int E, int N) {
   RouteWs r;
   char* p = (char*)ws;
-  r.cnt = (int32_t*)p;   p += (size_t)kRouteMaxBlocks * E * 4;
-  r.psum = (float*)p;    p += (size_t)kRouteMaxBlocks * E * 4;
+  r.cell = (int2*)p;     p += (size_t)kRouteMaxBlocks * E * 8;
   r.home = (int32_t*)p;  p += (size_t)kRouteMaxBlocks * N * 4;
   r.local = (int32_t*)p;
   return r;
 }
 
-template <int S, int EPL>
-__global__ __launch_bounds__(kRouteThreads) void route_kernel(
-    const float* __restrict__ g, const float* __restrict__ eps, const int32_t* __restrict__ home,
-    const int32_t* __restrict__ e2n, int32_t* __restrict__ eid, float* __restrict__ w, void* ws, int T,
-    int E, int N, int relu, int tokens_per_block) {
-  constexpr int G = kRouteThreads / S;  // groups (tokens in flight) per block
-  extern __shared__ char smem[];
-  int32_t* hist = (int32_t*)smem;            // [E]
-  int32_t* hhist = hist + E;                 // [N]
-  int32_t* local = hhist + N;                // [1]
-  float* pacc = (float*)(local + 1);         // [G][E]
-  for (int i = threadIdx.x; i < E + N + 1; i += kRouteThreads) hist[i] = 0;
-  __syncthreads();
-
+// Tokens tok0 .. tok1 - 1 by a work-group of THREADS: eid and w to memory; counts per expert (hist), per home node (hhist) and
+// of tokens that stay on their node (local), and each group's probability sums (pacc [THREADS / S][E]) to LDS.  The LDS
+// words are complete behind the caller's next barrier.
+template <int S, int EPL, int THREADS>
+__device__ __forceinline__ void route_tokens(const float* __restrict__ g, const float* __restrict__ eps,
+                                             const int32_t* __restrict__ home, const int32_t* __restrict__ e2n,
+                                             int32_t* __restrict__ eid, float* __restrict__ w, int32_t* hist,
+                                             int32_t* hhist, int32_t* local, float* pacc, int tok0, int tok1, int E,
+                                             int N, int relu) {
+  constexpr int G = THREADS / S;  // groups (tokens in flight) per block
   const int grp = threadIdx.x / S, j = threadIdx.x % S;
   const int per_node = E / N;  // used only when e2n is NULL (then E % N == 0)
   float epsv[EPL];
@@ -76,8 +70,6 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
 #pragma unroll
   for (int k = 0; k < EPL; ++k) acc[k] = 0.f;
 
-  const int tok0 = blockIdx.x * tokens_per_block;
-  const int tok1 = min(T, tok0 + tokens_per_block);
   // the loads of the next batch of tokens are issued before the current batch is reduced
   // (the tokens' home nodes come with the batch: fetched where they are used, behind the arg-max, each was a
   // memory round trip of its own on the critical path)
@@ -149,13 +141,30 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(
     const int i = j + k * S;
     if (i < E) pacc[grp * E + i] = acc[k];
   }
+}
+
+template <int S, int EPL>
+__global__ __launch_bounds__(kRouteThreads) void route_kernel(
+    const float* __restrict__ g, const float* __restrict__ eps, const int32_t* __restrict__ home,
+    const int32_t* __restrict__ e2n, int32_t* __restrict__ eid, float* __restrict__ w, void* ws, int T,
+    int E, int N, int relu, int tokens_per_block) {
+  constexpr int G = kRouteThreads / S;
+  extern __shared__ char smem[];
+  int32_t* hist = (int32_t*)smem;            // [E]
+  int32_t* hhist = hist + E;                 // [N]
+  int32_t* local = hhist + N;                // [1]
+  float* pacc = (float*)(local + 1);         // [G][E]
+  for (int i = threadIdx.x; i < E + N + 1; i += kRouteThreads) hist[i] = 0;
+  __syncthreads();
+  const int tok0 = blockIdx.x * tokens_per_block;
+  route_tokens<S, EPL, kRouteThreads>(g, eps, home, e2n, eid, w, hist, hhist, local, pacc, tok0,
+                                      min(T, tok0 + tokens_per_block), E, N, relu);
   __syncthreads();
   RouteWs r = route_ws(ws, E, N);
   for (int i = threadIdx.x; i < E; i += kRouteThreads) {
     float s = 0.f;
     for (int q = 0; q < G; ++q) s += pacc[q * E + i];
-    r.psum[(size_t)blockIdx.x * E + i] = s;
-    r.cnt[(size_t)blockIdx.x * E + i] = hist[i];
+    r.cell[(size_t)blockIdx.x * E + i] = make_int2(hist[i], __float_as_int(s));
   }
   for (int i = threadIdx.x; i < N; i += kRouteThreads) r.home[(size_t)blockIdx.x * N + i] = hhist[i];
   if (threadIdx.x == 0) r.local[blockIdx.x] = *local;
@@ -166,16 +175,18 @@ constexpr int kFinWaves = kFinThreads / kWave;
 
 // Sums (and one maximum) over the block of NQ doubles per thread, in a fixed order: a butterfly inside each wave
 // (lane i adds lane i ^ o for o = 32 .. 1), the sixteen wave results through LDS, added in wave order by every
-// thread.  Two barriers for all NQ quantities together.
+// thread.  Two barriers for all NQ quantities together.  With `one` only the first wave holds anything and is asked.
 template <int NQ>
-__device__ __forceinline__ void block_sums(double (&v)[NQ], double& vmax, double (*part)[kFinWaves]) {
+__device__ __forceinline__ void block_sums(double (&v)[NQ], double& vmax, double (*part)[kFinWaves], bool one) {
+  const int wave = threadIdx.x / kWave;
+  if (one && wave) return;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) v[q] += __shfl_xor(v[q], o);
     vmax = fmax(vmax, __shfl_xor(vmax, o));
   }
-  const int wave = threadIdx.x / kWave;
+  if (one) return;
   if (threadIdx.x % kWave == 0) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) part[q][wave] = v[q];
@@ -195,109 +206,66 @@ __device__ __forceinline__ void block_sums(double (&v)[NQ], double& vmax, double
   vmax = m;
 }
 
-// One block: column sums of the per-block partials, then the scalars of Eq. 5 / Eq. 6.
-__global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
-    void* ws, const int32_t* __restrict__ e2n, int has_home, int32_t* __restrict__ cnt,
-    float* __restrict__ Psum, float* __restrict__ stats, int nb, int T, int E, int N, float alpha, float mu) {
-  __shared__ double part[6][kFinWaves];
-  __shared__ double dpart[kFinThreads];
-  __shared__ int32_t ipart[kFinThreads];
-  __shared__ int32_t s_cnt[1024];
-  __shared__ double s_P[1024];
-  __shared__ int32_t s_home[1024];
-  __shared__ int32_t s_pernode[1024];
-  RouteWs r = route_ws(ws, E, N);
+// Adds up columns that thread (q, e), q = tid / E < R, holds a part of: first the parts of up to eight q in a row, then
+// these sums in order, so that no thread adds more than some R / 8 + 8 words one after the other (all R of them in one
+// thread took 3 us of a small layer's route).  Result in thread e < E.
+__device__ __forceinline__ void column_sums(int32_t& ci, double& ps, int32_t* ipart, double* dpart, int E, int R) {
   const int tid = threadIdx.x;
-  if (tid < N) { s_home[tid] = 0; s_pernode[tid] = 0; }
-  int local = 0;
-  int32_t hi = 0;
-  {  // cnt and Psum: thread (rb, e) adds rows rb, rb+R, ... in order; then the row groups are added in order.
-     // The home-node counts the same way.
-    const int R = kFinThreads / E;
-    const int e = tid % E, rb = tid / E;
-    int32_t ci = 0;
-    double ps = 0.0;
-    // Loads are unconditional (rows past the end re-read the thread's first row and are not added) and all of
-    // a round's loads - counts, probability sums, home counts, locality counts - are issued before the first
-    // is used: the partials were written by other XCDs, every dependent round trip costs microseconds, and with
-    // the bound inside the loop every load waited for the one before it.
-    constexpr int U = 32, UH = 8;
-    const int Rn = kFinThreads / N;
-    const int nu = tid % N, rn = tid / N;
-    const bool cols = rb < R && rb < nb, hcols = has_home && rn < Rn && rn < nb;
-    for (int b0 = 0; b0 < nb; b0 += U * R) {
-      int32_t cv[U];
-      float pv[U];
-      int32_t hvv[UH];
-      if (cols) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int b = b0 + rb + u * R;
-          const size_t at = (size_t)(b < nb ? b : rb) * E + e;
-          cv[u] = r.cnt[at];
-          pv[u] = r.psum[at];
-        }
-      }
-      const bool hround = hcols && b0 == 0;   // the home counts go with the first round (looped below if they are many)
-      if (hround) {
-#pragma unroll
-        for (int u = 0; u < UH; ++u) {
-          const int b = rn + u * Rn;
-          hvv[u] = r.home[(size_t)(b < nb ? b : rn) * N + nu];
-        }
-      }
-      if (has_home && b0 == 0)
-        for (int b = tid; b < nb; b += kFinThreads) local += r.local[b];
-      if (cols) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const bool live = b0 + rb + u * R < nb;
-          ci += live ? cv[u] : 0;
-          ps += live ? (double)pv[u] : 0.0;
-        }
-      }
-      if (hround) {
-#pragma unroll
-        for (int u = 0; u < UH; ++u) hi += (rn + u * Rn < nb) ? hvv[u] : 0;
-      }
-    }
-    if (hcols)  // home counts beyond the first UH rows of this thread (few nodes per thread group: rare)
-      for (int b = rn + UH * Rn; b < nb; b += Rn) hi += r.home[(size_t)b * N + nu];
-    ipart[tid] = ci;
-    dpart[tid] = ps;
-    __syncthreads();
-    if (tid < E) {
-      int32_t c = 0;
-      double p = 0.0;
-      for (int q = 0; q < R; ++q) { c += ipart[q * E + tid]; p += dpart[q * E + tid]; }
-      s_cnt[tid] = c;
-      s_P[tid] = p;
-      cnt[tid] = c;
-      Psum[tid] = (float)p;
-    }
-    if (has_home) {  // integer adds: any order gives the same counts
-      if (hi) atomicAdd(&s_home[tid % N], hi);
-      if (tid < E) atomicAdd(&s_pernode[e2n ? e2n[tid] : tid / (E / N)], 1);
-    }
-    __syncthreads();
+  ipart[tid] = ci;
+  dpart[tid] = ps;
+  __syncthreads();
+  const int q = tid / E, e = tid - q * E;
+  const int runs = R < 8 ? R : 8, len = (R + runs - 1) / runs;  // run j: q = j len .. + len
+  ci = 0;
+  ps = 0.0;
+  if (q < runs) {
+    const int q1 = min(R, (q + 1) * len);
+#pragma unroll 8
+    for (int i = q * len; i < q1; ++i) { ci += ipart[i * E + e]; ps += dpart[i * E + e]; }
   }
+  __syncthreads();
+  if (q < runs) { ipart[tid] = ci; dpart[tid] = ps; }
+  __syncthreads();
+  if (tid < E) {
+#pragma unroll
+    for (int j = 1; j < 8; ++j) {
+      if (j < runs) { ci += ipart[j * E + tid]; ps += dpart[j * E + tid]; }
+    }
+  }
+}
+
+struct FinShared {
+  double part[6][kFinWaves];
+  double dpart[kFinThreads];
+  int32_t ipart[kFinThreads];
+  int32_t home[1024], pernode[1024];
+};
+
+// cnt, Psum and the scalars of Eq. 5 / Eq. 6 from the totals: thread e < E holds expert e's, home[] the tokens per home node
+// and pernode[] the experts per node (both behind a barrier), and the threads together the tokens that stay on their node.
+__device__ __forceinline__ void route_scalars(FinShared& sh, int32_t c, double p, int local, bool local_first_wave,
+                                              const int32_t* e2n, int has_home, int32_t* cnt, float* Psum, float* stats,
+                                              int T, int E, int N, float alpha, float mu) {
+  const int tid = threadIdx.x;
   // Eq. 5: L_aux = alpha * n * sum_i f_i P_i
   double q[5] = {0.0, 0.0, 0.0, (double)local, 0.0};  // f P, KL(f || D_l), KL(P || D_l) terms, local tokens, empty experts
   double mx = 0.0;
   if (tid < E) {
-    const double f = (double)s_cnt[tid] / T, P = s_P[tid] / T;
+    cnt[tid] = c;
+    Psum[tid] = (float)p;
+    const double f = (double)c / T, P = p / T;
     q[0] = f * P;
-    mx = (double)s_cnt[tid];
-    q[4] = s_cnt[tid] == 0 ? 1.0 : 0.0;
+    mx = (double)c;
+    q[4] = c == 0 ? 1.0 : 0.0;
     if (has_home) {
       // Eq. 6 over experts: D_l[i] = T_node(i) / (T * experts on node(i))
       const int nu = e2n ? e2n[tid] : tid / (E / N);
-      const double Dl = (double)s_home[nu] / ((double)T * (double)s_pernode[nu]);
+      const double Dl = (double)sh.home[nu] / ((double)T * (double)sh.pernode[nu]);
       if (f > 0.0) q[1] = Dl > 0.0 ? f * log(f / Dl) : INFINITY;
       if (P > 0.0) q[2] = Dl > 0.0 ? P * log(P / Dl) : INFINITY;
     }
   }
-  block_sums<5>(q, mx, part);
+  block_sums<5>(q, mx, sh.part, E <= kWave && local_first_wave);
   if (tid == 0) {
     stats[0] = (float)((double)alpha * E * q[0]);
     stats[1] = (float)q[1];
@@ -310,9 +278,133 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
   }
 }
 
+// One block: column sums of the per-block partials, then the scalars of Eq. 5 / Eq. 6.  Bound by latencies (the launch,
+// one round trip to partials that other XCDs wrote, LDS, a few double-precision logarithms).  U: rows that a thread adds in
+// a round; the loads are unconditional (rows past the end re-read the thread's first row and are not added) and all of a
+// round's are issued before the first is used, so U is no larger than the partials need: with 32 rows always, 64 partials
+// took 64 loads in each of 1024 threads (T = 8 192, E = 16: 11.4 us).
+template <int U>
+__global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
+    void* ws, const int32_t* __restrict__ e2n, int has_home, int32_t* __restrict__ cnt,
+    float* __restrict__ Psum, float* __restrict__ stats, int nb, int T, int E, int N, float alpha, float mu) {
+  __shared__ FinShared sh;
+  RouteWs r = route_ws(ws, E, N);
+  const int tid = threadIdx.x;
+  if (tid < N) { sh.home[tid] = 0; sh.pernode[tid] = 0; }
+  const int R = kFinThreads / E;  // thread (rb, e) adds rows rb, rb+R, ... in order
+  const int rb = tid / E, e = tid - rb * E;
+  constexpr int UH = 8;
+  const int Rn = kFinThreads / N;
+  const int rn = tid / N, nu = tid - rn * N;
+  const bool cols = rb < R && rb < nb, hcols = has_home && rn < Rn && rn < nb;
+  int32_t ci = 0, hi = 0;
+  double ps = 0.0;
+  int local = 0;
+  int32_t hvv[UH];
+  for (int b0 = 0; b0 < nb; b0 += U * R) {
+    int2 v[U];
+    if (cols) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int b = b0 + rb + u * R;
+        v[u] = r.cell[(unsigned)((b < nb ? b : rb) * E + e)];
+      }
+    }
+    if (hcols && b0 == 0) {  // the home counts go with the first round (looped below if they are many)
+      hvv[0] = r.home[(size_t)rn * N + nu];
+      if (Rn < nb) {
+#pragma unroll
+        for (int u = 1; u < UH; ++u) {
+          const int b = rn + u * Rn;
+          hvv[u] = r.home[(size_t)(b < nb ? b : rn) * N + nu];
+        }
+      }
+    }
+    if (has_home && b0 == 0 && tid < nb) local = r.local[tid];  // (nb <= 512)
+    if (cols) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool live = b0 + rb + u * R < nb;
+        ci += live ? v[u].x : 0;
+        ps += live ? (double)__int_as_float(v[u].y) : 0.0;
+      }
+    }
+  }
+  if (hcols) {
+    hi = hvv[0];
+    if (Rn < nb) {
+#pragma unroll
+      for (int u = 1; u < UH; ++u) hi += (rn + u * Rn < nb) ? hvv[u] : 0;
+      for (int b = rn + UH * Rn; b < nb; b += Rn) hi += r.home[(size_t)b * N + nu];  // (few nodes per thread group: rare)
+    }
+  }
+  column_sums(ci, ps, sh.ipart, sh.dpart, E, R);  // (its barriers stand behind the zeros above)
+  if (has_home) {  // integer adds: any order gives the same counts
+    if (hi) atomicAdd(&sh.home[nu], hi);
+    if (tid < E) atomicAdd(&sh.pernode[e2n ? e2n[tid] : tid / (E / N)], 1);
+  }
+  __syncthreads();
+  route_scalars(sh, ci, ps, local, nb <= kWave, e2n, has_home, cnt, Psum, stats, T, E, N, alpha, mu);
+}
+
+// lanes per token: the whole expert axis up to 16 experts; beyond that, up to 128 experts, 16 lanes with
+// several experts each (four tokens per wave side by side: the cross-lane reductions, which dominate the
+// instruction count, shrink from six steps to four and are shared by four tokens); one wave per token above
+inline int route_lanes(int E) {
+  int S = 4;
+  while (S < E && S < 16) S *= 2;
+  return E > 128 ? 64 : S;
+}
+
+// One work-group where its groups take the tokens in one batch.  us in one / two launches: E = 4, 1 024 tokens 8.5 / 11.0,
+// 2 048 11.2 / 11.0;  E = 8, 512 tokens 8.5 / 10.2, 1 024 11.4 / 10.3;  E = 16, 192 tokens 8.2 / 9.7, 512 11.9 / 10.0;
+// E = 64, 192 tokens 10.4 / 11.1;  E = 128, 192 tokens 16.7 / 16.9.
+inline bool route_in_one(int T, int E) { return E <= 64 && T <= kFinThreads / route_lanes(E) * kTokPerGroup; }
+
+// Few tokens: one work-group does all of it, which saves the second launch and the way of the partials through memory.
+template <int S, int EPL>
+__global__ __launch_bounds__(kFinThreads) void route_one_kernel(
+    const float* __restrict__ g, const float* __restrict__ eps, const int32_t* __restrict__ home,
+    const int32_t* __restrict__ e2n, int32_t* __restrict__ eid, float* __restrict__ w, int32_t* __restrict__ cnt,
+    float* __restrict__ Psum, float* __restrict__ stats, int T, int E, int N, int relu, float alpha, float mu) {
+  constexpr int G = kFinThreads / S;
+  __shared__ FinShared sh;
+  __shared__ int32_t s_local;
+  extern __shared__ char smem[];
+  int32_t* hist = (int32_t*)smem;    // [E]
+  float* pacc = (float*)(hist + E);  // [G][E]
+  const int tid = threadIdx.x;
+  if (tid < E) hist[tid] = 0;
+  if (tid < N) { sh.home[tid] = 0; sh.pernode[tid] = 0; }
+  if (tid == 0) s_local = 0;
+  __syncthreads();
+  route_tokens<S, EPL, kFinThreads>(g, eps, home, e2n, eid, w, hist, sh.home, &s_local, pacc, 0, T, E, N, relu);
+  if (home && tid < E) atomicAdd(&sh.pernode[e2n ? e2n[tid] : tid / (E / N)], 1);
+  __syncthreads();
+  const int R = kFinThreads / E, rb = tid / E, e = tid - rb * E;
+  int32_t ci = 0;
+  double ps = 0.0;
+  if (rb < R) {
+#pragma unroll 4
+    for (int q = rb; q < G; q += R) ps += (double)pacc[q * E + e];
+  }
+  column_sums(ci, ps, sh.ipart, sh.dpart, E, R);
+  route_scalars(sh, tid < E ? hist[tid] : 0, ps, tid == 0 ? s_local : 0, true, e2n, home ? 1 : 0, cnt, Psum, stats, T, E, N,
+                alpha, mu);
+}
+
 template <int S, int EPL>
 void launch_route(const locmoe_desc* p, const float* g, const float* eps, const int32_t* home,
-                  const int32_t* e2n, int32_t* eid, float* w, void* ws, int nb, int tpb, hipStream_t st) {
+                  const int32_t* e2n, int32_t* eid, float* w, int32_t* cnt, float* Psum, float* stats, void* ws, int nb,
+                  int tpb, hipStream_t st) {
+  if constexpr (S <= 16) {
+    if (route_in_one(p->T, p->E)) {
+      const size_t smem = (size_t)p->E * 4 + (size_t)(kFinThreads / S) * p->E * 4;
+      hipLaunchKernelGGL((route_one_kernel<S, EPL>), dim3(1), dim3(kFinThreads), smem, st, g, eps, home, e2n, eid, w, cnt,
+                         Psum, stats, p->T, p->E, p->N, p->relu, p->alpha, p->mu);
+      return;
+    }
+  }
   constexpr int G = kRouteThreads / S;
   const size_t smem = (size_t)(p->E + p->N + 1) * 4 + (size_t)G * p->E * 4;
   hipLaunchKernelGGL((route_kernel<S, EPL>), dim3(nb), dim3(kRouteThreads), smem, st, g, eps, home, e2n, eid,
@@ -333,19 +425,14 @@ extern "C" int locmoe_route(const locmoe_desc* desc, const float* g, const float
   if (!ws || ws_bytes < locmoe_workspace_bytes(desc)) return LOCMOE_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
   const int E = desc->E;
-  // lanes per token: the whole expert axis up to 16 experts; beyond that, up to 128 experts, 16 lanes with
-  // several experts each (four tokens per wave side by side: the cross-lane reductions, which dominate the
-  // instruction count, shrink from six steps to four and are shared by four tokens); one wave per token above
-  int S = 4;
-  while (S < E && S < 16) S *= 2;
-  if (E > 128) S = 64;
+  const int S = route_lanes(E);
   const int G = kRouteThreads / S;
   const int step = G * kTokPerGroup;
   int tpb = ceil_div(desc->T, kRouteMaxBlocks);
   tpb = ceil_div(tpb, step) * step;
   const int nb = ceil_div(desc->T, tpb);
   const int epl = ceil_div(E, S);
-#define LOCMOE_ROUTE(SS, EE) launch_route<SS, EE>(desc, g, eps, home, e2n, eid, w, ws, nb, tpb, s)
+#define LOCMOE_ROUTE(SS, EE) launch_route<SS, EE>(desc, g, eps, home, e2n, eid, w, cnt, Psum, stats, ws, nb, tpb, s)
   if (S == 4) LOCMOE_ROUTE(4, 1);
   else if (S == 8) LOCMOE_ROUTE(8, 1);
   else if (S == 16 && epl == 1) LOCMOE_ROUTE(16, 1);
@@ -358,7 +445,12 @@ extern "C" int locmoe_route(const locmoe_desc* desc, const float* g, const float
 #undef LOCMOE_ROUTE
   st = launch_status();
   if (st != LOCMOE_OK) return st;
-  hipLaunchKernelGGL(route_finalize_kernel, dim3(1), dim3(kFinThreads), 0, s, ws, e2n, home ? 1 : 0, cnt, Psum,
-                     stats, nb, desc->T, E, desc->N, desc->alpha, desc->mu);
+  if (route_in_one(desc->T, E)) return LOCMOE_OK;
+  const int rounds = ceil_div(nb, kFinThreads / E);  // rows of partials per thread
+  auto fin = rounds <= 1 ? route_finalize_kernel<1> : rounds <= 2 ? route_finalize_kernel<2>
+           : rounds <= 4 ? route_finalize_kernel<4> : rounds <= 8 ? route_finalize_kernel<8>
+           : route_finalize_kernel<16>;
+  hipLaunchKernelGGL(fin, dim3(1), dim3(kFinThreads), 0, s, ws, e2n, home ? 1 : 0, cnt, Psum, stats, nb, desc->T, E,
+                     desc->N, desc->alpha, desc->mu);
   return launch_status();
 }
