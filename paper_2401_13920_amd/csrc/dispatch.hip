@@ -1,11 +1,13 @@
 // Capacity-bounded stable dispatch (capacity: Section 3.2.3).
-//   1. dispatch_hist_kernel   per block of 1024 tokens: count of tokens per expert (few blocks: counted by step 2)
+// Up to kDispOneTokens tokens dispatch_one_kernel does it all in one launch; else
+//   1. dispatch_hist_kernel   per block of 1024 tokens: count of tokens per expert
 //   2. dispatch_slots_kernel  every block re-derives, from the [blocks,E] count matrix, the
 //      tokens before it per expert and the totals, hence kept[], the buffer order and the
 //      segment offsets; then ranks its own tokens (wave ballots + ordered wave prefixes)
 //   3. dispatch_copy_kernel   send[r,:] = x[row_token[r],:] for r < K, 16-byte vectors
 // Integer-only; LDS integer atomics appear only where the result does not depend on their
 // order, so slots are bit-identical from run to run.
+#include <algorithm>
 #include <atomic>
 
 #include "common.h"
@@ -37,22 +39,169 @@ constexpr int kDispThreads = 256;
 constexpr int kDispWaves = kDispThreads / kWave;
 constexpr int kTokPerWave = kDispatchTokensPerBlock / kDispWaves;  // contiguous tokens per wave
 constexpr int kIter = kTokPerWave / kWave;
-// Up to this many blocks the slots kernel counts the tokens per expert itself, every block all of them, and the
-// histogram's launch is saved.  The line lies where no distribution of the tokens loses.  Whole dispatch, d = 256, us,
-// own counts / both kernels, tokens spread evenly over 16 experts; all on one; half each on two of 64:
-//     192 tokens  7.9 /  9.3   7.0 /  8.8   9.8 / 11.5
-//   4 096 tokens  9.6 / 10.6   9.3 / 10.4  12.1 / 12.6
-//   5 120 tokens 10.1 / 10.4   9.8 / 10.4  12.6 / 12.7
-//   6 000 tokens 10.4 / 10.8  10.0 / 10.4  12.9 / 13.0   (on two of 16: 10.3 / 10.2)
-//   8 192 tokens 11.3 / 10.9  10.8 / 10.7  13.9 / 13.0
-// (Counted with one addition per token, 8 192 tokens on one expert took 14.5.)
-constexpr int kDispSelfBlocks = 5;
-
 // Orders this wave's LDS accesses before the call against those after it, for all lanes.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Buffer order (experts sorted by (node, id)): rank[e], and seg[r], the first row of the expert at rank r (seg[E] = K), from
+// the kept rows tot[e] and nodes node[e].  Called by a work-group of kDispThreads; ends with a barrier.
+__device__ __forceinline__ void buffer_order(const int32_t* e2n, const int32_t* tot, const int32_t* node, int32_t* rank,
+                                             int32_t* seg, int E) {
+  const int tid = threadIdx.x, lane = tid % kWave;
+  for (int e = tid; e < E; e += kDispThreads) {
+    int r = e;
+    if (e2n) {
+      r = 0;
+      const int ne = node[e];
+#pragma unroll 8
+      for (int q = 0; q < E; ++q) r += (node[q] < ne || (node[q] == ne && q < e)) ? 1 : 0;
+    }
+    rank[e] = r;
+    seg[r + 1] = tot[e];  // staged: kept of the expert at rank r, scanned below
+  }
+  __syncthreads();
+  if (tid / kWave == 0) {  // inclusive scan of seg[1..E] by one wave: lane owns a contiguous run
+    const int per = ceil_div(E, kWave);
+    const int lo = lane * per, hi = min(E, lo + per);
+    int s = 0;
+    for (int i = lo; i < hi; ++i) s += seg[i + 1];
+    int incl = s;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int o = __shfl_up(incl, d);
+      if (lane >= d) incl += o;
+    }
+    int run = incl - s;
+    if (lane == 0) seg[0] = 0;
+    for (int i = lo; i < hi; ++i) {
+      run += seg[i + 1];
+      seg[i + 1] = run;
+    }
+  }
+  __syncthreads();
+}
+
+// The outputs per expert and node, by one work-group.  by_rank: LDS for E words
+__device__ __forceinline__ void write_segments(const int32_t* tot, const int32_t* node, const int32_t* rank,
+                                               const int32_t* seg, int32_t* by_rank, int32_t* kept, int32_t* seg_off,
+                                               int32_t* node_off, int32_t* buf_expert, int E, int N) {
+  const int tid = threadIdx.x;
+  for (int e = tid; e < E; e += kDispThreads) {
+    kept[e] = tot[e];
+    buf_expert[rank[e]] = e;
+    by_rank[rank[e]] = node[e];
+  }
+  for (int i = tid; i <= E; i += kDispThreads) seg_off[i] = seg[i];
+  __syncthreads();
+  // node nu starts where its first expert (or the next node's that has one) starts; the nodes ascend with the rank
+  for (int r = tid; r <= E; r += kDispThreads) {
+    const int last = r < E ? min(by_rank[r], N) : N;
+    for (int nu = r ? max(by_rank[r - 1], -1) + 1 : 0; nu <= last; ++nu) node_off[nu] = seg[r];
+  }
+}
+
+// The lanes of a wave that hold the same expert as this one (none of those that are not valid)
+__device__ __forceinline__ unsigned long long same_expert(int e, bool valid, int nbits) {
+  unsigned long long peers = __ballot(valid);
+  for (int bit = 0; bit < nbits; ++bit) {
+    const bool set = (e >> bit) & 1;
+    const unsigned long long bm = __ballot(valid && set);
+    peers &= set ? bm : ~bm;
+  }
+  return peers;
+}
+
+// Few tokens: every work-group counts all tokens' experts for itself (those before its own `per` tokens and the rest),
+// hence kept[], the buffer order and its tokens' slots, and copies their rows, whose first kOneLoads 16-byte pieces per
+// thread are fetched ahead of the counting.  Bound by latencies: the launch, one round trip to eid, some ten barriers.
+// us, this / two launches (slots by blocks of 1024 tokens that count for themselves, then a copy over the kept rows):
+//     192 tokens: d = 1024, E = 16 4.7 / 8.1;  d = 1600, E = 40 4.8 / 10.0;  d = 5120, E = 128 5.1 / 14.4
+//   4 096 tokens: 8.1 / 11.0;  9.7 / 15.0;  21.5 / 29.8;  4 of 5 tokens on one expert 7.7 / 10.2;  9.1 / 12.9;  16.0 / 20.8
+// The line lies where no distribution of the tokens loses (the rows of dropped tokens are fetched in vain); this / three
+// launches: 5 120 tokens, 4 of 5 on one expert, d = 1024, E = 16 8.3 / 10.7;  d = 5120, E = 128 19.4 / 17.4.
+constexpr int kDispOneTokens = 4096, kOneMaxTok = kWave, kOneLoads = 8, kOneMaxChunks = 2048;
+__global__ __launch_bounds__(kDispThreads) void dispatch_one_kernel(
+    const uint4* __restrict__ x, const int32_t* __restrict__ eid, const int32_t* __restrict__ e2n,
+    int32_t* __restrict__ pos, int32_t* __restrict__ slot, int32_t* __restrict__ kept, int32_t* __restrict__ seg_off,
+    int32_t* __restrict__ node_off, int32_t* __restrict__ buf_expert, int32_t* __restrict__ row_token,
+    uint4* __restrict__ send, int T, int E, int N, int C, int per, int chunks, int nbits) {
+  extern __shared__ int32_t sm[];
+  __shared__ int32_t s_slot[kOneMaxTok];
+  int32_t* off = sm;        // [E] tokens before this work-group's
+  int32_t* tot = off + E;   // [E] the others, then kept rows
+  int32_t* node = tot + E;
+  int32_t* rank = node + E;
+  int32_t* seg = rank + E;  // [E+1], indexed by buffer rank
+  int32_t* by_rank = seg + E + 1;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int base = blockIdx.x * per, n = min(per, T - base);
+  const unsigned pieces = (unsigned)n * chunks;  // the tokens' rows, one run of 16-byte pieces
+  const uint4* src = x + (size_t)base * chunks;
+  uint4 v[kOneLoads];
+  const int my_e = tid < n ? eid[base + tid] : 0;
+  for (int i = tid; i < 2 * E; i += kDispThreads) sm[i] = 0;
+  __syncthreads();
+  constexpr int U = 10;
+  for (int i0 = 0; i0 < T; i0 += U * kDispThreads) {  // (every thread comes by: the rows are fetched behind the first loads)
+    int c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = eid[min(i0 + tid + u * kDispThreads, T - 1)];
+    if (i0 == 0) {
+#pragma unroll
+      for (int u = 0; u < kOneLoads; ++u) v[u] = nt_load16(src + min((unsigned)(tid + u * kDispThreads), pieces - 1));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = i0 + tid + u * kDispThreads;
+      if (m < T) {
+        // the tokens of the first lane's expert are added at once: additions to one word wait for each other
+        const int first = __builtin_amdgcn_readfirstlane(c[u]);
+        const bool mine = c[u] == first && m < base == (__builtin_amdgcn_readfirstlane(m) < base);
+        const unsigned long long same = __ballot(mine);
+        if (!mine || lane == __builtin_ctzll(same))
+          atomicAdd((m < base ? off : tot) + c[u], mine ? __builtin_popcountll(same) : 1);
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < E; e += kDispThreads) {
+    const int all = off[e] + tot[e];
+    tot[e] = all < C ? all : C;  // kept[e] = min(cnt[e], C)
+    node[e] = e2n ? e2n[e] : e / (E / N);
+  }
+  __syncthreads();
+  buffer_order(e2n, tot, node, rank, seg, E);
+  if (blockIdx.x == 0) write_segments(tot, node, rank, seg, by_rank, kept, seg_off, node_off, buf_expert, E, N);
+  if (tid < kWave) {  // the work-group's tokens, one per lane
+    const bool valid = tid < n;
+    const unsigned long long peers = same_expert(my_e, valid, nbits);
+    if (valid) {
+      const int p = off[my_e] + __popcll(peers & ((1ull << lane) - 1ull));
+      const int s = p < C ? seg[rank[my_e]] + p : -1;
+      pos[base + tid] = p;
+      slot[base + tid] = s;
+      if (s >= 0) row_token[s] = base + tid;
+      s_slot[tid] = s;
+    }
+  }
+  __syncthreads();
+  for (unsigned c0 = tid; c0 < pieces; c0 += kOneLoads * kDispThreads) {
+    int s[kOneLoads];
+    unsigned in[kOneLoads];
+#pragma unroll
+    for (int u = 0; u < kOneLoads; ++u) {
+      const unsigned c = min(c0 + u * kDispThreads, pieces - 1), t = c / (unsigned)chunks;
+      s[u] = c0 + u * kDispThreads < pieces ? s_slot[t] : -1;
+      in[u] = c - t * chunks;
+      if (c0 >= kOneLoads * kDispThreads && s[u] >= 0) v[u] = nt_load16(src + c);  // (now only of kept tokens)
+    }
+#pragma unroll
+    for (int u = 0; u < kOneLoads; ++u)
+      if (s[u] >= 0) send[(size_t)s[u] * chunks + in[u]] = v[u];  // (plain: the FFN re-reads send right away)
+  }
 }
 
 __global__ __launch_bounds__(kDispThreads) void dispatch_hist_kernel(const int32_t* __restrict__ eid,
@@ -97,38 +246,7 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
 
   // tokens per expert in earlier blocks, and in all blocks: thread (rg, e) adds the rows q = rg, rg+R, ...
   // of the [blocks, E] count matrix (independent loads), then the R partials are added in order
-  if (!blockcnt) {  // few tokens: counted here, by every block for itself
-    int32_t* earlier = wcnt;     // [E] tokens before this block's
-    int32_t* later = wcnt + E;   // [E] this block's and after
-    for (int i = tid; i < 2 * E; i += kDispThreads) wcnt[i] = 0;
-    __syncthreads();
-    const int base = b * kDispatchTokensPerBlock;
-    constexpr int U = 8;
-    for (int m0 = tid; m0 < T; m0 += U * kDispThreads) {
-      int c[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) c[u] = eid[min(m0 + u * kDispThreads, T - 1)];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int m = m0 + u * kDispThreads;
-        if (m < T) {
-          // the tokens of the first lane's expert are added at once: additions to one word wait for each other
-          const int first = __builtin_amdgcn_readfirstlane(c[u]);
-          const unsigned long long same = __ballot(c[u] == first);
-          const bool mine = c[u] == first;
-          if (!mine || lane == __builtin_ctzll(same))
-            atomicAdd((m < base ? earlier : later) + c[u], mine ? __builtin_popcountll(same) : 1);
-        }
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < E; e += kDispThreads) {
-      const int all = earlier[e] + later[e];
-      off[e] = earlier[e];
-      tot[e] = all < C ? all : C;  // kept[e] = min(cnt[e], C)
-      node[e] = e2n ? e2n[e] : e / (E / N);
-    }
-  } else {
+  {
     const int R = E < kDispThreads ? kDispThreads / E : 1;  // row groups working on one chunk of experts
     int32_t* part_before = wcnt;                             // [R][E] scratch (wcnt is zeroed afterwards)
     int32_t* part_all = wcnt + kDispThreads;                 // R*E <= kDispThreads when R > 1
@@ -173,49 +291,12 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
   __syncthreads();
   for (int i = tid; i < kDispWaves * E; i += kDispThreads) wcnt[i] = 0;
   __syncthreads();
-  // buffer order: experts sorted by (node, id)
-  for (int e = tid; e < E; e += kDispThreads) {
-    int r = e;
-    if (e2n) {
-      r = 0;
-      const int ne = node[e];
-      for (int q = 0; q < E; ++q) r += (node[q] < ne || (node[q] == ne && q < e)) ? 1 : 0;
-    }
-    rank[e] = r;
-    seg[r + 1] = tot[e];  // staged: kept of the expert at rank r, scanned below
-  }
-  __syncthreads();
-  if (wave == 0) {  // inclusive scan of seg[1..E] by one wave: lane owns a contiguous run
-    const int per = ceil_div(E, kWave);
-    const int lo = lane * per, hi = min(E, lo + per);
-    int s = 0;
-    for (int i = lo; i < hi; ++i) s += seg[i + 1];
-    int incl = s;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      const int o = __shfl_up(incl, d);
-      if (lane >= d) incl += o;
-    }
-    int run = incl - s;
-    if (lane == 0) seg[0] = 0;
-    for (int i = lo; i < hi; ++i) {
-      run += seg[i + 1];
-      seg[i + 1] = run;
-    }
-  }
-  __syncthreads();
+  buffer_order(e2n, tot, node, rank, seg, E);
   if (b == 0) {
-    for (int e = tid; e < E; e += kDispThreads) {
-      kept[e] = tot[e];
-      buf_expert[rank[e]] = e;
-    }
-    for (int i = tid; i <= E; i += kDispThreads) seg_off[i] = seg[i];
-    // node nu starts where its first expert starts: the number of kept rows on lower nodes
-    for (int nu = tid; nu <= N; nu += kDispThreads) {
-      int s = 0;
-      for (int e = 0; e < E; ++e) s += node[e] < nu ? tot[e] : 0;
-      node_off[nu] = s;
-    }
+    write_segments(tot, node, rank, seg, wcnt, kept, seg_off, node_off, buf_expert, E, N);
+    __syncthreads();
+    for (int i = tid; i < E; i += kDispThreads) wcnt[i] = 0;  // (it served as by_rank)
+    __syncthreads();
   }
 
   // rank of each token among the block's earlier tokens of the same expert
@@ -224,12 +305,7 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
   for (int k = 0; k < kIter; ++k) {
     const bool valid = my_e[k] >= 0;
     const int e = valid ? my_e[k] : 0;
-    unsigned long long peers = __ballot(valid);
-    for (int bit = 0; bit < nbits; ++bit) {
-      const bool set = (e >> bit) & 1;
-      const unsigned long long bm = __ballot(valid && set);
-      peers &= set ? bm : ~bm;
-    }
+    const unsigned long long peers = same_expert(e, valid, nbits);
     const unsigned long long lt = (1ull << lane) - 1ull;
     const int before = __popcll(peers & lt);
     int p = 0;
@@ -314,25 +390,28 @@ void launch_copy(const void* x, const int32_t* row_token, const int32_t* seg_off
 }
 
 
-// The launches of the dispatch: histogram, slots, copy.  `blockcnt` holds ceil(T/1024) x E counts (every one is written by
-// the first kernel before the second reads it: nothing has to be cleared); up to kDispSelfBlocks blocks of tokens there
-// is no histogram and `blockcnt` is not touched.
+// The launches of the dispatch: one for few tokens, which leaves `blockcnt` alone, else histogram, slots, copy.  `blockcnt`
+// holds ceil(T/1024) x E counts (every one is written by the first kernel before the second reads it: nothing has to be
+// cleared).
 int dispatch_launch(const locmoe_desc* desc, const void* x, const int32_t* eid, const int32_t* e2n, int32_t* pos,
                     int32_t* slot, int32_t* kept, int32_t* seg_off, int32_t* node_off, int32_t* buf_expert,
                     int32_t* row_token, void* send, int32_t* blockcnt, hipStream_t s) {
   const int T = desc->T, E = desc->E;
   const int nblocks = ceil_div(T, kDispatchTokensPerBlock);
-  int st = LOCMOE_OK;
-  if (nblocks <= kDispSelfBlocks) {
-    blockcnt = nullptr;
-  } else {
-    hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nblocks), dim3(kDispThreads), (size_t)E * 4, s, eid, blockcnt, T,
-                       E);
-    st = launch_status();
-    if (st != LOCMOE_OK) return st;
-  }
   int nbits = 0;
   while ((1 << nbits) < E) ++nbits;
+  const int chunks = desc->d * (desc->x_dtype == LOCMOE_BF16 ? 2 : 4) / 16;
+  if (T <= kDispOneTokens && chunks <= kOneMaxChunks) {
+    // tokens per work-group: as many as the loads ahead hold (not fewer than 8, each counts all), spread over 128 at least
+    const int per = std::min(std::min(kOneMaxTok, std::max(8, kOneLoads * kDispThreads / chunks)), ceil_div(T, 128));
+    hipLaunchKernelGGL(dispatch_one_kernel, dim3(ceil_div(T, per)), dim3(kDispThreads), ((size_t)E * 6 + 1) * 4, s,
+                       (const uint4*)x, eid, e2n, pos, slot, kept, seg_off, node_off, buf_expert, row_token, (uint4*)send,
+                       T, E, desc->N, desc->C, per, chunks, nbits);
+    return launch_status();
+  }
+  hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nblocks), dim3(kDispThreads), (size_t)E * 4, s, eid, blockcnt, T, E);
+  int st = launch_status();
+  if (st != LOCMOE_OK) return st;
   const size_t wcnt_ints = (size_t)kDispWaves * E > 2 * (size_t)kDispThreads ? (size_t)kDispWaves * E : 2 * (size_t)kDispThreads;
   const size_t smem = ((size_t)E * 5 + 1 + wcnt_ints) * 4;
   hipLaunchKernelGGL(dispatch_slots_kernel, dim3(nblocks), dim3(kDispThreads), smem, s, eid, e2n, blockcnt, pos,
@@ -342,7 +421,6 @@ int dispatch_launch(const locmoe_desc* desc, const void* x, const int32_t* eid, 
   // at most min(T, E*C) rows can be kept; the kernel reads the real K from seg_off[E]
   const long long cap = (long long)E * desc->C;
   const int rows = (int)(cap < T ? cap : T);
-  const int chunks = desc->d * (desc->x_dtype == LOCMOE_BF16 ? 2 : 4) / 16;
   // lanes per row: every lane should own at least 4 chunks so that 4 loads are in flight before the stores
   if (chunks >= 1024) launch_copy<256>(x, row_token, seg_off, send, E, rows, chunks, s);
   else if (chunks >= 512) launch_copy<128>(x, row_token, seg_off, send, E, rows, chunks, s);

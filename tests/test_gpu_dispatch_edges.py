@@ -26,14 +26,14 @@ def test_dispatch_counts_of_skewed_tokens(T, kind):
     check_dispatch(eid.astype(np.int32), E, 4, False)
 
 
-def check_dispatch(eid, E, N, free_map):
+def check_dispatch(eid, E, N, free_map, d=None):
     import torch
     from paper_2401_13920_amd import locmoe as lm
     assert torch.cuda.is_available(), "this test needs the MI355X"
     T = len(eid)
     e2n = (np.arange(E) * 7 % N if free_map else np.arange(E) // (E // N)).astype(np.int32)
     C = max(1, T // (2 * E))
-    d = 8 * E
+    d = d or 8 * E
     desc = lm.make_desc(T, d, E, N, 8, C, "bf16")
     b = lm.alloc_buffers(desc)
     x = torch.randn(T, d, device="cuda").to(torch.bfloat16)
@@ -46,6 +46,54 @@ def check_dispatch(eid, E, N, free_map):
         assert np.array_equal(getattr(b, name).cpu().numpy(), ref[name]), name
     kept = torch.from_numpy(ref["slot"] >= 0).cuda()
     assert torch.equal(b.send[b.slot[kept].long()], x[kept])
+
+
+# one launch up to 4 096 tokens and 2 048 16-byte pieces a row: fewer pieces than threads, one batch of loads and several,
+# one to 64 tokens per work-group, a last one that is not full; rows too long for it
+@pytest.mark.parametrize("T,E,d", [(1, 4, 8), (127, 4, 64), (129, 12, 1200), (1000, 8, 64), (3000, 128, 5120), (4095, 8, 2048),
+                                   (4096, 300, 1200), (4097, 12, 96), (65, 4, 16384), (65, 4, 16416)])
+@pytest.mark.parametrize("free_map", [False, True])
+def test_dispatch_in_one_launch(T, E, d, free_map):
+    rng = np.random.default_rng(T + E + d)
+    check_dispatch((rng.zipf(1.5, T) % E).astype(np.int32), E, 4 if E % 4 == 0 else 1, free_map, d=d)
+
+
+# the route in one launch (4 096 tokens' lanes: 1 024 tokens of 4 experts, 512 of 8, 256 of up to 64) and in two, with one to
+# sixteen rows of partials per thread and more
+@pytest.mark.parametrize("E,N,T", [(1, 1, 5), (4, 2, 1024), (4, 2, 1025), (6, 3, 512), (8, 2, 513), (16, 4, 1), (16, 4, 256),
+                                   (16, 4, 257), (40, 8, 255), (64, 8, 256), (64, 8, 257), (65, 5, 100), (64, 8, 30000),
+                                   (128, 16, 20000), (300, 3, 9000)])
+@pytest.mark.parametrize("home", [False, True])
+def test_route_in_one_and_two_launches(E, N, T, home):
+    import torch
+    from paper_2401_13920_amd import locmoe as lm
+    rng = np.random.default_rng(E * 7 + T)
+    g = rng.standard_normal((T, E)).astype(np.float32)
+    nodes = rng.integers(0, N, T).astype(np.int32)
+    nodes[:N] = np.arange(N)[:T]
+    eps = (0.05 * rng.standard_normal(E)).astype(np.float32)
+    e2n = np.arange(E) // (E // N)
+    desc = lm.make_desc(T, 8 * E, E, N, 8, max(1, T // E), "bf16")
+    b = lm.alloc_buffers(desc)
+    print(f"[route] T={T} E={E} N={N} home={home}", flush=True)
+    for t in (b.eid, b.cnt):
+        t.fill_(-1)
+    for t in (b.w, b.Psum, b.stats):
+        t.fill_(float("nan"))
+    b.ws.fill_(255)
+    lm.locmoe_route(desc, torch.from_numpy(g).cuda(), torch.from_numpy(eps).cuda(),
+                    torch.from_numpy(nodes).cuda() if home else None, None, b.eid, b.w, b.cnt, b.Psum, b.stats, b.ws,
+                    b.ws_bytes)
+    torch.cuda.synchronize()
+    eid, w, p, _ = orc.route(g, eps, True)
+    st = orc.route_stats(eid, p, nodes if home else None, e2n, N, desc.alpha, desc.mu)
+    assert np.array_equal(b.eid.cpu().numpy(), eid) and np.array_equal(b.cnt.cpu().numpy(), st["cnt"])
+    assert np.allclose(b.w.cpu().numpy(), w, rtol=1e-5, atol=0)
+    assert np.allclose(b.Psum.cpu().numpy(), st["Psum"], rtol=1e-5, atol=1e-7)
+    s = b.stats.cpu().numpy()
+    for k, name in enumerate(["L_aux", "KL_hard", "KL_soft", "L_loc", "locality_frac"]):
+        assert s[k] == pytest.approx(st[name], rel=1e-5, abs=2e-7), name
+    assert s[5] == st["cnt"].max() and s[6] == int((st["cnt"] == 0).sum()) and s[7] == 0
 
 
 @pytest.mark.parametrize("E,d", [(32, 64), (32, 128), (32, 192), (32, 320), (128, 128), (128, 256), (128, 384), (128, 640)])
