@@ -94,8 +94,22 @@ __global__ __launch_bounds__(kHomeThreads) void route_bwd_home_kernel(const int3
   for (int i = threadIdx.x; i < N; i += kHomeThreads) part[(size_t)blockIdx.x * N + i] = hist[i];
 }
 
-// One block: column sums of that matrix, experts per node, then the per-expert coefficient that every token's
-// dp receives: alpha n f_i / T (Eq. 5, f fixed) + mu (ln(P_i / D_l[i]) + 1) / T (Eq. 6 through P).
+// alpha n f_i / T (Eq. 5, f fixed) + mu (ln(P_i / D_l[i]) + 1) / T (Eq. 6 through P), from the tokens per home node and the
+// experts per node
+__device__ __forceinline__ float coef_of(int i, bool has_home, const int32_t* s_home, const int32_t* s_pernode,
+                                         const int32_t* e2n, const int32_t* cnt, const float* Psum, int T, int E, int N,
+                                         float alpha, float mu) {
+  double c = (double)alpha * E * ((double)cnt[i] / T) / T;
+  if (has_home && mu != 0.f) {
+    const int nu = e2n ? e2n[i] : i / (E / N);
+    const double Dl = (double)s_home[nu] / ((double)T * (double)s_pernode[nu]);
+    const double P = (double)Psum[i] / T;
+    c += (double)mu * (log(P / Dl) + 1.0) / T;
+  }
+  return (float)c;
+}
+
+// One block: column sums of that matrix, experts per node, then the per-expert coefficient that every token's dp receives.
 __global__ __launch_bounds__(1024) void route_bwd_coef_kernel(const int32_t* __restrict__ part, int nblk,
                                                               const int32_t* __restrict__ e2n,
                                                               const int32_t* __restrict__ cnt,
@@ -128,36 +142,57 @@ __global__ __launch_bounds__(1024) void route_bwd_coef_kernel(const int32_t* __r
     if (tid < E) atomicAdd(&s_pernode[e2n ? e2n[tid] : tid / (E / N)], 1);
   }
   __syncthreads();
-  if (tid < E) {
-    double c = (double)alpha * E * ((double)cnt[tid] / T) / T;
-    if (part && mu != 0.f) {
-      const int nu = e2n ? e2n[tid] : tid / (E / N);
-      const double Dl = (double)s_home[nu] / ((double)T * (double)s_pernode[nu]);
-      const double P = (double)Psum[tid] / T;
-      c += (double)mu * (log(P / Dl) + 1.0) / T;
-    }
-    coef[tid] = (float)c;
-  }
+  if (tid < E) coef[tid] = coef_of(tid, part != nullptr, s_home, s_pernode, e2n, cnt, Psum, T, E, N, alpha, mu);
 }
 
-// G lanes per token; lane j owns experts j, j+G, ...  The softmax is recomputed from g as the forward did.
-template <int G>
-__global__ __launch_bounds__(kBwdThreads) void route_bwd_kernel(const float* __restrict__ g,
-                                                                const float* __restrict__ eps,
-                                                                const int32_t* __restrict__ eid,
-                                                                const float* __restrict__ dw,
-                                                                const float* __restrict__ coef,
-                                                                float* __restrict__ dg, int T, int E, int relu) {
+// G lanes per token; lane j owns experts j, j+G, ...  The softmax is recomputed from g as the forward did.  ONE (few
+// tokens): every work-group counts the tokens per home node and forms the coefficients for itself, where otherwise two
+// launches go before this one; work-group 0 writes them out.
+template <int G, bool ONE>
+__global__ __launch_bounds__(kBwdThreads) void route_bwd_kernel(
+    const float* __restrict__ g, const float* __restrict__ eps, const int32_t* __restrict__ eid,
+    const float* __restrict__ dw, float* __restrict__ coef, float* __restrict__ dg, int T, int E, int relu,
+    const int32_t* __restrict__ home, const int32_t* __restrict__ e2n, const int32_t* __restrict__ cnt,
+    const float* __restrict__ Psum, int N, float alpha, float mu) {
+  extern __shared__ int32_t sm[];  // ONE: coef[E], tokens per home node[N], experts per node[N]
   const int m = blockIdx.x * (kBwdThreads / G) + threadIdx.x / G;
-  if (m >= T) return;  // whole groups leave together
+  const bool live = m < T;  // (whole groups)
   const int j = threadIdx.x % G;
-  const float* gr = g + (size_t)m * E;
+  const float* gr = g + (size_t)(live ? m : 0) * E;
   float best = -INFINITY;
   for (int i = j; i < E; i += G) {
     float s = gr[i] + (eps ? eps[i] : 0.f);
     if (relu) s = fmaxf(s, 0.f);
     best = fmaxf(best, s);
   }
+  const float* cf = coef;
+  if (ONE) {
+    float* s_coef = (float*)sm;
+    int32_t *s_home = sm + E, *s_pernode = s_home + N;
+    if (home) {
+      for (int i = threadIdx.x; i < 2 * N; i += kBwdThreads) s_home[i] = 0;
+      __syncthreads();
+      constexpr int U = 8;
+      for (int m0 = threadIdx.x; m0 < T; m0 += U * kBwdThreads) {
+        int h[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) h[u] = home[min(m0 + u * kBwdThreads, T - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (m0 + u * kBwdThreads < T) atomicAdd(&s_home[h[u]], 1);
+      }
+      for (int i = threadIdx.x; i < E; i += kBwdThreads) atomicAdd(&s_pernode[e2n ? e2n[i] : i / (E / N)], 1);
+      __syncthreads();
+    }
+    for (int i = threadIdx.x; i < E; i += kBwdThreads) {
+      const float c = coef_of(i, home != nullptr, s_home, s_pernode, e2n, cnt, Psum, T, E, N, alpha, mu);
+      s_coef[i] = c;
+      if (blockIdx.x == 0) coef[i] = c;
+    }
+    __syncthreads();
+    cf = s_coef;
+  }
+  if (!live) return;
 #pragma unroll
   for (int o = G / 2; o > 0; o >>= 1) best = fmaxf(best, __shfl_xor(best, o));
   const int e = eid[m];
@@ -168,7 +203,7 @@ __global__ __launch_bounds__(kBwdThreads) void route_bwd_kernel(const float* __r
     if (relu) s = fmaxf(s, 0.f);
     const float z = expf(s - best);
     zs += z;
-    zc = fmaf(z, coef[i] + (i == e ? dwm : 0.f), zc);
+    zc = fmaf(z, cf[i] + (i == e ? dwm : 0.f), zc);
   }
   zs = group_sum<G>(zs);
   zc = group_sum<G>(zc);
@@ -178,7 +213,7 @@ __global__ __launch_bounds__(kBwdThreads) void route_bwd_kernel(const float* __r
     const float raw = gr[i] + (eps ? eps[i] : 0.f);
     const float s = relu ? fmaxf(raw, 0.f) : raw;
     const float p = expf(s - best) * inv;
-    const float v = p * (coef[i] + (i == e ? dwm : 0.f) - inner);
+    const float v = p * (cf[i] + (i == e ? dwm : 0.f) - inner);
     dg[(size_t)m * E + i] = (relu && !(raw > 0.f)) ? 0.f : v;  // ReLU'(0) = 0
   }
 }
@@ -263,12 +298,16 @@ extern "C" int locmoe_route_bwd(const locmoe_desc* desc, const float* g, const f
   if (!e2n && desc->E % desc->N != 0) return LOCMOE_ERR_SHAPE;
   hipStream_t s = as_stream(stream);
   const int E = desc->E, T = desc->T;
+  const int N = desc->N;
+  // One launch where counting all tokens in every work-group costs less than two launches more.  us, one / three back to
+  // back in a graph: E = 16: 1 000 tokens 4.4 / 7.0, 4 096 5.2 / 7.0, 8 192 8.9 / 7.2;  E = 64: 2 048 5.1 / 7.3, 4 096
+  // 7.8 / 7.5;  E = 300: 2 048 9.7 / 10.4, 4 096 15.7 / 11.2.
+  const bool one = T <= 2048 || (T <= 4096 && E <= 40);
   // tokens per home node: partial counts of up to 256 blocks in the front of dg (T E words; N <= E, so a matrix
   // of at most T rows always fits), summed by the coefficient kernel before dg itself is written
-  const int N = desc->N;
   int32_t* part = nullptr;
   int nblk = 0;
-  if (home) {
+  if (home && !one) {
     const long long fit = (long long)T * E / N;
     nblk = (int)std::min<long long>(std::min<long long>(256, ceil_div(T, kHomeThreads)), fit);
     const int per_block = ceil_div(T, nblk);
@@ -277,15 +316,19 @@ extern "C" int locmoe_route_bwd(const locmoe_desc* desc, const float* g, const f
     hipLaunchKernelGGL(route_bwd_home_kernel, dim3(nblk), dim3(kHomeThreads), (size_t)N * 4, s, home, part, T, N,
                        per_block);
   }
-  hipLaunchKernelGGL(route_bwd_coef_kernel, dim3(1), dim3(1024), 0, s, part, nblk, e2n, cnt, Psum, coef, T, E, N,
-                     desc->alpha, desc->mu);
+  if (!one)
+    hipLaunchKernelGGL(route_bwd_coef_kernel, dim3(1), dim3(1024), 0, s, part, nblk, e2n, cnt, Psum, coef, T, E, N,
+                       desc->alpha, desc->mu);
   int G = 1;
   while (G < 64 && 2 * G <= E) G *= 2;
-#define LOCMOE_ROUTE_BWD(GG)                                                                                      \
-  case GG:                                                                                                        \
-    hipLaunchKernelGGL(route_bwd_kernel<GG>, dim3((unsigned)ceil_div(T, kBwdThreads / GG)), dim3(kBwdThreads), 0, \
-                       s, g, eps, eid, dw, coef, dg, T, E, desc->relu);                                           \
-    break;
+  const size_t lds = one ? ((size_t)E + 2 * N) * 4 : 0;
+#define LOCMOE_ROUTE_BWD(GG)                                                                                          \
+  case GG: {                                                                                                          \
+    auto kern = one ? route_bwd_kernel<GG, true> : route_bwd_kernel<GG, false>;                                       \
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(T, kBwdThreads / GG)), dim3(kBwdThreads), lds, s, g, eps, eid, dw, \
+                       coef, dg, T, E, desc->relu, home, e2n, cnt, Psum, N, desc->alpha, desc->mu);                    \
+    break;                                                                                                            \
+  }
   switch (G) {
     LOCMOE_ROUTE_BWD(1) LOCMOE_ROUTE_BWD(2) LOCMOE_ROUTE_BWD(4) LOCMOE_ROUTE_BWD(8) LOCMOE_ROUTE_BWD(16)
     LOCMOE_ROUTE_BWD(32) LOCMOE_ROUTE_BWD(64)
