@@ -35,8 +35,8 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 // them are overwritten with zeros by the wave that fetched them, so their products vanish.
 // Tiles: XCD x (work-groups x mod 8) owns whole segments, so an expert's operands live in one L2; inside a
 // segment, 32 consecutive tiles (the XCD's work-groups at one time) form a block of 4 m-tiles x 8 n-tiles
-// (12 operand tiles for 32 outputs).  Segments without rows are skipped here and zero-filled by
-// wgrad_zero_empty_kernel.
+// (12 operand tiles for 32 outputs).  Segments without rows have no tiles; their gradients are zero-filled at the end (a
+// launch of its own for that took 5 us).
 constexpr int kWgQBytes = kWgK * kWgTile * 2;   // the Q tile of a step: 32 rows x 256 columns, 16 KiB
 
 struct WgShape {
@@ -159,9 +159,23 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
     return __builtin_amdgcn_readfirstlane(t);
   };
 
+  // G[e] = 0 for experts whose segment has no rows: a share of every such matrix per work-group, at its end
+  auto zero_empty = [&]() {
+    const size_t chunks = (size_t)Mdim * Ndim / 8;
+    for (int r0 = 0; r0 < E; r0 += kWave) {
+      const int a = seg_off[min(r0 + lane, E)], b = seg_off[min(r0 + lane + 1, E)];
+      unsigned long long empty = __ballot(r0 + lane < E && a == b);
+      for (; empty; empty &= empty - 1) {
+        uint4* g = (uint4*)G + (size_t)buf_expert[r0 + __builtin_ctzll(empty)] * chunks;
+        for (size_t i = (size_t)blockIdx.x * kWgThreads + tid; i < chunks; i += (size_t)nwg * kWgThreads)
+          nt_store16(make_uint4(0, 0, 0, 0), g + i);
+      }
+    }
+  };
+
   WgTile cur;
   int t_cur = next_live(blockIdx.x, cur);
-  if (t_cur >= total) return;
+  if (t_cur >= total) return zero_empty();
 
   // ---- the copy side: a cursor kStages - 1 steps ahead of the compute side
   WgTile pf = cur;
@@ -303,18 +317,7 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
     t_cur = next_live(t_cur + nwg, cur);
     if (t_cur >= total) break;
   }
-}
-
-// G[e] = 0 for experts whose segment has no rows (the pipelined kernel skips them)
-__global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(uint4* __restrict__ G,
-                                                               const int32_t* __restrict__ seg_off,
-                                                               const int32_t* __restrict__ buf_expert,
-                                                               size_t chunks_per_expert) {
-  const int r = blockIdx.y;
-  if (seg_off[r + 1] != seg_off[r]) return;
-  uint4* g = G + (size_t)buf_expert[r] * chunks_per_expert;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < chunks_per_expert; i += (size_t)gridDim.x * 256)
-    g[i] = make_uint4(0, 0, 0, 0);
+  zero_empty();
 }
 
 // Any shape and either storage type of the operands that have one (the other operand is bf16): 128 x 128 tile of G per
@@ -542,9 +545,6 @@ int launch_wgrad(const void* P, const void* Q, void* G, const int32_t* seg_off, 
       auto kern = wgrad_dma_kernel;
       static std::atomic<uint64_t> lds_allowed;
       if (!allow_lds((const void*)kern, S::kSmem, lds_allowed)) return LOCMOE_ERR_HIP;
-      const size_t chunks = (size_t)Mdim * Ndim / 8;
-      hipLaunchKernelGGL(wgrad_zero_empty_kernel, dim3(64, E), dim3(256), 0, st, (uint4*)G, seg_off, buf_expert,
-                         chunks);
       const long long tiles = (long long)E * (Mdim / S::kTM) * (Ndim / kWgTile);
       const long long groups = std::min<long long>((cu_count() / 8) * 8, (tiles + 7) / 8 * 8);
       hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kWgThreads), S::kSmem, st, (const uint16_t*)P,
