@@ -18,7 +18,7 @@ namespace {
 
 constexpr int kWgTile = 256;              // output tile: 256 (m) x 256 (n)
 constexpr int kWgK = 32;                  // rows of the segment per step
-constexpr int kWgThreads = 256;           // four waves, each 128 x 128 of the tile
+constexpr int kWgThreads = 512;           // eight waves, each 64 x 128 of the tile
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -28,6 +28,11 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 // into a ring of four stages, so the short contraction (at most C rows: 16 steps at C = 501) never starts
 // cold.  Copies complete in issue order among themselves, so a counted wait (as many as were issued after the
 // step's own) tells when a step's data has landed, also with the previous tile's stores still in flight.
+// Eight waves, two per SIMD: one's fragment reads, address arithmetic and epilogue run beside the other's MFMAs, which is
+// worth more than the 24 transposing reads per 32 MFMAs (four waves of 128 x 128: 32 per 64) cost.  Both GEMMs, us, four
+// waves / eight: E = 64, d = 4096, h = 16384: 400 rows 7 876 / 7 607, uneven up to 501 6 523 / 6 056, 128 rows 3 995 / 3 708;
+// E = 32, d = 2048, h = 8192, uneven up to 1 024 rows 1 549 / 1 423 (986 TFLOP/s);  E = 16, d = 1024, h = 4096, up to 640
+// 162 / 145.  A higher wave priority around the MFMAs: up to 6 % slower.
 // LDS rows are 512 B with the 16-byte chunk index XORed by 2 s(row), s = row mod 4 plus
 // 4 (bit 3 of the row): the eight rows that 32 lanes of the transposing read touch (rows r..r+3 and r+8..r+11,
 // 32 B each) then fall into all 64 banks once; with row mod 4 alone half of the LDS cycles were bank conflicts.
@@ -40,8 +45,8 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 constexpr int kWgQBytes = kWgK * kWgTile * 2;   // the Q tile of a step: 32 rows x 256 columns, 16 KiB
 
 struct WgShape {
-  static constexpr int kMJ = 8;                    // 16-row m-subtiles per wave: a wave owns 128 x 128 of the tile
-  static constexpr int kTM = 2 * kMJ * 16;         // tile rows (m): 256
+  static constexpr int kMJ = 4;                    // 16-row m-subtiles per wave: a wave owns 64 x 128 of the tile
+  static constexpr int kTM = 4 * kMJ * 16;         // tile rows (m): 256
   static constexpr int kPRow = kTM * 2;            // bytes of a P row in LDS
   static constexpr int kPBytes = kWgK * kPRow;
   static constexpr int kStage = kPBytes + kWgQBytes;
@@ -49,8 +54,8 @@ struct WgShape {
   static constexpr int kSmem = kStages * kStage;   // 128 KiB: one work-group per compute unit
   static constexpr int kPLanes = kPRow / 16;       // lanes per P row in a copy
   static constexpr int kPRowsPerCopy = 64 / kPLanes;
-  static constexpr int kPCopies = 8 / kPRowsPerCopy;      // per wave and step (a wave copies 8 of the 32 rows)
-  static constexpr int kCopies = kPCopies + 4;            // ... plus four for the Q tile
+  static constexpr int kPCopies = 4 / kPRowsPerCopy;      // per wave and step (a wave copies 4 of the 32 rows)
+  static constexpr int kCopies = kPCopies + 2;            // ... plus two for the Q tile
 };
 
 struct WgTile {          // wave-uniform
@@ -184,35 +189,35 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
   const int prow = lane / S::kPLanes, pch = lane % S::kPLanes;  // P copies: row inside the copy, chunk
   const int qrow = lane >> 5, qch = lane & 31;                  // Q copies
   const uint32_t ldP = (uint32_t)Mdim * 2, ldQ = (uint32_t)Ndim * 2;
-  const int swz_hi = (wave & 1) << 2;  // bit 3 of the rows this wave copies (rows 8 wave .. 8 wave + 7)
+  const int swz_hi = ((wave >> 1) & 1) << 2;  // bit 3 of the rows this wave copies (rows 4 wave .. 4 wave + 3)
   // What a copy's source offset is made of, per lane and copy, computed once: the row's byte offset inside a step
   // and the (swizzled) chunk.  A step then costs an add, a min (rows past the segment's end re-read its last row)
   // and an add per copy instead of a multiplication and the swizzle arithmetic: with one wave per SIMD every
   // instruction between two MFMAs is MFMA time (the copies' address arithmetic was 1.1 ms of the 8.3 ms of both
-  // GEMMs at config 4).  The four copies of an operand land in consecutive KiB of LDS: one M0 write serves them,
+  // GEMMs at config 4).  The two copies of an operand land in consecutive KiB of LDS: one M0 write serves them,
   // each copy carries its KiB as immediate offset, which the hardware also adds to the source address; it is taken
   // off the chunk term again (from a base 4 KiB below the operand, so that the offset stays non-negative).
-  static_assert(S::kPCopies == 4 && S::kPRowsPerCopy == 2, "the copy tables assume 512-byte P rows");
-  uint32_t rowP[4], chP[4], rowQ[4], chQ[4];
+  static_assert(S::kPCopies == 2 && S::kPRowsPerCopy == 2, "the copy tables assume 512-byte P rows");
+  uint32_t rowP[2], chP[2], rowQ[2], chQ[2];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int r8p = 2 * q + prow, r8q = 2 * q + qrow;  // row inside the wave's eight
-    rowP[q] = (uint32_t)(8 * wave + r8p) * ldP;
-    chP[q] = (uint32_t)(pch ^ (((r8p & 3) | swz_hi) << 1)) * 16 + 4096 - q * 1024;
-    rowQ[q] = (uint32_t)(8 * wave + r8q) * ldQ;
-    chQ[q] = (uint32_t)(qch ^ (((r8q & 3) | swz_hi) << 1)) * 16 + 4096 - q * 1024;
+  for (int q = 0; q < 2; ++q) {
+    const int r4p = 2 * q + prow, r4q = 2 * q + qrow;  // row inside the wave's four
+    rowP[q] = (uint32_t)(4 * wave + r4p) * ldP;
+    chP[q] = (uint32_t)(pch ^ (((r4p & 3) | swz_hi) << 1)) * 16 + 4096 - q * 1024;
+    rowQ[q] = (uint32_t)(4 * wave + r4q) * ldQ;
+    chQ[q] = (uint32_t)(qch ^ (((r4q & 3) | swz_hi) << 1)) * 16 + 4096 - q * 1024;
   }
   auto issue = [&]() -> bool {
     if (!pf_live) return false;
     const uint32_t sbase = lds0 + (uint32_t)stage_pf * S::kStage;
     const uint32_t kP = (uint32_t)k_pf * ldP, kQ = (uint32_t)k_pf * ldQ;                     // this step's first row
     const uint32_t endP = (uint32_t)(pf.rows - 1) * ldP, endQ = (uint32_t)(pf.rows - 1) * ldQ;  // the segment's last row
-    dma_base(sbase + (uint32_t)wave * 8 * S::kPRow);
+    dma_base(sbase + (uint32_t)wave * 4 * S::kPRow);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) dma_1k_sub(pf.P - 4096, min(rowP[q] + kP, endP) + chP[q], q);
-    dma_base(sbase + S::kPBytes + (uint32_t)wave * 4096);
+    for (int q = 0; q < 2; ++q) dma_1k_sub(pf.P - 4096, min(rowP[q] + kP, endP) + chP[q], q);
+    dma_base(sbase + S::kPBytes + (uint32_t)wave * 2048);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) dma_1k_sub(pf.Q - 4096, min(rowQ[q] + kQ, endQ) + chQ[q], q);
+    for (int q = 0; q < 2; ++q) dma_1k_sub(pf.Q - 4096, min(rowQ[q] + kQ, endQ) + chQ[q], q);
     stage_pf = stage_pf + 1 == S::kStages ? 0 : stage_pf + 1;
     k_pf += kWgK;
     if (k_pf >= pf.rows) {
@@ -253,11 +258,11 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
       else wait_vmcnt<0>();
       const int rem = cur.rows - s * kWgK;  // live rows of this step
       if (rem < kWgK) {
-        char* pt = smem + stage * S::kStage + wave * 8 * S::kPRow;
+        char* pt = smem + stage * S::kStage + wave * 4 * S::kPRow;
 #pragma unroll
         for (int q = 0; q < S::kPCopies; ++q) {
-          const int r8 = S::kPRowsPerCopy * q + prow;
-          if (8 * wave + r8 >= rem) *(uint4*)(pt + r8 * S::kPRow + pch * 16) = make_uint4(0, 0, 0, 0);
+          const int r4 = S::kPRowsPerCopy * q + prow;
+          if (4 * wave + r4 >= rem) *(uint4*)(pt + r4 * S::kPRow + pch * 16) = make_uint4(0, 0, 0, 0);
         }
       }
       __syncthreads();
@@ -279,18 +284,17 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
     }
     // Epilogue through LDS: a lane holds 4 consecutive n of one row m, which stored directly are 8-byte
     // pieces in 32-byte runs (measured: 1.5 TB/s, twice the time of the MFMAs).  Each wave turns one 16-row
-    // subtile at a time into rows of 256 contiguous bytes in its quarter of the stage that the last step
-    // read (free until the next step's copies) and stores 16 bytes per lane, four whole rows per instruction.
-    // Two 4 KiB buffers alternate, so a subtile is written while the previous one is read back; the 16-byte
-    // chunk index is XORed with the row, which spreads both the 8-byte writes of 32 lanes (16 rows x 2 column
+    // subtile at a time into rows of 256 contiguous bytes in its eighth of the stage that the last step
+    // read (free until the next step's copies; a wave's LDS accesses stay in order) and stores 16 bytes per lane, four
+    // whole rows per instruction.  The 16-byte chunk index is XORed with the row, which spreads both the 8-byte writes of 32 lanes (16 rows x 2 column
     // groups) and the 16-byte reads of 16 lanes (one row) over all 64 banks.
     __syncthreads();  // every wave has finished reading that stage
     {
-      char* mine = smem + stage_last * S::kStage + wave * (S::kStage / 4);
+      char* mine = smem + stage_last * S::kStage + wave * (S::kStage / 8);
       uint16_t* Gw = cur.G + (size_t)(wm * (MJ * 16)) * Ndim + wn * 128;
       const int rrow = lane >> 4, rcol = lane & 15;
       auto put = [&](int mj) {
-        char* buf = mine + (mj & 1) * 4096 + l16 * 256 + (kq & 1) * 8;
+        char* buf = mine + l16 * 256 + (kq & 1) * 8;
 #pragma unroll
         for (int ni = 0; ni < 8; ++ni) {
           const f32x4 v = acc[ni][mj];
@@ -298,11 +302,10 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
               make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
         }
       };
-      put(0);
 #pragma unroll
       for (int mj = 0; mj < MJ; ++mj) {
-        if (mj + 1 < MJ) put(mj + 1);
-        const char* buf = mine + (mj & 1) * 4096;
+        put(mj);
+        const char* buf = mine;
 #pragma unroll
         for (int p4 = 0; p4 < 4; ++p4) {
           const int row = 4 * p4 + rrow;
@@ -334,6 +337,7 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
 // kept rows) both launches write 268 MB, 54 us at the rate of a large copy, and multiply 3 x 52 GFLOP, 132 us at the
 // rate of a large matrix product; they take 174 + 158 us (the scalar kernel: 12.8 ms).  64 KiB of LDS and 128-wide tiles
 // leave room for two work-groups per compute unit, so that one's stores run beside the other's MFMAs.
+constexpr int kAnyThreads = 256;                   // four waves of 64 x 64
 constexpr int kAnyTile = 128;
 constexpr int kAnyRow = kAnyTile * 2;              // bytes of an LDS row
 constexpr int kAnyPlane = kWgK * kAnyRow;          // 8 KiB: one bf16 plane of one operand's step
@@ -382,7 +386,7 @@ struct AnyStage {
   __device__ __forceinline__ void load(const char* base, size_t ld, int col0, int cols, int k0, int rows, int tid) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * kWgThreads, row = min(k0 + (c >> 4), rows - 1);
+      const int c = tid + i * kAnyThreads, row = min(k0 + (c >> 4), rows - 1);
       const int col = min(col0 + (c & 15) * 8, cols - 8);  // columns past the end repeat the last ones (not stored)
       const u32x4* p = (const u32x4*)(base + (size_t)row * ld + (size_t)col * (F32 ? 4 : 2));
       if (F32) { v[2 * i] = p[0]; v[2 * i + 1] = p[1]; }
@@ -392,7 +396,7 @@ struct AnyStage {
   __device__ __forceinline__ void store(char* lds, int k0, int rows, int tid) const {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * kWgThreads, row = c >> 4;
+      const int c = tid + i * kAnyThreads, row = c >> 4;
       const bool live = k0 + row < rows;
       char* dst = lds + row * kAnyRow + (((c & 15) ^ any_swz(row)) << 4);
       if (F32) {
@@ -409,7 +413,7 @@ struct AnyStage {
 };
 
 template <bool P_F32, bool Q_F32>
-__global__ __launch_bounds__(kWgThreads, 2) void wgrad_any_kernel(const char* __restrict__ P, const char* __restrict__ Q,
+__global__ __launch_bounds__(kAnyThreads, 2) void wgrad_any_kernel(const char* __restrict__ P, const char* __restrict__ Q,
                                                                   uint16_t* __restrict__ G,
                                                                   const int32_t* __restrict__ seg_off,
                                                                   const int32_t* __restrict__ buf_expert, int Mdim,
@@ -559,7 +563,7 @@ int launch_wgrad(const void* P, const void* Q, void* G, const int32_t* seg_off, 
   constexpr int smem = 2 * (AnyStage<P_F32>::kBytes + AnyStage<Q_F32>::kBytes);  // 32 or 64 KiB; the tile of G needs 32
   static std::atomic<uint64_t> any_lds;
   if (!allow_lds((const void*)any, smem, any_lds)) return LOCMOE_ERR_HIP;
-  hipLaunchKernelGGL(any, dim3((unsigned)tiles), dim3(kWgThreads), smem, st, (const char*)P, (const char*)Q,
+  hipLaunchKernelGGL(any, dim3((unsigned)tiles), dim3(kAnyThreads), smem, st, (const char*)P, (const char*)Q,
                      (uint16_t*)G, seg_off, buf_expert, Mdim, Ndim, MT, NT, (int)tiles);
   return launch_status();
 }
