@@ -323,103 +323,115 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
   zero_empty();
 }
 
-// Any shape and either storage type of the operands that have one (the other operand is bf16): 128 x 128 tile of G per
-// work-group, four waves of 64 x 64, 32 rows of the segment per step.  Both operands are staged through registers
-// (the next step's loads are in flight during the current step's MFMAs) into a double-buffered k-major LDS tile of
-// 256-byte rows and fetched with the transposing LDS read; the chunk swizzle is the one of the kernel above.
+// Any shape and either storage type of the operands that have one (the other operand is bf16): a tile of G per work-group,
+// four waves of 64 x 64, or of 128 x 64 with 128 columns of the bf16 operand (launch_wgrad says which), 32 rows of the
+// segment per step.  Both operands are staged through registers (the next step's loads are in flight during the current
+// one's MFMAs) into double-buffered k-major LDS tiles and fetched with the transposing LDS read; the chunk swizzle is the
+// one of the kernel above.
 // fp32 values keep all their 24 bits: x = a + b + c with a, b, c the bf16 numbers that hold bits 0..7, 8..15 and
 // 16..23 of the significand (cut, not rounded: each remainder is exact), so that three MFMAs sum the same exact
 // products as fp32 multiplications would, in fp32: at 60, 500 and 3 000 rows 131, 368 and 1 766 of 2 to 4 million elements
 // are not the rounded float64 sum (one thread per element with scalar products, which this replaces: 242, 655, 2 874).
 // Bits below bf16's least subnormal, 2^-133, are lost: values under 2^-109 keep fewer than 24 bits (a single product is
 // still the rounded one down to 2^-118).  Infinities: see behind the loop.
-// The contraction is short and the output large: at T = 4096, d = 1024, h = 4096, 16 experts, fp32 storage (3 112
-// kept rows) both launches write 268 MB, 54 us at the rate of a large copy, and multiply 3 x 52 GFLOP, 132 us at the
-// rate of a large matrix product; they take 174 + 158 us (the scalar kernel: 12.8 ms).  64 KiB of LDS and 128-wide tiles
-// leave room for two work-groups per compute unit, so that one's stores run beside the other's MFMAs.
-constexpr int kAnyThreads = 256;                   // four waves of 64 x 64
-constexpr int kAnyTile = 128;
-constexpr int kAnyRow = kAnyTile * 2;              // bytes of an LDS row
-constexpr int kAnyPlane = kWgK * kAnyRow;          // 8 KiB: one bf16 plane of one operand's step
+// The contraction is short and the output large: at T = 4096, d = 1024, h = 4096, 16 experts, fp32 storage (3 662
+// kept rows) both launches write 268 MB, 54 us at the rate of a large copy, and multiply 3 x 61 GFLOP, 142 us at the
+// rate of a large matrix product; they take 202 us.  Splitting a value was 12 vector operations beside two per MFMA's share
+// of a 128 x 128 tile, more than the MFMAs' own cycles; with the remainders unguarded and the upper halves taken by one
+// byte permutation per pair it is 5.5: 296 -> 268 us; the wide tile does it, and the LDS reads of the fp32 planes, for twice
+// as many products: 202.  At most 80 KiB of LDS leave room for two work-groups per compute unit, so that one's stores run
+// beside the other's MFMAs.
+constexpr int kAnyThreads = 256;    // four waves, 2 along m x 2 along n
 
 __device__ __forceinline__ int any_swz(int row) { return ((row & 3) | (((row >> 3) & 1) << 2)) << 1; }
 
-// 8 fp32 values -> the three bf16 planes described above, 16 bytes each
-__device__ __forceinline__ void split3(const u32x4& lo4, const u32x4& hi4, uint4 (&out)[3]) {
-  uint32_t part[3][8];
+// 8 fp32 values -> the three bf16 planes described above, 16 bytes each.  (An infinity leaves a NaN for its remainder: see
+// behind the loop.)
+__device__ __forceinline__ void split3(const u32x4& lo4, const u32x4& hi4, u32x4 (&out)[3]) {
+  uint32_t x[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    float x = __uint_as_float(i < 4 ? lo4[i] : hi4[i - 4]);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const uint32_t cut = __float_as_uint(x) & 0xFFFF0000u;
-      part[q][i] = cut;
-      x = x == __uint_as_float(cut) ? 0.f : x - __uint_as_float(cut);  // (an infinity leaves no remainder)
-    }
-  }
+  for (int i = 0; i < 8; ++i) x[i] = i < 4 ? lo4[i] : hi4[i - 4];
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    auto two = [&](int i) { return (part[q][i] >> 16) | part[q][i + 1]; };
-    out[q] = make_uint4(two(0), two(2), two(4), two(6));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[q][i] = __builtin_amdgcn_perm(x[2 * i + 1], x[2 * i], 0x07060302u);  // the upper halves
+    if (q < 2) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        x[i] = __float_as_uint(__uint_as_float(x[i]) - __uint_as_float(x[i] & 0xFFFF0000u));
+    }
   }
 }
 
-__device__ __forceinline__ bool acc_has_nan(const f32x4 (&acc)[4][4]) {
+template <int NI, int MJ>
+__device__ __forceinline__ bool acc_has_nan(const f32x4 (&acc)[NI][MJ]) {
   bool nan = false;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NI; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < MJ; ++b)
 #pragma unroll
       for (int v = 0; v < 4; v += 2) nan |= __builtin_isunordered(acc[a][b][v], acc[a][b][v + 1]);
   return nan;
 }
 
-// One operand's share of a step for this thread: two pieces of 8 consecutive columns of one row each
-template <bool F32>
+// One operand's share of a step for this thread: SUB / 2 pieces of 8 consecutive columns of one row each; the operand's tile
+// is 32 rows x 32 SUB columns (SUB 16-column subtiles per wave)
+template <bool F32, int SUB>
 struct AnyStage {
   static constexpr int kPlanes = F32 ? 3 : 1;
-  static constexpr int kBytes = kPlanes * kAnyPlane;
-  u32x4 v[F32 ? 4 : 2];
+  static constexpr int kRow = 64 * SUB;              // bytes of an LDS row
+  static constexpr int kPlane = kWgK * kRow;         // one bf16 plane
+  static constexpr int kBytes = kPlanes * kPlane;
+  static constexpr int kPieces = SUB / 2, kPerRow = 4 * SUB;
+  u32x4 v[F32 ? 2 * kPieces : kPieces];
 
   // rows at or past `rows` re-read the last row here and become zeros in store()
   __device__ __forceinline__ void load(const char* base, size_t ld, int col0, int cols, int k0, int rows, int tid) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * kAnyThreads, row = min(k0 + (c >> 4), rows - 1);
-      const int col = min(col0 + (c & 15) * 8, cols - 8);  // columns past the end repeat the last ones (not stored)
+    for (int i = 0; i < kPieces; ++i) {
+      const int c = tid + i * kAnyThreads, row = min(k0 + c / kPerRow, rows - 1);
+      const int col = min(col0 + (c % kPerRow) * 8, cols - 8);  // columns past the end repeat the last ones (not stored)
       const u32x4* p = (const u32x4*)(base + (size_t)row * ld + (size_t)col * (F32 ? 4 : 2));
       if (F32) { v[2 * i] = p[0]; v[2 * i + 1] = p[1]; }
       else v[i] = p[0];
     }
   }
-  __device__ __forceinline__ void store(char* lds, int k0, int rows, int tid) const {
+  __device__ __forceinline__ void store(char* lds, int k0, int rows, int tid) {
+    if (k0 + kWgK > rows) {
+      const u32x4 z = {0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * kAnyThreads, row = c >> 4;
-      const bool live = k0 + row < rows;
-      char* dst = lds + row * kAnyRow + (((c & 15) ^ any_swz(row)) << 4);
+      for (int i = 0; i < kPieces; ++i)
+        if (k0 + (tid + i * kAnyThreads) / kPerRow >= rows) {
+          if (F32) v[2 * i] = v[2 * i + 1] = z;
+          else v[i] = z;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      const int c = tid + i * kAnyThreads, row = c / kPerRow;
+      char* dst = lds + row * kRow + (((c % kPerRow) ^ any_swz(row)) << 4);
       if (F32) {
-        uint4 part[3];
+        u32x4 part[3];
         split3(v[2 * i], v[2 * i + 1], part);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) *(uint4*)(dst + q * kAnyPlane) = live ? part[q] : make_uint4(0, 0, 0, 0);
+        for (int q = 0; q < 3; ++q) *(u32x4*)(dst + q * kPlane) = part[q];
       } else {
-        const u32x4 z = {0, 0, 0, 0};
-        *(u32x4*)dst = live ? v[i] : z;
+        *(u32x4*)dst = v[i];
       }
     }
   }
 };
 
-template <bool P_F32, bool Q_F32>
+// MJ, NI: 16-wide subtiles of a wave along m and n (the tile is 32 MJ x 32 NI)
+template <bool P_F32, bool Q_F32, int MJ, int NI>
 __global__ __launch_bounds__(kAnyThreads, 2) void wgrad_any_kernel(const char* __restrict__ P, const char* __restrict__ Q,
                                                                   uint16_t* __restrict__ G,
                                                                   const int32_t* __restrict__ seg_off,
                                                                   const int32_t* __restrict__ buf_expert, int Mdim,
                                                                   int Ndim, int MT, int NT, int total) {
-  using SP = AnyStage<P_F32>;
-  using SQ = AnyStage<Q_F32>;
+  using SP = AnyStage<P_F32, MJ>;
+  using SQ = AnyStage<Q_F32, NI>;
   constexpr int kStageBytes = SP::kBytes + SQ::kBytes;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // consecutive tiles of a segment share operand tiles: an XCD (work-groups with equal id mod 8) walks a contiguous run
@@ -428,26 +440,26 @@ __global__ __launch_bounds__(kAnyThreads, 2) void wgrad_any_kernel(const char* _
   const int mt = lin % MT, nt = (lin / MT) % NT, r = lin / (MT * NT);
   const int seg0 = seg_off[r], rows = seg_off[r + 1] - seg0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = mt * kAnyTile, n0 = nt * kAnyTile;
+  const int m0 = mt * 32 * MJ, n0 = nt * 32 * NI;
   const size_t ldP = (size_t)Mdim * (P_F32 ? 4 : 2), ldQ = (size_t)Ndim * (Q_F32 ? 4 : 2);
   const char* Ps = P + (size_t)seg0 * ldP;
   const char* Qs = Q + (size_t)seg0 * ldQ;
 
   const int wm = wave >> 1, wn = wave & 1;
   const int kq = lane >> 4, l16 = lane & 15;
-  int off_m[4], off_n[4];
+  int off_m[MJ], off_n[NI];
   {
     const int row = 8 * kq + (l16 >> 2), b1 = (l16 & 3) >> 1, inner = (l16 & 1) * 8, sw = any_swz(row);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) off_m[j] = row * kAnyRow + (((8 * wm + 2 * j + b1) ^ sw) << 4) + inner;
+    for (int j = 0; j < MJ; ++j) off_m[j] = row * SP::kRow + (((2 * MJ * wm + 2 * j + b1) ^ sw) << 4) + inner;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) off_n[j] = SP::kBytes + row * kAnyRow + (((8 * wn + 2 * j + b1) ^ sw) << 4) + inner;
+    for (int j = 0; j < NI; ++j) off_n[j] = SP::kBytes + row * SQ::kRow + (((2 * NI * wn + 2 * j + b1) ^ sw) << 4) + inner;
   }
-  f32x4 acc[4][4];  // [n subtile][m subtile]
+  f32x4 acc[NI][MJ];  // [n subtile][m subtile]
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NI; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < MJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   if (rows > 0) {
     SP sp;
@@ -463,79 +475,112 @@ __global__ __launch_bounds__(kAnyThreads, 2) void wgrad_any_kernel(const char* _
       sp.load(Ps, ldP, m0, Mdim, k0 + kWgK, rows, tid);
       sq.load(Qs, ldQ, n0, Ndim, k0 + kWgK, rows, tid);
       lds_cptr pt = (lds_cptr)(uintptr_t)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)st;
-      bf16x8 fm[SP::kPlanes][4], fn[SQ::kPlanes][4];
+      // (the operand with one plane stays in registers, the other's planes come one after the other)
+      if constexpr (SP::kPlanes == 1) {
+        bf16x8 fm[MJ];
 #pragma unroll
-      for (int q = 0; q < SP::kPlanes; ++q)
+        for (int j = 0; j < MJ; ++j) fm[j] = read_tr8_sw<SP::kRow>(pt + off_m[j]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) fm[q][j] = read_tr8_sw<kAnyRow>(pt + q * kAnyPlane + off_m[j]);
+        for (int q = 0; q < SQ::kPlanes; ++q) {
+          bf16x8 fn[NI];
 #pragma unroll
-      for (int q = 0; q < SQ::kPlanes; ++q)
+          for (int j = 0; j < NI; ++j) fn[j] = read_tr8_sw<SQ::kRow>(pt + q * SQ::kPlane + off_n[j]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) fn[q][j] = read_tr8_sw<kAnyRow>(pt + q * kAnyPlane + off_n[j]);
+          for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-      for (int qp = 0; qp < SP::kPlanes; ++qp)
+            for (int mj = 0; mj < MJ; ++mj)
+              acc[ni][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[ni], fm[mj], acc[ni][mj], 0, 0, 0);
+        }
+      } else {
+        bf16x8 fn[NI];
 #pragma unroll
-        for (int qq = 0; qq < SQ::kPlanes; ++qq)
+        for (int j = 0; j < NI; ++j) fn[j] = read_tr8_sw<SQ::kRow>(pt + off_n[j]);
 #pragma unroll
-          for (int ni = 0; ni < 4; ++ni)
+        for (int q = 0; q < SP::kPlanes; ++q) {
+          bf16x8 fm[MJ];
 #pragma unroll
-            for (int mj = 0; mj < 4; ++mj)
-              acc[ni][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[qq][ni], fm[qp][mj], acc[ni][mj], 0, 0, 0);
+          for (int j = 0; j < MJ; ++j) fm[j] = read_tr8_sw<SP::kRow>(pt + q * SP::kPlane + off_m[j]);
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int mj = 0; mj < MJ; ++mj)
+              acc[ni][mj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fn[ni], fm[mj], acc[ni][mj], 0, 0, 0);
+        }
+      }
       buf ^= 1;
     }
   }
-  // An infinity in the bf16 operand times an fp32 value of at most 16 significant bits (1.0) meets a plane of zeros, and
-  // 0 * inf is a NaN where the product is an infinity.  A wave whose part of the tile holds a NaN therefore sums it again
-  // with the products themselves, row by row in fp32.  (The look at the sums costs 2 % where a segment has 160 rows.)
+  // An infinity in the fp32 operand has NaNs for its lower planes, and one in the bf16 operand times an fp32 value of at
+  // most 16 significant bits (1.0) meets a plane of zeros, where 0 * inf is a NaN and the product an infinity.  A wave whose
+  // part of the tile holds a NaN therefore sums it again with the products themselves, row by row in fp32.  (The look at
+  // the sums costs 2 % where a segment has 160 rows.)
   if ((P_F32 || Q_F32) && __builtin_expect(__any(acc_has_nan(acc)), 0)) {
-    int lm = wm * 64 + l16, ln = wn * 64 + kq * 4;
+    int lm = wm * 16 * MJ + l16, ln = wn * 16 * NI + kq * 4;
     asm volatile("" : "+v"(lm), "+v"(ln));  // (none of this belongs ahead of the loop)
     const int m = m0 + lm, n = n0 + ln;
     auto value = [](const char* row, bool f32, int c) {
       return f32 ? ((const float*)row)[c] : bf16_bits_to_f32(((const uint16_t*)row)[c]);
     };
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NI; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int b = 0; b < MJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma nounroll
     for (int k = 0; k < rows; ++k) {
-      float p[4];
+      float p[MJ];
 #pragma unroll
-      for (int mj = 0; mj < 4; ++mj) p[mj] = value(Ps + k * ldP, P_F32, min(m + mj * 16, Mdim - 1));
+      for (int mj = 0; mj < MJ; ++mj) p[mj] = value(Ps + k * ldP, P_F32, min(m + mj * 16, Mdim - 1));
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni)
+      for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const float q = value(Qs + k * ldQ, Q_F32, min(n + ni * 16 + v, Ndim - 1));
 #pragma unroll
-          for (int mj = 0; mj < 4; ++mj) acc[ni][mj][v] = fmaf(p[mj], q, acc[ni][mj][v]);
+          for (int mj = 0; mj < MJ; ++mj) acc[ni][mj][v] = fmaf(p[mj], q, acc[ni][mj][v]);
         }
     }
   }
-  // Through LDS, so that a row of the tile leaves as 256 contiguous bytes (chunk index XORed with the row)
+  // Through LDS, so that a row of the tile leaves as 256 or 512 contiguous bytes (chunk index XORed with the row)
+  constexpr int kGRow = 64 * NI;
   __syncthreads();
 #pragma unroll
-  for (int mj = 0; mj < 4; ++mj) {
-    char* row = smem + (wm * 64 + mj * 16 + l16) * kAnyRow + (kq & 1) * 8;
+  for (int mj = 0; mj < MJ; ++mj) {
+    char* row = smem + (wm * 16 * MJ + mj * 16 + l16) * kGRow + (kq & 1) * 8;
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) {
+    for (int ni = 0; ni < NI; ++ni) {
       const f32x4 v = acc[ni][mj];
-      *(uint2*)(row + (((8 * wn + 2 * ni + (kq >> 1)) ^ l16) << 4)) =
+      *(uint2*)(row + (((2 * NI * wn + 2 * ni + (kq >> 1)) ^ l16) << 4)) =
           make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
     }
   }
   __syncthreads();
   uint16_t* Gt = G + ((size_t)buf_expert[r] * Mdim + m0) * Ndim + n0;
-  const int rrow = tid >> 4, rcol = tid & 15;
+  constexpr int kRowLanes = 4 * NI, kRows = kAnyThreads / kRowLanes;  // lanes per row, rows at a time
+  const int rrow = tid / kRowLanes, rcol = tid % kRowLanes;
   if (n0 + rcol * 8 < Ndim) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = rrow + 16 * i;
-      const uint4 v = *(const uint4*)(smem + row * kAnyRow + ((rcol ^ (row & 15)) << 4));
+    for (int i = 0; i < 32 * MJ / kRows; ++i) {
+      const int row = rrow + kRows * i;
+      const uint4 v = *(const uint4*)(smem + row * kGRow + ((rcol ^ (row & 15)) << 4));
       if (m0 + row < Mdim) nt_store16(v, (uint4*)(Gt + (size_t)row * Ndim + rcol * 8));
     }
   }
+}
+
+template <bool P_F32, bool Q_F32, int MJ, int NI>
+int launch_wgrad_any(const void* P, const void* Q, void* G, const int32_t* seg_off, const int32_t* buf_expert, int E,
+                     int Mdim, int Ndim, hipStream_t st) {
+  const int MT = ceil_div(Mdim, 32 * MJ), NT = ceil_div(Ndim, 32 * NI);
+  const long long tiles = (long long)E * MT * NT;
+  if (tiles > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+  auto any = wgrad_any_kernel<P_F32, Q_F32, MJ, NI>;
+  constexpr int stages = 2 * (AnyStage<P_F32, MJ>::kBytes + AnyStage<Q_F32, NI>::kBytes);
+  constexpr int smem = std::max(stages, 32 * MJ * 64 * NI);  // 32 to 80 KiB (the tile of G goes through it too)
+  static std::atomic<uint64_t> any_lds;
+  if (!allow_lds((const void*)any, smem, any_lds)) return LOCMOE_ERR_HIP;
+  hipLaunchKernelGGL(any, dim3((unsigned)tiles), dim3(kAnyThreads), smem, st, (const char*)P, (const char*)Q,
+                     (uint16_t*)G, seg_off, buf_expert, Mdim, Ndim, MT, NT, (int)tiles);
+  return launch_status();
 }
 
 template <bool P_F32, bool Q_F32>
@@ -556,16 +601,17 @@ int launch_wgrad(const void* P, const void* Q, void* G, const int32_t* seg_off, 
       return launch_status();
     }
   }
-  const int MT = ceil_div(Mdim, kAnyTile), NT = ceil_div(Ndim, kAnyTile);
-  const long long tiles = (long long)E * MT * NT;
-  if (tiles > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
-  auto any = wgrad_any_kernel<P_F32, Q_F32>;
-  constexpr int smem = 2 * (AnyStage<P_F32>::kBytes + AnyStage<Q_F32>::kBytes);  // 32 or 64 KiB; the tile of G needs 32
-  static std::atomic<uint64_t> any_lds;
-  if (!allow_lds((const void*)any, smem, any_lds)) return LOCMOE_ERR_HIP;
-  hipLaunchKernelGGL(any, dim3((unsigned)tiles), dim3(kAnyThreads), smem, st, (const char*)P, (const char*)Q,
-                     (uint16_t*)G, seg_off, buf_expert, Mdim, Ndim, MT, NT, (int)tiles);
-  return launch_status();
+  // With fp32 storage 256 columns of the bf16 operand per tile where that leaves three tiles per compute unit: the fp32
+  // operand is split and read from LDS half as often.  Both GEMMs, us, 128 x 128 tiles / 256 wide: E = 16, d = 1024, h = 4096,
+  // 229 rows 268 / 202;  E = 4, d = 2048, h = 4096, 714 rows (4 tiles per unit) 295 / 230;  E = 20, d = 640, h = 1712, 60 rows
+  // (2.7) 38.1 / 39.2;  E = 6, d = 768, h = 1536, 298 rows (0.8) 39 / 45.  Two bf16 operands: E = 24, d = 768, h = 3072, 455
+  // rows 150 / 152;  E = 48, d = 384, h = 1536, 65 rows 30 / 35.
+  constexpr int MJ = Q_F32 ? 8 : 4, NI = P_F32 ? 8 : 4;
+  if constexpr (MJ != NI) {
+    if ((long long)E * ceil_div(Mdim, 32 * MJ) * ceil_div(Ndim, 32 * NI) >= 3 * cu_count())
+      return launch_wgrad_any<P_F32, Q_F32, MJ, NI>(P, Q, G, seg_off, buf_expert, E, Mdim, Ndim, st);
+  }
+  return launch_wgrad_any<P_F32, Q_F32, 4, 4>(P, Q, G, seg_off, buf_expert, E, Mdim, Ndim, st);
 }
 
 }  // namespace

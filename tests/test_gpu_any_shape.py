@@ -69,6 +69,32 @@ def test_weight_gradients_of_any_shape(env, d, h, dtype):
             assert ((got.double() - ref).abs() <= bound).all(), (r, z - a)
 
 
+# fp32 storage with enough tiles for the wide ones (three per compute unit): remainders along both axes, and rows at the
+# edges of a step
+@pytest.mark.parametrize("d,h", [(1032, 3080), (2040, 1544)])
+def test_weight_gradients_of_wide_tiles(env, d, h):
+    torch, lm = env
+    rows = [33, 0, 1, 97, 32, 64, 31, 2] * 3
+    E, K = len(rows), sum(rows)
+    print(f"[wgrad wide] d={d} h={h} rows={rows}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(d + h)
+    off, seg, be = segments(torch, rows)
+    desc = lm.make_desc(600, d, E, 1, h, 100, "f32")
+    send, dout = (rows_with_nan_tail(torch, K, 40, d, torch.float32, gen) for _ in range(2))
+    H, dZ = (rows_with_nan_tail(torch, K, 40, h, torch.bfloat16, gen) for _ in range(2))
+    dW_in = torch.full((E, h, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    dW_out = torch.full((E, d, h), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lm.locmoe_expert_ffn_wgrad(desc, send, H, dout, dZ, seg, be, dW_in, dW_out)
+    torch.cuda.synchronize()
+    for r in range(E):
+        e, a, z = E - 1 - r, off[r], off[r + 1]
+        for got, P, Q in ((dW_in[e], dZ, send), (dW_out[e], dout, H)):
+            p, q = P[a:z].double(), Q[a:z].double()
+            ref = p.T @ q
+            bound = 2.0 ** -8 * (1 + 2.0 ** -8) * ref.abs() + (z - a) * 2.0 ** -23 * (p.abs().T @ q.abs())
+            assert ((got.double() - ref).abs() <= bound).all(), (r, z - a)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_weight_gradients_of_infinities(env, dtype):
     """An infinite or NaN operand gives what the products give: inf where 1.0 * inf, NaN only where 0 * inf or inf - inf.

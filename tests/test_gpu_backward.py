@@ -422,3 +422,40 @@ def test_backward_config3_full_size_large_capacity(env):
     """Capacity 2 048 (almost nothing dropped): segments of up to 2 048 rows (many m-tiles per weight tile in the data
     gradients, a hundred steps per tile in the weight gradients), very uneven."""
     run_backward_big(env, wl.CONFIGS[3], 2048)
+
+
+# one launch (up to 2 048 tokens, 4 096 with up to 40 experts) and three, against the formulas in float64
+@pytest.mark.parametrize("E,N,T", [(1, 1, 3), (8, 2, 1), (16, 4, 2048), (16, 4, 4096), (16, 4, 4097), (40, 8, 4096), (41, 1, 4096),
+                                   (64, 8, 2048), (64, 8, 2049), (300, 3, 2048)])
+@pytest.mark.parametrize("home", [False, True])
+def test_route_backward_in_one_and_three_launches(env, E, N, T, home):
+    torch, lm, _ = env
+    gen = torch.Generator(device="cuda").manual_seed(E * 5 + T)
+    g = torch.randn(T, E, generator=gen, device="cuda")
+    eps = 0.05 * torch.randn(E, generator=gen, device="cuda")
+    nodes = torch.randint(0, N, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    nodes[:N] = torch.arange(N, dtype=torch.int32, device="cuda")[:T]
+    dw = torch.randn(T, generator=gen, device="cuda")
+    s = (g + eps).clamp_min(0)
+    eid = s.argmax(1)
+    cnt = torch.bincount(eid, minlength=E).to(torch.int32)
+    Psum = s.double().softmax(1).sum(0).float()
+    desc = lm.make_desc(T, 8 * E, E, N, 8, T, "bf16", alpha=0.3, mu=0.2)
+    coef, dg = torch.full((E,), float("nan"), device="cuda"), torch.full((T, E), float("nan"), device="cuda")
+    say(f"[route bwd] T={T} E={E} N={N} home={home}")
+    lm.locmoe_route_bwd(desc, g, eps, nodes if home else None, None, eid.to(torch.int32), cnt, Psum, dw, coef, dg)
+    torch.cuda.synchronize()
+    c = desc.alpha * E * cnt.double() / T / T
+    if home:
+        node = torch.arange(E, device="cuda") // (E // N)
+        Dl = torch.bincount(nodes, minlength=N).double()[node] / (T * (E // N))
+        c += desc.mu * (torch.log(Psum.double() / T / Dl) + 1) / T
+    live = torch.isfinite(c)  # (a node without tokens has no finite coefficient)
+    assert ((coef.double() - c)[live].abs() <= 1e-5 * c[live].abs() + 1e-12).all()
+    if not live.all():
+        return
+    p = s.double().softmax(1)
+    dp = c.expand(T, E).clone()
+    dp[torch.arange(T, device="cuda"), eid] += dw.double()
+    ref = p * (dp - (p * dp).sum(1, keepdim=True)) * (g + eps > 0)
+    assert ((dg.double() - ref).abs() <= 2e-5 * (c.abs().max() + dw.double().abs())[:, None]).all()
