@@ -115,9 +115,10 @@ def _check(st: int) -> None:
 
 
 def _ptr(t) -> int | None:
-    """Device (or host) address of a torch tensor / numpy array, None stays NULL."""
-    if t is None:
-        return None
+    """Device (or host) address of a torch tensor / numpy array, None stays NULL, an address stays itself.  (The launches of
+    a small layer take about as long as this marshalling: the common cases come first.)"""
+    if t is None or t.__class__ is int:
+        return t
     if isinstance(t, np.ndarray):
         return t.ctypes.data
     if isinstance(t, int):
@@ -128,6 +129,8 @@ def _ptr(t) -> int | None:
 
 
 def _stream(stream) -> int | None:
+    if stream.__class__ is int:
+        return stream
     if stream is None:
         import torch
         return torch.cuda.current_stream().cuda_stream
@@ -346,15 +349,25 @@ def alloc_buffers(desc: locmoe_desc, device="cuda") -> Buffers:
         ws_bytes=wsb, ffn_ws=torch.zeros(LOCMOE_FFN_WS_BYTES, dtype=torch.uint8, device=device))
 
 
+def _route_and_dispatch(desc, x, home, e2n, b: Buffers, eps, stream):
+    """Gate, route and dispatch on one stream; returns the addresses that the later steps share."""
+    x, home, e2n, eps = _ptr(x), _ptr(home), _ptr(e2n), _ptr(eps)
+    g, eid, w, ws, slot, seg_off, buf_expert, send = (_ptr(t) for t in (b.g, b.eid, b.w, b.ws, b.slot, b.seg_off,
+                                                                        b.buf_expert, b.send))
+    locmoe_gate(desc, x, g, stream)
+    locmoe_route(desc, g, eps, home, e2n, eid, w, b.cnt, b.Psum, b.stats, ws, b.ws_bytes, stream)
+    locmoe_dispatch(desc, x, eid, e2n, b.pos, slot, b.kept, seg_off, b.node_off, buf_expert, b.row_token, send, ws,
+                    b.ws_bytes, stream)
+    return w, slot, seg_off, buf_expert, send
+
+
 def forward(desc, x, home, e2n, W_in, W_out, b: Buffers, eps=None, stream=None):
     """Enqueues the five steps of the hot path back to back on one stream."""
-    locmoe_gate(desc, x, b.g, stream)
-    locmoe_route(desc, b.g, eps, home, e2n, b.eid, b.w, b.cnt, b.Psum, b.stats, b.ws, b.ws_bytes, stream)
-    locmoe_dispatch(desc, x, b.eid, e2n, b.pos, b.slot, b.kept, b.seg_off, b.node_off, b.buf_expert, b.row_token,
-                    b.send, b.ws, b.ws_bytes, stream)
-    locmoe_expert_ffn_ws(desc, b.send, b.seg_off, b.buf_expert, W_in, W_out, b.H, b.out, b.ffn_ws,
-                         LOCMOE_FFN_WS_BYTES, stream)
-    locmoe_combine(desc, b.out, b.slot, b.w, b.y, stream)
+    stream = _stream(stream)
+    w, slot, seg_off, buf_expert, send = _route_and_dispatch(desc, x, home, e2n, b, eps, stream)
+    out = _ptr(b.out)
+    locmoe_expert_ffn_ws(desc, send, seg_off, buf_expert, W_in, W_out, b.H, out, b.ffn_ws, LOCMOE_FFN_WS_BYTES, stream)
+    locmoe_combine(desc, out, slot, w, b.y, stream)
     return b.y
 
 
@@ -389,24 +402,25 @@ def alloc_grad_buffers(desc: locmoe_desc, device="cuda") -> GradBuffers:
 
 def forward_train(desc, x, home, e2n, W_in, W_out, b: Buffers, gb: GradBuffers, eps=None, stream=None):
     """The forward path with the pre-activation Z kept for the backward."""
-    locmoe_gate(desc, x, b.g, stream)
-    locmoe_route(desc, b.g, eps, home, e2n, b.eid, b.w, b.cnt, b.Psum, b.stats, b.ws, b.ws_bytes, stream)
-    locmoe_dispatch(desc, x, b.eid, e2n, b.pos, b.slot, b.kept, b.seg_off, b.node_off, b.buf_expert, b.row_token,
-                    b.send, b.ws, b.ws_bytes, stream)
-    locmoe_expert_ffn_in_save_ws(desc, b.send, b.seg_off, b.buf_expert, W_in, b.H, gb.Z, b.ffn_ws,
-                                 LOCMOE_FFN_WS_BYTES, stream)
-    locmoe_expert_ffn_out_ws(desc, b.H, b.seg_off, b.buf_expert, W_out, b.out, b.ffn_ws, LOCMOE_FFN_WS_BYTES, stream)
-    locmoe_combine(desc, b.out, b.slot, b.w, b.y, stream)
+    stream = _stream(stream)
+    w, slot, seg_off, buf_expert, send = _route_and_dispatch(desc, x, home, e2n, b, eps, stream)
+    H, out, ffn_ws = _ptr(b.H), _ptr(b.out), _ptr(b.ffn_ws)
+    locmoe_expert_ffn_in_save_ws(desc, send, seg_off, buf_expert, W_in, H, gb.Z, ffn_ws, LOCMOE_FFN_WS_BYTES, stream)
+    locmoe_expert_ffn_out_ws(desc, H, seg_off, buf_expert, W_out, out, ffn_ws, LOCMOE_FFN_WS_BYTES, stream)
+    locmoe_combine(desc, out, slot, w, b.y, stream)
     return b.y
 
 
 def backward(desc, dy, home, e2n, W_in_t, W_out_t, b: Buffers, gb: GradBuffers, eps=None, stream=None):
     """Enqueues the backward steps on one stream, in reverse order of the forward; W_in_t / W_out_t are the
     transposed weights in the layout desc.w_packed names.  Leaves dx, dW_in, dW_out in gb."""
-    locmoe_combine_bwd(desc, dy, b.out, b.slot, b.w, gb.dout, gb.dw, stream)
-    locmoe_expert_ffn_dgrad_ws(desc, gb.dout, gb.Z, b.seg_off, b.buf_expert, W_out_t, W_in_t, gb.dZ, gb.dsend,
-                               b.ffn_ws, LOCMOE_FFN_WS_BYTES, stream)
-    locmoe_expert_ffn_wgrad(desc, b.send, b.H, gb.dout, gb.dZ, b.seg_off, b.buf_expert, gb.dW_in, gb.dW_out, stream)
-    locmoe_route_bwd(desc, b.g, eps, home, e2n, b.eid, b.cnt, b.Psum, gb.dw, gb.coef, gb.dg, stream)
-    locmoe_dispatch_bwd(desc, gb.dsend, b.slot, gb.dg, gb.dx, stream)
+    stream = _stream(stream)
+    slot, seg_off, buf_expert, dout, dw, dZ, dsend, dg = (_ptr(t) for t in (b.slot, b.seg_off, b.buf_expert, gb.dout, gb.dw,
+                                                                            gb.dZ, gb.dsend, gb.dg))
+    locmoe_combine_bwd(desc, dy, b.out, slot, b.w, dout, dw, stream)
+    locmoe_expert_ffn_dgrad_ws(desc, dout, gb.Z, seg_off, buf_expert, W_out_t, W_in_t, dZ, dsend, b.ffn_ws,
+                               LOCMOE_FFN_WS_BYTES, stream)
+    locmoe_expert_ffn_wgrad(desc, b.send, b.H, dout, dZ, seg_off, buf_expert, gb.dW_in, gb.dW_out, stream)
+    locmoe_route_bwd(desc, b.g, eps, home, e2n, b.eid, b.cnt, b.Psum, dw, gb.coef, dg, stream)
+    locmoe_dispatch_bwd(desc, dsend, slot, dg, gb.dx, stream)
     return gb.dx
