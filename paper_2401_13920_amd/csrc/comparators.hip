@@ -130,8 +130,106 @@ __global__ __launch_bounds__(kDgThreads) void gate_dense_mfma_kernel(const uint1
   }
 }
 
+// Dense gate, fp32 storage, d a multiple of 32: the same tile and staging with 32 features (128 bytes) per step and
+// v_mfma_f32_32x32x2_f32.  Bound by the pass over x up to some 32 experts, above by the fp32 matrix rate (157 TFLOP/s).
+// The sums are kept short: two MFMAs from zero, eight such sums per step in fp32, the steps in double, so that the error
+// against float64 is no larger than with one wave per token (relative 2-norm 6.8e-8 at any d, which is the last rounding; one wave per token 8e-8 at
+// d = 384, 1.2e-7 at 2 048, 1.7e-7 at 5 120).  us, one wave per token / this: T = 32 768, d = 2048, E = 32 1 428 / 90;
+// T = 60 000, d = 1280, E = 40 2 096 / 158;  T = 16 000, d = 5120, E = 128 6 922 / 706;  T = 4 193, d = 384, E = 64 57 / 33.
+template <int NT>
+__global__ __launch_bounds__(kDgThreads) void gate_dense_f32_kernel(const float* __restrict__ x, const float* __restrict__ Wg,
+                                                                    float* __restrict__ g, int T, int d, int E) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int kBK = kDgRowBytes / 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.x * kDgTokens;
+  const int e0 = blockIdx.y * 128;
+  const float* gx[4];
+  const float* gw[NT];
+  int lds_x[4], lds_w[NT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = tid + i * kDgThreads, row = c >> 3, kc = c & 7;
+    gx[i] = x + (size_t)min(m0 + row, T - 1) * d + kc * 4;  // rows past T re-read the last token (never stored)
+    lds_x[i] = row * kDgRowBytes + dg_swz(row, kc);
+  }
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int c = tid + i * kDgThreads, row = c >> 3, kc = c & 7;
+    gw[i] = Wg + (size_t)min(e0 + row, E - 1) * d + kc * 4;  // rows past E re-read the last expert (never stored)
+    lds_w[i] = row * kDgRowBytes + dg_swz(row, kc);
+  }
+  const int frow = lane & 31, khalf = lane >> 5;
+  const int xrow = wave * 32 + frow;
+  double sum[NT][16];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum[t][i] = 0.0;
+
+  u32x4 rx[4], rw[NT];  // the k-step after the one in LDS
+  const int KT = d / kBK;
+  auto load = [&](int kt) {
+    const int ko = min(kt, KT - 1) * kBK;  // (a step after the last re-reads the last: never consumed)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rx[i] = *(const u32x4*)(gx[i] + ko);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) rw[i] = *(const u32x4*)(gw[i] + ko);
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(u32x4*)(smem + buf * kDgTile + lds_x[i]) = rx[i];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) *(u32x4*)(smem + (2 + buf) * kDgTile + lds_w[i]) = rw[i];
+  };
+  load(0);
+  store(0);
+  load(1);
+  __syncthreads();
+  for (int kt = 0; kt < KT; ++kt) {
+    const char* sx = smem + (kt & 1) * kDgTile;
+    const char* sw = smem + (2 + (kt & 1)) * kDgTile;
+    f32x16 part[NT];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {  // (a lane's four features go one by one: any order does that both operands have)
+      const int kc = ks * 2 + khalf;
+      const f32x4 fx = *(const f32x4*)(sx + xrow * kDgRowBytes + dg_swz(xrow, kc));
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int wrow = t * 32 + frow;
+        const f32x4 fw = *(const f32x4*)(sw + wrow * kDgRowBytes + dg_swz(wrow, kc));
+        f32x16 a = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[0], fx[0], (f32x16){0}, 0, 0, 0);  // D[expert][token]
+        f32x16 b = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[2], fx[2], (f32x16){0}, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[1], fx[1], a, 0, 0, 0);
+        b = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[3], fx[3], b, 0, 0, 0);
+        part[t] = ks ? part[t] + (a + b) : a + b;
+      }
+    }
+    store((kt + 1) & 1);
+    load(kt + 2);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum[t][i] += (double)part[t][i];
+    __syncthreads();
+  }
+  const int m = m0 + xrow;
+  if (m < T) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int vq = 0; vq < 4; ++vq) {
+        const int i0 = e0 + t * 32 + vq * 8 + khalf * 4;
+        float* dst = g + (size_t)m * E + i0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (i0 + q < E) dst[q] = (float)sum[t][vq * 4 + q];
+      }
+  }
+}
+
 // Any shape and either storage type: one wave per token, lanes stride over the features, the wave's sum by a
-// fixed butterfly.  Correct for every descriptor; used for fp32 storage and hidden sizes that are no multiple of 64.
+// fixed butterfly.  Correct for every descriptor; used for bf16 rows that are no multiple of 64 and fp32 rows that are no multiple of 32.
 template <bool BF16>
 __global__ __launch_bounds__(256) void gate_dense_generic_kernel(const void* __restrict__ x,
                                                                  const void* __restrict__ Wg,
@@ -222,6 +320,25 @@ extern "C" int locmoe_gate_dense(const locmoe_desc* desc, const void* x, const v
     if (!allow_lds((const void*)kern, kDgSmem, lds_allowed)) return LOCMOE_ERR_HIP;                              \
     hipLaunchKernelGGL(kern, grid, dim3(kDgThreads), kDgSmem, s, (const uint16_t*)x, (const uint16_t*)Wg, g, T, \
                        d, E);                                                                                    \
+  }
+    if (nt == 1) LOCMOE_DG(1) else if (nt == 2) LOCMOE_DG(2) else if (nt == 3) LOCMOE_DG(3) else LOCMOE_DG(4)
+#undef LOCMOE_DG
+    return launch_status();
+  }
+  // A tile's step takes about 1.3 us per 32 experts however few its tokens are, one wave per token as much for some 22
+  // experts' 32 features, up to 8 192 tokens at a time.  us, one wave per token / tiles: T = 300, d = 2048, E = 8 29 / 80;
+  // T = 574, d = 768, E = 12 18 / 32;  T = 9 000, d = 128, E = 4 5.7 / 7.5;  T = 60 000, E = 4 21 / 12;  T = 200, d = 5120,
+  // E = 128 1 242 / 696.
+  if (desc->x_dtype == LOCMOE_F32 && d % (kDgRowBytes / 4) == 0 && (E >= 24 || (long long)T * E >= 192000)) {
+    const int passes = ceil_div(E, 128);
+    const int nt = passes > 1 ? 4 : ceil_div(E, 32);
+    const dim3 grid(ceil_div(T, kDgTokens), passes);
+#define LOCMOE_DG(N)                                                                                                   \
+  {                                                                                                                    \
+    static std::atomic<uint64_t> lds_allowed;                                                                          \
+    auto kern = gate_dense_f32_kernel<N>;                                                                              \
+    if (!allow_lds((const void*)kern, kDgSmem, lds_allowed)) return LOCMOE_ERR_HIP;                                    \
+    hipLaunchKernelGGL(kern, grid, dim3(kDgThreads), kDgSmem, s, (const float*)x, (const float*)Wg, g, T, d, E);       \
   }
     if (nt == 1) LOCMOE_DG(1) else if (nt == 2) LOCMOE_DG(2) else if (nt == 3) LOCMOE_DG(3) else LOCMOE_DG(4)
 #undef LOCMOE_DG
