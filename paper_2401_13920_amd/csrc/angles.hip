@@ -8,13 +8,15 @@
 // the results do not depend on the order in which tokens arrive.
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 namespace locmoe {
 namespace {
 
 constexpr int kAngThreads = 1024;        // 16 waves: each block gathers its tokens' counts in LDS first
-constexpr int kAngTokens = 1024;         // tokens per block
+constexpr int kAngMaxTokens = 1024;      // tokens per block at most
 constexpr int kAngLdsBytes = 48 * 1024;  // histograms larger than this are counted in global memory directly
 constexpr float kNoCosine = 2.0f;        // what an expert without tokens reports: no cosine reaches it
 
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(kAngThreads) void angle_kernel(const float* __restr
                                                             int32_t* __restrict__ hist_self,
                                                             int32_t* __restrict__ hist_other,
                                                             int32_t* __restrict__ cmin_image, int T, int E,
-                                                            int shift, int nbins, float scale, int lds_cells) {
+                                                            int shift, int nbins, float scale, int lds_cells, int per_block) {
   extern __shared__ int32_t sm[];  // [E] images of the minima, then two histograms of lds_cells (or none)
   int32_t* s_min = sm;
   int32_t* s_self = sm + E;
@@ -61,9 +63,9 @@ __global__ __launch_bounds__(kAngThreads) void angle_kernel(const float* __restr
   __syncthreads();
   const int j = threadIdx.x % G, grp = threadIdx.x / G;
   const int units = E / V;
-  const int m_end = min(T, (int)(blockIdx.x + 1) * kAngTokens);
+  const int m_end = (int)min((long long)T, (long long)(blockIdx.x + 1) * per_block);
 #pragma unroll 2
-  for (int m = blockIdx.x * kAngTokens + grp; m < m_end; m += kAngThreads / G) {
+  for (int m = blockIdx.x * per_block + grp; m < m_end; m += kAngThreads / G) {
     const float* qr = q + (size_t)m * E;
     float part = 0.f;
     for (int u = j; u < units; u += G) {
@@ -110,11 +112,11 @@ __global__ __launch_bounds__(kAngThreads) void angle_kernel(const float* __restr
 template <int V>
 void launch_angles(int G, dim3 grid, size_t lds, hipStream_t s, const float* g, const float* q, const int32_t* eid,
                    float* c_self, float* c_other, int32_t* hist_self, int32_t* hist_other, int32_t* cmin_image, int T,
-                   int E, int shift, int nbins, float scale, int lds_cells) {
+                   int E, int shift, int nbins, float scale, int lds_cells, int per_block) {
 #define LOCMOE_ANGLES(GG)                                                                                        \
   case GG:                                                                                                       \
     hipLaunchKernelGGL((angle_kernel<GG, V>), grid, dim3(kAngThreads), lds, s, g, q, eid, c_self, c_other,       \
-                       hist_self, hist_other, cmin_image, T, E, shift, nbins, scale, lds_cells);                 \
+                       hist_self, hist_other, cmin_image, T, E, shift, nbins, scale, lds_cells, per_block);      \
     break;
   switch (G) {
     LOCMOE_ANGLES(1) LOCMOE_ANGLES(2) LOCMOE_ANGLES(4) LOCMOE_ANGLES(8) LOCMOE_ANGLES(16) LOCMOE_ANGLES(32)
@@ -126,8 +128,8 @@ void launch_angles(int G, dim3 grid, size_t lds, hipStream_t s, const float* g, 
 // the minima back to floats, and delta_hat = the smallest of them
 __global__ __launch_bounds__(1024) void angle_final_kernel(int32_t* __restrict__ cmin_image, float* __restrict__ stats,
                                                            int E) {
-  __shared__ float red[1024];
-  __shared__ int cnt[1024];
+  __shared__ float red[1024 / kWave];
+  __shared__ int cnt[1024 / kWave];
   float best = kNoCosine;
   int nonempty = 0;
   for (int i = threadIdx.x; i < E; i += 1024) {
@@ -136,17 +138,21 @@ __global__ __launch_bounds__(1024) void angle_final_kernel(int32_t* __restrict__
     best = fminf(best, c);
     nonempty += c < kNoCosine ? 1 : 0;
   }
-  red[threadIdx.x] = best;
-  cnt[threadIdx.x] = nonempty;
-  __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      red[threadIdx.x] = fminf(red[threadIdx.x], red[threadIdx.x + s]);
-      cnt[threadIdx.x] += cnt[threadIdx.x + s];
-    }
-    __syncthreads();
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    best = fminf(best, __shfl_xor(best, o));
+    nonempty += __shfl_xor(nonempty, o);
   }
+  if (threadIdx.x % kWave == 0) {
+    red[threadIdx.x / kWave] = best;
+    cnt[threadIdx.x / kWave] = nonempty;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
+    for (int w = 1; w < 1024 / kWave; ++w) {
+      red[0] = fminf(red[0], red[w]);
+      cnt[0] += cnt[w];
+    }
     stats[0] = red[0];           // delta_hat
     stats[1] = (float)cnt[0];    // experts that received tokens
     stats[2] = 0.f;
@@ -176,14 +182,19 @@ extern "C" int locmoe_angle_stats(const locmoe_desc* desc, const float* g, const
   while (G < 64 && 2 * G <= E / V) G *= 2;
   const int lds_cells = (size_t)(2 * cells + E) * 4 <= (size_t)kAngLdsBytes ? cells : 0;
   const size_t lds = (size_t)(2 * lds_cells + E) * 4;
-  const dim3 grid((unsigned)ceil_div(desc->T, kAngTokens));
+  // tokens per block: a batch of its groups, or more where that leaves two blocks per compute unit (all three kernels, us,
+  // blocks of 1 024 tokens / these: 4 096 tokens of 128 experts 49 / 10, 16 000 51 / 18, 20 000 of 80 21 / 16, 32 768 of 32
+  // 12.9 / 11.2)
+  const int batch = kAngThreads / G;
+  const int per_block = std::min(kAngMaxTokens, ceil_div(ceil_div(desc->T, 2 * cu_count()), batch) * batch);
+  const dim3 grid((unsigned)ceil_div(desc->T, per_block));
   const float scale = sqrtf((float)desc->d / (float)E);
   if (V == 4)
     launch_angles<4>(G, grid, lds, s, g, q, eid, c_self, c_other, hist_self, hist_other, (int32_t*)cmin, desc->T, E,
-                     sh, nbins, scale, lds_cells);
+                     sh, nbins, scale, lds_cells, per_block);
   else
     launch_angles<1>(G, grid, lds, s, g, q, eid, c_self, c_other, hist_self, hist_other, (int32_t*)cmin, desc->T, E,
-                     sh, nbins, scale, lds_cells);
+                     sh, nbins, scale, lds_cells, per_block);
   hipLaunchKernelGGL(angle_final_kernel, dim3(1), dim3(1024), 0, s, (int32_t*)cmin, stats, E);
   return launch_status();
 }
