@@ -12,7 +12,7 @@ namespace locmoe {
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// Dense gate, bf16 storage, d a multiple of 64: 128 tokens x up to 128 experts per work-group, four waves of
+// Dense gate, bf16 storage, d a multiple of 64: 64 or 128 tokens x up to 128 experts per work-group, waves of
 // 32 tokens each, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  E is small, so the kernel is bound by the
 // one pass over x (T d 2 bytes): 2 T d E flops are 64 flops per byte at E = 64, far below the machine's ridge.
 // The weight [E,d] is re-read by every work-group from L2.  Operands go global -> registers -> LDS (16-byte
@@ -28,27 +28,32 @@ constexpr int kDgSmem = 4 * kDgTile;                 // x and W, double buffered
 
 __device__ __forceinline__ int dg_swz(int row, int chunk) { return (chunk ^ ((row >> 1) & 7)) << 4; }
 
-template <int NT>  // 32-expert tiles per pass: experts [e0, e0 + 32 NT)
-__global__ __launch_bounds__(kDgThreads) void gate_dense_mfma_kernel(const uint16_t* __restrict__ x,
+// NT: 32-expert tiles per pass, experts [e0, e0 + 32 NT).  TOK: tokens per work-group, 32 per wave: 64 with up to 64 experts,
+// where twice as many work-groups hide more than the weight's second reading costs (us, 128 tokens / 64: T = 32 768, d = 2048,
+// E = 32 34.1 / 32.0;  T = 8 192, d = 1024, E = 16 7.5 / 6.4;  T = 300, d = 2048, E = 8 11.7 / 9.5;  T = 20 000, d = 1280,
+// E = 80 17.9 / 22.1).
+template <int NT, int TOK>
+__global__ __launch_bounds__(2 * TOK) void gate_dense_mfma_kernel(const uint16_t* __restrict__ x,
                                                                      const uint16_t* __restrict__ Wg,
                                                                      float* __restrict__ g, int T, int d, int E) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int kThreads = 2 * TOK, NW = 8 * 32 * NT / kThreads, kXTile = TOK * kDgRowBytes, kWTile = NT * 32 * kDgRowBytes;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.x * kDgTokens;
+  const int m0 = blockIdx.x * TOK;
   const int e0 = blockIdx.y * 128;
-  // global -> LDS assignment: four x chunks and NT W chunks of 16 bytes per thread and k-step
+  // global -> LDS assignment: four x chunks and NW W chunks of 16 bytes per thread and k-step
   const uint16_t* gx[4];
-  const uint16_t* gw[NT];
-  int lds_x[4], lds_w[NT];
+  const uint16_t* gw[NW];
+  int lds_x[4], lds_w[NW];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int c = tid + i * kDgThreads, row = c >> 3, kc = c & 7;
+    const int c = tid + i * kThreads, row = c >> 3, kc = c & 7;
     gx[i] = x + (size_t)min(m0 + row, T - 1) * d + kc * 8;  // rows past T re-read the last token (never stored)
     lds_x[i] = row * kDgRowBytes + dg_swz(row, kc);
   }
 #pragma unroll
-  for (int i = 0; i < NT; ++i) {
-    const int c = tid + i * kDgThreads, row = c >> 3, kc = c & 7;
+  for (int i = 0; i < NW; ++i) {
+    const int c = tid + i * kThreads, row = c >> 3, kc = c & 7;
     gw[i] = Wg + (size_t)min(e0 + row, E - 1) * d + kc * 8;  // rows past E re-read the last expert (never stored)
     lds_w[i] = row * kDgRowBytes + dg_swz(row, kc);
   }
@@ -65,25 +70,25 @@ __global__ __launch_bounds__(kDgThreads) void gate_dense_mfma_kernel(const uint1
   // (they stay in the last-level cache) 20.7 and 22.5.  With more than 96 experts the loads past the last k-step are left
   // out: T = 4 096, d = 2048, E = 128, the same tokens: 24.2 us, 28.7 with them, 25.7 with one set of registers.  Below
   // that the branch costs more than they do: T = 65 536, d = 4096, E = 64: 132 us, 122 without it.
-  u32x4 rx[2][4], rw[2][NT];
+  u32x4 rx[2][4], rw[2][NW];
   const int KT = d / kDgBK;
   auto load = [&](int set, int kt) {
     const int ko = min(kt, KT - 1) * kDgBK;  // (steps after the last re-read the last: never consumed)
 #pragma unroll
     for (int i = 0; i < 4; ++i) rx[set][i] = *(const u32x4*)(gx[i] + ko);
 #pragma unroll
-    for (int i = 0; i < NT; ++i) rw[set][i] = *(const u32x4*)(gw[i] + ko);
+    for (int i = 0; i < NW; ++i) rw[set][i] = *(const u32x4*)(gw[i] + ko);
   };
   auto store = [&](int set) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) *(u32x4*)(smem + set * kDgTile + lds_x[i]) = rx[set][i];
+    for (int i = 0; i < 4; ++i) *(u32x4*)(smem + set * kXTile + lds_x[i]) = rx[set][i];
 #pragma unroll
-    for (int i = 0; i < NT; ++i) *(u32x4*)(smem + (2 + set) * kDgTile + lds_w[i]) = rw[set][i];
+    for (int i = 0; i < NW; ++i) *(u32x4*)(smem + 2 * kXTile + set * kWTile + lds_w[i]) = rw[set][i];
   };
   auto step = [&](auto par_, int kt) {  // k-step kt, which is in LDS buffer PAR
     constexpr int PAR = decltype(par_)::value;
-    const char* sx = smem + PAR * kDgTile;
-    const char* sw = smem + (2 + PAR) * kDgTile;
+    const char* sx = smem + PAR * kXTile;
+    const char* sw = smem + 2 * kXTile + PAR * kWTile;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int kc = ks * 2 + khalf;
@@ -272,20 +277,23 @@ __global__ void zero_i32_kernel(int32_t* p, int n) {
   if (i < n) p[i] = 0;
 }
 
-constexpr int kHashThreads = 256, kHashPerThread = 8;
+constexpr int kHashThreads = 256, kHashPerThread = 8, kHashOneTokens = 2048;
 
 // eid, w and the per-expert counts.  Counts: LDS histogram per block, one integer atomic per non-empty cell
-// into cnt (integer sums: the result does not depend on the order).
-__global__ __launch_bounds__(kHashThreads) void route_hash_kernel(const int32_t* __restrict__ key, uint32_t offset,
+// into cnt (integer sums: the result does not depend on the order).  ONE: a single block of more threads takes all tokens
+// and writes its counts, which need not be cleared before (one launch: up to 2 048 tokens).
+template <bool ONE>
+__global__ __launch_bounds__(ONE ? 1024 : kHashThreads) void route_hash_kernel(const int32_t* __restrict__ key, uint32_t offset,
                                                                   int32_t* __restrict__ eid, float* __restrict__ w,
                                                                   int32_t* __restrict__ cnt, int T, int E) {
   extern __shared__ int32_t hist[];
-  for (int i = threadIdx.x; i < E; i += kHashThreads) hist[i] = 0;
+  constexpr int kThreads = ONE ? 1024 : kHashThreads, kPer = ONE ? kHashOneTokens / 1024 : kHashPerThread;
+  for (int i = threadIdx.x; i < E; i += kThreads) hist[i] = 0;
   __syncthreads();
-  const int base = blockIdx.x * kHashThreads * kHashPerThread;
+  const int base = blockIdx.x * kThreads * kPer;
 #pragma unroll
-  for (int k = 0; k < kHashPerThread; ++k) {
-    const int m = base + k * kHashThreads + threadIdx.x;
+  for (int k = 0; k < kPer; ++k) {
+    const int m = base + k * kThreads + threadIdx.x;
     if (m < T) {
       const uint32_t kv = key ? (uint32_t)key[m] : (uint32_t)m;
       const int e = (int)(mix32(kv + offset) % (uint32_t)E);
@@ -295,8 +303,9 @@ __global__ __launch_bounds__(kHashThreads) void route_hash_kernel(const int32_t*
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < E; i += kHashThreads)
-    if (hist[i]) atomicAdd(&cnt[i], hist[i]);
+  for (int i = threadIdx.x; i < E; i += kThreads)
+    if (ONE) cnt[i] = hist[i];
+    else if (hist[i]) atomicAdd(&cnt[i], hist[i]);
 }
 
 }  // namespace
@@ -312,14 +321,14 @@ extern "C" int locmoe_gate_dense(const locmoe_desc* desc, const void* x, const v
   if (desc->x_dtype == LOCMOE_BF16 && d % kDgBK == 0) {
     const int passes = ceil_div(E, 128);
     const int nt = passes > 1 ? 4 : ceil_div(E, 32);  // 32-expert tiles per pass
-    const dim3 grid(ceil_div(T, kDgTokens), passes);
 #define LOCMOE_DG(N)                                                                                             \
   {                                                                                                              \
+    constexpr int tok = N <= 2 ? 64 : 128, lds = 2 * (tok + 32 * N) * kDgRowBytes;                               \
     static std::atomic<uint64_t> lds_allowed;                                                                    \
-    auto kern = gate_dense_mfma_kernel<N>;                                                                       \
-    if (!allow_lds((const void*)kern, kDgSmem, lds_allowed)) return LOCMOE_ERR_HIP;                              \
-    hipLaunchKernelGGL(kern, grid, dim3(kDgThreads), kDgSmem, s, (const uint16_t*)x, (const uint16_t*)Wg, g, T, \
-                       d, E);                                                                                    \
+    auto kern = gate_dense_mfma_kernel<N, tok>;                                                                  \
+    if (!allow_lds((const void*)kern, lds, lds_allowed)) return LOCMOE_ERR_HIP;                                  \
+    hipLaunchKernelGGL(kern, dim3(ceil_div(T, tok), passes), dim3(2 * tok), lds, s, (const uint16_t*)x,          \
+                       (const uint16_t*)Wg, g, T, d, E);                                                         \
   }
     if (nt == 1) LOCMOE_DG(1) else if (nt == 2) LOCMOE_DG(2) else if (nt == 3) LOCMOE_DG(3) else LOCMOE_DG(4)
 #undef LOCMOE_DG
@@ -360,10 +369,15 @@ extern "C" int locmoe_route_hash(const locmoe_desc* desc, const int32_t* key, ui
   if (st != LOCMOE_OK) return st;
   hipStream_t s = as_stream(stream);
   const int T = desc->T, E = desc->E;
+  if (T <= kHashOneTokens) {
+    hipLaunchKernelGGL(route_hash_kernel<true>, dim3(1), dim3(1024), (size_t)E * 4, s, key, seed * 0x9E3779B9u, eid, w, cnt,
+                       T, E);
+    return launch_status();
+  }
   hipLaunchKernelGGL(zero_i32_kernel, dim3(ceil_div(E, 256)), dim3(256), 0, s, cnt, E);
   int rc = launch_status();
   if (rc != LOCMOE_OK) return rc;
-  hipLaunchKernelGGL(route_hash_kernel, dim3(ceil_div(T, kHashThreads * kHashPerThread)), dim3(kHashThreads),
+  hipLaunchKernelGGL(route_hash_kernel<false>, dim3(ceil_div(T, kHashThreads * kHashPerThread)), dim3(kHashThreads),
                      (size_t)E * 4, s, key, seed * 0x9E3779B9u, eid, w, cnt, T, E);
   return launch_status();
 }

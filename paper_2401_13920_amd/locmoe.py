@@ -46,11 +46,12 @@ class LocMoEError(RuntimeError):
 
 
 _lib = None
+_raw_stream = None  # torch's address of a device's current stream, if it has such a call
 
 
 def lib() -> C.CDLL:
     """Loads the shared library once.  Fails loudly when it has not been built."""
-    global _lib
+    global _lib, _raw_stream
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -59,7 +60,7 @@ def lib() -> C.CDLL:
     # PyTorch ships its own HIP runtime; it has to be resident before this library is mapped, so that both
     # resolve to one runtime (device pointers and streams come from torch).  Loaded the other way round, the
     # library binds to the system runtime and every launch on a torch stream fails.
-    import torch  # noqa: F401
+    import torch
     L = C.CDLL(LIB_PATH)
     P, I32, SZ, DBL = C.c_void_p, C.c_int32, C.c_size_t, C.c_double
     D = C.POINTER(locmoe_desc)
@@ -101,6 +102,7 @@ def lib() -> C.CDLL:
     for n in EXPORTS:
         if n not in ("locmoe_status_string", "locmoe_workspace_bytes", "locmoe_packed_weights_bytes"):
             getattr(L, n).restype = C.c_int
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _lib = L
     return L
 
@@ -128,12 +130,19 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
+def _current_stream() -> int:
+    """torch.cuda.current_stream().cuda_stream; without making a Stream object where torch says the address itself."""
+    import torch
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
 def _stream(stream) -> int | None:
     if stream.__class__ is int:
         return stream
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
