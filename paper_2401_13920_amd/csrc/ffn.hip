@@ -610,8 +610,10 @@ double tiles_time(int E, int rows, int Kdim, int Ndim, bool persistent, double* 
 // 16-byte chunk p of the block holds row p/4, k-chunk (p%4) ^ (row/2 mod 4).  A copy, bound by memory: a work-group
 // makes two blocks at a time, so that a row's 128 bytes (one line) are read together, and has eight loads per thread
 // in flight.
-// At 134 MB per weight (d = 1024, h = 4096, E = 16): 46 us; one block per work-group, 64 bytes of a row at a time and
-// one load per thread, which this replaces: 57 us.
+// The packed weights are not read again before the whole of them is written, so the stores are non-temporal: they leave
+// the weights, which the transposing pass reads next, in the caches.  Both weights of d = 1024, h = 4096, E = 16 (134 MB
+// each): 79 us, 6.8 TB/s read and written (104 us with plain stores); d = 2048, h = 8192, E = 32: 816 us (838); d = 4096,
+// h = 16384, E = 64: 6 675 us (6 830).  Non-temporal loads too: 95, 796 and 6 675 us, not taken.
 __global__ __launch_bounds__(256) void pack_weights_kernel(const uint4* __restrict__ W, uint4* __restrict__ Wp,
                                                            int Ndim, int Kdim) {
   const int KP = Kdim / (2 * kDmaBK), NT = Ndim / kBN;
@@ -626,7 +628,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uint4* __restri
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = src[(long long)i * 32 * (Kdim / 8)];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) dst[i * 128] = v[i];  // (32 rows on: the same swizzle)
+  for (int i = 0; i < 8; ++i) nt_store16(v[i], dst + i * 128);  // (32 rows on: the same swizzle)
 }
 
 // The packed layout of W^T straight from the row-major W [Rk rows, Cn columns] (the data gradients contract
@@ -634,6 +636,8 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const uint4* __restri
 // 32 x 256 piece W[kt*32 ..][nt*256 ..].  The piece goes through LDS (512-byte rows, chunk index XORed with a
 // 3-bit function of the row) and comes back through gfx950's transposing LDS read: 16 lanes receive the 8
 // k-values of 16 consecutive columns, which is one 16-byte chunk of the packed block per lane.
+// Bound by memory as above, non-temporal stores for the same reason; the three sizes above: 78, 738 and 6 770 us (with
+// plain stores 95, 806 and 7 060).  Two blocks per work-group, eight loads per thread: 78, 756 and 6 860 us, not taken.
 typedef __attribute__((ext_vector_type(4))) short pk_s16x4;
 __global__ __launch_bounds__(256) void transpose_pack_kernel(const uint16_t* __restrict__ W, uint4* __restrict__ Xp,
                                                              int Rk, int Cn) {
@@ -671,7 +675,7 @@ __global__ __launch_bounds__(256) void transpose_pack_kernel(const uint16_t* __r
     v.y = (uint32_t)(uint16_t)lo[2] | ((uint32_t)(uint16_t)lo[3] << 16);
     v.z = (uint32_t)(uint16_t)hi[0] | ((uint32_t)(uint16_t)hi[1] << 16);
     v.w = (uint32_t)(uint16_t)hi[2] | ((uint32_t)(uint16_t)hi[3] << 16);
-    dst[n * 4 + (g ^ ((n >> 1) & 3))] = v;
+    nt_store16(v, dst + n * 4 + (g ^ ((n >> 1) & 3)));
   }
 }
 
