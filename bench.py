@@ -24,7 +24,7 @@ if ROOT not in sys.path:
 # needs for a plain 1 GiB copy in the same run; WRITE_SIZE needs none.  The summary records a hash of the kernel
 # sources it was taken with: when the sources have changed since, `traffic` is reported as null.
 PROFILE = os.path.join(ROOT, "profiles", "bench_config4_kernels_and_hbm_counters.txt")
-KERNEL_SOURCES = ("ffn.hip", "common.h", "gelu_coef.h")
+KERNEL_SOURCES = ("ffn.hip", "ffn_epilogue.h", "common.h", "gelu_coef.h")
 FETCH_FACTOR, WRITE_FACTOR = 2.0, 1.0
 
 
@@ -360,8 +360,9 @@ def main() -> int:
     dom = "ffn_in" if ms["ffn_in"] >= ms["ffn_out"] else "ffn_out"
     achieved = flops / (ms[dom] * 1e-3) / 1e12
     kname = "ffn_gemm_any"
-    if desc.w_packed:  # (at most 64 rows per expert: either packed kernel, by shape)
-        kname = "ffn_gemm_dma_persistent" if min(C, c.T) > 64 else "ffn_gemm_few or ffn_gemm_dma_persistent"
+    if desc.w_packed:  # (by shape: few rows, or too few 256-row tiles to fill the chip)
+        few = min(C, c.T) <= 192 or c.E * -(-min(C, c.T) // 256) * (min(c.d, c.h) // 256) < 1024
+        kname = "ffn_gemm_dma_persistent, ffn_gemm_any or ffn_gemm_few" if few else "ffn_gemm_dma_persistent"
     traffic, traffic_note = None, "the tracked counters are for the config-4 bench workload with packed weights"
     if desc.w_packed and c.cfg == 4 and not args.capacity:
         kib, traffic_note = profiled_traffic()

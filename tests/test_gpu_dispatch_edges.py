@@ -155,3 +155,19 @@ def test_angle_statistics_over_blocks(T, E):
         assert torch.equal(h.flatten().long(), torch.bincount(cell, minlength=E * 64))
     ref = torch.full((E,), 2.0, **f32).scatter_reduce(0, e, c_self, "amin")
     assert torch.equal(cmin, ref) and stats[0] == ref.min() and stats[1] == (ref < 2).sum()
+
+
+# hash routing in one launch, up to 2 048 tokens, and with its counts cleared by a kernel of their own
+@pytest.mark.parametrize("E", [1, 7, 1000])
+@pytest.mark.parametrize("T", [1, 1023, 1025, 2048, 2049])
+def test_hash_routing_in_one_and_two_launches(T, E):
+    import torch
+    from paper_2401_13920_amd import locmoe as lm
+    keys = np.random.default_rng(T + E).integers(-2 ** 31, 2 ** 31, T).astype(np.int32)
+    eid, cnt = (torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (T, E))
+    w = torch.full((T,), float("nan"), device="cuda")
+    print(f"[hash] T={T} E={E}", flush=True)
+    lm.locmoe_route_hash(lm.make_desc(T, 8 * E, E, 1, 8, 1, "bf16"), torch.from_numpy(keys).cuda(), 11, eid, w, cnt)
+    torch.cuda.synchronize()
+    for got, ref in zip((eid, w, cnt), orc.route_hash(keys, E, 11)):
+        assert np.array_equal(got.cpu().numpy(), ref)
