@@ -7,6 +7,9 @@
 // ring of stages that fills half of a compute unit's LDS: two work-groups per compute unit (one's epilogue and barriers
 // run beside the other's MFMAs).  Slot functions: 64-byte weight rows (packed, or beside fp32) chunk ^ (row/2 mod 4),
 // 128-byte rows chunk ^ (row/2 mod 8); a packed block's 16-column groups are that image already and are copied as they are.
+// An fp32 row's even chunks come ahead of its odd ones: a lane's 8 values are two chunks side by side, and in plain order
+// conflicts took 0.40 of the LDS-active cycles (now 0; d = 1024, h = 4096, E = 16, 3 330 rows, first GEMM 66.7 -> 65.9 us, with
+// Z stored 69.2 -> 68.1: the copies, not the reads, are what the steps wait for).
 // Copies past K are clamped into the row and overwritten with zeros on both sides by the lanes that fetched them (an
 // infinity times zero would be a NaN).
 //
@@ -60,12 +63,14 @@ struct AnyShape : AnyK<A_F32> {
   static_assert(kStages >= 2, "one stage is filled while another is read");
 };
 // Byte offset, inside a row of RB bytes (a k-step), of the 16-byte chunk that this lane of a 1 KiB copy fetches; the
-// copy's block of 1024 / RB rows is number wave + 4 i of the operand
-template <int RB>
+// copy's block of 1024 / RB rows is number wave + 4 i of the operand.  PAIRS (fp32 rows, whose fragments are two chunks
+// side by side): the even chunks of a row come first, so that a read meets the banks as a read of a bf16 row does.
+template <int RB, bool PAIRS>
 __device__ __forceinline__ uint32_t any_chunk(int wave, int lane) {
   constexpr int L = RB / 16;
   const int row = (RB == 128 ? (wave & 1) * 8 : 0) + lane / L;  // modulo 16
-  return (uint32_t)(((lane & (L - 1)) ^ ((row >> 1) & (L - 1))) << 4);
+  const int c = (lane & (L - 1)) ^ ((row >> 1) & (L - 1));
+  return (uint32_t)((PAIRS ? (c & (L / 2 - 1)) * 2 + c / (L / 2) : c) << 4);
 }
 
 // vmcnt(n C) for a run-time n <= MAX
@@ -116,7 +121,7 @@ __device__ __forceinline__ void any_tile(const char* __restrict__ A, const char*
       rowW[i] = (off_t)min((wave + 4 * i) * kWRows + lane / (64 / kWRows), Ndim - n0 - 1) * ldW;
     }
   }
-  const uint32_t chA = any_chunk<S::kARow>(wave, lane), chW = any_chunk<S::kWRow>(wave, lane);
+  const uint32_t chA = any_chunk<S::kARow, A_F32>(wave, lane), chW = any_chunk<S::kWRow, false>(wave, lane);
   const int KT = (Kdim - 1) / S::kBK + 1;
   auto copy = [](const char* base, off_t off, uint32_t lds) {
     if constexpr (FAR) dma_1k_far(base + off, lds);
@@ -141,7 +146,7 @@ __device__ __forceinline__ void any_tile(const char* __restrict__ A, const char*
     const int ra = wm * 16 + l16, rw = wn * 16 + l16;  // (subtiles are 32 rows apart: the same swizzle)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-      off_a[i] = ra * S::kARow + (((A_F32 ? 2 * kq + i : 4 * i + kq) ^ ((ra >> 1) & 7)) << 4);
+      off_a[i] = ra * S::kARow + (((4 * i + kq) ^ ((ra >> 1) & 7)) << 4);
 #pragma unroll
     for (int i = 0; i < kSub; ++i) {
       if (PACKED) off_w[i] = S::kABytes + i * BN * 64 + rw * 64 + ((kq ^ ((rw >> 1) & 3)) << 4);
