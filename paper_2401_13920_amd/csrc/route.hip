@@ -282,7 +282,9 @@ __device__ __forceinline__ void route_scalars(FinShared& sh, int32_t c, double p
 // one round trip to partials that other XCDs wrote, LDS, a few double-precision logarithms).  U: rows that a thread adds in
 // a round; the loads are unconditional (rows past the end re-read the thread's first row and are not added) and all of a
 // round's are issued before the first is used, so U is no larger than the partials need: with 32 rows always, 64 partials
-// took 64 loads in each of 1024 threads (T = 8 192, E = 16: 11.4 us).
+// took 64 loads in each of 1024 threads (T = 8 192, E = 16: 11.4 us).  With more than 16 rows a thread (E = 64 from 32 769
+// tokens on) two rounds of 16 were two round trips to memory: both launches at T = 65 536, E = 64 21.4 us, one round of 32
+// 20.8; E = 128 29.5 / 28.4; E = 300 72.2 / 69.5.
 template <int U>
 __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
     void* ws, const int32_t* __restrict__ e2n, int has_home, int32_t* __restrict__ cnt,
@@ -301,29 +303,48 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
   double ps = 0.0;
   int local = 0;
   int32_t hvv[UH];
-  for (int b0 = 0; b0 < nb; b0 += U * R) {
-    int2 v[U];
-    if (cols) {
+  if (hcols) {  // the home counts go with the first round (looped below if they are many)
+    hvv[0] = r.home[(size_t)rn * N + nu];
+    if (Rn < nb) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int b = b0 + rb + u * R;
-        v[u] = r.cell[(unsigned)((b < nb ? b : rb) * E + e)];
+      for (int u = 1; u < UH; ++u) {
+        const int b = rn + u * Rn;
+        hvv[u] = r.home[(size_t)(b < nb ? b : rn) * N + nu];
       }
     }
-    if (hcols && b0 == 0) {  // the home counts go with the first round (looped below if they are many)
-      hvv[0] = r.home[(size_t)rn * N + nu];
-      if (Rn < nb) {
+  }
+  if (has_home && tid < nb) local = r.local[tid];  // (nb <= 512)
+  int b0 = 0;
+  if constexpr (U == 32) {  // the first half of the rows is there for certain: one offset per thread, scalar distances
+    for (; b0 + U / 2 * R < nb; b0 += U * R) {
+      int2 v[U];
+      if (cols) {
 #pragma unroll
-        for (int u = 1; u < UH; ++u) {
-          const int b = rn + u * Rn;
-          hvv[u] = r.home[(size_t)(b < nb ? b : rn) * N + nu];
+        for (int u = 0; u < U; ++u) {
+          const int b = b0 + rb + u * R;
+          if (u < U / 2) v[u] = (r.cell + (size_t)(b0 + u * R) * E)[(unsigned)(rb * E + e)];
+          else v[u] = r.cell[(unsigned)((b < nb ? b : rb) * E + e)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool live = u < U / 2 || b0 + rb + u * R < nb;
+          ci += live ? v[u].x : 0;
+          ps += live ? (double)__int_as_float(v[u].y) : 0.0;
         }
       }
     }
-    if (has_home && b0 == 0 && tid < nb) local = r.local[tid];  // (nb <= 512)
+  }
+  constexpr int UT = U == 32 ? 16 : U;
+  for (; b0 < nb; b0 += UT * R) {
+    int2 v[UT];
     if (cols) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < UT; ++u) {
+        const int b = b0 + rb + u * R;
+        v[u] = r.cell[(unsigned)((b < nb ? b : rb) * E + e)];
+      }
+#pragma unroll
+      for (int u = 0; u < UT; ++u) {
         const bool live = b0 + rb + u * R < nb;
         ci += live ? v[u].x : 0;
         ps += live ? (double)__int_as_float(v[u].y) : 0.0;
@@ -449,7 +470,7 @@ extern "C" int locmoe_route(const locmoe_desc* desc, const float* g, const float
   const int rounds = ceil_div(nb, kFinThreads / E);  // rows of partials per thread
   auto fin = rounds <= 1 ? route_finalize_kernel<1> : rounds <= 2 ? route_finalize_kernel<2>
            : rounds <= 4 ? route_finalize_kernel<4> : rounds <= 8 ? route_finalize_kernel<8>
-           : route_finalize_kernel<16>;
+           : rounds <= 16 ? route_finalize_kernel<16> : route_finalize_kernel<32>;
   hipLaunchKernelGGL(fin, dim3(1), dim3(kFinThreads), 0, s, ws, e2n, home ? 1 : 0, cnt, Psum, stats, nb, desc->T, E,
                      desc->N, desc->alpha, desc->mu);
   return launch_status();
