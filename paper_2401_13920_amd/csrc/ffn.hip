@@ -679,19 +679,12 @@ __global__ __launch_bounds__(256) void transpose_pack_kernel(const uint16_t* __r
   }
 }
 
-template <int EPI>
-int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
-               int rows_max, int T, int Kdim, int Ndim, unsigned int* queue, hipStream_t st) {
-  const int MT = ceil_div(rows_max, kBM), NT = Ndim / kBN;
-  const long long total = (long long)E * MT * NT;
-  if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+// Which kernel takes a GEMM with packed weights
+enum class PackedKernel { kFew, kAny, kPersistent, kTile };
+PackedKernel pick_packed(int E, int rows_max, int T, int Kdim, int Ndim, bool keeps_z) {
   const bool persistent = E % 8 == 0 && E <= 512;
   const long long waves = (long long)E * (Ndim / kFewCols);
-  if (rows_max <= kFewRows && waves >= 2 * cu_count() && waves <= 0x7FFFFFFFLL) {
-    hipLaunchKernelGGL(ffn_gemm_few<EPI>, dim3((unsigned)waves), dim3(64), 0, st, (const uint16_t*)A, (const uint16_t*)Wp,
-                       (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
-    return launch_status();
-  }
+  if (rows_max <= kFewRows && waves >= 2 * cu_count() && waves <= 0x7FFFFFFFLL) return PackedKernel::kFew;
   // Few rows per segment, few experts, narrow outputs: tiles of 256 columns, which cost a prologue of some 10 us, leave
   // compute units idle or empty, and the smaller tiles of ffn_any.hip are faster (us, tiles here / there):
   //   E = 16, d = 1024, h = 4096, both GEMMs: 96 rows 44 + 65 / 29 + 30;  255 rows 53 + 70 / 53 + 60;  640 uneven 97 + 86 / 83 + 74
@@ -704,10 +697,26 @@ int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t*
   const int rows = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
   double turns = 0.0;
   const double here = tiles_time(E, rows, Kdim, Ndim, persistent, &turns);
-  if (any_gemm_time(E, rows, Kdim, Ndim) < (E <= 16 && turns <= 2.0 && EPI <= kEpiGelu ? 1.0 : 0.9) * here)
+  if (any_gemm_time(E, rows, Kdim, Ndim) < (E <= 16 && turns <= 2.0 && !keeps_z ? 1.0 : 0.9) * here) return PackedKernel::kAny;
+  return persistent ? PackedKernel::kPersistent : PackedKernel::kTile;
+}
+
+template <int EPI>
+int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t* seg_off, const int32_t* buf_expert, int E,
+               int rows_max, int T, int Kdim, int Ndim, unsigned int* queue, hipStream_t st) {
+  const int MT = ceil_div(rows_max, kBM), NT = Ndim / kBN;
+  const long long total = (long long)E * MT * NT;
+  if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
+  const PackedKernel pick = pick_packed(E, rows_max, T, Kdim, Ndim, EPI > kEpiGelu);
+  if (pick == PackedKernel::kFew) {
+    hipLaunchKernelGGL(ffn_gemm_few<EPI>, dim3((unsigned)(E * (Ndim / kFewCols))), dim3(64), 0, st, (const uint16_t*)A,
+                       (const uint16_t*)Wp, (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
+    return launch_status();
+  }
+  if (pick == PackedKernel::kAny)
     return any_gemm<false, true, EPI, false>(A, Wp, C, aux, seg_off, buf_expert, E, rows_max, T, Kdim, Ndim, st);
   static std::atomic<uint64_t> lds_allowed[2];  // per kernel of this instantiation: devices whose LDS limit is raised
-  if (persistent) {
+  if (pick == PackedKernel::kPersistent) {
     auto kern = ffn_gemm_dma_persistent<EPI>;
     if (!allow_lds((const void*)kern, kDmaSmem, lds_allowed[0])) return LOCMOE_ERR_HIP;
     // one work-group per compute unit (160 KiB of LDS each), a multiple of 8 so that every XCD gets as many
@@ -845,6 +854,26 @@ int ffn_dgrad(const locmoe_desc* desc, const void* dout, const void* Z, const in
 }  // namespace locmoe
 
 using namespace locmoe;
+
+extern "C" const char* locmoe_internal_ffn_kernel(const locmoe_desc* desc, int second, int keeps_z) {
+  if (check_desc(desc) != LOCMOE_OK || (desc->w_packed && (desc->x_dtype != LOCMOE_BF16 || !packable(desc)))) return "";
+  const int rows_max = std::min(desc->C, desc->T), K = second ? desc->h : desc->d, N = second ? desc->d : desc->h;
+  if (desc->w_packed) {
+    switch (pick_packed(desc->E, rows_max, desc->T, K, N, keeps_z && !second)) {
+      case PackedKernel::kFew: return "ffn_gemm_few";
+      case PackedKernel::kPersistent: return "ffn_gemm_dma_persistent";
+      case PackedKernel::kTile: return "ffn_gemm_dma";
+      case PackedKernel::kAny: break;
+    }
+  }
+  const AnyTiles t = any_tiles(desc->x_dtype == LOCMOE_F32 && !second, desc->w_packed, desc->E, rows_max, desc->T, K, N);
+  if (t.far) return t.bm == 128 ? "ffn_gemm_any<128, 128, dealt, far>" : "ffn_gemm_any<192, 128, far>";
+  if (t.bn == 160) return "ffn_gemm_any<160, 160>";
+  if (t.bn == 32) return "ffn_gemm_any<128, 32>";
+  if (t.bn == 64) return t.dealt ? "ffn_gemm_any<128, 64, dealt>" : "ffn_gemm_any<128, 64>";
+  if (t.bm == 128) return "ffn_gemm_any<128, 128, dealt>";
+  return t.dealt ? "ffn_gemm_any<192, 128, dealt>" : "ffn_gemm_any<192, 128>";
+}
 
 // ---- without a workspace: stateless, fixed tile assignment ---------------------------------------------------
 extern "C" int locmoe_expert_ffn_in(const locmoe_desc* desc, const void* send, const int32_t* seg_off,

@@ -374,23 +374,41 @@ double any_time(int BM, int BN, int E, int rows, int Kdim, int Ndim) {
   return soft_max(t, 2.5 + (double)E * Ndim * Kdim * 2 / 5e6);
 }
 
-// the tile shape of a GEMM (index into the switch of any_gemm) and its expected time
-int any_pick(int E, int rows, int Kdim, int Ndim, double* us) {
+// the tile shape of a GEMM with the shortest expected time, and that time
+AnyTiles any_fastest(int E, int rows, int Kdim, int Ndim, double* us) {
   static constexpr int shape[4][2] = {{192, 128}, {160, 160}, {128, 64}, {128, 32}};
   int best = 0;
   for (int i = 0; i < 4; ++i) {
     const double t = any_time(shape[i][0], shape[i][1], E, rows, Kdim, Ndim);
     if (i == 0 || t < *us) { *us = t; best = i; }
   }
-  return best;
+  return {shape[best][0], shape[best][1], false, false};
 }
 
 }  // namespace
 
 double any_gemm_time(int E, int rows, int Kdim, int Ndim) {
   double us = 0.0;
-  any_pick(E, rows, Kdim, Ndim, &us);
+  any_fastest(E, rows, Kdim, Ndim, &us);
   return us;
+}
+
+AnyTiles any_tiles(bool a_f32, bool packed, int E, int rows_max, int T, int Kdim, int Ndim) {
+  const int rows = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
+  if (a_f32) {
+    if ((long long)Kdim * 4 * 128 > 0xFFFFFFFFLL) return {128, 128, true, true};
+    // 128 columns per tile, or 64 where that leaves some of the chip's work-group slots (two per compute unit) empty
+    const bool wide = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows, 128) >= 2 * cu_count();
+    return {128, wide ? 128 : 64, true, false};
+  }
+  // (packed weights have shorter rows; the weight rows' offsets are no larger)
+  if (!packed && (long long)Kdim * 2 * 192 > 0xFFFFFFFFLL) return {192, 128, false, true};
+  double us;
+  AnyTiles t = any_fastest(E, rows, Kdim, Ndim, &us);
+  // Weight tiles dealt to the XCDs where eight times the activations are fewer bytes than the weights: first GEMM of
+  // d = 1600, h = 6400, E = 40, 157 rows: 192 us, 199 to 204 with runs (second GEMM: 220 and 216, with the other tile 195)
+  t.dealt = !packed && t.bm == 192 && 8LL * rows < Ndim;
+  return t;
 }
 
 template <bool A_F32, bool PACKED, int EPI, bool OUT_F32>
@@ -399,30 +417,23 @@ int any_gemm(const void* A, const void* W, void* C, void* aux, const int32_t* se
   // (a limit of the interface, see the header; the grid has none that buffers of a card reach)
   if (!PACKED && (A_F32 || Kdim % 64 || Ndim % 256) && (long long)E * ceil_div(rows_max, 64) > 65535)
     return LOCMOE_ERR_SHAPE;
-  const int rows = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
+  const AnyTiles t = any_tiles(A_F32, PACKED, E, rows_max, T, Kdim, Ndim);
 #define LOCMOE_ANY(BM, BN, DEALT, FAR)                                                                                    \
   return launch_any<A_F32, PACKED, EPI, OUT_F32, AnyTile<BM, BN>, DEALT, FAR>(A, W, C, aux, seg_off, buf_expert, E,        \
                                                                               rows_max, T, Kdim, Ndim, st)
   if constexpr (A_F32) {
-    if ((long long)Kdim * 4 * 128 > 0xFFFFFFFFLL) LOCMOE_ANY(128, 128, true, true);
-    // 128 columns per tile, or 64 where that leaves some of the chip's work-group slots (two per compute unit) empty
-    if ((long long)E * ceil_div(Ndim, 128) * ceil_div(rows, 128) >= 2 * cu_count()) LOCMOE_ANY(128, 128, true, false);
+    if (t.far) LOCMOE_ANY(128, 128, true, true);
+    if (t.bn == 128) LOCMOE_ANY(128, 128, true, false);
     LOCMOE_ANY(128, 64, true, false);
   } else {
-    if constexpr (!PACKED) {  // (packed weights have shorter rows; the weight rows' offsets are no larger)
-      if ((long long)Kdim * 2 * 192 > 0xFFFFFFFFLL) LOCMOE_ANY(192, 128, false, true);
-    }
-    double us;
-    const int pick = any_pick(E, rows, Kdim, Ndim, &us);
-    // Weight tiles dealt to the XCDs where eight times the activations are fewer bytes than the weights: first GEMM of
-    // d = 1600, h = 6400, E = 40, 157 rows: 192 us, 199 to 204 with runs (second GEMM: 220 and 216, with the other tile 195)
     if constexpr (!PACKED) {
-      if (pick == 0 && 8LL * rows < Ndim) LOCMOE_ANY(192, 128, true, false);
+      if (t.far) LOCMOE_ANY(192, 128, false, true);
+      if (t.dealt) LOCMOE_ANY(192, 128, true, false);
     }
-    switch (pick) {
-      case 1: LOCMOE_ANY(160, 160, false, false);
-      case 2: LOCMOE_ANY(128, 64, false, false);
-      case 3: LOCMOE_ANY(128, 32, false, false);
+    switch (t.bn) {
+      case 160: LOCMOE_ANY(160, 160, false, false);
+      case 64: LOCMOE_ANY(128, 64, false, false);
+      case 32: LOCMOE_ANY(128, 32, false, false);
       default: LOCMOE_ANY(192, 128, false, false);
     }
   }

@@ -102,6 +102,8 @@ def lib() -> C.CDLL:
     for n in EXPORTS:
         if n not in ("locmoe_status_string", "locmoe_workspace_bytes", "locmoe_packed_weights_bytes"):
             getattr(L, n).restype = C.c_int
+    L.locmoe_internal_ffn_kernel.restype = C.c_char_p
+    L.locmoe_internal_ffn_kernel.argtypes = [D, C.c_int, C.c_int]
     _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _lib = L
     return L
@@ -260,6 +262,12 @@ def locmoe_expert_ffn_dgrad_ws(desc, dout, Z, seg_off, buf_expert, W_out_t, W_in
     _check(lib().locmoe_expert_ffn_dgrad_ws(C.byref(desc), _ptr(dout), _ptr(Z), _ptr(seg_off), _ptr(buf_expert),
                                             _ptr(W_out_t), _ptr(W_in_t), _ptr(dZ), _ptr(dsend), _ptr(ws), ws_bytes,
                                             _stream(stream)))
+
+
+def ffn_kernel(desc: locmoe_desc, second: bool = False, keeps_z: bool = False) -> str:
+    """The kernel that the library takes for the first or second GEMM of desc's FFN (`keeps_z`: of the forms that store or
+    read Z); not part of the interface."""
+    return lib().locmoe_internal_ffn_kernel(C.byref(desc), int(second), int(keeps_z)).decode()
 
 
 def locmoe_packed_weights_bytes(desc: locmoe_desc) -> int:
