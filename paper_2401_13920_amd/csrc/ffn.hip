@@ -12,7 +12,7 @@
 //                            by locmoe_pack_weights into the LDS image of each k-step; four waves with the
 //                            accumulators in the accumulation registers; one work-group per compute unit
 //                            works through a queue of tiles (expert counts that are multiples of 8, up to 512)
-//   ffn_gemm_few             packed weights and at most 16 rows per segment: weight fragments straight to registers
+//   ffn_gemm_few             packed weights and at most 32 rows per segment: weight fragments straight to registers
 //   ffn_gemm_dma             the same pipeline with one tile per work-group (other expert counts)
 //
 // The weight rows feed the MFMA's A operand and the activation rows its B operand, i.e. the
@@ -528,21 +528,17 @@ __global__ __launch_bounds__(kDmaThreads) void ffn_gemm_dma_persistent(const uin
 }
 
 // ---------------------------------------------------------------------------------------------
-// At most 16 rows per segment (by capacity or token count), packed weights: the weights are read once
+// At most 32 rows per segment (by capacity or token count), packed weights: the weights are read once
 // for a handful of rows, so this is a stream of weights that has to keep the memory busy.  A work-group is one wave
-// and takes 64 columns of one segment, all of its rows and all of K.  Weight fragments come straight from memory
-// into registers: 16 columns of a packed block are one contiguous KiB per load, and eight k-steps (32 KiB per wave)
-// are always in flight; activation fragments come from L2.  No barrier,
-// no LDS, and four times as many work-groups as 256-column tiles.
+// and takes 64 columns of one segment, all of its rows (one or two 16-row subtiles) and all of K.  Weight fragments come
+// straight from memory into registers: 16 columns of a packed block are one contiguous KiB per load, and eight k-steps
+// (32 KiB per wave) are always in flight; activation fragments come from L2.  No barrier, no LDS, and four times as many
+// work-groups as 256-column tiles.
 // Every output element is one chain of MFMAs over K in ascending order, as in the tile kernels: same bits.
-// With fewer than two waves per compute unit, and with more rows, the smaller tiles of ffn_any.hip are faster; us, here /
-// there: E = 40, d = 2560, h = 10240, even in 0 .. 4 rows 231 + 254 / 259 + 341;  E = 24, d = 3072, h = 12288, 9 rows
-// 312 + 395 / 332 + 428;  E = 16, d = 1024, h = 4096, 16 rows 26 + 28 / 26 + 26 (second GEMM: 256 waves);  two 16-row
-// subtiles: E = 16, d = 2560, h = 10240, 32 rows 176 + 172 / 151 + 146;  E = 32, d = 1280, h = 5120, 20 rows 82 + 83 / 77 + 76.
 // ---------------------------------------------------------------------------------------------
-constexpr int kFewRows = 16, kFewCols = 64, kFewDepth = 8;  // (k-steps in flight)
+constexpr int kFewRows = 32, kFewCols = 64, kFewDepth = 8;  // (k-steps in flight)
 
-template <int EPI>
+template <int NJ, int EPI>
 __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict__ A, const uint16_t* __restrict__ Wp,
                                                       uint16_t* __restrict__ Cout, uint16_t* aux,
                                                       const int32_t* __restrict__ seg_off,
@@ -554,21 +550,29 @@ __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict
   const int steps = Kdim / kDmaBK;  // a multiple of 8 (Kdim is one of 256), hence of D
   const char* pw = (const char*)Wp + ((size_t)buf_expert[r] * Ndim + (size_t)(cg >> 2) * kBN) * Kdim * 2 +
                    (cg & 3) * (kFewCols * 64) + l16 * 64 + ((kq ^ ((l16 >> 1) & 3)) << 4);
-  for (int m0 = 0; m0 < rows; m0 += kFewRows) {  // (once, unless a segment holds more rows than the descriptor says)
-    // (rows past the segment's end repeat the last one: not stored)
-    const uint16_t* pa = A + ((size_t)seg0 + min(m0 + l16, rows - 1)) * Kdim + kq * 8;
-    f32x4 acc[4];
+  for (int m0 = 0; m0 < rows; m0 += 16 * NJ) {  // (once, unless a segment holds more rows than the descriptor says)
+    const uint16_t* pa[NJ];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bf16x8 w[D][4], x[D];
+    for (int j = 0; j < NJ; ++j)  // rows past the segment's end repeat the last one (not stored)
+      pa[j] = A + ((size_t)seg0 + min(m0 + 16 * j + l16, rows - 1)) * Kdim + kq * 8;
+    f32x4 acc[4][NJ];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < NJ; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 w[D][4], x[D][NJ];
     auto load = [&](int u, int s) {
 #pragma unroll
       for (int ni = 0; ni < 4; ++ni) w[u][ni] = *(const bf16x8*)(pw + (size_t)s * kPackBlock + ni * 1024);
-      x[u] = *(const bf16x8*)(pa + (size_t)s * kDmaBK);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) x[u][j] = *(const bf16x8*)(pa[j] + (size_t)s * kDmaBK);
     };
     auto mul = [&](int u) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni) acc[ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u], acc[ni], 0, 0, 0);
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni)
+          acc[ni][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u][ni], x[u][j], acc[ni][j], 0, 0, 0);
     };
 #pragma unroll
     for (int u = 0; u < D; ++u) load(u, u);
@@ -582,11 +586,15 @@ __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict
     }
 #pragma unroll
     for (int u = 0; u < D; ++u) mul(u);
-    if (m0 + l16 < rows) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni)
-        store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m0 + l16, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][0],
-                               acc[ni][1], acc[ni][2], acc[ni][3]);
+    for (int j = 0; j < NJ; ++j) {
+      const int m = m0 + 16 * j + l16;
+      if (m < rows) {
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni)
+          store_quad<EPI, false>(Cout, aux, (size_t)seg0 + m, Ndim, cg * kFewCols + 16 * ni + kq * 4, acc[ni][j][0],
+                                 acc[ni][j][1], acc[ni][j][2], acc[ni][j][3]);
+      }
     }
   }
 }
@@ -684,12 +692,24 @@ enum class PackedKernel { kFew, kAny, kPersistent, kTile };
 PackedKernel pick_packed(int E, int rows_max, int T, int Kdim, int Ndim, bool keeps_z) {
   const bool persistent = E % 8 == 0 && E <= 512;
   const long long waves = (long long)E * (Ndim / kFewCols);
-  if (rows_max <= kFewRows && waves >= 2 * cu_count() && waves <= 0x7FFFFFFFLL) return PackedKernel::kFew;
-  // Few rows per segment, few experts, narrow outputs: tiles of 256 columns, which cost a prologue of some 10 us, leave
+  // Up to 64 rows the weights are what is moved, and the tiles of 256 columns never are the fastest.  ffn_gemm_few where its
+  // waves fill the chip: from two waves per compute unit on with up to 16 rows, from four with up to 32; ffn_gemm_any
+  // otherwise.  us, few / any / 256-column tiles, with evenly spread tokens; with 60 % of them on one expert:
+  //   up to 16 rows: E = 64, d = 1024, h = 4096, T / E = 11, first GEMM (16 waves per unit) 97 / 100 / 115;  94 / 99 / 112
+  //   up to 32 rows: E = 32, d = 2048, h = 8192, 22 rows, first (16 waves per unit) 188 / 195 / 210;  181 / 185 / 200
+  //       second (4) 185 / 190 / 198;  182 / 184 / 195
+  //     E = 128, d = 1024, h = 2816, 32 rows, T / E = 16, first (22) 136 / 136 / 160;  129 / 130 / 156
+  //     E = 32, d = 1280, h = 5120, 22 rows, second (2.5) 84 / 76 / 97;  77 / 74 / 96
+  //     E = 24, d = 768, h = 3072, 30 rows, second (1.1) 32 / 26 / 52;  27 / 24 / 51
+  //   up to 64 rows (few with three subtiles, which is not kept): E = 32, d = 2048, h = 8192, 44 rows, T / E = 22, first
+  //     195 / 193 / 209;  185 / 188 / 206;  E = 128, d = 1024, h = 2816, 40 rows, first 162 / 150 / 170;  134 / 138 / 158
+  if (rows_max <= kFewRows && waves >= (rows_max <= 16 ? 2 : 4) * cu_count() && waves <= 0x7FFFFFFFLL) return PackedKernel::kFew;
+  if (rows_max <= 64) return PackedKernel::kAny;
+  // Some hundred rows per segment, few experts, narrow outputs: tiles of 256 columns, which cost a prologue of some 10 us, leave
   // compute units idle or empty, and the smaller tiles of ffn_any.hip are faster (us, tiles here / there):
   //   E = 16, d = 1024, h = 4096, both GEMMs: 96 rows 44 + 65 / 29 + 30;  255 rows 53 + 70 / 53 + 60;  640 uneven 97 + 86 / 83 + 74
   //   E = 4, d = 2048, h = 8192: 100 rows 42 + 117 / 33 + 46;  250 rows 54 + 155 / 48 + 60
-  //   E = 64, d = 1024, h = 4096: 48 rows 123 + 110 / 111 + 98;  256 rows 180 + 146 / 203 + 187
+  //   E = 64, d = 1024, h = 4096: 256 rows 180 + 146 / 203 + 187
   //   E = 8, d = 4096, h = 16384: 200 rows 228 + 278 / 313 + 283;  500 rows 426 + 380 / 561 + 578
   // A tenth is asked for, so that a misjudged time does not cost more than is gained, but not with up to two segments per
   // XCD and two turns of tiles: there uneven segments, which the times do not know, speak for the small tiles (E = 16 above:
@@ -709,7 +729,8 @@ int launch_dma(const void* A, const void* Wp, void* C, void* aux, const int32_t*
   if (total > 0x7FFFFFFFLL) return LOCMOE_ERR_SHAPE;
   const PackedKernel pick = pick_packed(E, rows_max, T, Kdim, Ndim, EPI > kEpiGelu);
   if (pick == PackedKernel::kFew) {
-    hipLaunchKernelGGL(ffn_gemm_few<EPI>, dim3((unsigned)(E * (Ndim / kFewCols))), dim3(64), 0, st, (const uint16_t*)A,
+    auto few = rows_max <= 16 ? ffn_gemm_few<1, EPI> : ffn_gemm_few<2, EPI>;
+    hipLaunchKernelGGL(few, dim3((unsigned)(E * (Ndim / kFewCols))), dim3(64), 0, st, (const uint16_t*)A,
                        (const uint16_t*)Wp, (uint16_t*)C, (uint16_t*)aux, seg_off, buf_expert, Kdim, Ndim);
     return launch_status();
   }

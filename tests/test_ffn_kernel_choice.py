@@ -1,0 +1,25 @@
+"""Which kernel a GEMM of the expert FFN goes to, asked of the library's own rule (which the launches follow) for 256
+compute units, without a GPU.  The GPU tests that are meant for one kernel ask the same way, so that a change of the rule
+cannot take their shapes away unseen."""
+import pytest
+
+from paper_2401_13920_amd import locmoe as lm
+
+
+def kernels(T, d, E, h, C, dtype="bf16", packed=True):
+    desc = lm.make_desc(T, d, E, 1, h, C, dtype, w_packed=packed)
+    return [lm.ffn_kernel(desc, second, keeps_z) for second, keeps_z in ((False, False), (False, True), (True, False))]
+
+
+# up to 32 rows per segment and four waves per compute unit: a stream of weights (the tiles of 256 columns take 1.05 to 1.5
+# times as long, whatever the spread of the tokens); up to 64 rows never those tiles
+@pytest.mark.parametrize("T,d,E,h,C", [(192, 1024, 64, 4096, 6), (700, 1024, 64, 4096, 16), (700, 2048, 32, 8192, 17),
+                                       (700, 2048, 32, 8192, 22), (2000, 1024, 128, 2816, 32), (5000, 512, 256, 1024, 20)])
+def test_few_rows_go_to_the_stream_of_weights(T, d, E, h, C):
+    assert kernels(T, d, E, h, C) == ["ffn_gemm_few"] * 3
+
+
+@pytest.mark.parametrize("T,d,E,h,C", [(700, 2048, 32, 8192, 44), (2000, 2048, 32, 8192, 63), (2000, 2048, 64, 8192, 64),
+                                       (5000, 1024, 128, 2816, 40), (192, 4096, 8, 16384, 48), (700, 2560, 20, 10240, 35)])
+def test_no_wide_tiles_up_to_64_rows(T, d, E, h, C):
+    assert all(k.startswith("ffn_gemm_any") for k in kernels(T, d, E, h, C))

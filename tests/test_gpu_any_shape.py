@@ -192,6 +192,24 @@ def test_bits_do_not_depend_on_capacity_or_token_count(env, d, h, rows):
             assert env[0].equal(got[name], ref[name]), name
 
 
+# the stream of weights (ffn_gemm_few) in its two forms, with every epilogue: rows at the edges of its 16-row subtiles,
+# segments without rows, and segments longer than min(C, T), which it walks in passes.  The same bits as the persistent
+# kernel and the row-major one give.
+@pytest.mark.parametrize("rows,C", [([16, 1, 15, 0, 9, 2, 16, 8], 16), ([0, 16, 17, 130, 64, 33, 1, 32], 16),
+                                    ([32, 17, 0, 5, 31, 16, 1, 2], 32), ([32, 33, 0, 65, 31, 130, 64, 1], 32)])
+def test_few_rows_kernel(env, rows, C):
+    torch, lm = env
+    d, h, rows = 768, 2048, rows * 16
+    E = len(rows)
+    for second in (False, True):
+        for cap, kernel in ((C, "ffn_gemm_few"), (1000, "ffn_gemm_dma_persistent")):
+            assert lm.ffn_kernel(lm.make_desc(E * cap, d, E, 1, h, cap, w_packed=True), second, not second) == kernel
+    got = ffn_outputs(env, d, h, rows, E * C, C)
+    for ref in (ffn_outputs(env, d, h, rows, E * 1000, 1000), ffn_outputs(env, d, h, rows, E * C, C, packed=False)):
+        for name in ref:
+            assert torch.equal(got[name], ref[name]), name
+
+
 # segments may hold more rows than min(C, T) (rows of other ranks' tokens): seg_off decides
 @pytest.mark.parametrize("T,C", [(600, 16), (600, 32), (600, 64), (16, 300)])
 def test_few_rows_kernel_covers_longer_segments(env, T, C):
