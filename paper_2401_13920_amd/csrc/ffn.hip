@@ -711,13 +711,21 @@ PackedKernel pick_packed(int E, int rows_max, int T, int Kdim, int Ndim, bool ke
   //   E = 4, d = 2048, h = 8192: 100 rows 42 + 117 / 33 + 46;  250 rows 54 + 155 / 48 + 60
   //   E = 64, d = 1024, h = 4096: 256 rows 180 + 146 / 203 + 187
   //   E = 8, d = 4096, h = 16384: 200 rows 228 + 278 / 313 + 283;  500 rows 426 + 380 / 561 + 578
-  // A tenth is asked for, so that a misjudged time does not cost more than is gained, but not with up to two segments per
-  // XCD and two turns of tiles: there uneven segments, which the times do not know, speak for the small tiles (E = 16 above:
-  // judged alike at 512 rows, though not with Z to write or read: 106 + 110 / 106 + 121; E = 64, d = 2048, h = 8192, even in 0 .. 200 rows, second GEMM, judged alike: 427 / 468).
+  // A tenth is asked for, so that neither a misjudged time nor uneven segments, which the times do not know, cost more than is
+  // gained.  Over 547 GEMMs of 16 layers of more than 64 rows, each with four spreads of the tokens (even; a power law; 60 % on
+  // one expert; 80 % on four): 1.24 times as fast as with the tiles here alone; 12 of them are more than 5 % slower for one of
+  // the spreads, 2 more than 10 % (E = 8, d = 4096, h = 16384, 192 tokens without a limit, second GEMM, tiles here / there: even
+  // 254 / 183, 60 % on one expert 272 / 305).  With a twentieth 1.26, 42 and 8; with three twentieths 1.22, 5 and 1.
+  // Nothing is asked for with up to two segments per XCD, two turns of tiles and full tiles: there uneven segments leave XCDs
+  // idle here, and speak for the small tiles (E = 16 above, judged alike, second GEMM: 750 rows even 99 / 101, 60 % on one expert
+  // 89 / 63; though not with Z to write or read, 8 192 tokens: 106 + 110 / 106 + 121).  With shorter segments or another number
+  // of experts the same cost up to 13 % (E = 8 above, 175 rows, first GEMM 221 / 249; E = 4, d = 2048, h = 8192, 12 000 rows,
+  // second GEMM 386 / 489).
   const int rows = std::min(rows_max, ceil_div(T, E));  // with evenly spread tokens
   double turns = 0.0;
   const double here = tiles_time(E, rows, Kdim, Ndim, persistent, &turns);
-  if (any_gemm_time(E, rows, Kdim, Ndim) < (E <= 16 && turns <= 2.0 && !keeps_z ? 1.0 : 0.9) * here) return PackedKernel::kAny;
+  const bool xcds_idle = persistent && E <= 16 && turns <= 2.0 && rows >= kBM && !keeps_z;
+  if (any_gemm_time(E, rows, Kdim, Ndim) < (xcds_idle ? 1.0 : 0.9) * here) return PackedKernel::kAny;
   return persistent ? PackedKernel::kPersistent : PackedKernel::kTile;
 }
 

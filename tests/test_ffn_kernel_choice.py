@@ -23,3 +23,18 @@ def test_few_rows_go_to_the_stream_of_weights(T, d, E, h, C):
                                        (5000, 1024, 128, 2816, 40), (192, 4096, 8, 16384, 48), (700, 2560, 20, 10240, 35)])
 def test_no_wide_tiles_up_to_64_rows(T, d, E, h, C):
     assert all(k.startswith("ffn_gemm_any") for k in kernels(T, d, E, h, C))
+
+
+# above, the small tiles only where they are expected to be a tenth faster.  Uneven tokens made the first four lose 6 to 22 %
+# of what the tiles of 256 columns take
+@pytest.mark.parametrize("T,d,E,h,C,second", [(192, 4096, 8, 16384, 192, False), (700, 4096, 8, 16384, 175, False),
+                                              (12000, 2048, 4, 8192, 12000, True), (700, 2560, 16, 10240, 700, True),
+                                              (65536, 4096, 64, 16384, 501, True), (32768, 2048, 32, 8192, 1280, False)])
+def test_wide_tiles_unless_the_small_ones_win_clearly(T, d, E, h, C, second):
+    assert kernels(T, d, E, h, C)[2 * second] == ("ffn_gemm_dma_persistent" if E % 8 == 0 else "ffn_gemm_dma")
+
+
+@pytest.mark.parametrize("T,d,E,h,C", [(8192, 1024, 16, 4096, 255), (2000, 2048, 4, 8192, 500), (2000, 768, 12, 3072, 334),
+                                       (8192, 1024, 16, 4096, 640)])
+def test_small_tiles_for_small_layers(T, d, E, h, C):
+    assert kernels(T, d, E, h, C)[2].startswith("ffn_gemm_any")
