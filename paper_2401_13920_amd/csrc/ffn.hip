@@ -899,7 +899,7 @@ extern "C" const char* locmoe_internal_ffn_kernel(const locmoe_desc* desc, int s
   if (t.far) return t.bm == 128 ? "ffn_gemm_any<128, 128, dealt, far>" : "ffn_gemm_any<192, 128, far>";
   if (t.bn == 160) return "ffn_gemm_any<160, 160>";
   if (t.bn == 32) return "ffn_gemm_any<128, 32>";
-  if (t.bn == 64) return t.dealt ? "ffn_gemm_any<128, 64, dealt>" : "ffn_gemm_any<128, 64>";
+  if (t.bn == 64) return t.bm == 192 ? "ffn_gemm_any<192, 64, dealt>" : t.dealt ? "ffn_gemm_any<128, 64, dealt>" : "ffn_gemm_any<128, 64>";
   if (t.bm == 128) return "ffn_gemm_any<128, 128, dealt>";
   return t.dealt ? "ffn_gemm_any<192, 128, dealt>" : "ffn_gemm_any<192, 128>";
 }

@@ -19,7 +19,7 @@
 // What bounds it: with few rows the weight stream (5.0 to 5.5 TB/s of 820 MB at 32 to 64 rows per expert, d = 1600,
 // h = 6400, E = 40), with more rows all copies to LDS together, 8 to 13 TB/s, of which the activations are the larger part
 // the more rows and the fewer columns a tile has.  Hence
-//   - the widest tile that still fills the chip in whole turns (any_time below picks it);
+//   - the widest tile that still fills the chip in whole turns (any_tiles below picks it);
 //   - the tiles of one segment on one XCD, whose L2 then fetches the segment's activations once.  Dealt to the XCDs in turn
 //     each L2 fetched all of them: second GEMM at 128 rows of that layer 270 -> 243 us (E = 64, d = 2048, h = 8192, 100 rows:
 //     432 -> 396), with 160 columns instead of 128, so that 400 tiles fit the 512 slots where 520 did not, 185;
@@ -241,7 +241,7 @@ __device__ __forceinline__ int wave_scan(int v) {
 // engines in turn, and where every second one leaves at once, half of the engines stay empty.  Rows even in 0 .. 224,
 // d = 2048, h = 8192, E = 32: 340 + 363 us so, 261 + 267 from a list.)
 // DEALT: weight tile nt of segment r is XCD (r NT + nt) mod 8's instead, and every XCD has a list of its own: with fp32
-// activations (E = 16, d = 1024, h = 4096, 255 rows: 68 against 72 us) and long lists of row-major weights (any_gemm).
+// activations (E = 16, d = 1024, h = 4096, 255 rows: 68 against 72 us) and most lists of row-major weights (any_tiles).
 // A list that fills the XCD's `slots` (two per compute unit) once or twice is cut into m-tiles of kFine rows where
 // that does not take another turn: rows even in 0 .. 256, d = 4096, h = 16384, E = 8, second GEMM: 389 us with up to 192
 // rows, 308 with up to 128.
@@ -403,11 +403,31 @@ AnyTiles any_tiles(bool a_f32, bool packed, int E, int rows_max, int T, int Kdim
   }
   // (packed weights have shorter rows; the weight rows' offsets are no larger)
   if (!packed && (long long)Kdim * 2 * 192 > 0xFFFFFFFFLL) return {192, 128, false, true};
-  double us;
-  AnyTiles t = any_fastest(E, rows, Kdim, Ndim, &us);
-  // Weight tiles dealt to the XCDs where eight times the activations are fewer bytes than the weights: first GEMM of
-  // d = 1600, h = 6400, E = 40, 157 rows: 192 us, 199 to 204 with runs (second GEMM: 220 and 216, with the other tile 195)
-  t.dealt = !packed && t.bm == 192 && 8LL * rows < Ndim;
+  if (packed) {
+    double us;
+    return any_fastest(E, rows, Kdim, Ndim, &us);
+  }
+  // Row-major weights: tiles of 192 rows and 128 columns, or 64 where that leaves slots empty, dealt to the XCDs.  Uneven tokens
+  // cost the least there, and the expected times know nothing of them, so that a shape has to be expected 1.15 times as fast
+  // to be taken instead, and 1.25 times that of 160 x 160, whose runs suffer most, unless the experts are many.  Over 588
+  // GEMMs of 14 layers, each with four spreads of the tokens (even; a power law; 60 % on one expert; 80 % on four), against the
+  // two shapes alone: 1.03 times as fast, 12 GEMMs more than 7 % slower for one of the spreads (3 of them where it is the same
+  // kernel), 4 more than 10 %.  The shape expected fastest, whatever the distance: 1.05, 88 and 47.
+  const bool wide = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows, 192) >= 2 * cu_count();
+  AnyTiles t = {192, wide ? 128 : 64, true, false};
+  double us = any_time(t.bm, t.bn, E, rows, Kdim, Ndim);
+  auto consider = [&](AnyTiles other, double times) {
+    const double u = times * any_time(other.bm, other.bn, E, rows, Kdim, Ndim);
+    if (u < us) { us = u; t = other; }
+  };
+  if (!wide) consider({192, 128, true, false}, 1.15);
+  consider({160, 160, false, false}, E >= 32 ? 1.15 : 1.25);
+  consider({128, 32, false, false}, 1.15);
+  // In runs where the XCDs together would fetch more bytes of activations than there are weights, the inner size is the longer
+  // one and a segment's activations are not far beyond an XCD's 4 MiB of L2.  Second GEMM, dealt / runs: E = 16, d = 1024,
+  // h = 4096, 750 rows 131 / 97 us;  E = 64, d = 1024, h = 2736, 188 rows 166 / 124;  E = 40, d = 1600, h = 6400, 820 rows (10 MB)
+  // 832 / 753;  E = 8, d = 2048, h = 8192, 4 096 rows (67 MB) 1 243 / 1 351.  First GEMM of E = 16, 750 rows 118 / 122.
+  if (t.bm == 192 && t.bn == 128) t.dealt = !(8LL * rows >= Ndim && Kdim > Ndim && (long long)rows * Kdim <= 8000000);
   return t;
 }
 
@@ -428,11 +448,12 @@ int any_gemm(const void* A, const void* W, void* C, void* aux, const int32_t* se
   } else {
     if constexpr (!PACKED) {
       if (t.far) LOCMOE_ANY(192, 128, false, true);
-      if (t.dealt) LOCMOE_ANY(192, 128, true, false);
+      if (t.dealt && t.bn == 128) LOCMOE_ANY(192, 128, true, false);
+      if (t.dealt) LOCMOE_ANY(192, 64, true, false);
     }
     switch (t.bn) {
       case 160: LOCMOE_ANY(160, 160, false, false);
-      case 64: LOCMOE_ANY(128, 64, false, false);
+      case 64: if constexpr (PACKED) LOCMOE_ANY(128, 64, false, false);
       case 32: LOCMOE_ANY(128, 32, false, false);
       default: LOCMOE_ANY(192, 128, false, false);
     }
