@@ -153,8 +153,8 @@ int locmoe_dispatch(const locmoe_desc* desc, const void* x, const int32_t* eid, 
  * LOCMOE_ERR_HIP if the lookup fails.  Every call on a device uses that device's one array: calls that overlap
  * on one device (other streams, other threads) race and must not be made; calls on one stream are ordered.
  * Nothing in the array has to be zero on entry (every count is written before it is read), and its contents
- * after a call are unspecified.  (Up to 4 096 tokens of at most 32 KiB are counted without any scratch: neither the
- * array nor locmoe_dispatch's ws is touched, but both are asked for as always.)
+ * after a call are unspecified.  (Up to 5 120 tokens are counted without any scratch: neither the array nor
+ * locmoe_dispatch's ws is touched, but both are asked for as always.)
  * All other arguments, outputs and errors as locmoe_dispatch. */
 #define LOCMOE_DISPATCH_STATIC_MAX_COUNTS 262144
 int locmoe_dispatch_static(const locmoe_desc* desc, const void* x, const int32_t* eid, const int32_t* e2n,

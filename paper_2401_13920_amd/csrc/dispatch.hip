@@ -1,6 +1,6 @@
 // Capacity-bounded stable dispatch (capacity: Section 3.2.3).
 // Up to kDispOneTokens tokens dispatch_one_kernel does it all in one launch; else
-//   1. dispatch_hist_kernel   per block of 1024 tokens: count of tokens per expert
+//   1. dispatch_hist_kernel   per block of 1024 tokens: count of tokens per expert (few blocks: counted by step 2)
 //   2. dispatch_slots_kernel  every block re-derives, from the [blocks,E] count matrix, the
 //      tokens before it per expert and the totals, hence kept[], the buffer order and the
 //      segment offsets; then ranks its own tokens (wave ballots + ordered wave prefixes)
@@ -46,10 +46,10 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Buffer order (experts sorted by (node, id)): rank[e], and seg[r], the first row of the expert at rank r (seg[E] = K), from
-// the kept rows tot[e] and nodes node[e].  Called by a work-group of kDispThreads; ends with a barrier.
+// Buffer order (experts sorted by (node, id)): rank[e]; by_rank[r], the node, and seg[r], the first row of the expert at rank r
+// (seg[E] = K), from the kept rows tot[e] and nodes node[e].  Called by a work-group of kDispThreads; ends with a barrier.
 __device__ __forceinline__ void buffer_order(const int32_t* e2n, const int32_t* tot, const int32_t* node, int32_t* rank,
-                                             int32_t* seg, int E) {
+                                             int32_t* by_rank, int32_t* seg, int E) {
   const int tid = threadIdx.x, lane = tid % kWave;
   for (int e = tid; e < E; e += kDispThreads) {
     int r = e;
@@ -60,6 +60,7 @@ __device__ __forceinline__ void buffer_order(const int32_t* e2n, const int32_t* 
       for (int q = 0; q < E; ++q) r += (node[q] < ne || (node[q] == ne && q < e)) ? 1 : 0;
     }
     rank[e] = r;
+    by_rank[r] = node[e];
     seg[r + 1] = tot[e];  // staged: kept of the expert at rank r, scanned below
   }
   __syncthreads();
@@ -84,18 +85,16 @@ __device__ __forceinline__ void buffer_order(const int32_t* e2n, const int32_t* 
   __syncthreads();
 }
 
-// The outputs per expert and node, by one work-group.  by_rank: LDS for E words
-__device__ __forceinline__ void write_segments(const int32_t* tot, const int32_t* node, const int32_t* rank,
-                                               const int32_t* seg, int32_t* by_rank, int32_t* kept, int32_t* seg_off,
+// The outputs per expert and node, by one work-group
+__device__ __forceinline__ void write_segments(const int32_t* tot, const int32_t* rank, const int32_t* by_rank,
+                                               const int32_t* seg, int32_t* kept, int32_t* seg_off,
                                                int32_t* node_off, int32_t* buf_expert, int E, int N) {
   const int tid = threadIdx.x;
   for (int e = tid; e < E; e += kDispThreads) {
     kept[e] = tot[e];
     buf_expert[rank[e]] = e;
-    by_rank[rank[e]] = node[e];
   }
   for (int i = tid; i <= E; i += kDispThreads) seg_off[i] = seg[i];
-  __syncthreads();
   // node nu starts where its first expert (or the next node's that has one) starts; the nodes ascend with the rank
   for (int r = tid; r <= E; r += kDispThreads) {
     const int last = r < E ? min(by_rank[r], N) : N;
@@ -114,6 +113,33 @@ __device__ __forceinline__ unsigned long long same_expert(int e, bool valid, int
   return peers;
 }
 
+// Tokens per expert, counted by one work-group of kDispThreads into LDS that is zero: before[e] of the tokens ahead of
+// `base`, rest[e] of the others.  ALIGNED: base is a multiple of the wave.  Every thread comes by behind(i0) between a round's
+// loads and their use.
+template <int U, bool ALIGNED, class F>
+__device__ __forceinline__ void count_tokens(const int32_t* __restrict__ eid, int32_t* before, int32_t* rest, int base, int T,
+                                             F behind) {
+  const int tid = threadIdx.x, lane = tid % kWave;
+  for (int i0 = 0; i0 < T; i0 += U * kDispThreads) {
+    int c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = eid[min(i0 + tid + u * kDispThreads, T - 1)];
+    behind(i0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = i0 + tid + u * kDispThreads;
+      if (m < T) {
+        // the tokens of the first lane's expert are added at once: additions to one word wait for each other
+        const int first = __builtin_amdgcn_readfirstlane(c[u]);
+        const bool mine = c[u] == first && (ALIGNED || (m < base) == (__builtin_amdgcn_readfirstlane(m) < base));
+        const unsigned long long same = __ballot(mine);
+        if (!mine || lane == __builtin_ctzll(same))
+          atomicAdd((m < base ? before : rest) + c[u], mine ? __builtin_popcountll(same) : 1);
+      }
+    }
+  }
+}
+
 // Few tokens: every work-group counts all tokens' experts for itself (those before its own `per` tokens and the rest),
 // hence kept[], the buffer order and its tokens' slots, and copies their rows, whose first kOneLoads 16-byte pieces per
 // thread are fetched ahead of the counting.  Bound by latencies: the launch, one round trip to eid, some ten barriers.
@@ -122,6 +148,11 @@ __device__ __forceinline__ unsigned long long same_expert(int e, bool valid, int
 //   4 096 tokens: 8.1 / 11.0;  9.7 / 15.0;  21.5 / 29.8;  4 of 5 tokens on one expert 7.7 / 10.2;  9.1 / 12.9;  16.0 / 20.8
 // The line lies where no distribution of the tokens loses (the rows of dropped tokens are fetched in vain); this / three
 // launches: 5 120 tokens, 4 of 5 on one expert, d = 1024, E = 16 8.3 / 10.7;  d = 5120, E = 128 19.4 / 17.4.
+// From there to kDispSelfBlocks blocks, and with rows beyond kOneMaxChunks pieces, the two launches stay: the slots kernel
+// counts for itself.  us, two / three launches: 4 500 tokens, 4 of 5 on one expert, d = 768 fp32, E = 6 10.7 / 11.5;  d = 16 640,
+// E = 8: 65 tokens 7.9 / 9.5, 1 024 11.3 / 13.1.  Beyond, some spread loses: 6 000 tokens on two of 16 experts 10.3 / 10.2;
+// 8 192 tokens evenly spread 11.3 / 10.9.
+constexpr int kDispSelfBlocks = 5;
 constexpr int kDispOneTokens = 4096, kOneMaxTok = kWave, kOneLoads = 8, kOneMaxChunks = 2048;
 __global__ __launch_bounds__(kDispThreads) void dispatch_one_kernel(
     const uint4* __restrict__ x, const int32_t* __restrict__ eid, const int32_t* __restrict__ e2n,
@@ -144,28 +175,12 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_one_kernel(
   const int my_e = tid < n ? eid[base + tid] : 0;
   for (int i = tid; i < 2 * E; i += kDispThreads) sm[i] = 0;
   __syncthreads();
-  constexpr int U = 10;
-  for (int i0 = 0; i0 < T; i0 += U * kDispThreads) {  // (every thread comes by: the rows are fetched behind the first loads)
-    int c[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = eid[min(i0 + tid + u * kDispThreads, T - 1)];
+  count_tokens<10, false>(eid, off, tot, base, T, [&](int i0) {  // (the rows are fetched behind the first loads)
     if (i0 == 0) {
 #pragma unroll
       for (int u = 0; u < kOneLoads; ++u) v[u] = nt_load16(src + min((unsigned)(tid + u * kDispThreads), pieces - 1));
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int m = i0 + tid + u * kDispThreads;
-      if (m < T) {
-        // the tokens of the first lane's expert are added at once: additions to one word wait for each other
-        const int first = __builtin_amdgcn_readfirstlane(c[u]);
-        const bool mine = c[u] == first && m < base == (__builtin_amdgcn_readfirstlane(m) < base);
-        const unsigned long long same = __ballot(mine);
-        if (!mine || lane == __builtin_ctzll(same))
-          atomicAdd((m < base ? off : tot) + c[u], mine ? __builtin_popcountll(same) : 1);
-      }
-    }
-  }
+  });
   __syncthreads();
   for (int e = tid; e < E; e += kDispThreads) {
     const int all = off[e] + tot[e];
@@ -173,8 +188,8 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_one_kernel(
     node[e] = e2n ? e2n[e] : e / (E / N);
   }
   __syncthreads();
-  buffer_order(e2n, tot, node, rank, seg, E);
-  if (blockIdx.x == 0) write_segments(tot, node, rank, seg, by_rank, kept, seg_off, node_off, buf_expert, E, N);
+  buffer_order(e2n, tot, node, rank, by_rank, seg, E);
+  if (blockIdx.x == 0) write_segments(tot, rank, by_rank, seg, kept, seg_off, node_off, buf_expert, E, N);
   if (tid < kWave) {  // the work-group's tokens, one per lane
     const bool valid = tid < n;
     const unsigned long long peers = same_expert(my_e, valid, nbits);
@@ -220,7 +235,7 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_hist_kernel(const int32
   for (int i = threadIdx.x; i < E; i += kDispThreads) blockcnt[(size_t)blockIdx.x * E + i] = hist[i];
 }
 
-// LDS layout of the slots kernel (ints): off[E] tot[E] node[E] rank[E] seg[E+1] wcnt[waves][E]
+// LDS layout of the slots kernel (ints): off[E] tot[E] node[E] rank[E] by_rank[E] seg[E+1] wcnt[waves][E]
 __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
     const int32_t* __restrict__ eid, const int32_t* __restrict__ e2n, const int32_t* __restrict__ blockcnt,
     int32_t* __restrict__ pos, int32_t* __restrict__ slot, int32_t* __restrict__ kept,
@@ -231,7 +246,8 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
   int32_t* tot = off + E;
   int32_t* node = tot + E;
   int32_t* rank = node + E;
-  int32_t* seg = rank + E;  // [E+1], indexed by buffer rank
+  int32_t* by_rank = rank + E;
+  int32_t* seg = by_rank + E;  // [E+1], indexed by buffer rank
   int32_t* wcnt = seg + E + 1;
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int b = blockIdx.x;
@@ -246,7 +262,20 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
 
   // tokens per expert in earlier blocks, and in all blocks: thread (rg, e) adds the rows q = rg, rg+R, ...
   // of the [blocks, E] count matrix (independent loads), then the R partials are added in order
-  {
+  if (!blockcnt) {  // few blocks: counted here, by every block for itself
+    int32_t* earlier = wcnt;     // [E] tokens before this block's
+    int32_t* later = wcnt + E;   // [E] this block's and after
+    for (int i = tid; i < 2 * E; i += kDispThreads) wcnt[i] = 0;
+    __syncthreads();
+    count_tokens<8, true>(eid, earlier, later, b * kDispatchTokensPerBlock, T, [](int) {});
+    __syncthreads();
+    for (int e = tid; e < E; e += kDispThreads) {
+      const int all = earlier[e] + later[e];
+      off[e] = earlier[e];
+      tot[e] = all < C ? all : C;  // kept[e] = min(cnt[e], C)
+      node[e] = e2n ? e2n[e] : e / (E / N);
+    }
+  } else {
     const int R = E < kDispThreads ? kDispThreads / E : 1;  // row groups working on one chunk of experts
     int32_t* part_before = wcnt;                             // [R][E] scratch (wcnt is zeroed afterwards)
     int32_t* part_all = wcnt + kDispThreads;                 // R*E <= kDispThreads when R > 1
@@ -291,13 +320,8 @@ __global__ __launch_bounds__(kDispThreads) void dispatch_slots_kernel(
   __syncthreads();
   for (int i = tid; i < kDispWaves * E; i += kDispThreads) wcnt[i] = 0;
   __syncthreads();
-  buffer_order(e2n, tot, node, rank, seg, E);
-  if (b == 0) {
-    write_segments(tot, node, rank, seg, wcnt, kept, seg_off, node_off, buf_expert, E, N);
-    __syncthreads();
-    for (int i = tid; i < E; i += kDispThreads) wcnt[i] = 0;  // (it served as by_rank)
-    __syncthreads();
-  }
+  buffer_order(e2n, tot, node, rank, by_rank, seg, E);
+  if (b == 0) write_segments(tot, rank, by_rank, seg, kept, seg_off, node_off, buf_expert, E, N);
 
   // rank of each token among the block's earlier tokens of the same expert
   int32_t* wc = wcnt + wave * E;
@@ -390,9 +414,9 @@ void launch_copy(const void* x, const int32_t* row_token, const int32_t* seg_off
 }
 
 
-// The launches of the dispatch: one for few tokens, which leaves `blockcnt` alone, else histogram, slots, copy.  `blockcnt`
-// holds ceil(T/1024) x E counts (every one is written by the first kernel before the second reads it: nothing has to be
-// cleared).
+// The launches of the dispatch: one for few tokens, else histogram, slots, copy, up to kDispSelfBlocks blocks of tokens without
+// the histogram.  `blockcnt` holds ceil(T/1024) x E counts (every one is written by the first kernel before the second reads
+// it: nothing has to be cleared); without a histogram it is not touched.
 int dispatch_launch(const locmoe_desc* desc, const void* x, const int32_t* eid, const int32_t* e2n, int32_t* pos,
                     int32_t* slot, int32_t* kept, int32_t* seg_off, int32_t* node_off, int32_t* buf_expert,
                     int32_t* row_token, void* send, int32_t* blockcnt, hipStream_t s) {
@@ -402,18 +426,24 @@ int dispatch_launch(const locmoe_desc* desc, const void* x, const int32_t* eid, 
   while ((1 << nbits) < E) ++nbits;
   const int chunks = desc->d * (desc->x_dtype == LOCMOE_BF16 ? 2 : 4) / 16;
   if (T <= kDispOneTokens && chunks <= kOneMaxChunks) {
-    // tokens per work-group: as many as the loads ahead hold (not fewer than 8, each counts all), spread over 128 at least
+    // tokens per work-group: as many as the loads ahead hold, or 8 where they hold fewer (each work-group counts all tokens),
+    // and at most ceil(T / 128): 128 work-groups, fewer where T / 128 is rounded up, more where the rows are long
     const int per = std::min(std::min(kOneMaxTok, std::max(8, kOneLoads * kDispThreads / chunks)), ceil_div(T, 128));
     hipLaunchKernelGGL(dispatch_one_kernel, dim3(ceil_div(T, per)), dim3(kDispThreads), ((size_t)E * 6 + 1) * 4, s,
                        (const uint4*)x, eid, e2n, pos, slot, kept, seg_off, node_off, buf_expert, row_token, (uint4*)send,
                        T, E, desc->N, desc->C, per, chunks, nbits);
     return launch_status();
   }
-  hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nblocks), dim3(kDispThreads), (size_t)E * 4, s, eid, blockcnt, T, E);
-  int st = launch_status();
-  if (st != LOCMOE_OK) return st;
+  int st = LOCMOE_OK;
+  if (nblocks <= kDispSelfBlocks) {
+    blockcnt = nullptr;
+  } else {
+    hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nblocks), dim3(kDispThreads), (size_t)E * 4, s, eid, blockcnt, T, E);
+    st = launch_status();
+    if (st != LOCMOE_OK) return st;
+  }
   const size_t wcnt_ints = (size_t)kDispWaves * E > 2 * (size_t)kDispThreads ? (size_t)kDispWaves * E : 2 * (size_t)kDispThreads;
-  const size_t smem = ((size_t)E * 5 + 1 + wcnt_ints) * 4;
+  const size_t smem = ((size_t)E * 6 + 1 + wcnt_ints) * 4;
   hipLaunchKernelGGL(dispatch_slots_kernel, dim3(nblocks), dim3(kDispThreads), smem, s, eid, e2n, blockcnt, pos,
                      slot, kept, seg_off, node_off, buf_expert, row_token, T, E, desc->N, desc->C, nblocks, nbits);
   st = launch_status();

@@ -1,5 +1,5 @@
-"""The slots kernel at the edges of its blocks and on both sides of the line up to which it counts the tokens itself,
-against the integer oracle; and the dense gate at one, two and three k-steps."""
+"""The kernels around the expert FFN on both sides of the lines between their forms: the dispatch in one launch, two and three,
+the route, hash routing and the angle statistics in one launch or block and several, the dense gates."""
 import numpy as np
 import pytest
 
@@ -56,6 +56,27 @@ def check_dispatch(eid, E, N, free_map, d=None):
 def test_dispatch_in_one_launch(T, E, d, free_map):
     rng = np.random.default_rng(T + E + d)
     check_dispatch((rng.zipf(1.5, T) % E).astype(np.int32), E, 4 if E % 4 == 0 else 1, free_map, d=d)
+
+
+# up to 5 120 tokens are counted without scratch, in one launch or in two
+@pytest.mark.parametrize("T,E,d", [(4096, 8, 64), (4097, 12, 96), (5120, 300, 1200), (65, 4, 16416), (5120, 4, 16416)])
+def test_dispatch_leaves_its_scratch_alone(T, E, d):
+    import torch
+    from paper_2401_13920_amd import locmoe as lm
+    rng = np.random.default_rng(T + d)
+    eid = rng.integers(0, E, T).astype(np.int32)
+    desc = lm.make_desc(T, d, E, 1, 8, 2 * T // E, "bf16")
+    b = lm.alloc_buffers(desc)
+    x = torch.randn(T, d, device="cuda").to(torch.bfloat16)
+    b.ws.fill_(171)
+    print(f"[dispatch scratch] T={T} E={E} d={d}", flush=True)
+    lm.locmoe_dispatch(desc, x, torch.from_numpy(eid).cuda(), None, b.pos, b.slot, b.kept, b.seg_off, b.node_off, b.buf_expert,
+                       b.row_token, b.send, b.ws, b.ws_bytes)
+    torch.cuda.synchronize()
+    assert bool((b.ws == 171).all())
+    ref = orc.slots(eid, E, desc.C, np.zeros(E, dtype=np.int32), 1)
+    for name in ("pos", "slot", "kept", "seg_off", "buf_expert"):
+        assert np.array_equal(getattr(b, name).cpu().numpy(), ref[name]), name
 
 
 # the route in one launch (4 096 tokens' lanes: 1 024 tokens of 4 experts, 512 of 8, 256 of up to 64) and in two, with one to
