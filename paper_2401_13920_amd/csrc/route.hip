@@ -175,18 +175,19 @@ constexpr int kFinWaves = kFinThreads / kWave;
 
 // Sums (and one maximum) over the block of NQ doubles per thread, in a fixed order: a butterfly inside each wave
 // (lane i adds lane i ^ o for o = 32 .. 1), the sixteen wave results through LDS, added in wave order by every
-// thread.  Two barriers for all NQ quantities together.  With `one` only the first wave holds anything and is asked.
-template <int NQ>
-__device__ __forceinline__ void block_sums(double (&v)[NQ], double& vmax, double (*part)[kFinWaves], bool one) {
+// thread.  Two barriers for all NQ quantities together.  ONE: only the first wave holds anything and is asked (with a branch at run
+// time instead the finalize kernel took 0.8 us longer either way).
+template <int NQ, bool ONE>
+__device__ __forceinline__ void block_sums(double (&v)[NQ], double& vmax, double (*part)[kFinWaves]) {
   const int wave = threadIdx.x / kWave;
-  if (one && wave) return;
+  if (ONE && wave) return;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) v[q] += __shfl_xor(v[q], o);
     vmax = fmax(vmax, __shfl_xor(vmax, o));
   }
-  if (one) return;
+  if (ONE) return;
   if (threadIdx.x % kWave == 0) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) part[q][wave] = v[q];
@@ -206,31 +207,36 @@ __device__ __forceinline__ void block_sums(double (&v)[NQ], double& vmax, double
   vmax = m;
 }
 
-// Adds up columns that thread (q, e), q = tid / E < R, holds a part of: first the parts of up to eight q in a row, then
-// these sums in order, so that no thread adds more than some R / 8 + 8 words one after the other (all R of them in one
-// thread took 3 us of a small layer's route).  Result in thread e < E.
+// Adds up columns that thread (q, e), q = tid / E < R, holds a part of.  Result in thread e < E.  More than 16 parts: first
+// those of up to eight q in a row, then these sums in order, so that no thread adds more than some R / 8 + 8 words one after
+// the other (all R of them in one thread took 3 us of a small layer's route).  Up to 16 parts that costs more in barriers
+// than it saves.
 __device__ __forceinline__ void column_sums(int32_t& ci, double& ps, int32_t* ipart, double* dpart, int E, int R) {
   const int tid = threadIdx.x;
   ipart[tid] = ci;
   dpart[tid] = ps;
   __syncthreads();
-  const int q = tid / E, e = tid - q * E;
-  const int runs = R < 8 ? R : 8, len = (R + runs - 1) / runs;  // run j: q = j len .. + len
-  ci = 0;
-  ps = 0.0;
-  if (q < runs) {
-    const int q1 = min(R, (q + 1) * len);
+  int parts = R;
+  if (R > 16) {
+    const int q = tid / E, e = tid - q * E;
+    const int len = (R + 7) / 8;  // run j: q = j len .. + len
+    parts = 8;
+    if (q < parts) {
+      const int q1 = min(R, (q + 1) * len);
+      ci = 0;
+      ps = 0.0;
 #pragma unroll 8
-    for (int i = q * len; i < q1; ++i) { ci += ipart[i * E + e]; ps += dpart[i * E + e]; }
-  }
-  __syncthreads();
-  if (q < runs) { ipart[tid] = ci; dpart[tid] = ps; }
-  __syncthreads();
-  if (tid < E) {
-#pragma unroll
-    for (int j = 1; j < 8; ++j) {
-      if (j < runs) { ci += ipart[j * E + tid]; ps += dpart[j * E + tid]; }
+      for (int i = q * len; i < q1; ++i) { ci += ipart[i * E + e]; ps += dpart[i * E + e]; }
     }
+    __syncthreads();
+    if (q < parts) { ipart[tid] = ci; dpart[tid] = ps; }
+    __syncthreads();
+  }
+  if (tid < E) {
+    ci = 0;
+    ps = 0.0;
+#pragma unroll 4
+    for (int q = 0; q < parts; ++q) { ci += ipart[q * E + tid]; ps += dpart[q * E + tid]; }
   }
 }
 
@@ -243,8 +249,9 @@ struct FinShared {
 
 // cnt, Psum and the scalars of Eq. 5 / Eq. 6 from the totals: thread e < E holds expert e's, home[] the tokens per home node
 // and pernode[] the experts per node (both behind a barrier), and the threads together the tokens that stay on their node.
-__device__ __forceinline__ void route_scalars(FinShared& sh, int32_t c, double p, int local, bool local_first_wave,
-                                              const int32_t* e2n, int has_home, int32_t* cnt, float* Psum, float* stats,
+// ONE: these and the experts are all in the first wave.
+template <bool ONE>
+__device__ __forceinline__ void route_scalars(FinShared& sh, int32_t c, double p, int local, const int32_t* e2n, int has_home, int32_t* cnt, float* Psum, float* stats,
                                               int T, int E, int N, float alpha, float mu) {
   const int tid = threadIdx.x;
   // Eq. 5: L_aux = alpha * n * sum_i f_i P_i
@@ -265,7 +272,7 @@ __device__ __forceinline__ void route_scalars(FinShared& sh, int32_t c, double p
       if (P > 0.0) q[2] = Dl > 0.0 ? P * log(P / Dl) : INFINITY;
     }
   }
-  block_sums<5>(q, mx, sh.part, E <= kWave && local_first_wave);
+  block_sums<5, ONE>(q, mx, sh.part);
   if (tid == 0) {
     stats[0] = (float)((double)alpha * E * q[0]);
     stats[1] = (float)q[1];
@@ -283,9 +290,10 @@ __device__ __forceinline__ void route_scalars(FinShared& sh, int32_t c, double p
 // a round; the loads are unconditional (rows past the end re-read the thread's first row and are not added) and all of a
 // round's are issued before the first is used, so U is no larger than the partials need: with 32 rows always, 64 partials
 // took 64 loads in each of 1024 threads (T = 8 192, E = 16: 11.4 us).  With more than 16 rows a thread (E = 64 from 32 769
-// tokens on) two rounds of 16 were two round trips to memory: both launches at T = 65 536, E = 64 21.4 us, one round of 32
-// 20.8; E = 128 29.5 / 28.4; E = 300 72.2 / 69.5.
-template <int U>
+// tokens on) two rounds of 16 were two round trips to memory.  Both launches at T = 65 536, us: E = 64 20.1, E = 128 27.5,
+// E = 300 68.5, of which a choice at run time between one wave and all in block_sums took 0.8, the second step of
+// column_sums 0.3, and loads that waited for earlier ones 0.2; T = 8 192, E = 16: 10.2.
+template <int U, bool ONE>
 __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
     void* ws, const int32_t* __restrict__ e2n, int has_home, int32_t* __restrict__ cnt,
     float* __restrict__ Psum, float* __restrict__ stats, int nb, int T, int E, int N, float alpha, float mu) {
@@ -314,6 +322,8 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
     }
   }
   if (has_home && tid < nb) local = r.local[tid];  // (nb <= 512)
+  // (24-bit products: a 64-bit multiply-add took a register of a load under way for its unused upper half, and waited for it)
+  auto at = [&](int b) { return __umul24(b < nb ? b : rb, E) + e; };
   int b0 = 0;
   if constexpr (U == 32) {  // the first half of the rows is there for certain: one offset per thread, scalar distances
     for (; b0 + U / 2 * R < nb; b0 += U * R) {
@@ -323,8 +333,9 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
         for (int u = 0; u < U; ++u) {
           const int b = b0 + rb + u * R;
           if (u < U / 2) v[u] = (r.cell + (size_t)(b0 + u * R) * E)[(unsigned)(rb * E + e)];
-          else v[u] = r.cell[(unsigned)((b < nb ? b : rb) * E + e)];
+          else v[u] = r.cell[at(b)];
         }
+        __builtin_amdgcn_sched_barrier(0);  // (or the first are waited for before the last are issued)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const bool live = u < U / 2 || b0 + rb + u * R < nb;
@@ -341,8 +352,9 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
 #pragma unroll
       for (int u = 0; u < UT; ++u) {
         const int b = b0 + rb + u * R;
-        v[u] = r.cell[(unsigned)((b < nb ? b : rb) * E + e)];
+        v[u] = r.cell[at(b)];
       }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < UT; ++u) {
         const bool live = b0 + rb + u * R < nb;
@@ -359,13 +371,14 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(
       for (int b = rn + UH * Rn; b < nb; b += Rn) hi += r.home[(size_t)b * N + nu];  // (few nodes per thread group: rare)
     }
   }
+  asm volatile("" : "+v"(local));  // (its conversion to double stays behind the cells' loads: ahead of them it waited for itself)
   column_sums(ci, ps, sh.ipart, sh.dpart, E, R);  // (its barriers stand behind the zeros above)
   if (has_home) {  // integer adds: any order gives the same counts
     if (hi) atomicAdd(&sh.home[nu], hi);
     if (tid < E) atomicAdd(&sh.pernode[e2n ? e2n[tid] : tid / (E / N)], 1);
   }
   __syncthreads();
-  route_scalars(sh, ci, ps, local, nb <= kWave, e2n, has_home, cnt, Psum, stats, T, E, N, alpha, mu);
+  route_scalars<ONE>(sh, ci, ps, local, e2n, has_home, cnt, Psum, stats, T, E, N, alpha, mu);
 }
 
 // lanes per token: the whole expert axis up to 16 experts; beyond that, up to 128 experts, 16 lanes with
@@ -410,8 +423,8 @@ __global__ __launch_bounds__(kFinThreads) void route_one_kernel(
     for (int q = rb; q < G; q += R) ps += (double)pacc[q * E + e];
   }
   column_sums(ci, ps, sh.ipart, sh.dpart, E, R);
-  route_scalars(sh, tid < E ? hist[tid] : 0, ps, tid == 0 ? s_local : 0, true, e2n, home ? 1 : 0, cnt, Psum, stats, T, E, N,
-                alpha, mu);
+  route_scalars<true>(sh, tid < E ? hist[tid] : 0, ps, tid == 0 ? s_local : 0, e2n, home ? 1 : 0, cnt, Psum, stats, T, E, N,
+                      alpha, mu);  // (E <= 64)
 }
 
 template <int S, int EPL>
@@ -468,9 +481,12 @@ extern "C" int locmoe_route(const locmoe_desc* desc, const float* g, const float
   if (st != LOCMOE_OK) return st;
   if (route_in_one(desc->T, E)) return LOCMOE_OK;
   const int rounds = ceil_div(nb, kFinThreads / E);  // rows of partials per thread
-  auto fin = rounds <= 1 ? route_finalize_kernel<1> : rounds <= 2 ? route_finalize_kernel<2>
-           : rounds <= 4 ? route_finalize_kernel<4> : rounds <= 8 ? route_finalize_kernel<8>
-           : rounds <= 16 ? route_finalize_kernel<16> : route_finalize_kernel<32>;
+  const bool one = E <= kWave && nb <= kWave;  // (then at most four rows)
+  auto fin = rounds <= 1 ? (one ? route_finalize_kernel<1, true> : route_finalize_kernel<1, false>)
+           : rounds <= 2 ? (one ? route_finalize_kernel<2, true> : route_finalize_kernel<2, false>)
+           : rounds <= 4 ? (one ? route_finalize_kernel<4, true> : route_finalize_kernel<4, false>)
+           : rounds <= 8 ? route_finalize_kernel<8, false>
+           : rounds <= 16 ? route_finalize_kernel<16, false> : route_finalize_kernel<32, false>;
   hipLaunchKernelGGL(fin, dim3(1), dim3(kFinThreads), 0, s, ws, e2n, home ? 1 : 0, cnt, Psum, stats, nb, desc->T, E,
                      desc->N, desc->alpha, desc->mu);
   return launch_status();

@@ -80,10 +80,12 @@ def test_dispatch_leaves_its_scratch_alone(T, E, d):
 
 
 # the route in one launch (4 096 tokens' lanes: 1 024 tokens of 4 experts, 512 of 8, 256 of up to 64) and in two, with one to
-# sixteen rows of partials per thread and more
+# 32 rows of partials per thread and more, in the last round all of them, half, fewer; up to 16 parts of a column and more;
+# its scalars from one wave (up to 64 experts and partials) and from all
 @pytest.mark.parametrize("E,N,T", [(1, 1, 5), (4, 2, 1024), (4, 2, 1025), (6, 3, 512), (8, 2, 513), (16, 4, 1), (16, 4, 256),
                                    (16, 4, 257), (40, 8, 255), (64, 8, 256), (64, 8, 257), (65, 5, 100), (64, 8, 30000),
-                                   (128, 16, 20000), (300, 3, 9000)])
+                                   (128, 16, 20000), (300, 3, 9000), (48, 4, 70001), (64, 8, 33000), (64, 8, 8192), (60, 4, 9001),
+                                   (512, 8, 5000)])
 @pytest.mark.parametrize("home", [False, True])
 def test_route_in_one_and_two_launches(E, N, T, home):
     import torch
