@@ -28,10 +28,8 @@ constexpr int kDgSmem = 4 * kDgTile;                 // x and W, double buffered
 
 __device__ __forceinline__ int dg_swz(int row, int chunk) { return (chunk ^ ((row >> 1) & 7)) << 4; }
 
-// NT: 32-expert tiles per pass, experts [e0, e0 + 32 NT).  TOK: tokens per work-group, 32 per wave: 64 with up to 64 experts,
-// where twice as many work-groups hide more than the weight's second reading costs (us, 128 tokens / 64: T = 32 768, d = 2048,
-// E = 32 34.1 / 32.0;  T = 8 192, d = 1024, E = 16 7.5 / 6.4;  T = 300, d = 2048, E = 8 11.7 / 9.5;  T = 20 000, d = 1280,
-// E = 80 17.9 / 22.1).
+// NT: 32-expert tiles per pass, experts [e0, e0 + 32 NT).  TOK: tokens per work-group, 32 per wave; 64 with up to 64 experts
+// where the launch says so.
 template <int NT, int TOK>
 __global__ __launch_bounds__(2 * TOK) void gate_dense_mfma_kernel(const uint16_t* __restrict__ x,
                                                                      const uint16_t* __restrict__ Wg,
@@ -234,7 +232,8 @@ __global__ __launch_bounds__(kDgThreads) void gate_dense_f32_kernel(const float*
 }
 
 // Any shape and either storage type: one wave per token, lanes stride over the features, the wave's sum by a
-// fixed butterfly.  Correct for every descriptor; used for bf16 rows that are no multiple of 64 and fp32 rows that are no multiple of 32.
+// fixed butterfly.  Correct for every descriptor; used for bf16 rows that are no multiple of 64, fp32 rows that are no multiple
+// of 32, and few experts and tokens in fp32 storage.
 template <bool BF16>
 __global__ __launch_bounds__(256) void gate_dense_generic_kernel(const void* __restrict__ x,
                                                                  const void* __restrict__ Wg,
@@ -321,16 +320,28 @@ extern "C" int locmoe_gate_dense(const locmoe_desc* desc, const void* x, const v
   if (desc->x_dtype == LOCMOE_BF16 && d % kDgBK == 0) {
     const int passes = ceil_div(E, 128);
     const int nt = passes > 1 ? 4 : ceil_div(E, 32);  // 32-expert tiles per pass
-#define LOCMOE_DG(N)                                                                                             \
+#define LOCMOE_DG(N, TOK)                                                                                        \
   {                                                                                                              \
-    constexpr int tok = N <= 2 ? 64 : 128, lds = 2 * (tok + 32 * N) * kDgRowBytes;                               \
+    constexpr int lds = 2 * (TOK + 32 * N) * kDgRowBytes;                                                        \
     static std::atomic<uint64_t> lds_allowed;                                                                    \
-    auto kern = gate_dense_mfma_kernel<N, tok>;                                                                  \
+    auto kern = gate_dense_mfma_kernel<N, TOK>;                                                                  \
     if (!allow_lds((const void*)kern, lds, lds_allowed)) return LOCMOE_ERR_HIP;                                  \
-    hipLaunchKernelGGL(kern, dim3(ceil_div(T, tok), passes), dim3(2 * tok), lds, s, (const uint16_t*)x,          \
+    hipLaunchKernelGGL(kern, dim3(ceil_div(T, TOK), passes), dim3(2 * TOK), lds, s, (const uint16_t*)x,          \
                        (const uint16_t*)Wg, g, T, d, E);                                                         \
   }
-    if (nt == 1) LOCMOE_DG(1) else if (nt == 2) LOCMOE_DG(2) else if (nt == 3) LOCMOE_DG(3) else LOCMOE_DG(4)
+    // 64 tokens per work-group, which read the weight twice as often, where they take half a turn less of the compute units
+    // (up to two turns of 128), and with up to 32 experts where rows are multiples of 4 KiB, which meet in the same channels.
+    // In the mean over d = 384 .. 5 120, 128 tokens' time over 64 tokens' (8 to 32 experts; 48 and 64): 16 384 tokens (half a turn
+    // of 128) 1.11; 1.21, 24 000 (0.7) 0.99; 0.94, 32 768 (1) 1.02; 0.96, 40 000 (1.2) 1.12; 1.10, 57 000 (1.7) 0.98; 0.91, 65 536 (2) 1.00;
+    // 0.93, 80 000 (2.4) 1.04; 0.95.  d = 4 096 with up to 32 experts 1.10 at 32 768 and 65 536 tokens, d = 5 120 0.98 and 0.98.
+    const int cus = cu_count(), groups = ceil_div(T, 128);
+    const bool few = (groups <= 2 * cus && ceil_div(2 * groups, cus) % 2 == 1) || (nt == 1 && d % 2048 == 0);
+    if (nt == 1 && few) LOCMOE_DG(1, 64)
+    else if (nt == 1) LOCMOE_DG(1, 128)
+    else if (nt == 2 && few) LOCMOE_DG(2, 64)
+    else if (nt == 2) LOCMOE_DG(2, 128)
+    else if (nt == 3) LOCMOE_DG(3, 128)
+    else LOCMOE_DG(4, 128)
 #undef LOCMOE_DG
     return launch_status();
   }
