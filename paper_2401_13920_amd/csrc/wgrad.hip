@@ -192,10 +192,9 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_dma_kernel(
   const int swz_hi = ((wave >> 1) & 1) << 2;  // bit 3 of the rows this wave copies (rows 4 wave .. 4 wave + 3)
   // What a copy's source offset is made of, per lane and copy, computed once: the row's byte offset inside a step
   // and the (swizzled) chunk.  A step then costs an add, a min (rows past the segment's end re-read its last row)
-  // and an add per copy instead of a multiplication and the swizzle arithmetic: with one wave per SIMD every
-  // instruction between two MFMAs is MFMA time (the copies' address arithmetic was 1.1 ms of the 8.3 ms of both
-  // GEMMs at config 4).  The two copies of an operand land in consecutive KiB of LDS: one M0 write serves them,
-  // each copy carries its KiB as immediate offset, which the hardware also adds to the source address; it is taken
+  // and an add per copy instead of a multiplication and the swizzle arithmetic (1.1 ms of the 8.3 ms of both GEMMs at E = 64,
+  // d = 4096, h = 16384, C = 501, with four waves).  The two copies of an operand land in consecutive KiB of LDS: one M0
+  // write serves them, each copy carries its KiB as immediate offset, which the hardware also adds to the source address; it is taken
   // off the chunk term again (from a base 4 KiB below the operand, so that the offset stays non-negative).
   static_assert(S::kPCopies == 2 && S::kPRowsPerCopy == 2, "the copy tables assume 512-byte P rows");
   uint32_t rowP[2], chP[2], rowQ[2], chQ[2];
@@ -604,11 +603,14 @@ int launch_wgrad(const void* P, const void* Q, void* G, const int32_t* seg_off, 
   // With fp32 storage 256 columns of the bf16 operand per tile where that leaves three tiles per compute unit: the fp32
   // operand is split and read from LDS half as often.  Both GEMMs, us, 128 x 128 tiles / 256 wide: E = 16, d = 1024, h = 4096,
   // 229 rows 268 / 202;  E = 4, d = 2048, h = 4096, 714 rows (4 tiles per unit) 295 / 230;  E = 20, d = 640, h = 1712, 60 rows
-  // (2.7) 38.1 / 39.2;  E = 6, d = 768, h = 1536, 298 rows (0.8) 39 / 45.  Two bf16 operands: E = 24, d = 768, h = 3072, 455
+  // (2.7) 38.1 / 39.2;  E = 6, d = 768, h = 1536, 298 rows (0.8) 39 / 45.  With fewer than 32 tiles per expert also where a segment
+  // can be long: E = 48, d = 384, h = 1536 (18), up to 30 rows, 15 in the mean 34.3 / 35.2, with four tokens of five on four experts
+  // 33.6 / 34.7;  up to 342 rows 97 / 81 and 70 / 74.  Two bf16 operands: E = 24, d = 768, h = 3072, 455
   // rows 150 / 152;  E = 48, d = 384, h = 1536, 65 rows 30 / 35.
   constexpr int MJ = Q_F32 ? 8 : 4, NI = P_F32 ? 8 : 4;
   if constexpr (MJ != NI) {
-    if ((long long)E * ceil_div(Mdim, 32 * MJ) * ceil_div(Ndim, 32 * NI) >= 3 * cu_count())
+    const long long per_expert = (long long)ceil_div(Mdim, 32 * MJ) * ceil_div(Ndim, 32 * NI);
+    if (E * per_expert >= 3 * cu_count() && (per_expert >= 32 || rows_max >= 128))
       return launch_wgrad_any<P_F32, Q_F32, MJ, NI>(P, Q, G, seg_off, buf_expert, E, Mdim, Ndim, st);
   }
   return launch_wgrad_any<P_F32, Q_F32, 4, 4>(P, Q, G, seg_off, buf_expert, E, Mdim, Ndim, st);

@@ -95,14 +95,16 @@ def test_weight_gradients_of_wide_tiles(env, d, h):
             assert ((got.double() - ref).abs() <= bound).all(), (r, z - a)
 
 
+# 2 experts: tiles of 128 x 128.  24: with fp32 storage tiles of 256 columns of the bf16 operand (three per compute unit); each
+# axis has a last tile that is not full, with infinities in it
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_weight_gradients_of_infinities(env, dtype):
+@pytest.mark.parametrize("rows,d,h", [([40, 33], 136, 264), ([40, 33] + [0] * 22, 1032, 3080)])
+def test_weight_gradients_of_infinities(env, rows, d, h, dtype):
     """An infinite or NaN operand gives what the products give: inf where 1.0 * inf, NaN only where 0 * inf or inf - inf.
     The other operand's values (small whole numbers) have few significant bits."""
     torch, lm = env
-    rows, d, h = [40, 33], 136, 264
     E, K, C = len(rows), sum(rows), 40
-    print(f"[wgrad inf] {dtype}", flush=True)
+    print(f"[wgrad inf] {dtype} d={d} h={h}", flush=True)
     gen = torch.Generator(device="cuda").manual_seed(5)
     off, seg, be = segments(torch, rows)
     ints = lambda cols, t: torch.randint(-3, 4, (K, cols), generator=gen, device="cuda").to(t)
@@ -113,6 +115,9 @@ def test_weight_gradients_of_infinities(env, dtype):
                        (dZ, 45, 0, float("nan")), (dZ, 72, 200, inf), (send, 2, 17, inf), (send, 60, 135, -inf),
                        (dout, 11, 64, inf), (dout, 3, 70, -inf)):
         t[r, c] = v
+    for t, r, c, v in ((H, 5, h - 1, inf), (H, 41, h - 70, -inf), (dZ, 9, h - 1, inf), (dZ, 61, h - 140, float("nan")),
+                       (send, 30, d - 1, inf), (dout, 44, d - 2, -inf)):
+        t[r, c] = v
     desc = lm.make_desc(600, d, E, 1, h, C, dtype)
     dW_in = torch.empty((E, h, d), dtype=torch.bfloat16, device="cuda")
     dW_out = torch.empty((E, d, h), dtype=torch.bfloat16, device="cuda")
@@ -120,6 +125,9 @@ def test_weight_gradients_of_infinities(env, dtype):
     torch.cuda.synchronize()
     for r in range(E):
         e, a, z = E - 1 - r, off[r], off[r + 1]
+        if a == z:
+            assert not dW_in[e].any() and not dW_out[e].any()
+            continue
         for got, P, Q in ((dW_in[e], dZ, send), (dW_out[e], dout, H)):
             ref = torch.zeros(P.shape[1], Q.shape[1], dtype=torch.float64, device="cuda")
             for k in range(a, z):
