@@ -4,6 +4,7 @@ cannot take their shapes away unseen."""
 import pytest
 
 from paper_2401_13920_amd import locmoe as lm
+from test_gpu_any_shape import KERNEL_SHAPES, other_tiles
 
 
 def kernels(T, d, E, h, C, dtype="bf16", packed=True):
@@ -52,3 +53,22 @@ def test_row_major_tiles_are_dealt(T, d, E, h, C, second, bn):
                                               (12000, 1024, 64, 2736, 188, "192, 128")])
 def test_row_major_tiles_in_runs(T, d, E, h, C, kernel):
     assert kernels(T, d, E, h, C, packed=False)[2] == f"ffn_gemm_any<{kernel}>"
+
+
+@pytest.mark.parametrize("packed,first,second,E,d,h,T,C,rows", KERNEL_SHAPES)
+def test_shapes_reach_the_kernels_they_are_meant_for(packed, first, second, E, d, h, T, C, rows):
+    assert len(rows) == E and max(rows) <= min(C, T) and min(rows) == 0
+    assert kernels(T, d, E, h, C, packed=packed) == [first, first, second]
+
+
+def test_every_kernel_has_a_shape():
+    packed = {k for p, a, b, *_ in KERNEL_SHAPES if p for k in (a, b)}
+    plain = {k for p, a, b, *_ in KERNEL_SHAPES if not p for k in (a, b)}
+    tiles = {f"ffn_gemm_any<{t}>" for t in ("192, 128", "160, 160", "128, 32")}
+    assert packed == tiles | {"ffn_gemm_any<128, 64>", "ffn_gemm_dma", "ffn_gemm_dma_persistent"}  # (ffn_gemm_few: its own test)
+    assert plain == tiles | {"ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 64, dealt>"}
+
+
+@pytest.mark.parametrize("packed,first,second,E,d,h,T,C,rows", KERNEL_SHAPES)
+def test_shapes_have_other_tiles_to_be_compared_with(packed, first, second, E, d, h, T, C, rows):
+    other_tiles(lm, first, second, E, d, h)

@@ -5,6 +5,8 @@ Bars: a result is a sum of `n` exact products accumulated in fp32 and rounded on
 |diff| <= 2^-8 (1 + 2^-8) |ref| + n 2^-23 sum |a b| (bf16 has a significand of 8 bits: rounding to nearest moves a value
 by at most 2^-8 of itself); where the result is kept in fp32 the first term is 2^-23 |ref|.
 """
+import random
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -153,8 +155,8 @@ def test_expert_ffn_of_any_shape(env, d, h, dtype):
     check_expert_ffn(env, d, h, dtype, [0, 1, 16, 17, 128, 259], 300)
 
 
-# few rows per segment with packed weights: each row-subtile variant (capacity 16, 32, 64), one to three pairs of
-# k-steps per wave (K = 256, 512, 768), the capacity above and many experts of more than 32 rows, which take the tiles
+# few rows per segment and few experts with packed weights: the narrow tiles of ffn_gemm_any (128 x 32), K = 256 .. 1280, segments
+# at the edges of its row subtiles; 64 experts: its wider ones
 @pytest.mark.parametrize("rows", [[0, 1, 15, 16], [32, 17, 0, 5], [64, 0, 33, 48, 1, 63, 2, 16], [65, 0, 64, 1], [33] * 64])
 @pytest.mark.parametrize("d,h", [(768, 256), (256, 768), (512, 1280)])
 def test_expert_ffn_of_few_rows(env, d, h, rows):
@@ -227,18 +229,68 @@ def test_few_rows_kernel_covers_longer_segments(env, T, C):
         assert env[0].equal(got[name], ref[name]), name
 
 
-# every tile shape, packed and row-major (weight tiles in runs and dealt out), lists of up to 64 segments and of more, and
-# weight tiles that end in the next block of 256 packed columns or past the last: the bits that one other shape gives
-@pytest.mark.parametrize("d,h,rows", [(256, 512, [150, 0, 1, 97, 128, 129, 33, 16]),                 # 128 x 32
-                                      (256, 2304, [161, 0, 160, 1, 130, 96, 65, 32] * 4),            # 160 x 160, 128 x 64
-                                      (512, 1280, [150, 33, 149, 0, 64, 150, 128, 17] * 8),          # 160 x 160, 192 x 128
-                                      (256, 768, [140, 0, 139, 1, 96, 97, 15, 129] * 16)])           # 128 segments
-def test_tile_shapes_give_the_same_bits(env, d, h, rows):
-    ref = ffn_outputs(env, d, h, rows, 600, 300, packed=False)
-    for packed in (False, True):
-        got = ffn_outputs(env, d, h, rows, len(rows) * max(rows), max(rows), packed=packed)
-        for name in ref:
-            assert env[0].equal(got[name], ref[name]), (name, packed)
+def spread(E, top, every=1):
+    """Rows per expert, 0 .. top, only every `every`-th expert with any; the longest and lengths of one and none are there."""
+    r = random.Random(E)
+    rows = [r.randint(0, top) if e % every == 0 else 0 for e in range(E)]
+    rows[0], rows[every % E], rows[-1] = top, 1, 0
+    return rows
+
+
+# (packed, kernels of the first and second GEMM, E, d, h, T, C, rows).  test_ffn_kernel_choice.py checks without a GPU that
+# the shapes reach these kernels.
+KERNEL_SHAPES = [
+    # the persistent kernel: uneven and empty segments; a list so short that its m-tiles are cut to 64 rows; the most experts it
+    # takes; the shortest K (four double steps) and the shortest N; three m-tiles per segment; more tiles per XCD than
+    # work-groups, also of segments without rows
+    (True, "ffn_gemm_dma_persistent", "ffn_gemm_dma_persistent", 8, 1536, 4096, 3200, 400, [400, 0, 257, 256, 1, 129, 64, 300]),
+    (True, "ffn_gemm_dma_persistent", "ffn_gemm_dma_persistent", 64, 2048, 2048, 2080, 65, spread(64, 65, 8)),
+    (True, "ffn_gemm_dma_persistent", "ffn_gemm_dma_persistent", 512, 1024, 768, 16640, 65, spread(512, 65, 2)),
+    (True, "ffn_gemm_dma_persistent", "ffn_gemm_dma_persistent", 256, 256, 8192, 8320, 65, spread(256, 65, 3)),
+    (True, "ffn_gemm_dma_persistent", "ffn_gemm_dma_persistent", 16, 1024, 1024, 48000, 3000, spread(16, 700)),
+    (True, "ffn_gemm_dma_persistent", "ffn_gemm_dma_persistent", 128, 768, 4096, 4160, 65, spread(128, 65)),
+    # one tile per work-group: expert counts that are no multiple of 8, or above 512
+    (True, "ffn_gemm_dma", "ffn_gemm_dma", 4, 3072, 4096, 4000, 1000, [1000, 0, 333, 257]),
+    (True, "ffn_gemm_dma", "ffn_gemm_dma", 12, 1536, 8192, 4200, 700, spread(12, 700)),
+    (True, "ffn_gemm_dma", "ffn_gemm_dma", 1024, 1024, 512, 33280, 65, spread(1024, 65, 2)),
+    # every tile shape of ffn_gemm_any, in lists of up to 64 segments and of more; weight tiles that end in the next block of
+    # 256 packed columns, or past the last column
+    (True, "ffn_gemm_any<128, 32>", "ffn_gemm_any<128, 32>", 8, 256, 512, 1200, 150, [150, 0, 1, 97, 128, 129, 33, 16]),
+    (True, "ffn_gemm_any<160, 160>", "ffn_gemm_any<128, 64>", 32, 256, 2304, 5152, 161, [161, 0, 160, 1, 130, 96, 65, 32] * 4),
+    (True, "ffn_gemm_any<160, 160>", "ffn_gemm_any<192, 128>", 64, 512, 1280, 9600, 150, [150, 33, 149, 0, 64, 150, 128, 17] * 8),
+    (True, "ffn_gemm_any<192, 128>", "ffn_gemm_any<192, 128>", 128, 256, 768, 17920, 140, [140, 0, 139, 1, 96, 97, 15, 129] * 16),
+    (False, "ffn_gemm_any<128, 32>", "ffn_gemm_any<128, 32>", 8, 256, 512, 1200, 150, [150, 0, 1, 97, 128, 129, 33, 16]),
+    (False, "ffn_gemm_any<160, 160>", "ffn_gemm_any<192, 64, dealt>", 32, 256, 2304, 5152, 161, [161, 0, 160, 1, 130, 96, 65, 32] * 4),
+    (False, "ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 64, dealt>", 128, 256, 768, 17920, 140,
+     [140, 0, 139, 1, 96, 97, 15, 129] * 16),
+    (False, "ffn_gemm_any<192, 128>", "ffn_gemm_any<192, 128, dealt>", 128, 512, 256, 24704, 193, spread(128, 193)),
+    (False, "ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 128>", 128, 256, 512, 24704, 193, spread(128, 193, 2)),
+    (False, "ffn_gemm_any<192, 64, dealt>", "ffn_gemm_any<160, 160>", 48, 768, 256, 6192, 129, spread(48, 129)),
+]
+
+
+def other_tiles(lm, first, second, E, d, h):
+    """T and C with which the row-major kernel takes other tiles, in both GEMMs if there are such."""
+    def same(tc):
+        desc = lm.make_desc(tc[0], d, E, 1, h, tc[1])
+        return (lm.ffn_kernel(desc) == first) + (lm.ffn_kernel(desc, True) == second)
+    best = min(((600, 3000), (8, 8), (E * 100, 100), (E * 600, 600), (E * 4000, 4000)), key=same)
+    assert same(best) < 2
+    return best
+
+
+@pytest.mark.parametrize("packed,first,second,E,d,h,T,C,rows", KERNEL_SHAPES)
+def test_each_kernel_gives_the_same_bits(env, packed, first, second, E, d, h, T, C, rows):
+    """H, Z, out and both data gradients, bit for bit as the row-major kernel with another tile shape makes them (which
+    check_expert_ffn above holds against the formulas in float64)."""
+    torch, lm = env
+    desc = lm.make_desc(T, d, E, 1, h, C, w_packed=packed)
+    for i, name in enumerate((first, second)):
+        assert lm.ffn_kernel(desc, bool(i), i == 0) == lm.ffn_kernel(desc, bool(i)) == name
+    other = other_tiles(lm, first, second, E, d, h)
+    ref, got = ffn_outputs(env, d, h, rows, *other, packed=False), ffn_outputs(env, d, h, rows, T, C, packed=packed)
+    for name in ref:
+        assert torch.equal(got[name], ref[name]), name
 
 
 # row-major weights: a work-group per weight tile (min(C, T) <= 128) and lists of tiles, shorter and longer than the grid

@@ -355,23 +355,24 @@ def test_expert_count_limits(env):
 
 
 def test_tuned_gemm_tiles_with_ragged_segments(env):
-    # d, h multiples of the tuned tile; capacity spans several 256-row tiles with ragged tails
+    """Forwards with packed weights and ragged segments, over the kernels that such small layers go to (ffn_gemm_any and, with
+    at most 32 rows per segment, ffn_gemm_few); the 256-column tile kernels, which take larger layers, are compared with the
+    row-major kernel, shape by shape, in test_gpu_any_shape.py, and run in the configurations at full size."""
+    # d, h multiples of the packed tile; capacity spans several m-tiles with ragged tails
     run_full(env, wl.small_config(T=4096, d=256, E=4, N=2, h=512, clusters=3), 700)
     run_full(env, wl.small_config(T=3000, d=512, E=8, N=2, h=256, clusters=4, dtype="bf16"), 300)
-    # many segments for few tiles: empty segments, one- and two-tile segments in one persistent launch
+    # many segments for few tiles: empty segments, one- and two-tile segments in one launch
     run_full(env, wl.small_config(T=6000, d=256, E=64, N=8, h=512, clusters=5), 300)
-    # the largest expert count of the persistent kernel (64 segments per XCD queue), mostly tiny or empty segments (a
-    # capacity of at most 64 rows would go to the few-rows kernel)
+    # many experts, mostly tiny or empty segments; expert counts that are a multiple of 8 and not
     run_full(env, wl.small_config(T=5000, d=512, E=512, N=8, h=256, clusters=6), 80)
-    # above it, and an expert count that is no multiple of 8: one tile per work-group
     run_full(env, wl.small_config(T=3000, d=1024, E=1024, N=32, h=256, clusters=7), 80)
     run_full(env, wl.small_config(T=2000, d=768, E=12, N=4, h=256, clusters=3), 400)
-    # many experts of few rows: the few-rows kernel
+    # many experts of few rows: above and in the range of the few-rows kernel
     run_full(env, wl.small_config(T=5000, d=512, E=512, N=8, h=256, clusters=6), 40)
     run_full(env, wl.small_config(T=3000, d=1024, E=1024, N=32, h=256, clusters=7), 8)
-    # the shortest K the packed layout allows (four double steps) with three m-tiles per segment
+    # the shortest K the packed layout allows
     run_full(env, wl.small_config(T=3000, d=256, E=8, N=2, h=256, clusters=2), 700)
-    # a long contraction (h = 8192) behind wide rows (d = 4096): more tiles on every XCD than it has work-groups
+    # a long contraction (h = 8192) behind wide rows (d = 4096): the persistent kernel in the first GEMM at least
     run_full(env, wl.small_config(T=6000, d=4096, E=8, N=2, h=8192, clusters=2), 700)
 
 
@@ -431,17 +432,20 @@ def test_ffn_tile_claims_against_fixed_assignment_across_launches_and_streams(en
     fixed form is checked against the oracle first); a workspace must come back zeroed, so that many launches in
     a row can share one; launches that overlap on two streams use a workspace each."""
     torch, lm, hz = env
-    # 8 experts = one segment per XCD, up to 2 x 32 tiles each for 32 work-groups: tiles are claimed dynamically
-    c = wl.small_config(T=3000, d=512, E=8, N=2, h=8192, clusters=4)
-    run_full(env, c, 300)
-    x, home = wl.hidden_states(c)
-    desc = lm.make_desc(c.T, c.d, c.E, c.N, c.h, 300, c.dtype)
-    ws = [wl.expert_weights(c, e) for e in range(c.E)]
-    W_in = torch.stack([hz.to_device(w[0], "bf16") for w in ws]); W_out = torch.stack([hz.to_device(w[1], "bf16") for w in ws])
+    # 16 segments per XCD with some rows, 48 and more tiles for 32 work-groups: tiles are claimed dynamically in both GEMMs
+    E, d, h, T, C = 128, 768, 4096, 4160, 65
+    desc = lm.make_desc(T, d, E, 8, h, C)
     dp = packed_desc(lm, desc)
+    assert lm.ffn_kernel(dp) == lm.ffn_kernel(dp, False, True) == lm.ffn_kernel(dp, True) == "ffn_gemm_dma_persistent"
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    W_in = (torch.randn(E, h, d, generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)
+    W_out = (torch.randn(E, d, h, generator=gen, device="cuda") * h ** -0.5).to(torch.bfloat16)
+    x = torch.randn(T, d, generator=gen, device="cuda").to(torch.bfloat16)
+    home = torch.randint(0, 8, (T,), generator=gen, device="cuda", dtype=torch.int32)
     Wi, Wo = pack(env, desc, W_in, W_out)
+    say(f"[tile claims] T={T} d={d} E={E} h={h} C={C}")
     b = lm.alloc_buffers(dp)
-    lm.forward(dp, hz.to_device(x, c.dtype), i32(torch, home), None, Wi, Wo, b)
+    lm.forward(dp, x, home, None, Wi, Wo, b)
     torch.cuda.synchronize()
     K = int(b.seg_off[-1])
     bits = lambda t: t[:K].view(torch.int16).cpu().numpy().tobytes()
@@ -449,6 +453,9 @@ def test_ffn_tile_claims_against_fixed_assignment_across_launches_and_streams(en
     lm.locmoe_expert_ffn(dp, b.send, b.seg_off, b.buf_expert, Wi, Wo, b.H, b.out)          # fixed assignment
     torch.cuda.synchronize()
     ref, refH = bits(b.out), bits(b.H)
+    lm.locmoe_expert_ffn(desc, b.send, b.seg_off, b.buf_expert, W_in, W_out, b.H, b.out)          # row-major
+    torch.cuda.synchronize()
+    assert bits(b.out) == ref and bits(b.H) == refH
     nws = lm.LOCMOE_FFN_WS_BYTES
     for it in range(70):
         poison(b.H, b.out)
