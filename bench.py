@@ -359,10 +359,7 @@ def main() -> int:
         backward = time_backward(lm, hz, wl, torch, np, c, desc, sets, W_in_rm, W_out_rm, W_in, W_out, stream, reps, K)
     dom = "ffn_in" if ms["ffn_in"] >= ms["ffn_out"] else "ffn_out"
     achieved = flops / (ms[dom] * 1e-3) / 1e12
-    kname = "ffn_gemm_any"
-    if desc.w_packed:  # (by shape: few rows, or too few 256-row tiles to fill the chip)
-        few = min(C, c.T) <= 192 or c.E * -(-min(C, c.T) // 256) * (min(c.d, c.h) // 256) < 1024
-        kname = "ffn_gemm_dma_persistent, ffn_gemm_any or ffn_gemm_few" if few else "ffn_gemm_dma_persistent"
+    kname = lm.ffn_kernel(desc, dom == "ffn_out")
     traffic, traffic_note = None, "the tracked counters are for the config-4 bench workload with packed weights"
     if desc.w_packed and c.cfg == 4 and not args.capacity:
         kib, traffic_note = profiled_traffic()

@@ -182,11 +182,11 @@ extern "C" int locmoe_angle_stats(const locmoe_desc* desc, const float* g, const
   while (G < 64 && 2 * G <= E / V) G *= 2;
   const int lds_cells = (size_t)(2 * cells + E) * 4 <= (size_t)kAngLdsBytes ? cells : 0;
   const size_t lds = (size_t)(2 * lds_cells + E) * 4;
-  // Tokens per block: whole batches of its groups, few enough for some 64 blocks (up to 16 experts), 128, or 2 E up to two per compute unit, but at most
-  // 1 024: fewer blocks leave compute units empty, and every block adds its cells to the same few counters in memory.  All
-  // three kernels, 64 bins, us, blocks of 1 024 tokens / always two blocks per compute unit / these: E = 16: 32 768 tokens
-  // 9.8 / 9.3 / 8.7, 65 536 10.1 / 11.4 / 9.9;  E = 32: 32 768 13.2 / 11.9 / 10.3;  E = 64: 65 536 21.6 / 19.4 / 18.9;
-  // E = 128: 4 096 50 / 10 / 10, 65 536 53 / 31 / 27;  E = 300: 65 536 115 / 36 / 36.
+  // Tokens per block: whole batches of its groups, few enough for some 64 blocks (up to 16 experts), 128, or 2 E up to two per
+  // compute unit, but at most 1 024: fewer blocks leave compute units empty, and every block adds its cells to the same few
+  // counters in memory.  All three kernels, 64 bins, us, blocks of 1 024 tokens / always two blocks per compute unit / these:
+  // E = 16: 32 768 tokens 9.8 / 9.3 / 8.7, 65 536 10.1 / 11.4 / 9.9;  E = 32: 32 768 13.2 / 11.9 / 10.3;  E = 64: 65 536 21.6 /
+  // 19.4 / 18.9;  E = 128: 4 096 50 / 10 / 10, 65 536 53 / 31 / 27;  E = 300: 65 536 115 / 36 / 36.
   const int batch = kAngThreads / G, blocks = desc->E <= 16 ? 64 : std::min(std::max(128, 2 * desc->E), 2 * cu_count());
   const int per_block = std::min(kAngMaxTokens, ceil_div(ceil_div(desc->T, blocks), batch) * batch);
   const dim3 grid((unsigned)ceil_div(desc->T, per_block));

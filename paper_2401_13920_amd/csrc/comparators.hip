@@ -331,9 +331,10 @@ extern "C" int locmoe_gate_dense(const locmoe_desc* desc, const void* x, const v
   }
     // 64 tokens per work-group, which read the weight twice as often, where they take half a turn less of the compute units
     // (up to two turns of 128), and with up to 32 experts where rows are multiples of 4 KiB, which meet in the same channels.
-    // In the mean over d = 384 .. 5 120, 128 tokens' time over 64 tokens' (8 to 32 experts; 48 and 64): 16 384 tokens (half a turn
-    // of 128) 1.11; 1.21, 24 000 (0.7) 0.99; 0.94, 32 768 (1) 1.02; 0.96, 40 000 (1.2) 1.12; 1.10, 57 000 (1.7) 0.98; 0.91, 65 536 (2) 1.00;
-    // 0.93, 80 000 (2.4) 1.04; 0.95.  d = 4 096 with up to 32 experts 1.10 at 32 768 and 65 536 tokens, d = 5 120 0.98 and 0.98.
+    // In the mean over d = 384 .. 5 120, 128 tokens' time over 64 tokens' (8 to 32 experts; 48 and 64): 16 384 tokens (half a
+    // turn of 128) 1.11; 1.21, 24 000 (0.7) 0.99; 0.94, 32 768 (1) 1.02; 0.96, 40 000 (1.2) 1.12; 1.10, 57 000 (1.7) 0.98;
+    // 0.91, 65 536 (2) 1.00; 0.93, 80 000 (2.4) 1.04; 0.95.  d = 4 096 with up to 32 experts 1.10 at 32 768 and 65 536 tokens,
+    // d = 5 120 0.98 and 0.98.
     const int cus = cu_count(), groups = ceil_div(T, 128);
     const bool few = (groups <= 2 * cus && ceil_div(2 * groups, cus) % 2 == 1) || (nt == 1 && d % 2048 == 0);
     if (nt == 1 && few) LOCMOE_DG(1, 64)

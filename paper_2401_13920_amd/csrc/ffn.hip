@@ -601,8 +601,8 @@ __global__ __launch_bounds__(64, 1) void ffn_gemm_few(const uint16_t* __restrict
 
 // Expected time in us of the tile kernels above with `rows` rows in each of E segments: prologue and launch, turns of tiles (one
 // per compute unit; a long list ends in half a turn), each an epilogue and K/64 double steps, no faster than the weights
-// (4.9 TB/s).  A fit to 44 launches of the persistent kernel (E = 8 .. 128, d = 512 .. 4096, h = 2048 .. 16384, 96 to 800
-// rows), which it meets to 9 % in the mean.
+// (4.9 TB/s).  A fit to 44 launches of the persistent kernel; over 282 others (E = 8 .. 256, d = 512 .. 4096, h = 1024 .. 16384, 65
+// to 4 096 rows: profiles/ffn_kernels_by_shape_and_spread.txt) it is 9 % off in the mean, over 92 of the other kernel 23 %.
 double tiles_time(int E, int rows, int Kdim, int Ndim, bool persistent, double* turns) {
   const int cus = cu_count(), NT = Ndim / kBN;
   int bm = kBM;

@@ -1,6 +1,6 @@
 // The expert FFN's grouped GEMM for any K and N that are multiples of 8: row-major weights with fp32 (rounded to bf16 between
 // LDS and the MFMA) or bf16 activations, and packed weights where the tiles here are faster than the 256 x 256 tiles of
-// ffn.hip (few rows per segment, few experts, narrow outputs: see ffn.hip's launch).
+// ffn.hip (few rows per segment, few experts, narrow outputs: pick_packed there).
 //
 // A work-group makes tiles of up to BM rows x BN columns in k-steps of 64 (fp32: 32) with four waves (2 along m x 2 along
 // n, 16-row subtiles interleaved between the waves of an axis).  Both operands reach LDS by direct-to-LDS copies into a
@@ -20,11 +20,10 @@
 // h = 6400, E = 40), with more rows all copies to LDS together, 8 to 13 TB/s, of which the activations are the larger part
 // the more rows and the fewer columns a tile has.  Hence
 //   - the widest tile that still fills the chip in whole turns (any_tiles below picks it);
-//   - the tiles of one segment on one XCD, whose L2 then fetches the segment's activations once.  Dealt to the XCDs in turn
-//     each L2 fetched all of them: second GEMM at 128 rows of that layer 270 -> 243 us (E = 64, d = 2048, h = 8192, 100 rows:
-//     432 -> 396), with 160 columns instead of 128, so that 400 tiles fit the 512 slots where 520 did not, 185;
+//   - in runs the tiles of one segment are on one XCD, whose L2 then fetches the segment's activations once, where tiles dealt
+//     to the XCDs make each L2 fetch all of them (any_tiles says where that pays);
 //   - packed weights here too: E = 16, d = 1024, h = 4096, both GEMMs: 64 rows 37 + 41 -> 29 + 28 us (one wave per 64
-//     columns with the weights straight in registers, which this replaces; 16 rows 26 + 28 -> 26 + 26), 128 rows 45 + 68
+//     columns with the weights straight in registers, as ffn_gemm_few has it up to 32 rows), 128 rows 45 + 68
 //     (256 x 256 tiles) -> 32 + 36; E = 4, d = 2048, h = 8192, 100 rows, second GEMM 117 -> 46.
 #include <math.h>
 
@@ -352,9 +351,10 @@ int launch_any(const void* A, const void* W, void* C, void* aux, const int32_t* 
 // Expected time in us of a GEMM with `rows` rows in each of E segments in tiles of BM x BN: turns of tiles (one or two
 // work-groups per compute unit), each an epilogue and K/64 steps, a step bounded by the latency of a stage's copies, by what
 // all compute units together copy (17 TB/s) or by LDS and MFMA cycles; all of it no faster than the weights (5 TB/s).
-// The constants are a fit to 212 launches (E = 4 .. 128, d = 128 .. 4096, h = 512 .. 16384, 8 to 800 rows, packed and
-// row-major), which it meets to 14 % in the mean; of the four shapes of any_gemm it picks one that is on average 1.0 % (at
-// most 23 %) slower than the best of them.  Always 192 x 128: 14 %; 160 x 160: 19 %; 128 x 64: 17 %; 128 x 32: 40 %.
+// The constants are a fit to 212 launches; over 750 other GEMMs of 24 layers (E = 4 .. 256, d = 256 .. 4096, h = 512 .. 16384, 1 to
+// 4 096 rows per expert, packed and row-major: profiles/ffn_kernels_by_shape_and_spread.txt) it is 12 % off in the mean, and
+// of the four shapes of any_fastest it picks one that is on average 1.3 % (at most 23 %) slower than the best of them.  Always
+// 192 x 128: 8 %; 160 x 160: 12 %; 128 x 64: 22 %; 128 x 32: 63 %.
 double any_time(int BM, int BN, int E, int rows, int Kdim, int Ndim) {
   const int cus = cu_count(), NT = ceil_div(Ndim, BN);
   int mt = ceil_div(rows, BM);
