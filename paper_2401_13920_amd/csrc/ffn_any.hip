@@ -409,20 +409,23 @@ AnyTiles any_tiles(bool a_f32, bool packed, int E, int rows_max, int T, int Kdim
   }
   // Row-major weights: tiles of 192 rows and 128 columns, or 64 where that leaves slots empty, dealt to the XCDs.  Uneven tokens
   // cost the least there, and the expected times know nothing of them, so that a shape has to be expected 1.15 times as fast
-  // to be taken instead, and 1.25 times that of 160 x 160, whose runs suffer most, unless the experts are many.  Over 588
-  // GEMMs of 14 layers, each with four spreads of the tokens (even; a power law; 60 % on one expert; 80 % on four), against the
-  // two shapes alone: 1.03 times as fast, 12 GEMMs more than 7 % slower for one of the spreads (3 of them where it is the same
-  // kernel), 4 more than 10 %.  The shape expected fastest, whatever the distance: 1.05, 88 and 47.
+  // to be taken instead, 1.25 times that of 160 x 160, whose runs suffer most, unless the experts are many, and 1.05 times
+  // that of 128 x 32, which makes so many tiles that they hardly matter.  Nothing is asked for where no segment is longer than
+  // a subtile or two and few are empty: every tile is much the same there.  Over 588 GEMMs of 14 layers, each with four spreads
+  // of the tokens (even; a power law; 60 % on one expert; 80 % on four), against the two shapes alone: 1.04 times as fast, 12
+  // GEMMs more than 7 % slower for one of the spreads (3 of them where it is the same kernel), 4 more than 10 %.  The shape
+  // expected fastest, whatever the distance: 1.05, 88 and 47.
   const bool wide = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows, 192) >= 2 * cu_count();
   AnyTiles t = {192, wide ? 128 : 64, true, false};
   double us = any_time(t.bm, t.bn, E, rows, Kdim, Ndim);
+  const bool alike = rows_max <= 32 && T > 4LL * E;
   auto consider = [&](AnyTiles other, double times) {
-    const double u = times * any_time(other.bm, other.bn, E, rows, Kdim, Ndim);
+    const double u = (alike ? 1.0 : times) * any_time(other.bm, other.bn, E, rows, Kdim, Ndim);
     if (u < us) { us = u; t = other; }
   };
   if (!wide) consider({192, 128, true, false}, 1.15);
   consider({160, 160, false, false}, E >= 32 ? 1.15 : 1.25);
-  consider({128, 32, false, false}, 1.15);
+  consider({128, 32, false, false}, 1.05);
   // In runs where the XCDs together would fetch more bytes of activations than there are weights, the inner size is the longer
   // one and a segment's activations are not far beyond an XCD's 4 MiB of L2.  Second GEMM, dealt / runs: E = 16, d = 1024,
   // h = 4096, 750 rows 131 / 97 us;  E = 64, d = 1024, h = 2736, 188 rows 166 / 124;  E = 40, d = 1600, h = 6400, 820 rows (10 MB)
