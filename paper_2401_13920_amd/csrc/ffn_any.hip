@@ -407,30 +407,43 @@ AnyTiles any_tiles(bool a_f32, bool packed, int E, int rows_max, int T, int Kdim
     double us;
     return any_fastest(E, rows, Kdim, Ndim, &us);
   }
-  // Row-major weights: tiles of 192 rows and 128 columns, or 64 where that leaves slots empty, dealt to the XCDs.  Uneven tokens
-  // cost the least there, and the expected times know nothing of them, so that a shape has to be expected 1.15 times as fast
-  // to be taken instead, 1.25 times that of 160 x 160, whose runs suffer most, unless the experts are many, and 1.05 times
-  // that of 128 x 32, which makes so many tiles that they hardly matter.  Nothing is asked for where no segment is longer than
-  // a subtile or two and few are empty: every tile is much the same there.  Over 588 GEMMs of 14 layers, each with four spreads
-  // of the tokens (even; a power law; 60 % on one expert; 80 % on four), against the two shapes alone: 1.04 times as fast, 12
-  // GEMMs more than 7 % slower for one of the spreads (3 of them where it is the same kernel), 4 more than 10 %.  The shape
-  // expected fastest, whatever the distance: 1.05, 88 and 47.
+  // Row-major weights.  192 x 128 goes in runs where the XCDs together would fetch more bytes of activations than there are
+  // weights, unless a segment's activations are far beyond an XCD's 4 MiB of L2, and with the inner size the shorter one only
+  // from twice as many on.  us, dealt / runs, second GEMM: E = 16, d = 1024, h = 4096, 750 rows 131 / 97, 2 048 rows (17 MB)
+  // 324 / 276;  E = 64, d = 1024, h = 2736, 188 rows 166 / 124;  E = 6, d = 768, h = 3072, 5 462 rows (34 MB) 227 / 192;
+  // E = 8, d = 2048, h = 8192, 4 096 rows (67 MB) 1 243 / 1 351.  First: E = 16, 750 rows 118 / 122;  E = 48, d = 384, h = 1536,
+  // 683 rows 81 / 73.
+  const bool runs = 8LL * rows >= Ndim && (Kdim > Ndim || 4LL * rows >= Ndim) && (long long)rows * Kdim <= 30000000;
+  // 192 x 128, or 192 x 64 dealt where that leaves slots empty, unless another shape is expected 1.05 times as fast (160 x 160
+  // of 64 experts or more: 1.03).  The expected times know nothing of uneven tokens, which cost the least in dealt tiles and the
+  // most in 160 x 160 of few experts and short lists: 1.25 there (E = 12, d = 1536, h = 4096, 417 rows, first GEMM, these /
+  // 192 x 128 dealt: even 80 / 93, 60 % on one expert 71 / 50).  Nothing is asked for where no segment is longer than a subtile or
+  // two and few are empty, or the capacity cuts at two thirds of the even share or less: every tile is much the same there.  192 x 64 makes each XCD fetch all activations once more, which the
+  // times do not know either: where 192 x 128 goes in runs, it is taken unless it is expected 5 % slower (E = 4, d = 512,
+  // h = 2048, 3 000 rows, second GEMM 58 / 32).
+  // Over 588 GEMMs of 14 layers, each with four spreads of the tokens (even; a power law; 60 % on one expert; 80 % on four),
+  // against 192 x 128 and 192 x 64 dealt alone: 1.05 times as fast (even: 1.07), 39 GEMMs more than 7 % slower for one of the
+  // spreads, 14 more than 15 % (the last rule's tiles as 192 x 64 dealt).  With 1.15 and 1.25 asked for and runs for K > N and up to 16 MB only: 1.03 (1.04), 12 and 3; the shape
+  // expected fastest, whatever the distance: 1.05 (1.08), 105 and 42 of 518.
   const bool wide = (long long)E * ceil_div(Ndim, 128) * ceil_div(rows, 192) >= 2 * cu_count();
-  AnyTiles t = {192, wide ? 128 : 64, true, false};
-  double us = any_time(t.bm, t.bn, E, rows, Kdim, Ndim);
-  const bool alike = rows_max <= 32 && T > 4LL * E;
+  const double wide_us = any_time(192, 128, E, rows, Kdim, Ndim), narrow_us = any_time(192, 64, E, rows, Kdim, Ndim);
+  const bool alike = (rows_max <= 32 && T > 4LL * E) || 2LL * T >= 3LL * E * rows_max;
+  AnyTiles t = {192, wide || (runs && wide_us < 1.05 * narrow_us) ? 128 : 64, !runs, false};
+  if (t.bn == 64) t.dealt = true;
+  double us = t.bn == 128 ? wide_us : narrow_us;
   auto consider = [&](AnyTiles other, double times) {
     const double u = (alike ? 1.0 : times) * any_time(other.bm, other.bn, E, rows, Kdim, Ndim);
     if (u < us) { us = u; t = other; }
   };
-  if (!wide) consider({192, 128, true, false}, 1.15);
-  consider({160, 160, false, false}, E >= 32 ? 1.15 : 1.25);
+  if (wide) consider({192, 64, true, false}, 1.05);
+  else if (!runs) consider({192, 128, true, false}, 1.05);
+  consider({160, 160, false, false}, E >= 64 ? 1.03 : E >= 16 || rows >= 700 ? 1.05 : 1.25);
   consider({128, 32, false, false}, 1.05);
-  // In runs where the XCDs together would fetch more bytes of activations than there are weights, the inner size is the longer
-  // one and a segment's activations are not far beyond an XCD's 4 MiB of L2.  Second GEMM, dealt / runs: E = 16, d = 1024,
-  // h = 4096, 750 rows 131 / 97 us;  E = 64, d = 1024, h = 2736, 188 rows 166 / 124;  E = 40, d = 1600, h = 6400, 820 rows (10 MB)
-  // 832 / 753;  E = 8, d = 2048, h = 8192, 4 096 rows (67 MB) 1 243 / 1 351.  First GEMM of E = 16, 750 rows 118 / 122.
-  if (t.bm == 192 && t.bn == 128) t.dealt = !(8LL * rows >= Ndim && Kdim > Ndim && (long long)rows * Kdim <= 8000000);
+  // 128 x 64 in runs for 192 x 64 dealt where segments are cut at, or little above, the even share: second GEMM of E = 16, d = 1024,
+  // h = 4096, 256 rows, C = 320, 60.4 us (192 x 128 in runs 64.6); E = 40, d = 1600, h = 3200, 8 rows 68.1 / 71.5 dealt.
+  // Not where 128 rows make more tiles of a segment (E = 8, d = 4096, h = 10 928, 138 rows, a training step: 2 184 / 2 229 us).
+  if (t.bm == 192 && t.bn == 64 && 3LL * rows_max <= 4LL * rows && any_time(128, 64, E, rows, Kdim, Ndim) <= 1.02 * narrow_us)
+    t = {128, 64, false, false};
   return t;
 }
 
@@ -456,7 +469,7 @@ int any_gemm(const void* A, const void* W, void* C, void* aux, const int32_t* se
     }
     switch (t.bn) {
       case 160: LOCMOE_ANY(160, 160, false, false);
-      case 64: if constexpr (PACKED) LOCMOE_ANY(128, 64, false, false);
+      case 64: LOCMOE_ANY(128, 64, false, false);
       case 32: LOCMOE_ANY(128, 32, false, false);
       default: LOCMOE_ANY(192, 128, false, false);
     }

@@ -260,12 +260,12 @@ KERNEL_SHAPES = [
     (True, "ffn_gemm_any<160, 160>", "ffn_gemm_any<192, 128>", 64, 512, 1280, 9600, 150, [150, 33, 149, 0, 64, 150, 128, 17] * 8),
     (True, "ffn_gemm_any<192, 128>", "ffn_gemm_any<192, 128>", 128, 256, 768, 17920, 140, [140, 0, 139, 1, 96, 97, 15, 129] * 16),
     (False, "ffn_gemm_any<128, 32>", "ffn_gemm_any<128, 32>", 8, 256, 512, 1200, 150, [150, 0, 1, 97, 128, 129, 33, 16]),
-    (False, "ffn_gemm_any<160, 160>", "ffn_gemm_any<192, 64, dealt>", 32, 256, 2304, 5152, 161, [161, 0, 160, 1, 130, 96, 65, 32] * 4),
-    (False, "ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 64, dealt>", 128, 256, 768, 17920, 140,
+    (False, "ffn_gemm_any<160, 160>", "ffn_gemm_any<128, 64>", 32, 256, 2304, 5152, 161, [161, 0, 160, 1, 130, 96, 65, 32] * 4),
+    (False, "ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 128>", 128, 256, 768, 17920, 140,
      [140, 0, 139, 1, 96, 97, 15, 129] * 16),
-    (False, "ffn_gemm_any<192, 128>", "ffn_gemm_any<192, 128, dealt>", 128, 512, 256, 24704, 193, spread(128, 193)),
-    (False, "ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 128>", 128, 256, 512, 24704, 193, spread(128, 193, 2)),
-    (False, "ffn_gemm_any<192, 64, dealt>", "ffn_gemm_any<160, 160>", 48, 768, 256, 6192, 129, spread(48, 129)),
+    (False, "ffn_gemm_any<192, 128>", "ffn_gemm_any<192, 128>", 128, 512, 256, 24704, 193, spread(128, 193)),
+    (False, "ffn_gemm_any<192, 128, dealt>", "ffn_gemm_any<192, 128>", 128, 256, 2048, 24704, 193, spread(128, 193, 2)),
+    (False, "ffn_gemm_any<192, 64, dealt>", "ffn_gemm_any<160, 160>", 48, 768, 256, 6192, 400, spread(48, 129)),
 ]
 
 
